@@ -47,7 +47,7 @@ MFMA_PEAK_TFLOPS = 2500.0   # dense bf16
 
 
 def measured_traffic(workload):
-    """HBM bytes per k_step launch from the rocprofv3 --pmc runs (FETCH_SIZE + WRITE_SIZE, scaled by a
+    """HBM bytes per step from the rocprofv3 --pmc runs (FETCH_SIZE + WRITE_SIZE, scaled by a
     copy kernel of known size); the summary under profiles/ carries the figure on a `traffic_bytes_per_launch:`
     line.  None when no such measurement exists for the workload."""
     path = os.path.join(ROOT, "profiles", f"k_step_{workload}_pmc.md")
@@ -155,19 +155,19 @@ def timed_steps(workload, steps, warmup, tau, by_length=False, keep_open=False):
         "config": {"workload": f"{wl.name}: {m.n_layers}L d={m.d_model} {m.dtype}, batch {B}, {M}-node tree, "
                                f"tau={tau}, L {int(np.mean(L0))}->{int(np.mean(L0) + np.mean(n_out))}",
                    "mean_committed_per_step": float(np.mean(n_out)) / min(seg, steps)},
-        # dominant kernel: k_step, the persistent kernel that runs a whole step; one launch per step,
-        # so its average launch duration is the event-timed region divided by the number of steps
+        # a step is one launch per map (some 65 of them at 12 layers): the whole step is priced, the event-timed region
+        # divided by the number of steps
         # the roof that bounds the step: HBM bytes at batch 1 (64 flop per weight byte); from ~1000
         # rows on the contractions at MFMA peak take longer than the bytes at HBM peak
         "roofline": ({"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                       "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(wl.name),
-                      "kernel": "k_step (one launch = one speculative step)",
+                      "kernel": "all kernels of one speculative step",
                       "avg_launch_us": ms_step * 1e3, "algorithmic_bytes_per_launch": nbytes,
                       "algorithmic_flops_per_launch": nflops, "tflops": tflops}
                      if nbytes / (HBM_PEAK_GBS * 1e9) >= nflops / (MFMA_PEAK_TFLOPS * 1e12) else
                      {"bound": "mfma", "achieved": tflops, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                       "frac": tflops / MFMA_PEAK_TFLOPS, "traffic": measured_traffic(wl.name),
-                      "kernel": "k_step (one launch = one speculative step)",
+                      "kernel": "all kernels of one speculative step",
                       "avg_launch_us": ms_step * 1e3, "algorithmic_bytes_per_launch": nbytes,
                       "algorithmic_flops_per_launch": nflops, "hbm_gbs": achieved}),
         "by_committed_length": by_L,
@@ -191,7 +191,7 @@ def main():
     ap.add_argument("--other-steps", type=int, default=20, help="timed steps of each of those workloads")
     ap.add_argument("--only-timed", action="store_true",
                     help="run the warm-up and the timed steps only (no by-length pass, AR / stochastic / dial legs, "
-                         "no CPU baseline): every k_step launch of the run is then a step of the workload or a "
+                         "no CPU baseline): every step of the run is then one of the workload or a "
                          "prefill chunk, which is what a per-kernel profile should average over")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a plain copy kernel of known size (256 MiB read + 256 MiB written, 8 launches): "

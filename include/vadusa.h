@@ -16,17 +16,12 @@
  *    throws or aborts across this boundary.  After an error the decoding state
  *    of the context is unchanged unless the code is VADUSA_EHIP.  A text for the
  *    last error of a context is available from vadusa_last_error().
- *  - The bf16 step runs as one persistent kernel whose workgroups meet at grid
- *    barriers, launched as an ordinary kernel with one workgroup per compute
- *    unit: it needs the GPU to itself while it runs (no other kernel on another
- *    stream or from another process at the same time).  Every wait is bounded: if a
- *    workgroup is not placed, the kernel gives up, the next call that
- *    synchronises (a step with result pointers, vadusa_read_output, the debug
- *    readers) returns VADUSA_EHIP, and from then on every call except
- *    vadusa_prefill, vadusa_load_weights and vadusa_destroy returns
- *    VADUSA_ESTATE; vadusa_prefill resets the barrier state and starts the
- *    sequences again.  VADUSA_COOPERATIVE_LAUNCH=1 makes the runtime verify
- *    residency at every launch instead (about 18 us per step).
+ *  - The error word: a context whose error word was raised (today only by
+ *    vadusa_debug_raise_error) reports it in the next call that synchronises
+ *    (a step with result pointers, vadusa_read_output, the debug readers) as
+ *    VADUSA_EHIP, and from then on every call except vadusa_prefill,
+ *    vadusa_load_weights and vadusa_destroy returns VADUSA_ESTATE;
+ *    vadusa_prefill resets it and starts the sequences again.
  *  - "host" / "device" in a comment says where a pointer must point.  The
  *    library never keeps a caller's host pointer after the call returns.
  *  - The library allocates no device memory: the caller passes one device
@@ -135,17 +130,14 @@ size_t vadusa_blob_floats(const vadusa_config* cfg);
  * stream).  *out receives the context (host object, freed by vadusa_destroy). */
 int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena_bytes,
                   void* hip_stream, vadusa_ctx** out);
-/* Environment variables read by vadusa_create, VADUSA_COOPERATIVE_LAUNCH at the process's first
- * step launch (debugging and test aids; none changes results):
- *   VADUSA_PHASE_LAUNCHES       one kernel launch per phase of the bf16 step instead of one
- *                               persistent launch with grid barriers
- *   VADUSA_COOPERATIVE_LAUNCH   launch the persistent kernel cooperatively
- *   VADUSA_PHASE_CLOCK=n        record the timing points of VADUSA_DBG_PHASE_CLOCK in workgroup n - 1 (only the
- *                               library built with -DVADUSA_CLOCK_BUILD, libvadusa_clock.so, has them)
- *   VADUSA_BIG_MIN_UNITS=n      many-row kernel (>= 256 rows): a linear map takes 128 x 128 output
- *                               units, and attention whole (sequence, head) units, from n such
- *                               units on (default 256 = one per compute unit); lets tests
- *                               reach those code paths with small shapes */
+/* Environment variables (debugging and test aids; none changes results):
+ *   VADUSA_PHASE_CLOCK          the binding loads libvadusa_clock.so (built with -DVADUSA_CLOCK_BUILD), which records
+ *                               the timing points of VADUSA_DBG_PHASE_CLOCK
+ *   VADUSA_BIG_MIN_UNITS=n      read by vadusa_create: a linear map of the bf16 model takes 64 x 128 output tiles
+ *                               from n such tiles on, whatever its size; lets tests reach that kernel with
+ *                               small shapes
+ * A step is one launch per map, so VADUSA_PHASE_LAUNCHES and VADUSA_COOPERATIVE_LAUNCH of earlier versions have no
+ * effect. */
 
 /* Frees the context (host object).  Makes no HIP call, so it is safe in a finaliser or an exit handler;
  * the caller drains the stream before it frees or reuses the arena. */
@@ -287,13 +279,11 @@ enum {
     VADUSA_DBG_PATH       = 7,  /* int32 [batch][n_draft_heads+2]: count, then node indices */
     VADUSA_DBG_FINISHED   = 8,  /* int32 [batch] */
     VADUSA_DBG_DRAFT_LOGITS = 9, /* float [batch][n_draft_heads][V+1], logits behind the lists */
-    VADUSA_DBG_PHASE_CLOCK = 10, /* int64 [128][8]: device clock (100 MHz) of workgroup 0 in the last launch of
-                                    the bf16 step kernel: [p][0] start of phase p, [p][1] its own units done,
-                                    [p][2..] points inside a unit, [127][0] end of the kernel.  Recorded only by
-                                    contexts created while the environment variable VADUSA_PHASE_CLOCK is set
-                                    (each point costs a few hundred ns); zero otherwise.  The points are compiled
-                                    into libvadusa_clock.so only (switched off they still cost the step 4 %);
-                                    the ordinary library returns VADUSA_ESTATE */
+    VADUSA_DBG_PHASE_CLOCK = 10, /* int64 [128][8]: [p][0] = device clock (100 MHz) ahead of the launch of phase p of the
+                                    last bf16 step: 0 embedding, 1 + 5 l .. 5 + 5 l layer l (QKV, attention,
+                                    out-projection, FFN1, FFN2), then from H = 1 + 5 n_layers on vocabulary map, edges,
+                                    (H + 3) continuation, draft maps (two), lists and compaction.  Recorded by
+                                    libvadusa_clock.so only; the ordinary library returns VADUSA_ESTATE */
     VADUSA_DBG_SCORES     = 11  /* float [batch][M][V+1]: the perturbed scores (s - log(-log u) on the nucleus,
                                     -inf elsewhere) of the last stochastic verification; VADUSA_ESTATE if the
                                     last verification was a deterministic one */
@@ -303,9 +293,8 @@ enum {
  * bytes must equal the item's size for the current batch and tree. */
 int vadusa_debug_read(vadusa_ctx* ctx, int32_t what, void* host_buf, size_t bytes);
 
-/* Test aid for the failure path described under "Conventions": sets the error word a step kernel raises when
- * it gives up at a grid barrier (bf16 contexts; VADUSA_ESTATE for fp32 ones).  No kernel is disturbed: the
- * stream is drained first. */
+/* Test aid for the error word described under "Conventions" (bf16 contexts; VADUSA_ESTATE for fp32 ones).  No kernel
+ * is disturbed: the stream is drained first. */
 int vadusa_debug_raise_error(vadusa_ctx* ctx);
 
 /* Copies K (which = 0) or V (1) rows pos0..pos0+npos-1 of a layer and sequence

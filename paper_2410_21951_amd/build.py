@@ -7,12 +7,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvadusa.so")
-LIB_CLOCK = os.path.join(HERE, "libvadusa_clock.so")   # the same library with the step kernel's timing points compiled in
+LIB_CLOCK = os.path.join(HERE, "libvadusa_clock.so")   # the same library with timing points compiled in
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-# -amdgpu-sched-strategy=max-ilp: the step kernel runs one wave per SIMD, so the scheduler's default
-# goal (registers for occupancy) buys nothing; ordering for instruction-level parallelism measured
-# 6 us per step faster (572 -> 566 us, valle_b1)
+# -amdgpu-sched-strategy=max-ilp: the linear maps request all operands of a chunk ahead of their use; the scheduler's
+# default goal (registers for occupancy) buys nothing there
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          "-mllvm", "-amdgpu-sched-strategy=max-ilp",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

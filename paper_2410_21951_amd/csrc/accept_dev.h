@@ -1,8 +1,8 @@
 // Device functions for verification with tolerance (Algorithm 1), choice of the
 // accepted path (Sec. 2.3), continuation from the last accepted node (Sec. 2.1),
 // KV compaction and the draft heads' top-k lists.  Each function is the body of
-// one workgroup of 256 threads (64 for the compaction); the generic kernels and
-// the persistent step kernel both call them.
+// one workgroup of 256 threads (64 for the compaction); the kernels of both models
+// call them.
 #pragma once
 #include "common.h"
 
@@ -245,8 +245,7 @@ __device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int
     const int root = block_argbest(s.logits + (size_t)r * D.V1, D.V1, INFINITY, -1, nullptr);
     T* hb = (T*)s.hbest + (size_t)b * D.d;
     if (from_x) {
-        // final LayerNorm of the accepted node's residual row.  The row was written by other
-        // workgroups of this launch: coherent loads, once, into registers (up to 16 values per
+        // final LayerNorm of the accepted node's residual row: read once, into registers (up to 16 values per
         // thread, d <= 4096; larger rows take the three-pass route below)
         const float* xr = s.x + (size_t)r * D.d;
         if (D.d <= 4096) {
@@ -354,9 +353,8 @@ __device__ inline void dev_commit_kv(const Dims& D, const DevState& s, int layer
         }
 }
 
-// The same for nl consecutive layers from layer0 on (the step kernel's compaction units: with many sequences a unit
-// takes several layers, so that a workgroup has one unit instead of a chain of them, each a few dependent trips to
-// memory).  The path is read once; four layers' rows are in flight together; a path whose rows already sit where they
+// The same for nl consecutive layers from layer0 on (with many sequences a workgroup takes several layers, so that the
+// chain of dependent trips to memory is paid once).  The path is read once; four layers' rows are in flight together; a path whose rows already sit where they
 // belong (the root alone, or nodes 0, 1, .. of the tree) moves nothing.
 template <class T>
 __device__ inline void dev_commit_kv_layers(const Dims& D, const DevState& s, int layer0, int nl, int b, int head, int dim) {

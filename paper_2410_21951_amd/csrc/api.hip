@@ -237,20 +237,15 @@ static size_t layout(const vadusa_config& c, char* base, DevState* s, std::vecto
     st.Kc = cv.take(kv);
     st.Vc = cv.take(kv);
     st.x = (float*)cv.take(R * d * 4);
-    const size_t nslots = c.dtype ? 2 * (size_t)c.n_layers + 1 : 0, per_layer = c.dtype ? c.n_layers : 1;
     const size_t Rp = (R + 15) / 16 * 16, Bp = (B + 15) / 16 * 16;   // tiled activation buffers hold whole row tiles
-    st.act_stride = Rp * d; st.stats_stride = (d / 16) * R * 2; st.hid_stride = Rp * F; st.draft_stride = Bp * d;
-    st.xb = (bf16_t*)cv.take(nslots * Rp * d * 2);
-    st.stats = (float*)cv.take(nslots * st.stats_stride * 4);
-    st.bar = (uint32_t*)cv.take((size_t)VADUSA_BAR_WORDS * 4);
+    st.draft_stride = Bp * d;
+    st.xb = c.dtype ? (bf16_t*)cv.take(Rp * d * 2) : nullptr;
+    st.stats = c.dtype ? (float*)cv.take((d / 16) * R * 2 * 4) : nullptr;
     st.tprof = (long long*)cv.take(1024 * 8);
-    st.gtab = (const uint32_t*)cv.take((size_t)5 * VADUSA_GREC_WORDS * 4);
-    st.layers_dev = (const LayerW*)cv.take(sizeof(LayerW) * c.n_layers);
-    st.draft_dev = (const DraftW*)cv.take(sizeof(DraftW) * Hh);
     st.xn = cv.take(R * d * e);
-    st.q = cv.take(per_layer * Rp * d * e);
-    st.att = cv.take(per_layer * Rp * d * e);
-    st.hid = cv.take(per_layer * Rp * F * e);
+    st.q = cv.take(Rp * d * e);
+    st.att = cv.take(Rp * d * e);
+    st.hid = cv.take(Rp * F * e);
     st.hn = cv.take(R * d * e);
     st.logits = (float*)cv.take(R * V1 * 4);
     st.hbest = cv.take(Bp * d * e);
@@ -312,17 +307,6 @@ static Dims make_dims(const vadusa_ctx* c, int B, int M) {
     return D;
 }
 
-// The launch-independent part of the step kernel's parameters.
-static StepParams base_params(const vadusa_ctx* c, const Dims& D) {
-    StepParams P{};
-    P.D = D; P.s = c->s; P.big_min = c->big_min; P.allq_min = c->allq_min;
-    P.lw0 = c->layers[0]; P.dw0 = c->draft[0];
-    P.lw_stride = c->layers.size() > 1 ? (size_t)((const char*)c->layers[1].Wqkv - (const char*)c->layers[0].Wqkv) : 0;
-    P.dw_stride = c->draft.size() > 1 ? (size_t)((const char*)c->draft[1].W1 - (const char*)c->draft[0].W1) : 0;
-    return P;
-}
-
-
 extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena_bytes, void* hip_stream,
                              vadusa_ctx** out) {
     if (!out) return VADUSA_EINVAL;
@@ -345,16 +329,9 @@ extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena
     layout(*cfg, c->arena, &c->s, &c->layers, &c->draft, nullptr, &c->staging_floats, &c->uniforms, &c->scores);
     c->sampled = 0;
     if (cfg->dtype) {
-        // the step kernel addresses layer l as layer 0 + l * stride: the layout must be that regular
+        // the draft maps of all heads are one launch, which addresses head i as head 0 + i * stride
         auto off = [](const void* a, const void* b) { return (const char*)a - (const char*)b; };
         bool ok = true;
-        for (size_t l = 1; l < c->layers.size() && ok; ++l) {
-            const LayerW &a = c->layers[0], &b = c->layers[l];
-            const ptrdiff_t st = off(c->layers[1].Wqkv, a.Wqkv) * (ptrdiff_t)l;
-            ok = off(b.Wqkv, a.Wqkv) == st && off(b.Wo, a.Wo) == st && off(b.W1, a.W1) == st && off(b.W2, a.W2) == st &&
-                 off(b.bo, a.bo) == st && off(b.b2, a.b2) == st && off(b.t_qkv, a.t_qkv) == st &&
-                 off(b.cs_qkv, a.cs_qkv) == st && off(b.t_w1, a.t_w1) == st && off(b.cs_w1, a.cs_w1) == st;
-        }
         for (size_t i = 1; i < c->draft.size() && ok; ++i) {
             const DraftW &a = c->draft[0], &b = c->draft[i];
             const ptrdiff_t st = off(c->draft[1].W1, a.W1) * (ptrdiff_t)i;
@@ -364,24 +341,12 @@ extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena
     }
     c->L_ub.assign(cfg->max_batch, 0);
     c->pending.assign(cfg->max_batch, 0);
-    c->epoch = 0;
     c->errored = 0;
-    c->persistent = getenv("VADUSA_PHASE_LAUNCHES") ? 0 : 1;
-    c->profile = getenv("VADUSA_PHASE_CLOCK") ? std::max(1, atoi(getenv("VADUSA_PHASE_CLOCK"))) : 0;   // n: workgroup n - 1 records
-    // 128 x 128 units from 129 of them on (more than half of the 256 compute units busy for one round: with fewer, the
-    // four times as many 64 x 64 units take two rounds of less than half the time each); whole-head attention units
-    // once there is one per compute unit
-    c->big_min = getenv("VADUSA_BIG_MIN_UNITS") ? std::max(1, atoi(getenv("VADUSA_BIG_MIN_UNITS"))) : 129;
-    c->allq_min = getenv("VADUSA_BIG_MIN_UNITS") ? c->big_min : 256;
+    c->big_min = getenv("VADUSA_BIG_MIN_UNITS") ? std::max(1, atoi(getenv("VADUSA_BIG_MIN_UNITS"))) : 0;
     {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) { delete c; return VADUSA_EHIP; }
-        c->n_cus = std::min(prop.multiProcessorCount, 1024);
-        // barrier flags and the error flag start at zero; an unwritten KV row must never hold NaN bits
+        // the error flag starts at zero; an unwritten KV row must never hold NaN bits
         const size_t kv = (size_t)cfg->n_layers * cfg->max_batch * cfg->n_heads * cfg->max_positions * 64 * c->elem;
-        hipError_t e0 = hipMemset(c->s.bar, 0, (size_t)VADUSA_BAR_WORDS * 4);
-        if (e0 == hipSuccess) e0 = hipMemset(c->s.tprof, 0, 1024 * 8);
+        hipError_t e0 = hipMemset(c->s.tprof, 0, 1024 * 8);
         if (e0 == hipSuccess) e0 = hipMemset(c->s.kerr, 0, 16);
         if (e0 == hipSuccess) e0 = hipMemset(c->s.Kc, 0, kv);
         if (e0 == hipSuccess) e0 = hipMemset(c->s.Vc, 0, kv);
@@ -413,11 +378,11 @@ extern "C" void vadusa_destroy(vadusa_ctx* c) {
     delete c;
 }
 
-// Test aid: raises the error word as a kernel that gave up at a grid barrier would (the next synchronising call
+// Test aid: raises the error word (the next synchronising call
 // reports VADUSA_EHIP and the context refuses work until vadusa_prefill has reset it).
 extern "C" int vadusa_debug_raise_error(vadusa_ctx* c) {
     if (!c) return VADUSA_EINVAL;
-    if (!c->cfg.dtype) return fail(c, VADUSA_ESTATE, "the fp32 path has no persistent kernel and no error word");
+    if (!c->cfg.dtype) return fail(c, VADUSA_ESTATE, "the fp32 path has no error word");
     const int32_t one = 1;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipMemcpy(c->s.kerr, &one, 4, hipMemcpyHostToDevice));
@@ -467,18 +432,9 @@ extern "C" int vadusa_load_weights(vadusa_ctx* c, const float* blob, size_t n_fl
     if (c->cfg.dtype) {
         for (auto& w : sl)   // t = beta W^T + bias, once every bias has arrived
             if (w.gamma && w.bias) launch_add_vec(w.tvec, w.bias, (int)w.rows, c->stream);
-        HIP_TRY(c, hipMemcpyAsync((void*)c->s.layers_dev, c->layers.data(), sizeof(LayerW) * c->layers.size(),
-                                  hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync((void*)c->s.draft_dev, c->draft.data(), sizeof(DraftW) * c->draft.size(),
-                                  hipMemcpyHostToDevice, c->stream));
-    }
-    if (c->cfg.dtype) {
-        const StepParams P = base_params(c, make_dims(c, 1, 1));
-        launch_build_gtab(P, (uint32_t*)c->s.gtab, c->stream);
     }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipGetLastError());
-    c->gtab_ready = c->cfg.dtype != 0;
     c->state = 1;
     return VADUSA_OK;
 }
@@ -489,38 +445,17 @@ extern "C" int vadusa_load_weights(vadusa_ctx* c, const float* blob, size_t n_fl
 // ---------------------------------------------------------------------------
 static void gemm(vadusa_ctx* c, const GemmArgs& a) { launch_gemm_simple(a, 0, c->stream); }
 
-// bf16 model: run phases [lo, hi) of the step kernel (see k_step.hip)
-static int run_phases(vadusa_ctx* c, const Dims& D, int table, int prefill_mode, int tau, int lo, int hi,
-                      int seq0, int nseq, float* rank_rows = nullptr) {
-    // Rows of more than 4096 logits: the draft lists come from the stand-alone top-k kernel (it
-    // handles such rows slice by slice; the step kernel's own top-k phase would re-scan the row
-    // once per list entry)
-    const bool topk_apart = D.V1 > 4096 && hi == 1 + 5 * D.Ly + TP_COUNT;
-    StepParams P = base_params(c, D);
-    if (rank_rows) P.s.logits = rank_rows;   // acceptance and continuation rank these rows instead of the logits
-    P.table = table; P.prefill_mode = prefill_mode; P.tau = tau;
-    P.ignore_eos = c->cfg.ignore_eos; P.ph_lo = lo; P.ph_hi = hi; P.persistent = c->persistent; P.profile = c->profile; P.wide = D.B * D.M >= 256; P.mid = !P.wide && D.B * D.M > 64;
-    P.epoch = c->epoch; P.seq0 = seq0; P.nseq = nseq; P.topk_apart = topk_apart;
-    {
-        const int Hp = 1 + 5 * D.Ly;
-        P.fuse_select = c->persistent && !prefill_mode && lo <= Hp + TP_SELECT && hi > Hp + TP_FINAL;
-    }
-    if (!c->gtab_ready) P.s.gtab = nullptr;
-    hipError_t e;
-    launch_step(P, c->n_cus, c->stream, &e);
-    if (e != hipSuccess) return fail(c, VADUSA_EHIP, "step kernel launch failed: %s", hipGetErrorString(e));
-    if (c->persistent) { const int live = step_live_phases(P); c->epoch += (uint32_t)(live > 0 ? live - 1 : 0); }
-    if (topk_apart) launch_topk(D, c->s, seq0, nseq, c->stream);
-    return VADUSA_OK;
+static int launched(vadusa_ctx* c) {
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? VADUSA_OK : fail(c, VADUSA_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
 }
 
-// After a synchronisation: did a kernel give up at a grid barrier?
+// After a synchronisation: was the error word raised?
 static int kerr_seen(vadusa_ctx* c, int32_t k) {
     if (k) {
-        // The launch that gave up left the barrier counters and the decoding state half-way: nothing the context
-        // holds can be trusted until vadusa_prefill has reset it (see recover()).
+        // Nothing the context holds can be trusted until vadusa_prefill has reset it (see recover()).
         c->errored = 1;
-        return fail(c, VADUSA_EHIP, "the step kernel timed out at a grid barrier; vadusa_prefill resets the context");
+        return fail(c, VADUSA_EHIP, "a kernel raised the error word; vadusa_prefill resets the context");
     }
     return VADUSA_OK;
 }
@@ -531,19 +466,17 @@ static int check_kerr(vadusa_ctx* c) {
     return kerr_seen(c, k);
 }
 
-// Every call except vadusa_prefill, vadusa_load_weights and vadusa_destroy refuses a context whose kernel gave up.
+// Every call except vadusa_prefill, vadusa_load_weights and vadusa_destroy refuses a context whose error word was raised.
 static int refuse_errored(vadusa_ctx* c) {
-    if (c->errored) return fail(c, VADUSA_ESTATE, "a step kernel gave up at a grid barrier earlier; vadusa_prefill resets the context");
+    if (c->errored) return fail(c, VADUSA_ESTATE, "a kernel raised the error word earlier; vadusa_prefill resets the context");
     return VADUSA_OK;
 }
 
-// Back to a clean start after a kernel gave up: nothing is running (the stream is drained), the barrier counters,
-// the error word and the host's epoch start again from zero.  The decoding state is rebuilt by the prefill that follows.
+// Back to a clean start after the error word was raised: nothing is running (the stream is drained), the error word
+// starts again from zero.  The decoding state is rebuilt by the prefill that follows.
 static int recover(vadusa_ctx* c) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    HIP_TRY(c, hipMemset(c->s.bar, 0, (size_t)VADUSA_BAR_WORDS * 4));
     HIP_TRY(c, hipMemset(c->s.kerr, 0, 16));
-    c->epoch = 0;
     c->errored = 0;
     std::fill(c->pending.begin(), c->pending.end(), 0);
     if (c->state > 1) c->state = 1;
@@ -672,10 +605,11 @@ extern "C" int vadusa_prefill(vadusa_ctx* c, int32_t batch, const int32_t* text_
         HIP_TRY(c, hipMemcpyAsync(s.n_rows, rows.data(), rows.size() * 4, hipMemcpyHostToDevice, c->stream));
         const bool last = ch == max_chunks - 1;
         if (c->cfg.dtype) {
-            // bf16 model: the chunk is a causal "tree" for the step kernel; the last chunk also runs
-            // the base head, the continuation and the draft heads (acceptance has no units here)
-            const int H = 1 + 5 * D.Ly;
-            int rc = run_phases(c, D, 1, 1, 1, 0, last ? H + TP_COUNT : H, 0, batch);
+            // bf16 model: the chunk is a causal "tree"; the last chunk also runs the base head, the continuation and the
+            // draft heads
+            launch_layers(D, s, c->layers, 1, 1, last, c->big_min, c->stream);
+            if (last) launch_continue(D, s, c->draft, 0, batch, 1, c->cfg.ignore_eos, false, c->stream);
+            int rc = launched(c);
             if (rc) return rc;
         } else {
             forward(c, D, 1, 1, last);
@@ -793,16 +727,12 @@ static int verify_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau,
     DevState sr = s;
     if (sp) sr.logits = c->scores;
     if (c->cfg.dtype) {
-        const int H = 1 + 5 * D.Ly;
-        const int end = fuse_compact ? H + TP_COUNT : H + TP_FINAL;
-        if (sp) {
-            rc = run_phases(c, D, 0, 0, tau, 0, H + TP_EDGES, 0, B);
-            if (rc) return rc;
-            launch_perturb(s.logits, c->uniforms, c->scores, B * M, D.V1, sp->temperature, sp->top_p, tau, c->stream);
-            rc = run_phases(c, D, 0, 0, tau, H + TP_EDGES, end, 0, B, c->scores);
-        } else {
-            rc = run_phases(c, D, 0, 0, tau, 0, end, 0, B);
-        }
+        launch_layers(D, s, c->layers, 0, 0, true, c->big_min, c->stream);
+        if (sp) launch_perturb(s.logits, c->uniforms, c->scores, B * M, D.V1, sp->temperature, sp->top_p, tau, c->stream);
+        // the path is chosen beside the continuation where that follows at once
+        launch_verify_tail(D, sr, tau, c->cfg.ignore_eos, !fuse_compact, c->stream);
+        if (fuse_compact) launch_continue(D, sr, c->draft, 0, B, 0, c->cfg.ignore_eos, true, c->stream);
+        rc = launched(c);
         if (rc) return rc;
     } else {
         forward(c, D, 0, 0, true);
@@ -861,12 +791,14 @@ extern "C" int vadusa_kv_compact(vadusa_ctx* c, int32_t seq, const int32_t* path
         }
     }
     if (c->cfg.dtype) {
-        const int H = 1 + 5 * D.Ly;
-        int rc = run_phases(c, D, 0, 0, 1, H + TP_FINAL, H + TP_COUNT, seq0, nseq, c->sampled ? c->scores : nullptr);
+        DevState sr = s;
+        if (c->sampled) sr.logits = c->scores;   // the next root is the first draw at the last committed node
+        launch_continue(D, sr, c->draft, seq0, nseq, 0, c->cfg.ignore_eos, false, c->stream);
+        int rc = launched(c);
         if (rc) return rc;
     } else {
         DevState sr = s;
-        if (c->sampled) sr.logits = c->scores;   // the next root is the first draw at the last committed node
+        if (c->sampled) sr.logits = c->scores;
         launch_finalize(D, sr, seq0, nseq, 0, c->cfg.ignore_eos, 0, c->stream);
         launch_commit_kv(D, s, seq0, nseq, 0, c->stream);
         draft_heads(c, D, seq0, nseq);
@@ -944,7 +876,7 @@ extern "C" int vadusa_debug_read(vadusa_ctx* c, int32_t what, void* host, size_t
     const size_t B = c->batch, M = c->M, d = c->cfg.d_model, V1 = c->cfg.speech_vocab + 1, Hh = c->cfg.n_draft_heads;
     const size_t Bmax = c->cfg.max_batch;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (what != VADUSA_DBG_PHASE_CLOCK) { int rc = check_kerr(c); if (rc) return rc; }   // data of a launch that gave up is never handed out
+    if (what != VADUSA_DBG_PHASE_CLOCK) { int rc = check_kerr(c); if (rc) return rc; }   // data behind a raised error word is never handed out
     const void* src = nullptr;
     size_t need = 0;
     switch (what) {
@@ -966,7 +898,7 @@ extern "C" int vadusa_debug_read(vadusa_ctx* c, int32_t what, void* host, size_t
     case VADUSA_DBG_H_NODES: {
         need = B * M * d * 4;
         if (bytes != need) return fail(c, VADUSA_EINVAL, "expected %zu bytes", need);
-        if (c->cfg.dtype)   // the step kernel keeps no node states: recompute them from the residual stream
+        if (c->cfg.dtype)   // the bf16 kernels keep no node states: recompute them from the residual stream
             launch_layernorm(s.x, s.lnf_g, s.lnf_b, s.hn, (int)(B * M), (int)d, 1, c->stream);
         launch_to_float(s.hn, s.staging, B * M * d, c->cfg.dtype, c->stream);
         HIP_TRY(c, hipStreamSynchronize(c->stream));

@@ -24,10 +24,9 @@ __device__ __forceinline__ float ldf(const bf16_t* p) { return bf2f(*p); }
 __device__ __forceinline__ void stf(float* p, float v) { *p = v; }
 __device__ __forceinline__ void stf(bf16_t* p, float v) { *p = f2bf(v); }
 
-// Every pointer the kernels dereference points into device (global) memory.  A pointer that
-// reaches a function as an argument, or is read from a parameter block in LDS, is a generic
-// pointer to the compiler and would be accessed with FLAT instructions (slower to issue, and
-// tied to the LDS counter as well); the helpers below state the address space.
+// Every pointer the kernels dereference points into device (global) memory.  A pointer read from
+// memory is a generic pointer to the compiler and would be accessed with FLAT instructions (slower
+// to issue, and tied to the LDS counter as well); the helpers below state the address space.
 #if defined(__HIP_DEVICE_COMPILE__)
 #define VADUSA_GLOBAL __attribute__((address_space(1)))
 #else
@@ -35,22 +34,6 @@ __device__ __forceinline__ void stf(bf16_t* p, float v) { *p = f2bf(v); }
 #endif
 template <class T>
 __device__ __forceinline__ T ldg(const T* p) { return *(const VADUSA_GLOBAL T*)p; }   // scalar T only
-// A pointer that is the same in every lane (read from the parameter block, derived from the unit
-// number): moved to scalar registers, so that loads can use "scalar base + lane offset" addresses.
-template <class T>
-__device__ __forceinline__ T* uniform_ptr(T* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (T*)(((uint64_t)hi << 32) | lo);
-}
-// Makes a loaded value count as used (the load stays, and is waited for here) without storing it anywhere.
-__device__ __forceinline__ void keep_alive(uint32_t v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : : "v"(v));
-#else
-    (void)v;
-#endif
-}
 // 8- and 16-byte loads (HIP's uint2 / uint4 / float2 are classes: their copy would go back to a generic reference)
 typedef uint32_t vadusa_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t vadusa_u32x2 __attribute__((ext_vector_type(2)));
@@ -68,36 +51,11 @@ __device__ __forceinline__ float2 ldgf2(const void* p) {
 }
 
 // Stores / loads that are coherent across the whole GPU without cache maintenance
-// (write-through to / read from the memory side).  The persistent step kernel uses them
-// for every value that crosses workgroups inside one launch.
+// (write-through to / read from the memory side), for values that a workgroup reads back through memory.
 __device__ __forceinline__ void stw32(void* p, uint32_t v) {
     __hip_atomic_store((VADUSA_GLOBAL uint32_t*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void stw64(void* p, uint64_t v) {
-    __hip_atomic_store((VADUSA_GLOBAL uint64_t*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// 16 bytes at once (no atomic type is that wide: the store instruction itself, with the same agent-scope bit; the
-// compiler does not count it among the outstanding memory operations, which only makes its later waits stricter).
-// A store of more than 8 bytes reads its data registers a little after it issues, and a vector instruction that
-// overwrites them must keep two wait states' distance: the compiler inserts those after the stores it knows, not
-// after inline assembly, so they are part of the statement.
-__device__ __forceinline__ void stw128(void* p, uint4 v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    typedef uint32_t u32x4_st __attribute__((ext_vector_type(4)));
-    const u32x4_st d = {v.x, v.y, v.z, v.w};
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(d) : "memory");
-#else
-    *(uint4*)p = v;
-#endif
-}
-__device__ __forceinline__ void stw16(void* p, uint16_t v) {
-    __hip_atomic_store((VADUSA_GLOBAL uint16_t*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ void stwi(int32_t* p, int32_t v) { stw32(p, (uint32_t)v); }
-__device__ __forceinline__ void stwf(float* p, float v) { stw32(p, __float_as_uint(v)); }
-__device__ __forceinline__ void stwf2(float* p, float a, float b) {
-    stw64(p, (uint64_t)__float_as_uint(a) | ((uint64_t)__float_as_uint(b) << 32));
-}
 __device__ __forceinline__ int32_t ldci(const int32_t* p) {
     return __hip_atomic_load((const VADUSA_GLOBAL int32_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -119,6 +77,7 @@ __device__ __forceinline__ size_t toff(int r, int k, int nks) {
 //      after S^T = K Q^T holds them for eight consecutive keys: exactly a B fragment of P^T for O^T += V^T P^T.)
 //   V: [block of 32 keys][dimension tile dt = dim >> 4][lane][8]: lane = (dim & 15) + 16 * ((pos & 31) >> 3),
 //      element pos & 7 (V transposed: a lane holds eight consecutive positions of one dimension).
+__host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ inline int kv_cap(int maxpos) { return (maxpos + 31) & ~31; }
 __host__ __device__ inline size_t kc_off(int pos, int dim) {
     const int k = pos & 31, t = (k >> 2) & 1, c = ((k >> 3) << 2) | (k & 3);
@@ -133,6 +92,19 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_cvt;
     const f32x2_cvt v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_cvt));
+}
+
+// GELU with the exact (erf) definition; erf by the rational approximation 7.1.26 of Abramowitz &
+// Stegun (absolute error below 1.5e-7, the size of an fp32 rounding of the result, which is then
+// stored as bf16): one exponential, one reciprocal and a fifth-degree polynomial instead of the
+// library routine's two branches.
+__device__ __forceinline__ float gelu_s(float v) {
+    const float x = fabsf(v) * 0.70710678118654752f;
+    const float t = __builtin_amdgcn_rcpf(1.f + 0.3275911f * x);   // one instruction, 1 ulp: far below the approximation's own error
+    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
+    const float erfc_x = poly * __expf(-x * x);            // 1 - erf(|x|)
+    const float one_plus_erf = v < 0.f ? erfc_x : 2.f - erfc_x;
+    return 0.5f * v * one_plus_erf;
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -218,7 +190,7 @@ struct Dims {
 struct LayerW {
     const float *ln1_g, *ln1_b, *bqkv, *bo, *ln2_g, *ln2_b, *b1, *b2;
     const void *Wqkv, *Wo, *W1, *W2;   // element type follows the context dtype
-    // bf16 model only: LayerNorm folded into the following linear map (see k_step.hip)
+    // bf16 model only: LayerNorm folded into the following linear map (see k_layer.hip)
     float *cs_qkv, *t_qkv, *cs_w1, *t_w1;
 };
 struct DraftW {
@@ -232,27 +204,19 @@ struct DevState {
     const float *lnf_g, *lnf_b;
     const void* W_out;
     float *cs_out, *t_out;          // bf16 model: folded final LayerNorm for the vocabulary map
-    const LayerW* layers_dev;       // bf16 model: the layer table in device memory
-    const DraftW* draft_dev;
     // KV cache, element type = dtype: K [Ly][Bmax][nH][maxpos][64], V [Ly][Bmax][nH][64][maxpos]
     void *Kc, *Vc;
     // activations
     float* x;        // [R][d]  residual stream
-    // bf16 model, persistent step kernel.  Buffers that cross workgroups are written once
-    // per launch, so there is one instance per producer: xb / stats have 2*Ly+1 slots
-    // (embedding, then after the out-projection and after FFN2 of every layer), q / att /
-    // hid one slot per layer.  Slot strides are in elements.
-    bf16_t* xb;      // [2Ly+1][R][d]  bf16 copy of the residual stream
-    float* stats;    // [2Ly+1][d/16][R][2] per 16-column tile: mean, sum of squared deviations
-    size_t act_stride, stats_stride, hid_stride, draft_stride;   // rows padded to a multiple of 16
-    uint32_t* bar;   // grid barrier: VADUSA_BAR_WORDS words; counters 64 words apart: 8 group counters, then 8 copies of the top counter
-    int32_t* kerr;   // [4] error flag raised by a kernel (barrier time-out)
-    const uint32_t* gtab;   // bf16 model: [5][VADUSA_GREC_WORDS] descriptors of the layers' linear maps (null: none)
-    long long* tprof; // [128][8] timing points of workgroup 0 in the last launch (device clock, 100 MHz)
+    bf16_t* xb;      // bf16 model: [R][d] copy of the residual stream, operand tiles (rows padded to a multiple of 16)
+    float* stats;    // bf16 model: [R][d/16][2] per 16-column tile: mean, sum of squared deviations
+    size_t draft_stride;   // elements from one draft head's rdraft to the next
+    int32_t* kerr;   // [4] error flag that the next synchronising call reports
+    long long* tprof; // [128][8] timing points (device clock, 100 MHz; -DVADUSA_CLOCK_BUILD)
     void* xn;        // [R][d]  LayerNorm output
-    void* q;         // [R][d]   (bf16 model: one slot per layer)
-    void* att;       // [R][d]   (bf16 model: one slot per layer)
-    void* hid;       // [R][F]   (bf16 model: one slot per layer)
+    void* q;         // [R][d]
+    void* att;       // [R][d]
+    void* hid;       // [R][F]
     void* hn;        // [R][d]  final-LayerNorm'd node states
     float* logits;   // [R][V1]
     void* hbest;     // [Bmax][d]
@@ -286,16 +250,11 @@ struct vadusa_ctx {
     std::vector<char> pending;   // per sequence: verification waits for compaction
     std::vector<int32_t> tree_parent, tree_rank, tree_depth;   // last uploaded tree
     size_t staging_floats;
-    int n_cus;                   // workgroups of the persistent step kernel (one per compute unit)
-    int persistent;              // 0: one launch per phase (debugging aid)
-    int profile;                 // 1: the step kernel records timing points (environment VADUSA_PHASE_CLOCK)
     float* uniforms;             // [max_batch * max_tree_nodes][V+1]: the caller's random numbers of a stochastic step
     float* scores;               // same shape: perturbed scores that replace the logits in such a step
     int sampled;                 // the pending / last verification was a stochastic one
-    int gtab_ready;              // the descriptor table of the layer maps has been written (after the weights are placed)
-    int big_min, allq_min;       // StepParams::big_min, allq_min (environment VADUSA_BIG_MIN_UNITS sets both, for tests of small shapes)
-    uint32_t epoch;              // grid-barrier epoch reached so far
-    int errored;                 // a step kernel gave up at a grid barrier: every call but vadusa_prefill refuses until that resets the context
+    int big_min;                 // many-row maps: k_big's tiles from this many on (environment VADUSA_BIG_MIN_UNITS, for tests of small shapes); 0: the rule
+    int errored;                 // the error word was raised: every call but vadusa_prefill refuses until that resets the context
     std::string err;
 };
 
@@ -323,48 +282,16 @@ struct GemmArgs {
     int M, nH, maxpos, d;
 };
 
-// Parameters of the persistent step kernel (bf16 model).
-struct StepParams {
-    Dims D;
-    DevState s;
-    int table;          // which tree table the rows use (0 tree, 1 causal chunk)
-    int prefill_mode;
-    int tau, ignore_eos;
-    int ph_lo, ph_hi;   // phases to run: [ph_lo, ph_hi)
-    int persistent;     // 1: one cooperative launch with grid barriers between phases
-    int wide;           // 1: B * M >= 256 rows: the layer maps and the base head use 64 x 64 output tiles
-    int mid;            // 1: 65 to 255 rows: QKV / FFN1 in 64 x 32 units, out-projection / FFN2 in 32 x 16 units
-    int profile;        // n > 0: workgroup n - 1 records timing points (costs a few hundred ns each)
-    uint32_t epoch;     // barrier epoch before the first barrier of this launch
-    int seq0, nseq;     // sequences the compaction phases act on
-    // Every layer's parameters sit at the same offsets from the previous layer's:
-    // layer l = layer 0 advanced by l * lw_stride bytes (likewise the draft heads), so no
-    // kernel has to fetch a parameter table from memory before it can address its weights.
-    LayerW lw0;
-    DraftW dw0;
-    size_t lw_stride, dw_stride;
-    int big_min;        // many-row kernel: a map takes 128 x 128 units if it has at least this many of them
-    int allq_min;       // many-row kernel: an attention unit is a whole (sequence, head) if there are at least this many
-    int topk_apart;     // 1: the last phase only compacts the KV cache; the draft lists come from the stand-alone top-k kernel
-    int fuse_select;    // 1: the continuation units choose their sequence's path themselves (the selection phase has no units)
-};
-// Phases of the step kernel after the decoder layers, as offsets from H = 1 + 5 * n_layers.
-// TP_COMMIT: first map of the draft heads; TP_TOPK: draft lists and, beside them (most workgroups
-// are idle in that phase), the compaction of the KV cache.
+// Phases of a bf16 step, as VADUSA_DBG_PHASE_CLOCK counts them: 0 embedding; 1 + 5 l .. layer l (QKV, attention,
+// out-projection, FFN1, FFN2); then H + TP_*, H = 1 + 5 * n_layers.  TP_COMMIT: first map of the draft heads; TP_TOPK: draft
+// lists and, beside them, the compaction of the KV cache.
 enum { TP_HEAD = 0, TP_EDGES, TP_SELECT, TP_FINAL, TP_COMMIT, TP_DRAFT2, TP_TOPK, TP_COUNT };
-int step_num_phases(int n_layers);
-// Phases of [ph_lo, ph_hi) that have units: a phase without units is skipped together with its grid barrier, so a
-// persistent launch passes this many barriers less one.
-int step_live_phases(const StepParams& p);
-// words of DevState::bar, the grid barrier's counters (16 of them, 64 words apart)
-#define VADUSA_BAR_WORDS 4096
-// One record per kind of layer phase: everything about a linear map that does not depend on the
-// launch (operand and result pointers of layer 0 with their advance per layer, K, N, epilogue),
-// written once per context by launch_build_gtab from the same code that otherwise derives it per unit.
-#define VADUSA_GREC_WORDS 32
-void launch_build_gtab(const StepParams& p, uint32_t* tab, hipStream_t st);
-// phase index: 0 embed; 1+5l.. layer l (qkv, attn, wo, ffn1, ffn2); then H + TP_*
-void launch_step(const StepParams& p, int n_cus, hipStream_t st, hipError_t* err);
+// bf16 model: embedding, decoder layers and (head) the vocabulary map (see k_layer.hip)
+void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st);
+// edge decisions, and (select) the path choice of every sequence
+void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eos, bool select, hipStream_t st);
+// (select: path choice,) continuation, draft heads, draft lists and KV compaction
+void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, hipStream_t st);
 void launch_pack_w_ln(const float* src, const float* gamma, const float* beta, void* dst, float* colsum,
                       float* tvec, int N, int K, hipStream_t st);
 void launch_add_vec(float* dst, const float* src, int n, hipStream_t st);

@@ -1,0 +1,892 @@
+// The decoder layers of the bf16 model, one launch per map: embedding, then per layer QKV, attention,
+// out-projection, FFN1 and FFN2, and the vocabulary map at the end (Sec. 2.1's tree-verify forward).
+//
+// Why launches and not one persistent kernel: on this GPU a launch that waits for the one before it costs 2.3 to
+// 2.8 us from end to end (chain of 256-workgroup kernels that read what the previous one wrote; host side 2.6 us,
+// less than a map takes), which is what a grid barrier with the write-through stores it needs cost inside one kernel
+// (1.6 us + 0.9 us of acknowledgement).  Between launches the caches are made coherent by the hardware, so results
+// are stored and read as ordinary memory, every map has a kernel with the registers and workgroups per compute unit
+// that suit it, and operand addresses come straight from the kernel arguments.
+//
+// LayerNorm is folded into the map that follows it:
+//   LN(x) W^T = rstd * (x (g*W)^T - mu * colsum(g*W)) + (beta W^T + bias),
+// so a map reads the bf16 copy of the raw residual stream and applies the row statistics in its epilogue.  The
+// statistics come from whoever wrote the residual stream (exact fp32 values, per 16 columns, [row][column tile]) and
+// are merged by the consumer: mean of the tile means; squared deviations = the tiles' own plus 16 x the spread of the
+// tile means, summed as distances from the row's first tile mean.  No atomics combine data: results are
+// bit-reproducible.
+#include <algorithm>
+#include <type_traits>
+
+#include "accept_dev.h"
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+// The compiler moves no instruction across a fence, and waits for a value at the place where it is declared arrived.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+#define ARRIVED(v) asm volatile("" : "+v"(v))
+#else
+#define SCHED_FENCE() ((void)0)
+#define ARRIVED(v) ((void)0)
+#endif
+
+enum { LE_QKV = 0, LE_GELU, LE_LOGITS, LE_RESID, LE_SILU, LE_F32 };   // LE_SILU, LE_F32: first and second map of the draft heads
+
+struct LinArgs {
+    const bf16_t* X;        // [R][K] operand tiles
+    const uint4* W;         // [N][K] operand tiles
+    const float *bias, *colsum;
+    const float2* stats;    // [R][K / 16] statistics of X's rows (LayerNorm-folded maps)
+    int nks, NT, R, N;      // K / 32, column tiles, rows, columns
+    bf16_t* out;            // operand tiles of the next map: q, hidden layer or the residual stream's bf16 copy
+    float* outf;            // logits, or the residual stream (LE_RESID)
+    float2* stats_out;      // [R][N / 16] (LE_RESID)
+    bf16_t *Kc, *Vc;        // LE_QKV: this layer's cache
+    const int32_t *L, *n_rows;
+    int M, nH, maxpos, d;
+    size_t z_w, z_b, z_x, z_out;   // LE_SILU, LE_F32: what a draft head's weights, bias (bytes), X and result (elements) are ahead of the previous head's
+};
+
+// Workgroup i runs on XCD i mod 8.  The first grid dimension counts column groups, padded to a multiple of 8, so that
+// the row blocks that share a weight tile share an XCD and its L2 and the tile leaves HBM once.
+__host__ __device__ inline int pad8(int a) { return (a + 7) & ~7; }
+
+// Sum over the two lanes l and l ^ 32.
+__device__ __forceinline__ float half_sum(float v) {
+    const vadusa_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
+// Row statistics of the LayerNorm folded into a map, for the ROWS rows of a workgroup, in two steps: request (ahead of
+// the operands, so that they return first) and merge (while the operands are on their way).  Eight (sixteen)
+// neighbouring lanes share a row and read its tile statistics two at a time, 128 (256) contiguous bytes per load.
+template <int ROWS>
+struct RowStats {
+    static constexpr int TPR = ROWS >= 32 ? 8 : 16, PASS = ROWS * TPR / 256, NV = 32 / TPR;   // NV loads: the 64 tiles of K = 1024
+    const float2* sp[PASS];
+    float c0[PASS];
+    uint4 v[PASS][NV];
+    __device__ __forceinline__ void request(const LinArgs& a, int row0) {
+        const int tiles = a.nks * 2, part = threadIdx.x % TPR;
+#pragma unroll
+        for (int p = 0; p < PASS; ++p) {
+            sp[p] = a.stats + (size_t)min(row0 + p * (256 / TPR) + (int)threadIdx.x / TPR, a.R - 1) * tiles;
+            c0[p] = ldg(&sp[p]->x);
+#pragma unroll
+            for (int j = 0; j < NV; ++j) v[p][j] = ldg4(sp[p] + (2 * (part + j * TPR) < tiles ? 2 * (part + j * TPR) : 0));
+        }
+    }
+    __device__ __forceinline__ void merge(const LinArgs& a, float* s_mean, float* s_rstd) {
+        const int tiles = a.nks * 2, part = threadIdx.x % TPR;
+#pragma unroll
+        for (int p = 0; p < PASS; ++p) {
+            float s1 = 0.f, s2 = 0.f, s3 = 0.f;   // sums of the tile means' distances from c0, of the tiles' squared deviations, of the squared distances
+            auto add = [&](const uint4& w) {
+                const float d0 = __uint_as_float(w.x) - c0[p], d1 = __uint_as_float(w.z) - c0[p];
+                s1 += d0 + d1;
+                s2 += __uint_as_float(w.y) + __uint_as_float(w.w);
+                s3 += d0 * d0 + d1 * d1;
+            };
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+                if (2 * (part + j * TPR) < tiles) add(v[p][j]);
+            for (int t = 2 * (part + NV * TPR); t < tiles; t += 2 * TPR) add(ldg4(sp[p] + t));
+            auto sum = [](float x) {
+                x = quad_sum(x);
+                x += __int_as_float(dpp_perm<0x141>(__float_as_int(x)));
+                if (TPR == 16) x += __int_as_float(dpp_perm<0x140>(__float_as_int(x)));
+                return x;
+            };
+            s1 = sum(s1);
+            s2 = sum(s2);
+            s3 = sum(s3);
+            if (part == 0) {
+                const int r = p * (256 / TPR) + (int)threadIdx.x / TPR;
+                const float m2 = s2 + 16.f * fmaxf(s3 - s1 * s1 / tiles, 0.f);
+                s_mean[r] = c0[p] + s1 / tiles;
+                s_rstd[r] = rsqrtf(m2 / (16 * tiles) + LN_EPS);
+            }
+        }
+    }
+};
+
+// Where row r of the QKV map goes in the cache: element offset of its sequence and position, or a negative position
+// if it has none (a finished sequence, or beyond the cache).
+struct KvRow { size_t base; int pos; };
+__device__ __forceinline__ KvRow kv_row(const LinArgs& a, int r) {
+    KvRow k{0, -1};
+    if (r >= a.R) return k;
+    const int b = r / a.M, pos = ldg(a.L + b) + (r - b * a.M);
+    k.base = (size_t)b * a.nH * kv_cap(a.maxpos) * 64;
+    if (pos < a.maxpos && ldg(a.n_rows + b) > 0) k.pos = pos;
+    return k;
+}
+
+// Stores four consecutive outputs of one row (columns n0 .. n0 + 3); LE_RESID: the new values of the residual stream.
+template <int EPI>
+__device__ __forceinline__ void store4(const LinArgs& a, int r, int n0, bool live, const float (&v)[4], const KvRow& kv) {
+    if constexpr (EPI == LE_LOGITS || EPI == LE_F32) {
+        if (live)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (n0 + j < a.N) a.outf[(size_t)r * a.N + n0 + j] = v[j];
+    } else if constexpr (EPI == LE_GELU) {
+        const uint2 pk = make_uint2(pack_bf16(gelu_s(v[0]), gelu_s(v[1])), pack_bf16(gelu_s(v[2]), gelu_s(v[3])));
+        if (live) *(uint2*)(a.out + toff(r, n0, a.N >> 5)) = pk;
+    } else if constexpr (EPI == LE_SILU) {
+        if (live) *(uint2*)(a.out + toff(r, n0, a.N >> 5)) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+    } else if constexpr (EPI == LE_RESID) {
+        if (live) {
+            *(float4*)(a.outf + (size_t)r * a.N + n0) = make_float4(v[0], v[1], v[2], v[3]);
+            *(uint2*)(a.out + toff(r, n0, a.N >> 5)) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+        }
+    } else {
+        const uint2 pk = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+        if (n0 < a.d) {
+            if (live) *(uint2*)(a.out + toff(r, n0, a.d >> 5)) = pk;
+        } else if (kv.pos >= 0) {
+            const int which = n0 >= 2 * a.d, cc = n0 - (which + 1) * a.d, head = cc >> 6, dim = cc & 63;
+            const size_t hb = kv.base + (size_t)head * kv_cap(a.maxpos) * 64;
+            if (which) {   // four dimensions of one position: four lanes of a value tile
+                bf16_t* vp = a.Vc + hb + vc_off(kv.pos, dim);
+                vp[0] = (bf16_t)pk.x; vp[8] = (bf16_t)(pk.x >> 16); vp[16] = (bf16_t)pk.y; vp[24] = (bf16_t)(pk.y >> 16);
+            } else {
+                *(uint2*)(a.Kc + hb + kc_off(kv.pos, dim)) = pk;   // four dimensions of one key: half of a lane's piece
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Linear map, one workgroup per 16 RT rows x 16 CT columns.  The four waves split the reduction; each loads its
+// operands (weights from HBM, activations from L2, both already in MFMA operand tiles: one contiguous KiB per wave
+// load) straight into registers, CH k-steps at a time with the next chunk's loads ahead of the current chunk's MFMAs;
+// the four partial sums are added in wave order through LDS.
+// ---------------------------------------------------------------------------
+template <int RT, int CT, int CH, int EPI>
+__global__ __launch_bounds__(256) void k_lin(LinArgs a) {
+    constexpr bool LN = EPI <= LE_LOGITS;
+    if constexpr (EPI == LE_SILU || EPI == LE_F32) {
+        const size_t z = blockIdx.z;
+        a.W = (const uint4*)((const char*)a.W + z * a.z_w);
+        a.bias = (const float*)((const char*)a.bias + z * a.z_b);
+        a.X += z * a.z_x;
+        a.out += z * a.z_out;
+        a.outf += z * a.z_out;
+    }
+    constexpr int T = RT * CT, NPW = (T + 3) / 4;   // output tiles, tiles per wave in the epilogue
+    constexpr int ROWS = RT == 3 ? 64 : RT * 16;   // rows whose statistics are merged
+    __shared__ f32x4_t red[4 * T * 64];
+    __shared__ float s_mean[ROWS], s_rstd[ROWS];
+    const int g = blockIdx.x, rb = blockIdx.y;
+    if (g * CT >= a.NT) return;   // padding of the XCD-aware numbering
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int lc = lane & 15, gq = lane >> 4, row0 = rb * RT * 16, last_rt = (a.R - 1) >> 4;
+    const int ks_lo = (a.nks * wave) >> 2, ks_hi = (a.nks * (wave + 1)) >> 2;
+    // epilogue inputs of this thread's tiles, and the row statistics: asked for first, needed last
+    float bias[NPW][4], cs[NPW][4], xr[NPW][4];
+    KvRow kv[NPW];
+    RowStats<ROWS> st;
+    if constexpr (LN) st.request(a, row0);
+#pragma unroll
+    for (int p = 0; p < NPW; ++p) {
+        const int t = wave + 4 * p, n0 = (g * CT + t % CT) * 16 + 4 * gq, r = row0 + (t / CT) * 16 + lc;
+        const bool have = t < T && g * CT + t % CT < a.NT;
+        uint4 b4 = make_uint4(0, 0, 0, 0), c4 = b4, x4 = b4;
+        kv[p] = KvRow{0, -1};
+        if (have) {
+            if (EPI != LE_F32) b4 = ldg4(a.bias + n0);
+            if (LN) c4 = ldg4(a.colsum + n0);
+            if (EPI == LE_RESID) x4 = ldg4(a.outf + (size_t)(r < a.R ? r : 0) * a.N + n0);
+            if (EPI == LE_QKV && n0 >= a.d) kv[p] = kv_row(a, r);
+        }
+        bias[p][0] = __uint_as_float(b4.x); bias[p][1] = __uint_as_float(b4.y); bias[p][2] = __uint_as_float(b4.z); bias[p][3] = __uint_as_float(b4.w);
+        cs[p][0] = __uint_as_float(c4.x); cs[p][1] = __uint_as_float(c4.y); cs[p][2] = __uint_as_float(c4.z); cs[p][3] = __uint_as_float(c4.w);
+        xr[p][0] = __uint_as_float(x4.x); xr[p][1] = __uint_as_float(x4.y); xr[p][2] = __uint_as_float(x4.z); xr[p][3] = __uint_as_float(x4.w);
+        if (EPI == LE_SILU && have) {   // the map's own input at the output's place (N = K)
+            const uint2 h = ldg2(a.X + toff(min(r, a.R - 1), n0, a.nks));
+            xr[p][0] = bf2f((bf16_t)h.x); xr[p][1] = bf2f((bf16_t)(h.x >> 16)); xr[p][2] = bf2f((bf16_t)h.y); xr[p][3] = bf2f((bf16_t)(h.y >> 16));
+        }
+    }
+    const char *Wp[CT], *Xp[RT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) Wp[c] = (const char*)(a.W + (size_t)min(g * CT + c, a.NT - 1) * a.nks * 64);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) Xp[r] = (const char*)((const uint4*)a.X + (size_t)min(rb * RT + r, last_rt) * a.nks * 64);
+    f32x4_t acc[CT][RT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) acc[c][r] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    // Loads are unconditional: a tile beyond the map's last row or column re-reads a valid one and only reaches
+    // accumulators that are never stored; a k-step beyond the last re-reads the last and is not multiplied.
+    uint4 wA[CH][CT], xA[CH][RT], wB[CH][CT], xB[CH][RT];
+    auto load = [&](int kb, uint4 (&w)[CH][CT], uint4 (&x)[CH][RT]) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const uint32_t off = (uint32_t)min(kb + i, a.nks - 1) * 1024u + (uint32_t)lane * 16u;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + off);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + off);
+        }
+    };
+    auto mul = [&](int n, const uint4 (&w)[CH][CT], const uint4 (&x)[CH][RT]) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+            if (i < n)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int r = 0; r < RT; ++r)   // weights first: a lane then holds four consecutive columns of one row
+                        acc[c][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[i][c]), __builtin_bit_cast(bf16x8_t, x[i][r]), acc[c][r], 0, 0, 0);
+    };
+    int kb = ks_lo;
+    load(kb, wA, xA);
+    if constexpr (LN) st.merge(a, s_mean, s_rstd);
+    bool in_a = true;
+    while (kb + CH < ks_hi) {
+        load(kb + CH, wB, xB);
+        mul(CH, wA, xA);
+        kb += CH;
+        in_a = false;
+        if (kb + CH >= ks_hi) break;
+        load(kb + CH, wA, xA);
+        mul(CH, wB, xB);
+        kb += CH;
+        in_a = true;
+    }
+    if (in_a) mul(ks_hi - kb, wA, xA);
+    else mul(ks_hi - kb, wB, xB);
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) red[(wave * T + r * CT + c) * 64 + lane] = acc[c][r];
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < NPW; ++p) {
+        const int t = wave + 4 * p;
+        if (t >= T) break;
+        const int c = t % CT, rl = (t / CT) * 16 + lc, r = row0 + rl, tile = g * CT + c, n0 = tile * 16 + 4 * gq;
+        if (tile >= a.NT) continue;
+        f32x4_t s = red[t * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) s += red[(w * T + t) * 64 + lane];
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float y = s[j];
+            if (LN) y = s_rstd[rl] * (y - s_mean[rl] * cs[p][j]);
+            v[j] = y + bias[p][j];
+            if (EPI == LE_RESID) v[j] += xr[p][j];
+            if (EPI == LE_SILU) v[j] = xr[p][j] + v[j] / (1.f + __expf(-v[j]));
+        }
+        if constexpr (EPI == LE_RESID) {   // statistics of the tile's 16 columns: four here, twelve in the lanes 16, 32 and 48 further on
+            const float mean = rows_sum(v[0] + v[1] + v[2] + v[3]) * (1.f / 16.f);
+            const float m2 = rows_sum((v[0] - mean) * (v[0] - mean) + (v[1] - mean) * (v[1] - mean) + (v[2] - mean) * (v[2] - mean) + (v[3] - mean) * (v[3] - mean));
+            if (r < a.R && gq == 0) a.stats_out[(size_t)r * (a.N >> 4) + tile] = make_float2(mean, m2);
+        }
+        store4<EPI>(a, r, n0, r < a.R, v, kv[p]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Linear map of many rows: one workgroup per 16 NRT rows x 64 NCT columns, wave w taking all rows and columns
+// 16 NCT w .. of them.  Activations pass through LDS (all four waves need all of them), weights go straight into the
+// registers of the one wave that needs them.  v_mfma_f32_32x32x16_bf16: with one wave per SIMD it reaches 2.26 PFLOP/s
+// where the 16 x 16 x 32 form reaches 1.4 (register operands, 256 workgroups); two row tiles (column tiles) and half
+// of their k-step make one operand, which is a permutation of the 16-byte pieces of the stored tiles.
+// The reduction runs in stages of two k-steps of 32.  A stage's activation tiles are fetched into registers by the four
+// waves (NRT / 2 tiles each), written to LDS two stages before they are multiplied, and four stages of activations and
+// three of weights are on their way behind the one being multiplied.
+// What bounds it: at 128 x 256 the compute unit pulls 24 KB and reads and writes 40 KB of LDS per k-step of 512
+// matrix-core clocks (48 B and 80 B per clock; 47 to 57 B per clock is what a compute unit gets through L2 when all
+// 256 pull).  With both operands through LDS and 64 x 64 per wave the LDS traffic alone would exceed the matrix cores'
+// time.
+// ---------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+// D = A B + C, A 32 x 16 (lane: row lane & 31, k 8 (lane >> 5) ..), B 16 x 32 alike; lane l, element i of D: column
+// l & 31, row (i & 3) + 8 (i >> 2) + 4 (l >> 5).
+__device__ __forceinline__ f32x16_t mfma_32x32(uint4 a, uint4 b, f32x16_t c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+#else   // host emulation of the kernels: the wave's operands meet in an array, between two lane exchanges
+    __shared__ uint4 ops[4][2][64];
+    const int w = (int)(threadIdx.x >> 6), l = (int)(threadIdx.x & 63);
+    ops[w][0][l] = a;
+    ops[w][1][l] = b;
+    (void)__shfl(0u, 0, 64);
+    for (int i = 0; i < 16; ++i)
+        for (int k = 0; k < 16; ++k) {
+            auto value = [&](int op, int row) { return bf2f(((const bf16_t*)&ops[w][op][row + 32 * (k >> 3)])[k & 7]); };
+            c[i] += value(0, (i & 3) + 8 * (i >> 2) + 4 * (l >> 5)) * value(1, l & 31);
+        }
+    (void)__shfl(0u, 0, 64);
+    return c;
+#endif
+}
+
+template <int NRT, int NCT, int DEPTH, int OCC, int EPI>
+__global__ __launch_bounds__(256, OCC) void k_big(LinArgs a) {
+    constexpr bool LN = EPI <= LE_LOGITS;
+    constexpr int ROWS = NRT * 16, NA = NRT / 2, NR2 = NRT / 2, NC2 = NCT / 2;   // NA: activation tiles a wave fetches per stage
+    __shared__ uint4 sA[4][NRT * 2 * 64];
+    __shared__ float s_mean[ROWS], s_rstd[ROWS];
+    const int ct0 = blockIdx.x * 4 * NCT, rb = blockIdx.y;
+    if (ct0 >= a.NT) return;   // padding of the XCD-aware numbering
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int row0 = rb * ROWS, last_rt = (a.R - 1) >> 4;
+    const int wt0 = ct0 + wave * NCT;      // this wave's first column tile
+    const int nst = a.nks >> 1;            // stages (K is a multiple of 64)
+    RowStats<ROWS> st;
+    if constexpr (LN) st.request(a, row0);
+    // Tiles beyond the map's last row or column re-read a valid one and only reach accumulators that are never stored.
+    const char* Xp[NA];
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {         // the wave's tiles of a stage: T = wave + 4 j is row tile T >> 1, k-step T & 1
+        const int T = wave + 4 * j;
+        Xp[j] = (const char*)((const uint4*)a.X + ((size_t)min(rb * NRT + (T >> 1), last_rt) * a.nks + (T & 1)) * 64);
+    }
+    const int second = (lane >> 4) & 1, piece = (lane & 15) + 16 * (lane >> 5);   // operand lane -> tile of the pair, piece of the tile's first half
+    uint32_t woff[NC2];
+#pragma unroll
+    for (int c = 0; c < NC2; ++c) woff[c] = (uint32_t)min(wt0 + 2 * c + second, a.NT - 1) * (uint32_t)a.nks * 1024u + (uint32_t)piece * 16u;
+    auto loadA = [&](int c, uint4 (&x)[NA]) {
+        const uint32_t off = (uint32_t)min(c, nst - 1) * 2048u + (uint32_t)lane * 16u;
+#pragma unroll
+        for (int j = 0; j < NA; ++j) x[j] = ldg4(Xp[j] + off);
+    };
+    auto loadW = [&](int c, uint4 (&w)[4][NC2]) {   // the four operand halves (k-step, half) of the stage
+        const char* base = (const char*)a.W + (uint32_t)min(c, nst - 1) * 2048u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < NC2; ++i) w[q][i] = ldg4(base + q * 512 + woff[i]);
+    };
+    auto writeA = [&](int buf, const uint4 (&x)[NA]) {
+#pragma unroll
+        for (int j = 0; j < NA; ++j) sA[buf][(wave + 4 * j) * 64 + lane] = x[j];
+    };
+    f32x16_t acc[NC2][NR2];
+#pragma unroll
+    for (int c = 0; c < NC2; ++c)
+#pragma unroll
+        for (int r = 0; r < NR2; ++r)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[c][r][i] = 0.f;
+    auto readA = [&](int buf, int k, uint4 (&x)[2][NR2]) {   // both halves of k-step k
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < NR2; ++r) x[h][r] = sA[buf][((2 * r + second) * 2 + k) * 64 + 32 * h + piece];
+    };
+    auto mul = [&](const uint4 (&x)[2][NR2], const uint4 (&w0)[NC2], const uint4 (&w1)[NC2]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < NR2; ++r)
+#pragma unroll
+                for (int c = 0; c < NC2; ++c)   // weights first: a lane then holds groups of four consecutive columns of one row
+                    acc[c][r] = mfma_32x32(h ? w1[c] : w0[c], x[h][r], acc[c][r]);
+    };
+    // Stage c reads LDS buffer c mod 4 and weight set c mod 4; set (c + 2) mod 4 of the activation registers holds stage
+    // c + 2, which goes into buffer (c + 2) mod 4, last read in stage c - 2.  The first k-step's operands of stage c are
+    // read at the end of stage c - 1, so that no multiplication waits for LDS; the scheduling fences keep the compiler
+    // from moving the reads next to their uses.  Every load, copy and read is unconditional, so that the waits count exactly
+    // the loads issued since: past the end the last stage is fetched again (from L2) and never multiplied.
+    uint4 A[DEPTH][NA], W[DEPTH][4][NC2], x0[2][NR2], x1[2][NR2];
+    loadA(0, A[0]);
+    loadA(1, A[1]);
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i) {
+        loadW(i, W[i]);
+        if (i >= 2) loadA(i, A[i]);
+    }
+    if constexpr (LN) st.merge(a, s_mean, s_rstd);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        writeA(i, A[i]);
+        loadA(DEPTH + i, A[i]);
+    }
+    __syncthreads();
+    readA(0, 0, x0);
+    auto stage = [&](int c, auto bc) {
+        constexpr int b = decltype(bc)::value;   // c mod 4
+        readA(b, 1, x1);
+        writeA((b + 2) & 3, A[(b + 2) % DEPTH]);
+        loadA(c + 2 + DEPTH, A[(b + 2) % DEPTH]);
+        SCHED_FENCE();
+        mul(x0, W[b % DEPTH][0], W[b % DEPTH][1]);
+        __syncthreads();
+        readA((b + 1) & 3, 0, x0);
+        SCHED_FENCE();
+        mul(x1, W[b % DEPTH][2], W[b % DEPTH][3]);
+        loadW(c + DEPTH, W[b % DEPTH]);
+        SCHED_FENCE();
+    };
+    constexpr std::integral_constant<int, 0> b0{};
+    constexpr std::integral_constant<int, 1> b1{};
+    constexpr std::integral_constant<int, 2> b2{};
+    constexpr std::integral_constant<int, 3> b3{};
+    int c = 0;
+    for (; c + 4 <= nst; c += 4) {
+        stage(c, b0);
+        stage(c + 1, b1);
+        stage(c + 2, b2);
+        stage(c + 3, b3);
+    }
+    if (c < nst) {
+        stage(c, b0);
+        if (c + 1 < nst) {
+            stage(c + 1, b1);
+            if (c + 2 < nst) stage(c + 2, b2);
+        }
+    }
+    // Everything the epilogue reads arrives before its first store: a wait between the stores would wait for them too
+    // (loads and stores share one counter).
+    const int lr = lane & 31, hi = lane >> 5;   // the lane's row of a 32-row block; its columns of a block: 8 q + 4 hi .. + 3, q = 0 .. 3
+    KvRow kv[NR2];
+    float mean[NR2], rstd[NR2];
+#pragma unroll
+    for (int ri = 0; ri < NR2; ++ri) {
+        kv[ri] = KvRow{0, -1};
+        if (EPI == LE_QKV && wt0 * 16 + 16 * NCT > a.d) kv[ri] = kv_row(a, row0 + ri * 32 + lr);
+        mean[ri] = LN ? s_mean[ri * 32 + lr] : 0.f;
+        rstd[ri] = LN ? s_rstd[ri * 32 + lr] : 1.f;
+    }
+#pragma unroll
+    for (int ci = 0; ci < NC2; ++ci) {
+        float bias[4][4], cs[4][4], xr[NR2][4][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int tile = min(wt0 + 2 * ci + (q >> 1), a.NT - 1), n0 = tile * 16 + 8 * (q & 1) + 4 * hi;
+            const uint4 b4 = ldg4(a.bias + n0), c4 = LN ? ldg4(a.colsum + n0) : make_uint4(0, 0, 0, 0);
+            bias[q][0] = __uint_as_float(b4.x); bias[q][1] = __uint_as_float(b4.y); bias[q][2] = __uint_as_float(b4.z); bias[q][3] = __uint_as_float(b4.w);
+            cs[q][0] = __uint_as_float(c4.x); cs[q][1] = __uint_as_float(c4.y); cs[q][2] = __uint_as_float(c4.z); cs[q][3] = __uint_as_float(c4.w);
+            if constexpr (EPI == LE_RESID)
+#pragma unroll
+                for (int ri = 0; ri < NR2; ++ri) {
+                    const uint4 x4 = ldg4(a.outf + (size_t)min(row0 + ri * 32 + lr, a.R - 1) * a.N + n0);
+                    xr[ri][q][0] = __uint_as_float(x4.x); xr[ri][q][1] = __uint_as_float(x4.y); xr[ri][q][2] = __uint_as_float(x4.z); xr[ri][q][3] = __uint_as_float(x4.w);
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            ARRIVED(bias[q][0]); ARRIVED(cs[q][0]);
+            if constexpr (EPI == LE_RESID)
+#pragma unroll
+                for (int ri = 0; ri < NR2; ++ri) ARRIVED(xr[ri][q][0]);
+        }
+        if (EPI == LE_QKV)
+#pragma unroll
+            for (int ri = 0; ri < NR2; ++ri) ARRIVED(kv[ri].pos);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int tile = wt0 + 2 * ci + t;
+            if (tile >= a.NT) break;
+#pragma unroll
+            for (int ri = 0; ri < NR2; ++ri) {
+                const int r = row0 + ri * 32 + lr;
+                float v[2][4];
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int q = 2 * t + g;
+                        float y = acc[ci][ri][4 * q + j];
+                        if (LN) y = rstd[ri] * (y - mean[ri] * cs[q][j]);
+                        v[g][j] = y + bias[q][j];
+                        if (EPI == LE_RESID) v[g][j] += xr[ri][q][j];
+                    }
+                if constexpr (EPI == LE_RESID) {
+                    // statistics of the tile's 16 columns: eight here, eight in the lane 32 further on
+                    const float mu = half_sum(((v[0][0] + v[0][1]) + (v[0][2] + v[0][3])) + ((v[1][0] + v[1][1]) + (v[1][2] + v[1][3]))) * (1.f / 16.f);
+                    float sq = 0.f;
+#pragma unroll
+                    for (int g = 0; g < 2; ++g)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) sq += (v[g][j] - mu) * (v[g][j] - mu);
+                    sq = half_sum(sq);
+                    if (r < a.R && hi == 0) a.stats_out[(size_t)r * (a.N >> 4) + tile] = make_float2(mu, sq);
+                }
+#pragma unroll
+                for (int g = 0; g < 2; ++g) store4<EPI>(a, r, tile * 16 + 8 * g + 4 * hi, r < a.R, v[g], kv[ri]);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Tree-masked attention (Sec. 2.1): one (sequence, head) and 16 query rows per workgroup.  Keys: cache positions
+// [0, L) and the rows of this forward at L + m where the query's mask bit m is set (CAUSAL: rows 0 .. n of a prompt
+// pass, which may have more rows than the mask table).  The four waves take 32-key blocks round-robin with a private
+// online softmax (S^T = K Q^T, O^T += V^T P^T on MFMA) and merge through LDS.  The cache keeps K and V^T in blocks of
+// 32 keys, each already in the layout of the MFMA operands (kc_off / vc_off in common.h).
+// ---------------------------------------------------------------------------
+struct AttnArgs {
+    const bf16_t* q;
+    bf16_t* att;
+    const bf16_t *Kc, *Vc;   // this layer's cache
+    const int32_t *L, *n_rows;
+    const uint32_t* mask;
+    int B, M, nH, d, maxpos;
+};
+template <bool CAUSAL>
+__global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
+    constexpr int SO = 17;   // floats per row of the merge buffer: the merge reads a dimension's 16 queries' worth 64 rows apart
+    __shared__ float sm_o[4 * 64 * SO], sm_m[64], sm_l[64];
+    const int bh = blockIdx.x, qt = blockIdx.y;
+    if (bh >= a.B * a.nH) return;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, gq = lane >> 4, c = lane & 15;
+    const int b = bh / a.nH, h = bh - b * a.nH;
+    const int n_rows = ldg(a.n_rows + b), L = ldg(a.L + b);
+    const int node = min(qt * 16 + c, a.M - 1);
+    const bf16x8_t Q0 = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(b * a.M + node, h * 64 + 8 * gq, a.d >> 5)));
+    const bf16x8_t Q1 = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(b * a.M + node, h * 64 + 32 + 8 * gq, a.d >> 5)));
+    uint4 mw = make_uint4(0, 0, 0, 0);
+    if constexpr (!CAUSAL) mw = ldg4(a.mask + (size_t)node * MASK_WORDS);
+    const int q_out = tid >> 4, d_out = (tid & 15) * 4, nd_out = qt * 16 + q_out;   // the merge's outputs of this thread
+    bf16_t* const dst = a.att + toff(b * a.M + min(nd_out, a.M - 1), h * 64 + d_out, a.d >> 5);
+    if (n_rows == 0) {
+        if (nd_out < a.M) *(uint2*)dst = make_uint2(0, 0);
+        return;
+    }
+    // (a causal pass: no query of the tile sees keys behind its last row)
+    const int T = min(CAUSAL ? L + min(qt * 16 + 16, a.M) : L + a.M, a.maxpos);
+    const size_t hb = ((size_t)b * a.nH + h) * kv_cap(a.maxpos) * 64;
+    const bf16_t *Kh = a.Kc + hb + lane * 8, *Vh = a.Vc + hb + lane * 8;
+    const int nblk = (T + 31) >> 5;
+    auto load_block = [&](int blk, uint4 (&kvb)[8]) {
+        const uint32_t off = (uint32_t)min(blk, nblk - 1) * 2048u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { kvb[i] = ldg4(Kh + off + i * 512); kvb[4 + i] = ldg4(Vh + off + i * 512); }
+    };
+    float m_run = -1e30f, l_run = 0.f;
+    f32x4_t O[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) O[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    constexpr int NB = 3;   // two blocks in flight behind the one being computed
+    uint4 buf[NB][8];
+    if (wave < nblk) {
+#pragma unroll
+        for (int j = 0; j < NB - 1; ++j) load_block(wave + 4 * j, buf[j]);
+    }
+    auto process = [&](const int blk, const uint4 (&cur)[8]) {
+        const int p0 = blk << 5, v0 = p0 + 8 * gq;
+        f32x4_t sa = (f32x4_t){0.f, 0.f, 0.f, 0.f}, sb = sa;
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[0]), Q0, sa, 0, 0, 0);
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[1]), Q1, sa, 0, 0, 0);
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[2]), Q0, sb, 0, 0, 0);
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[3]), Q1, sb, 0, 0, 0);
+        // this lane: query c, keys v0 + 0..3 (sa) and v0 + 4..7 (sb).  Instantiated twice: blocks inside the committed
+        // cache need no mask tests.
+        uint32_t pk[4];
+        float m_new, corr, psum = 0.f;
+        auto softmax_block = [&](const unsigned okm) {
+            float sc[8];
+            float mx = -1e30f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float sv = (j < 4 ? sa[j] : sb[j - 4]) * 0.125f;
+                sc[j] = (okm >> j) & 1u ? sv : -1e30f;
+                mx = fmaxf(mx, sc[j]);
+            }
+            mx = rows_max(mx);
+            m_new = fmaxf(m_run, mx);
+            corr = __expf(m_run - m_new);
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) {
+                const float p0f = (okm >> j) & 1u ? __expf(sc[j] - m_new) : 0.f;
+                const float p1f = (okm >> (j + 1)) & 1u ? __expf(sc[j + 1] - m_new) : 0.f;
+                psum += p0f + p1f;
+                pk[j >> 1] = pack_bf16(p0f, p1f);
+            }
+        };
+        if (p0 + 32 > L) {   // the block reaches into this forward's rows (same for the whole wave)
+            unsigned okm = 0;   // which of the lane's 8 keys the query may see
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int key = v0 + j, mm = key - L;
+                bool okj = key < L;
+                if (!okj && key < T) {
+                    if constexpr (CAUSAL) okj = mm <= node;
+                    else {
+                        const uint32_t w = mm < 32 ? mw.x : mm < 64 ? mw.y : mm < 96 ? mw.z : mw.w;
+                        okj = (w >> (mm & 31)) & 1u;
+                    }
+                }
+                okm |= okj ? (1u << j) : 0u;
+            }
+            softmax_block(okm);
+        } else {
+            softmax_block(0xffu);
+        }
+        l_run = l_run * corr + psum;
+        m_run = m_new;
+        const bf16x8_t pfrag = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) {
+            O[dt] *= corr;
+            O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[4 + dt]), pfrag, O[dt], 0, 0, 0);
+        }
+    };
+    for (int blk = wave; blk < nblk; blk += 4 * NB) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int bi = blk + 4 * i;
+            if (bi < nblk) {
+                load_block(bi + 4 * (NB - 1), buf[(i + NB - 1) % NB]);
+                process(bi, buf[i]);
+            }
+        }
+    }
+    l_run = rows_sum(l_run);
+    if (gq == 0) { sm_m[wave * 16 + c] = m_run; sm_l[wave * 16 + c] = l_run; }
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sm_o[(wave * 64 + dt * 16 + 4 * gq + i) * SO + c] = O[dt][i];
+    __syncthreads();
+    float mstar = sm_m[q_out];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) mstar = fmaxf(mstar, sm_m[w * 16 + q_out]);
+    float f[4], lsum = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) { f[w] = __expf(sm_m[w * 16 + q_out] - mstar); lsum += f[w] * sm_l[w * 16 + q_out]; }
+    const float inv = 1.f / lsum;
+    float o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) s += f[w] * sm_o[(w * 64 + d_out + j) * SO + q_out];
+        o[j] = s * inv;
+    }
+    if (nd_out < a.M) *(uint2*)dst = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+}
+
+// ---------------------------------------------------------------------------
+// Tree expansion + embedding (Sec. 2.1), one workgroup per row: the fp32 residual stream, its bf16 copy in operand
+// tiles and the statistics of each 16 columns.  In prefill mode the rows are consecutive prompt tokens: text ids are
+// passed as -(id + 1), speech ids as they are.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_embed_rows(Dims D, DevState s, int prefill_mode, int table) {
+    const int r = blockIdx.x, b = r / D.M, n = r - b * D.M, tid = threadIdx.x;
+    int rows;
+    if (prefill_mode) rows = ldg(s.n_rows + b);
+    else rows = ldg(s.finished + b) ? 0 : D.M;
+    if (!prefill_mode && n == 0 && tid == 0) s.n_rows[b] = rows;
+    const bool valid = n < rows;
+    int tok = 0, pos = 0;
+    const bf16_t* E = (const bf16_t*)s.E_speech;
+    if (valid) {
+        if (prefill_mode) {
+            const int t = ldg(s.chunk_tok + r);
+            pos = ldg(s.L + b) + n;
+            if (t < 0) { tok = -t - 1; E = (const bf16_t*)s.E_text; }
+            else tok = t;
+        } else {
+            const int dep = ldg(s.t_depth[table] + n);
+            pos = ldg(s.L + b) + dep;
+            tok = n == 0 ? ldg(s.root + b) : ldg(s.draft_topk + ((size_t)b * D.Hh + (dep - 1)) * VADUSA_MAX_TOPK + ldg(s.t_rank[table] + n));
+            // a row of logits without a largest entry (all NaN) leaves the arg-max and the draft lists without an
+            // answer: whatever they hold then, the row read below is one of the table's
+            if ((unsigned)tok >= (unsigned)D.V1) tok = 0;
+        }
+        if (pos >= D.maxpos) pos = D.maxpos - 1;   // the host checks capacity before launching
+    }
+    if (tid == 0) s.tok[r] = tok;
+    const bf16_t* e = E + (size_t)tok * D.d;
+    const bf16_t* p = (const bf16_t*)s.P + (size_t)pos * D.d;
+    for (int c0 = tid * 4; c0 < D.d; c0 += 1024) {
+        float v[4];
+        const uint2 ev = ldg2(e + c0), pv = ldg2(p + c0);
+        v[0] = bf2f((bf16_t)ev.x) + bf2f((bf16_t)pv.x);
+        v[1] = bf2f((bf16_t)(ev.x >> 16)) + bf2f((bf16_t)(pv.x >> 16));
+        v[2] = bf2f((bf16_t)ev.y) + bf2f((bf16_t)pv.y);
+        v[3] = bf2f((bf16_t)(ev.y >> 16)) + bf2f((bf16_t)(pv.y >> 16));
+        if (!valid) v[0] = v[1] = v[2] = v[3] = 0.f;
+        const float mean = quad_sum(v[0] + v[1] + v[2] + v[3]) * (1.f / 16.f);
+        const float m2 = quad_sum((v[0] - mean) * (v[0] - mean) + (v[1] - mean) * (v[1] - mean) + (v[2] - mean) * (v[2] - mean) + (v[3] - mean) * (v[3] - mean));
+        *(float4*)(s.x + (size_t)r * D.d + c0) = make_float4(v[0], v[1], v[2], v[3]);
+        *(uint2*)(s.xb + toff(r, c0, D.d >> 5)) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+        if ((tid & 3) == 0) ((float2*)s.stats)[(size_t)r * (D.d >> 4) + (c0 >> 4)] = make_float2(mean, m2);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// After the vocabulary map: Algorithm 1 on every edge (one wave per edge), Sec. 2.3's path choice with the continuation
+// (one workgroup per sequence), and, after the draft heads' maps, their top-k lists beside the KV compaction.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_edges(Dims D, DevState s, int tau) {
+    const int e = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    if (e >= D.B * D.M) return;
+    const int b = e / D.M, n = e - b * D.M;
+    const int ok = s.finished[b] ? 0 : dev_edge(D, s, b, n, tau);
+    if ((threadIdx.x & 63) == 0) s.edge_ok[e] = ok;
+}
+
+__global__ __launch_bounds__(256) void k_select(Dims D, DevState s, int seq0, int ignore_eos) { dev_select(D, s, seq0 + blockIdx.x, ignore_eos); }
+
+__global__ __launch_bounds__(256) void k_continue(Dims D, DevState s, int seq0, int prefill_mode, int ignore_eos, int select) {
+    if (select) {
+        // The path goes through memory (the compaction reads it there): acknowledged before the continuation reads it.
+        dev_select(D, s, seq0 + blockIdx.x, ignore_eos);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+    dev_finalize<bf16_t>(D, s, seq0 + blockIdx.x, prefill_mode, ignore_eos, 1);
+}
+
+// Workgroups below `lists`: one draft head's list of one sequence; the others: four heads (a wave each) of one
+// sequence's cache over `layers` layers.
+__global__ __launch_bounds__(256) void k_lists_commit(Dims D, DevState s, int lists, int seq0, int nseq, int layers) {
+    if ((int)blockIdx.x < lists) { dev_topk(D, s, blockIdx.x / D.B, blockIdx.x % D.B); return; }
+    const int u = (int)blockIdx.x - lists, hq = cdiv(D.nH, 4);
+    const int head = (u % hq) * 4 + (int)(threadIdx.x >> 6), b = (u / hq) % nseq, layer0 = u / (hq * nseq) * layers;
+    if (head < D.nH) dev_commit_kv_layers<bf16_t>(D, s, layer0, min(layers, D.Ly - layer0), seq0 + b, head, threadIdx.x & 63);
+}
+
+#ifdef VADUSA_CLOCK_BUILD
+__global__ void k_clock(DevState s, int ph) { s.tprof[ph * 8] = wall_clock64(); }
+#endif
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+// Tile shape of a map.  k_lin's time is what a compute unit has to pull in through L2: a workgroup reads its rows and its
+// columns of K values, and the 256 compute units get cdiv(workgroups, 256) of them each.
+struct LinShape { int rt, ct; };
+static LinShape lin_shape(int R, int NT) {
+    static const LinShape shapes[] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 4}, {3, 4}, {4, 2}, {4, 4}};
+    const int RT = cdiv(R, 16);
+    LinShape best = shapes[0];
+    long cost = -1;
+    for (const LinShape& s : shapes) {
+        const long c = (long)cdiv(cdiv(RT, s.rt) * cdiv(NT, s.ct), 256) * (s.rt + s.ct);
+        if (cost < 0 || c < cost) { cost = c; best = s; }
+    }
+    return best;
+}
+
+template <int RT, int CT, int CH, int EPI>
+static void lin_launch(const LinArgs& a, hipStream_t st, int nz = 1) {
+    hipLaunchKernelGGL((k_lin<RT, CT, CH, EPI>), dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(256), 0, st, a);
+}
+template <int NRT, int NCT, int DEPTH, int OCC, int EPI>
+static void big_launch(const LinArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL((k_big<NRT, NCT, DEPTH, OCC, EPI>), dim3(pad8(cdiv(a.NT, 4 * NCT)), cdiv(a.R, NRT * 16)), dim3(256), 0, st, a);
+}
+// k_big's 64 x 128 tiles from one tile per eight K values on (129 tiles at K = 1024): fewer leave compute units idle for
+// a whole reduction, where k_lin's smaller tiles split it over four waves.  Measured, K = 1024: 4096 columns, 320 rows
+// (160 tiles) 10.8 us against 12.2 in k_lin, 512 rows 11.0 against 14.6; 1024 columns, 1024 rows (128 tiles) 8.9 against
+// 7.8, 2048 rows 12.5 against 14.6.  K = 4096, 1024 columns: 1024 rows 26.8 against 17.0, 2048 rows 32 against 32, 4480
+// rows 67 against 72.
+template <int EPI>
+static void lin(const LinArgs& a, int big_min, hipStream_t st) {
+    const long tiles = (long)cdiv(a.R, 64) * cdiv(a.NT, 8);
+    if (big_min > 0 ? tiles >= big_min : tiles > 4 * a.nks) { big_launch<4, 2, 2, 3, EPI>(a, st); return; }
+    const LinShape s = lin_shape(a.R, a.NT);
+    switch (s.rt * 8 + s.ct) {
+    case 1 * 8 + 1: lin_launch<1, 1, 8, EPI>(a, st); break;
+    case 1 * 8 + 2: lin_launch<1, 2, 8, EPI>(a, st); break;
+    case 2 * 8 + 1: lin_launch<2, 1, 8, EPI>(a, st); break;
+    case 2 * 8 + 2: lin_launch<2, 2, EPI == LE_RESID ? 4 : 8, EPI>(a, st); break;
+    case 2 * 8 + 4: lin_launch<2, 4, 4, EPI>(a, st); break;
+    case 3 * 8 + 4: lin_launch<3, 4, 4, EPI>(a, st); break;
+    case 4 * 8 + 2: lin_launch<4, 2, 4, EPI>(a, st); break;
+    default: lin_launch<4, 4, 2, EPI>(a, st); break;
+    }
+}
+
+// Timing points (tprof[phase][0] = device clock ahead of the phase's launch): only in the library built with
+// -DVADUSA_CLOCK_BUILD, where each is a launch of its own.
+static void clock_point(const DevState& s, int ph, hipStream_t st) {
+#ifdef VADUSA_CLOCK_BUILD
+    if (ph < 128) hipLaunchKernelGGL(k_clock, dim3(1), dim3(1), 0, st, s, ph);
+#else
+    (void)s; (void)ph; (void)st;
+#endif
+}
+
+void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st) {
+    const int R = D.B * D.M, d = D.d;
+    const size_t kv_layer = (size_t)D.Bmax * D.nH * kv_cap(D.maxpos) * 64;
+    clock_point(s, 0, st);
+    hipLaunchKernelGGL(k_embed_rows, dim3(R), dim3(256), 0, st, D, s, prefill_mode, table);
+    LinArgs base{};
+    base.R = R; base.L = s.L; base.n_rows = s.n_rows; base.M = D.M; base.nH = D.nH; base.maxpos = D.maxpos; base.d = d;
+    base.stats = (const float2*)s.stats;
+    for (int l = 0; l < D.Ly; ++l) {
+        const LayerW& w = layers[l];
+        bf16_t *Kc = (bf16_t*)s.Kc + l * kv_layer, *Vc = (bf16_t*)s.Vc + l * kv_layer;
+        LinArgs a = base;
+        a.X = s.xb; a.W = (const uint4*)w.Wqkv; a.bias = w.t_qkv; a.colsum = w.cs_qkv; a.nks = d >> 5; a.N = 3 * d; a.NT = a.N >> 4;
+        a.out = (bf16_t*)s.q; a.Kc = Kc; a.Vc = Vc;
+        clock_point(s, 1 + 5 * l, st);
+        lin<LE_QKV>(a, big_min, st);
+        AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos};
+        clock_point(s, 2 + 5 * l, st);
+        const dim3 ga(pad8(D.B * D.nH), cdiv(D.M, 16));
+        if (table == 1) hipLaunchKernelGGL(k_attn<true>, ga, dim3(256), 0, st, t);
+        else hipLaunchKernelGGL(k_attn<false>, ga, dim3(256), 0, st, t);
+        LinArgs o = base;
+        o.X = (const bf16_t*)s.att; o.W = (const uint4*)w.Wo; o.bias = w.bo; o.nks = d >> 5; o.N = d; o.NT = d >> 4;
+        o.out = s.xb; o.outf = s.x; o.stats_out = (float2*)s.stats;
+        clock_point(s, 3 + 5 * l, st);
+        lin<LE_RESID>(o, big_min, st);
+        LinArgs f = base;
+        f.X = s.xb; f.W = (const uint4*)w.W1; f.bias = w.t_w1; f.colsum = w.cs_w1; f.nks = d >> 5; f.N = D.F; f.NT = D.F >> 4;
+        f.out = (bf16_t*)s.hid;
+        clock_point(s, 4 + 5 * l, st);
+        lin<LE_GELU>(f, big_min, st);
+        LinArgs g = base;
+        g.X = (const bf16_t*)s.hid; g.W = (const uint4*)w.W2; g.bias = w.b2; g.nks = D.F >> 5; g.N = d; g.NT = d >> 4;
+        g.out = s.xb; g.outf = s.x; g.stats_out = (float2*)s.stats;
+        clock_point(s, 5 + 5 * l, st);
+        lin<LE_RESID>(g, big_min, st);
+    }
+    if (head) {
+        LinArgs a = base;
+        a.X = s.xb; a.W = (const uint4*)s.W_out; a.bias = s.t_out; a.colsum = s.cs_out; a.nks = d >> 5; a.N = D.V1; a.NT = cdiv(D.V1, 16);
+        a.outf = s.logits;
+        clock_point(s, 1 + 5 * D.Ly + TP_HEAD, st);
+        lin<LE_LOGITS>(a, big_min, st);
+    }
+}
+
+void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eos, bool select, hipStream_t st) {
+    clock_point(s, 1 + 5 * D.Ly + TP_EDGES, st);
+    hipLaunchKernelGGL(k_edges, dim3(cdiv(D.B * D.M, 4)), dim3(256), 0, st, D, s, tau);
+    if (select) hipLaunchKernelGGL(k_select, dim3(D.B), dim3(256), 0, st, D, s, 0, ignore_eos);
+}
+
+// Rows of more than 4096 logits: the draft lists come from the stand-alone top-k kernel (it takes such rows slice by
+// slice; dev_topk would re-scan the row once per list entry).
+void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, hipStream_t st) {
+    const int H = 1 + 5 * D.Ly;
+    clock_point(s, H + TP_FINAL, st);
+    hipLaunchKernelGGL(k_continue, dim3(nseq), dim3(256), 0, st, D, s, seq0, prefill_mode, ignore_eos, select ? 1 : 0);
+    auto ahead = [&](const void* a, const void* b) { return D.Hh > 1 ? (size_t)((const char*)b - (const char*)a) : 0; };
+    const DraftW &d0 = draft[0], &d1 = draft[D.Hh > 1 ? 1 : 0];
+    LinArgs a{};
+    a.X = (const bf16_t*)s.hbest; a.W = (const uint4*)d0.W1; a.bias = d0.b1; a.nks = D.d >> 5; a.N = D.d; a.NT = D.d >> 4; a.R = D.B;
+    a.out = (bf16_t*)s.rdraft; a.z_w = ahead(d0.W1, d1.W1); a.z_b = ahead(d0.b1, d1.b1); a.z_out = s.draft_stride;
+    clock_point(s, H + TP_COMMIT, st);
+    if (D.B <= 16) lin_launch<1, 1, 8, LE_SILU>(a, st, D.Hh);
+    else lin_launch<4, 1, 4, LE_SILU>(a, st, D.Hh);
+    LinArgs z{};
+    z.X = (const bf16_t*)s.rdraft; z.W = (const uint4*)d0.W2; z.nks = D.d >> 5; z.N = D.V1; z.NT = cdiv(D.V1, 16); z.R = D.B;
+    z.outf = s.zdraft; z.z_w = ahead(d0.W2, d1.W2); z.z_x = s.draft_stride; z.z_out = (size_t)D.Bmax * D.V1;
+    clock_point(s, H + TP_DRAFT2, st);
+    if (D.B <= 16) lin_launch<1, 1, 8, LE_F32>(z, st, D.Hh);
+    else lin_launch<4, 1, 4, LE_F32>(z, st, D.Hh);
+    clock_point(s, H + TP_TOPK, st);
+    const int lists = D.V1 > 4096 ? 0 : D.Hh * D.B, per_layer = cdiv(D.nH, 4) * nseq;
+    const int layers = std::min(D.Ly, std::max(1, cdiv(D.Ly * per_layer, 256)));   // (layers per workgroup: one round of the 256 compute units)
+    const int commits = prefill_mode ? 0 : cdiv(D.Ly, layers) * per_layer;
+    if (lists + commits > 0) hipLaunchKernelGGL(k_lists_commit, dim3(lists + commits), dim3(256), 0, st, D, s, lists, seq0, nseq, layers);
+    if (lists == 0) launch_topk(D, s, seq0, nseq, st);
+}

@@ -315,7 +315,7 @@ class Vadusa:
         return out
 
     def debug_raise_error(self):
-        """Test aid: sets the error word of a kernel that gave up at a grid barrier."""
+        """Test aid: sets the error word."""
         self._check(self.lib.vadusa_debug_raise_error(self.h))
 
     def read_kv(self, layer, seq, which, pos0, npos, static=False):
