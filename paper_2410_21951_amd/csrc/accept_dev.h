@@ -135,78 +135,7 @@ __device__ inline void dev_choose(const Dims& D, const DevState& s, int b, int i
     __syncthreads();
 }
 
-// Algorithm 1 on every edge of sequence b at once, then Sec. 2.3's choice.
-// Edge n is accepted iff fewer than tau entries of the parent's logit row rank
-// before the node's token (one wave counts one edge).  path_ok[n] = every edge
-// from the root to n accepted; the chosen node is the deepest such node,
-// smallest index among equals (canonical order = leftmost).
-// Output: path[b] = {count, node indices...}; the count is cut after the first EOS.
-__device__ inline void dev_accept(const Dims& D, const DevState& s, int b, int tau, int ignore_eos) {
-    __shared__ int s_edge[VADUSA_MAX_TREE_NODES];
-    __shared__ int s_ok[VADUSA_MAX_TREE_NODES];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int32_t* path = s.path + (size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2);
-    if (s.finished[b]) {
-        if (threadIdx.x == 0) stwi(path, 0);
-        for (int n = threadIdx.x; n < D.M; n += 256) stwi(s.edge_ok + b * D.M + n, 0);
-        return;
-    }
-    const int32_t* parent = s.t_parent[0];
-    const int32_t* tok = s.tok + (size_t)b * D.M;
-    // Wave w owns the edges n = w + 4j.  Lane j first fetches parent, token and the token's logit
-    // of edge j, so that chain of three dependent loads is paid once per wave, not once per
-    // edge; then the wave streams the parents' rows, two edges at a time, 17 values per lane and
-    // batch (one batch covers 1088 logits).
-    const int nj = (D.M - wave + 3) / 4;   // edges of this wave, at most 32
-    int my_par = 0, my_t = 0;
-    float my_zt = 0.f;
-    if (lane < nj && wave + 4 * lane > 0) {
-        const int n = wave + 4 * lane;
-        my_par = parent[n];
-        my_t = tok[n];
-        my_zt = s.logits[((size_t)b * D.M + my_par) * D.V1 + my_t];
-    }
-    for (int j0 = 0; j0 < nj; j0 += 2) {
-        int cnt[2] = {0, 0};
-        const float* zrow[2];
-        int tt[2];
-        float ztv[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int j = j0 + e < nj ? j0 + e : j0;   // an odd tail repeats the edge (result unused)
-            zrow[e] = s.logits + ((size_t)b * D.M + __shfl(my_par, j, 64)) * D.V1;
-            tt[e] = __shfl(my_t, j, 64);
-            ztv[e] = __shfl(my_zt, j, 64);
-        }
-        for (int v0 = lane; v0 < D.V1; v0 += 64 * 17) {
-            float zv[2][17];
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-#pragma unroll
-                for (int q = 0; q < 17; ++q) zv[e][q] = v0 + 64 * q < D.V1 ? zrow[e][v0 + 64 * q] : -INFINITY;
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-#pragma unroll
-                for (int q = 0; q < 17; ++q)
-                    cnt[e] += (v0 + 64 * q < D.V1 && before(zv[e][q], v0 + 64 * q, ztv[e], tt[e])) ? 1 : 0;
-        }
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int n = wave + 4 * (j0 + e);
-            const int total = wave_sum_i_dpp(cnt[e]);
-            if (j0 + e < nj && lane == 0) {
-                const int edge = n == 0 ? 1 : (total < tau);
-                s_edge[n] = edge;   // stored to memory after the loop: a store inside it would
-            }                       // put a write acknowledgement into every wait for the next rows
-        }
-    }
-    __syncthreads();
-    for (int n = threadIdx.x; n < D.M; n += 256) stwi(s.edge_ok + b * D.M + n, s_edge[n]);
-    dev_choose(D, s, b, ignore_eos, s_edge, s_ok);
-}
-
-// Sec. 2.3's choice for sequence b when the edge decisions were taken by other workgroups
-// (dev_edge) and sit in edge_ok.
+// Sec. 2.3's choice for sequence b from the edge decisions in edge_ok (dev_edge).
 __device__ inline void dev_select(const Dims& D, const DevState& s, int b, int ignore_eos) {
     __shared__ int s_edge[VADUSA_MAX_TREE_NODES];
     __shared__ int s_ok[VADUSA_MAX_TREE_NODES];
@@ -221,13 +150,11 @@ __device__ inline void dev_select(const Dims& D, const DevState& s, int b, int i
 
 // Continue from the last accepted node (Sec. 2.1): advance L, append the
 // accepted tokens to the output, next root = best logit of that node's row, and
-// its final-LayerNorm'd hidden state for the draft heads (copied from hn, or, if
-// from_x, computed here from the residual stream).  acc_len[b] keeps the number
+// its final-LayerNorm'd hidden state for the draft heads (operand tiles in the bf16 model).  acc_len[b] keeps the number
 // of committed rows for the compaction that follows.  In prefill mode the
 // "path" is the chunk's last row and nothing is emitted.
 template <class T>
-__device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int prefill_mode, int ignore_eos,
-                                    int from_x) {
+__device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int prefill_mode, int ignore_eos) {
     __shared__ float s_red[8];
     int32_t* path = s.path + (size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2);
     int cnt, last;
@@ -243,8 +170,11 @@ __device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int
     const int32_t* tok = s.tok + (size_t)b * D.M;
     const int r = b * D.M + last;
     const int root = block_argbest(s.logits + (size_t)r * D.V1, D.V1, INFINITY, -1, nullptr);
-    T* hb = (T*)s.hbest + (size_t)b * D.d;
-    if (from_x) {
+    auto store = [&](int i, float a, float c) {
+        if constexpr (sizeof(T) == 4) *(float2*)((float*)s.hbest + (size_t)b * D.d + i) = make_float2(a, c);
+        else stw32((bf16_t*)s.hbest + toff(b, i, D.d >> 5), pack_bf16(a, c));   // tiled for the draft maps
+    };
+    {
         // final LayerNorm of the accepted node's residual row: read once, into registers (up to 16 values per
         // thread, d <= 4096; larger rows take the three-pass route below)
         const float* xr = s.x + (size_t)r * D.d;
@@ -278,7 +208,7 @@ __device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int
                 if (i < D.d) {
                     const float a = (xv[2 * j] - mu) * rstd * ldg(s.lnf_g + i) + ldg(s.lnf_b + i);
                     const float c2 = (xv[2 * j + 1] - mu) * rstd * ldg(s.lnf_g + i + 1) + ldg(s.lnf_b + i + 1);
-                    stw32((bf16_t*)s.hbest + toff(b, i, D.d >> 5), pack_bf16(a, c2));   // tiled for the draft maps
+                    store(i, a, c2);
                 }
             }
         } else {
@@ -297,12 +227,9 @@ __device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int
         for (int i = threadIdx.x * 2; i < D.d; i += 512) {
             const float a = (ldcf(xr + i) - mu) * rstd * s.lnf_g[i] + s.lnf_b[i];
             const float c2 = (ldcf(xr + i + 1) - mu) * rstd * s.lnf_g[i + 1] + s.lnf_b[i + 1];
-            stw32((bf16_t*)s.hbest + toff(b, i, D.d >> 5), pack_bf16(a, c2));   // tiled for the draft maps
+            store(i, a, c2);
         }
         }
-    } else {
-        const T* h = (const T*)s.hn + (size_t)r * D.d;
-        for (int i = threadIdx.x; i < D.d; i += 256) hb[i] = h[i];
     }
     if (threadIdx.x == 0) {
         stwi(s.root + b, root);
@@ -323,39 +250,12 @@ __device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int
     }
 }
 
-// KV compaction after dev_finalize: cache row L0 + j <- row L0 + path[j], where
+// KV compaction after dev_finalize, nl consecutive layers from layer0 on: cache row L0 + j <- row L0 + path[j], where
 // L0 = L - acc_len is the length before this step and acc_len the number of
 // committed rows.  path[j] >= j, so a destination row can be the source of an
 // earlier j: every thread owns one column of one head and reads all its sources
-// before writing.  64 threads (one per head dimension).
-template <class T>
-__device__ inline void dev_commit_kv(const Dims& D, const DevState& s, int layer, int b, int head, int dim) {
-    const int32_t* path = s.path + (size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2);
-    const int cnt = ldci(s.acc_len + b);
-    if (cnt <= 0) return;
-    const int L0 = ldci(s.L + b) - cnt;
-    const size_t hb = ((((size_t)layer * D.Bmax + b) * D.nH + head) * kv_cap(D.maxpos)) * 64;
-    T* Kh = (T*)s.Kc + hb;
-    T* Vh = (T*)s.Vc + hb;
-    T kr[VADUSA_MAX_DRAFT_HEADS + 1], vr[VADUSA_MAX_DRAFT_HEADS + 1];
-#pragma unroll
-    for (int j = 0; j < VADUSA_MAX_DRAFT_HEADS + 1; ++j)
-        if (j < cnt) {
-            const int src = ldci(path + 1 + j);
-            kr[j] = Kh[kc_off(L0 + src, dim)];
-            vr[j] = Vh[vc_off(L0 + src, dim)];
-        }
-#pragma unroll
-    for (int j = 0; j < VADUSA_MAX_DRAFT_HEADS + 1; ++j)
-        if (j < cnt) {
-            Kh[kc_off(L0 + j, dim)] = kr[j];
-            Vh[vc_off(L0 + j, dim)] = vr[j];
-        }
-}
-
-// The same for nl consecutive layers from layer0 on (with many sequences a workgroup takes several layers, so that the
-// chain of dependent trips to memory is paid once).  The path is read once; four layers' rows are in flight together; a path whose rows already sit where they
-// belong (the root alone, or nodes 0, 1, .. of the tree) moves nothing.
+// before writing.  64 threads (one per head dimension).  The path is read once; four layers' rows are in flight
+// together; a path whose rows already sit where they belong (the root alone, or nodes 0, 1, .. of the tree) moves nothing.
 template <class T>
 __device__ inline void dev_commit_kv_layers(const Dims& D, const DevState& s, int layer0, int nl, int b, int head, int dim) {
     constexpr int W = VADUSA_MAX_DRAFT_HEADS + 1, LB = 4;

@@ -242,7 +242,6 @@ static size_t layout(const vadusa_config& c, char* base, DevState* s, std::vecto
     st.xb = c.dtype ? (bf16_t*)cv.take(Rp * d * 2) : nullptr;
     st.stats = c.dtype ? (float*)cv.take((d / 16) * R * 2 * 4) : nullptr;
     st.tprof = (long long*)cv.take(1024 * 8);
-    st.xn = cv.take(R * d * e);
     st.q = cv.take(Rp * d * e);
     st.att = cv.take(Rp * d * e);
     st.hid = cv.take(Rp * F * e);
@@ -328,7 +327,7 @@ extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena
     c->M = 0;
     layout(*cfg, c->arena, &c->s, &c->layers, &c->draft, nullptr, &c->staging_floats, &c->uniforms, &c->scores);
     c->sampled = 0;
-    if (cfg->dtype) {
+    {
         // the draft maps of all heads are one launch, which addresses head i as head 0 + i * stride
         auto off = [](const void* a, const void* b) { return (const char*)a - (const char*)b; };
         bool ok = true;
@@ -439,12 +438,6 @@ extern "C" int vadusa_load_weights(vadusa_ctx* c, const float* blob, size_t n_fl
     return VADUSA_OK;
 }
 
-// ---------------------------------------------------------------------------
-// forward of B x M rows through the decoder (Sec. 2.1 tree attention; the
-// prefill uses the same path with a causal chunk as the "tree")
-// ---------------------------------------------------------------------------
-static void gemm(vadusa_ctx* c, const GemmArgs& a) { launch_gemm_simple(a, 0, c->stream); }
-
 static int launched(vadusa_ctx* c) {
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? VADUSA_OK : fail(c, VADUSA_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
@@ -483,57 +476,10 @@ static int recover(vadusa_ctx* c) {
     return VADUSA_OK;
 }
 
+// Forward of B x M rows through the decoder (Sec. 2.1 tree attention; the prefill uses it with a causal pass as the "tree").
 static void forward(vadusa_ctx* c, const Dims& D, int table, int prefill_mode, bool want_logits) {
-    const int dt = c->cfg.dtype;
-    const DevState& s = c->s;
-    hipStream_t st = c->stream;
-    const int R = D.B * D.M;
-    const size_t kv_layer = (size_t)D.Bmax * D.nH * kv_cap(D.maxpos) * 64 * c->elem;
-    launch_embed(D, s, dt, prefill_mode, table, st);
-    for (int l = 0; l < D.Ly; ++l) {
-        const LayerW& w = c->layers[l];
-        launch_layernorm(s.x, w.ln1_g, w.ln1_b, s.xn, R, D.d, dt, st);
-        GemmArgs a{};
-        a.X = s.xn; a.W = w.Wqkv; a.bias = w.bqkv; a.R = R; a.K = D.d; a.N = 3 * D.d; a.epi = EPI_QKV;
-        a.out = s.q; a.Kc = (char*)s.Kc + l * kv_layer; a.Vc = (char*)s.Vc + l * kv_layer;
-        a.L = s.L; a.M = D.M; a.nH = D.nH; a.maxpos = D.maxpos; a.d = D.d;
-        gemm(c, a);
-        launch_attn_simple(D, s, l, table, dt, st);
-        GemmArgs o{};
-        o.X = s.att; o.W = w.Wo; o.bias = w.bo; o.R = R; o.K = D.d; o.N = D.d; o.epi = EPI_RESID; o.outf = s.x;
-        gemm(c, o);
-        launch_layernorm(s.x, w.ln2_g, w.ln2_b, s.xn, R, D.d, dt, st);
-        GemmArgs f1{};
-        f1.X = s.xn; f1.W = w.W1; f1.bias = w.b1; f1.R = R; f1.K = D.d; f1.N = D.F; f1.epi = EPI_GELU; f1.out = s.hid;
-        gemm(c, f1);
-        GemmArgs f2{};
-        f2.X = s.hid; f2.W = w.W2; f2.bias = w.b2; f2.R = R; f2.K = D.F; f2.N = D.d; f2.epi = EPI_RESID; f2.outf = s.x;
-        gemm(c, f2);
-    }
-    if (want_logits) {
-        launch_layernorm(s.x, s.lnf_g, s.lnf_b, s.hn, R, D.d, dt, st);
-        GemmArgs h{};
-        h.X = s.hn; h.W = s.W_out; h.bias = nullptr; h.R = R; h.K = D.d; h.N = D.V1; h.epi = EPI_F32; h.outf = s.logits;
-        gemm(c, h);
-    }
-}
-
-// Draft heads on the hidden state of the last accepted node (Sec. 2.1,
-// Sec. 3.1.1): z_i = W2_i (h + SiLU(W1_i h + b1_i)), then the top-k lists.
-static void draft_heads(vadusa_ctx* c, const Dims& D, int seq0, int nseq) {
-    const DevState& s = c->s;
-    for (int i = 0; i < D.Hh; ++i) {
-        char* r = (char*)s.rdraft + ((size_t)i * D.Bmax + seq0) * D.d * c->elem;
-        GemmArgs a{};
-        a.X = (char*)s.hbest + (size_t)seq0 * D.d * c->elem; a.W = c->draft[i].W1; a.bias = c->draft[i].b1;
-        a.R = nseq; a.K = D.d; a.N = D.d; a.epi = EPI_SILU_RESID; a.out = r;
-        gemm(c, a);
-        GemmArgs z{};
-        z.X = r; z.W = c->draft[i].W2; z.bias = nullptr; z.R = nseq; z.K = D.d; z.N = D.V1; z.epi = EPI_F32;
-        z.outf = s.zdraft + ((size_t)i * D.Bmax + seq0) * D.V1;
-        gemm(c, z);
-    }
-    launch_topk(D, s, seq0, nseq, c->stream);
+    if (c->cfg.dtype) launch_layers(D, c->s, c->layers, table, prefill_mode, want_logits, c->big_min, c->stream);
+    else launch_layers32(D, c->s, c->layers, table, prefill_mode, want_logits, c->stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -604,22 +550,12 @@ extern "C" int vadusa_prefill(vadusa_ctx* c, int32_t batch, const int32_t* text_
         HIP_TRY(c, hipMemcpyAsync(s.chunk_tok, ctok.data(), ctok.size() * 4, hipMemcpyHostToDevice, c->stream));
         HIP_TRY(c, hipMemcpyAsync(s.n_rows, rows.data(), rows.size() * 4, hipMemcpyHostToDevice, c->stream));
         const bool last = ch == max_chunks - 1;
-        if (c->cfg.dtype) {
-            // bf16 model: the chunk is a causal "tree"; the last chunk also runs the base head, the continuation and the
-            // draft heads
-            launch_layers(D, s, c->layers, 1, 1, last, c->big_min, c->stream);
-            if (last) launch_continue(D, s, c->draft, 0, batch, 1, c->cfg.ignore_eos, false, c->stream);
-            int rc = launched(c);
-            if (rc) return rc;
-        } else {
-            forward(c, D, 1, 1, last);
-        }
+        // the chunk is a causal "tree"; the last one also runs the vocabulary map, the continuation and the draft heads
+        forward(c, D, 1, 1, last);
         if (!last) launch_advance(s, batch, c->stream);
     }
-    if (!c->cfg.dtype) {
-        launch_finalize(D, s, 0, batch, 1, c->cfg.ignore_eos, c->cfg.dtype, c->stream);
-        draft_heads(c, D, 0, batch);
-    }
+    launch_continue(D, s, c->draft, 0, batch, 1, c->cfg.ignore_eos, false, c->cfg.dtype, c->stream);
+    { int rc = launched(c); if (rc) return rc; }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipGetLastError());
     { int rc = check_kerr(c); if (rc) return rc; }
@@ -726,25 +662,13 @@ static int verify_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau,
     // and acceptance, choice and continuation rank the scores in place of the logits.
     DevState sr = s;
     if (sp) sr.logits = c->scores;
-    if (c->cfg.dtype) {
-        launch_layers(D, s, c->layers, 0, 0, true, c->big_min, c->stream);
-        if (sp) launch_perturb(s.logits, c->uniforms, c->scores, B * M, D.V1, sp->temperature, sp->top_p, tau, c->stream);
-        // the path is chosen beside the continuation where that follows at once
-        launch_verify_tail(D, sr, tau, c->cfg.ignore_eos, !fuse_compact, c->stream);
-        if (fuse_compact) launch_continue(D, sr, c->draft, 0, B, 0, c->cfg.ignore_eos, true, c->stream);
-        rc = launched(c);
-        if (rc) return rc;
-    } else {
-        forward(c, D, 0, 0, true);
-        if (sp) launch_perturb(s.logits, c->uniforms, c->scores, B * M, D.V1, sp->temperature, sp->top_p, tau, c->stream);
-        launch_accept(D, sr, tau, c->cfg.ignore_eos, c->stream);
-        if (fuse_compact) {
-            launch_finalize(D, sr, 0, B, 0, c->cfg.ignore_eos, 0, c->stream);
-            launch_commit_kv(D, s, 0, B, 0, c->stream);
-            draft_heads(c, D, 0, B);
-        }
-        HIP_TRY(c, hipGetLastError());
-    }
+    forward(c, D, 0, 0, true);
+    if (sp) launch_perturb(s.logits, c->uniforms, c->scores, B * M, D.V1, sp->temperature, sp->top_p, tau, c->stream);
+    // the path is chosen beside the continuation where that follows at once
+    launch_verify_tail(D, sr, tau, c->cfg.ignore_eos, !fuse_compact, c->stream);
+    if (fuse_compact) launch_continue(D, sr, c->draft, 0, B, 0, c->cfg.ignore_eos, true, c->cfg.dtype, c->stream);
+    rc = launched(c);
+    if (rc) return rc;
     c->state = 3;
     for (int b = 0; b < B; ++b) c->pending[b] = 1;
     if (fuse_compact) mark_compacted(c, 0, B, 0);
@@ -790,20 +714,10 @@ extern "C" int vadusa_kv_compact(vadusa_ctx* c, int32_t seq, const int32_t* path
             HIP_TRY(c, hipStreamSynchronize(c->stream));
         }
     }
-    if (c->cfg.dtype) {
-        DevState sr = s;
-        if (c->sampled) sr.logits = c->scores;   // the next root is the first draw at the last committed node
-        launch_continue(D, sr, c->draft, seq0, nseq, 0, c->cfg.ignore_eos, false, c->stream);
-        int rc = launched(c);
-        if (rc) return rc;
-    } else {
-        DevState sr = s;
-        if (c->sampled) sr.logits = c->scores;
-        launch_finalize(D, sr, seq0, nseq, 0, c->cfg.ignore_eos, 0, c->stream);
-        launch_commit_kv(D, s, seq0, nseq, 0, c->stream);
-        draft_heads(c, D, seq0, nseq);
-        HIP_TRY(c, hipGetLastError());
-    }
+    DevState sr = s;
+    if (c->sampled) sr.logits = c->scores;   // the next root is the first draw at the last committed node
+    launch_continue(D, sr, c->draft, seq0, nseq, 0, c->cfg.ignore_eos, false, c->cfg.dtype, c->stream);
+    { int rc = launched(c); if (rc) return rc; }
     mark_compacted(c, seq0, nseq, path_nodes ? n : 0);
     return VADUSA_OK;
 }
@@ -898,8 +812,8 @@ extern "C" int vadusa_debug_read(vadusa_ctx* c, int32_t what, void* host, size_t
     case VADUSA_DBG_H_NODES: {
         need = B * M * d * 4;
         if (bytes != need) return fail(c, VADUSA_EINVAL, "expected %zu bytes", need);
-        if (c->cfg.dtype)   // the bf16 kernels keep no node states: recompute them from the residual stream
-            launch_layernorm(s.x, s.lnf_g, s.lnf_b, s.hn, (int)(B * M), (int)d, 1, c->stream);
+        // no kernel keeps the node states: recompute them from the residual stream
+        launch_layernorm(s.x, s.lnf_g, s.lnf_b, s.hn, (int)(B * M), (int)d, c->cfg.dtype, c->stream);
         launch_to_float(s.hn, s.staging, B * M * d, c->cfg.dtype, c->stream);
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         HIP_TRY(c, hipMemcpy(host, s.staging, need, hipMemcpyDeviceToHost));

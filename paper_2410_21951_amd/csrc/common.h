@@ -161,6 +161,12 @@ __device__ __forceinline__ float rows_sum(float v) {
     r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(r.x) + __uint_as_float(r.y);
 }
+// Sum over the two lanes l and l ^ 32.
+__device__ __forceinline__ float half_sum(float v) {
+    const vadusa_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
 __device__ __forceinline__ int wave_sum_i_dpp(int v) {
     v += dpp_perm<0xB1>(v);    // quad_perm [1,0,3,2]
     v += dpp_perm<0x4E>(v);    // quad_perm [2,3,0,1]
@@ -213,7 +219,6 @@ struct DevState {
     size_t draft_stride;   // elements from one draft head's rdraft to the next
     int32_t* kerr;   // [4] error flag that the next synchronising call reports
     long long* tprof; // [128][8] timing points (device clock, 100 MHz; -DVADUSA_CLOCK_BUILD)
-    void* xn;        // [R][d]  LayerNorm output
     void* q;         // [R][d]
     void* att;       // [R][d]
     void* hid;       // [R][F]
@@ -258,28 +263,29 @@ struct vadusa_ctx {
     std::string err;
 };
 
-// Epilogues of the linear-map kernels.
+// Epilogues of the fp32 model's linear map.
 enum {
-    EPI_STORE = 0,      // out[r][n] = acc + bias              (stored in the context dtype)
     EPI_GELU = 1,       // out[r][n] = gelu(acc + bias)
-    EPI_RESID = 2,      // x[r][n] += acc + bias               (fp32 residual stream)
-    EPI_F32 = 3,        // outf[r][n] = acc (+ bias if given)
+    EPI_RESID = 2,      // x[r][n] += acc + bias
+    EPI_F32 = 3,        // outf[r][n] = acc
     EPI_SILU_RESID = 4, // out[r][n] = in[r][n] + silu(acc + bias)   (needs N == K)
     EPI_QKV = 5         // n < d: q[r][n]; else key / value rows of the KV cache at L[b] + node
 };
 
 struct GemmArgs {
-    const void* X;      // [R][K] context dtype
-    const void* W;      // [N][K] context dtype (layout depends on the kernel)
+    const void* X;      // [R][K]
+    const void* W;      // [N][K]
     const float* bias;  // [N] or null
     int R, K, N;
     int epi;
-    void* out;          // context dtype, [R][N]
+    void* out;          // [R][N]
     float* outf;        // fp32 target (EPI_RESID: x, EPI_F32: logits)
     // EPI_QKV
     void *Kc, *Vc;      // layer base of the cache
     const int32_t* L;
     int M, nH, maxpos, d;
+    const float *ln_g, *ln_b;      // X = LayerNorm of these rows with this scale and shift (null: the rows as they are)
+    size_t z_w, z_b, z_x, z_out;   // several draft heads in one launch: how far a head's weights, bias (bytes), X and result (elements) are ahead of the previous head's
 };
 
 // Phases of a bf16 step, as VADUSA_DBG_PHASE_CLOCK counts them: 0 embedding; 1 + 5 l .. layer l (QKV, attention,
@@ -291,20 +297,18 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
 // edge decisions, and (select) the path choice of every sequence
 void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eos, bool select, hipStream_t st);
 // (select: path choice,) continuation, draft heads, draft lists and KV compaction
-void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, hipStream_t st);
+void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, int dtype, hipStream_t st);
 void launch_pack_w_ln(const float* src, const float* gamma, const float* beta, void* dst, float* colsum,
                       float* tvec, int N, int K, hipStream_t st);
 void launch_add_vec(float* dst, const float* src, int n, hipStream_t st);
 
 // ---- launch wrappers (each enqueues on `st`, no synchronisation) ----
-void launch_embed(const Dims& D, const DevState& s, int dtype, int prefill_mode, int table, hipStream_t st);
+void launch_embed32(const Dims& D, const DevState& s, int prefill_mode, int table, hipStream_t st);
+// fp32 model: the same as launch_layers, and the draft heads' maps (see k_fp32.hip)
+void launch_layers32(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, hipStream_t st);
+void launch_draft32(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, hipStream_t st);
 void launch_layernorm(const float* x, const float* g, const float* b, void* out, int R, int d, int dtype, hipStream_t st);
-void launch_gemm_simple(const GemmArgs& a, int dtype, hipStream_t st);
 void launch_pack_w(const float* src, void* dst, int N, int K, hipStream_t st);
-void launch_attn_simple(const Dims& D, const DevState& s, int layer, int table, int dtype, hipStream_t st);
-void launch_accept(const Dims& D, const DevState& s, int tau, int ignore_eos, hipStream_t st);
-void launch_commit_kv(const Dims& D, const DevState& s, int seq0, int nseq, int dtype, hipStream_t st);
-void launch_finalize(const Dims& D, const DevState& s, int seq0, int nseq, int prefill_mode, int ignore_eos, int dtype, hipStream_t st);
 void launch_topk(const Dims& D, const DevState& s, int seq0, int nseq, hipStream_t st);
 void launch_perturb(const float* logits, const float* u, float* scores, int rows, int V1, float temperature,
                     float top_p, int tau, hipStream_t st);

@@ -53,12 +53,6 @@ struct LinArgs {
 // the row blocks that share a weight tile share an XCD and its L2 and the tile leaves HBM once.
 __host__ __device__ inline int pad8(int a) { return (a + 7) & ~7; }
 
-// Sum over the two lanes l and l ^ 32.
-__device__ __forceinline__ float half_sum(float v) {
-    const vadusa_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r.x) + __uint_as_float(r.y);
-}
-
 // Row statistics of the LayerNorm folded into a map, for the ROWS rows of a workgroup, in two steps: request (ahead of
 // the operands, so that they return first) and merge (while the operands are on their way).  Eight (sixteen)
 // neighbouring lanes share a row and read its tile statistics two at a time, 128 (256) contiguous bytes per load.
@@ -730,6 +724,7 @@ __global__ __launch_bounds__(256) void k_edges(Dims D, DevState s, int tau) {
 
 __global__ __launch_bounds__(256) void k_select(Dims D, DevState s, int seq0, int ignore_eos) { dev_select(D, s, seq0 + blockIdx.x, ignore_eos); }
 
+template <class T>
 __global__ __launch_bounds__(256) void k_continue(Dims D, DevState s, int seq0, int prefill_mode, int ignore_eos, int select) {
     if (select) {
         // The path goes through memory (the compaction reads it there): acknowledged before the continuation reads it.
@@ -737,16 +732,17 @@ __global__ __launch_bounds__(256) void k_continue(Dims D, DevState s, int seq0, 
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     }
-    dev_finalize<bf16_t>(D, s, seq0 + blockIdx.x, prefill_mode, ignore_eos, 1);
+    dev_finalize<T>(D, s, seq0 + blockIdx.x, prefill_mode, ignore_eos);
 }
 
 // Workgroups below `lists`: one draft head's list of one sequence; the others: four heads (a wave each) of one
 // sequence's cache over `layers` layers.
+template <class T>
 __global__ __launch_bounds__(256) void k_lists_commit(Dims D, DevState s, int lists, int seq0, int nseq, int layers) {
     if ((int)blockIdx.x < lists) { dev_topk(D, s, blockIdx.x / D.B, blockIdx.x % D.B); return; }
     const int u = (int)blockIdx.x - lists, hq = cdiv(D.nH, 4);
     const int head = (u % hq) * 4 + (int)(threadIdx.x >> 6), b = (u / hq) % nseq, layer0 = u / (hq * nseq) * layers;
-    if (head < D.nH) dev_commit_kv_layers<bf16_t>(D, s, layer0, min(layers, D.Ly - layer0), seq0 + b, head, threadIdx.x & 63);
+    if (head < D.nH) dev_commit_kv_layers<T>(D, s, layer0, min(layers, D.Ly - layer0), seq0 + b, head, threadIdx.x & 63);
 }
 
 #ifdef VADUSA_CLOCK_BUILD
@@ -865,28 +861,32 @@ void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eo
 
 // Rows of more than 4096 logits: the draft lists come from the stand-alone top-k kernel (it takes such rows slice by
 // slice; dev_topk would re-scan the row once per list entry).
-void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, hipStream_t st) {
+void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, int dtype, hipStream_t st) {
     const int H = 1 + 5 * D.Ly;
     clock_point(s, H + TP_FINAL, st);
-    hipLaunchKernelGGL(k_continue, dim3(nseq), dim3(256), 0, st, D, s, seq0, prefill_mode, ignore_eos, select ? 1 : 0);
-    auto ahead = [&](const void* a, const void* b) { return D.Hh > 1 ? (size_t)((const char*)b - (const char*)a) : 0; };
-    const DraftW &d0 = draft[0], &d1 = draft[D.Hh > 1 ? 1 : 0];
-    LinArgs a{};
-    a.X = (const bf16_t*)s.hbest; a.W = (const uint4*)d0.W1; a.bias = d0.b1; a.nks = D.d >> 5; a.N = D.d; a.NT = D.d >> 4; a.R = D.B;
-    a.out = (bf16_t*)s.rdraft; a.z_w = ahead(d0.W1, d1.W1); a.z_b = ahead(d0.b1, d1.b1); a.z_out = s.draft_stride;
-    clock_point(s, H + TP_COMMIT, st);
-    if (D.B <= 16) lin_launch<1, 1, 8, LE_SILU>(a, st, D.Hh);
-    else lin_launch<4, 1, 4, LE_SILU>(a, st, D.Hh);
-    LinArgs z{};
-    z.X = (const bf16_t*)s.rdraft; z.W = (const uint4*)d0.W2; z.nks = D.d >> 5; z.N = D.V1; z.NT = cdiv(D.V1, 16); z.R = D.B;
-    z.outf = s.zdraft; z.z_w = ahead(d0.W2, d1.W2); z.z_x = s.draft_stride; z.z_out = (size_t)D.Bmax * D.V1;
-    clock_point(s, H + TP_DRAFT2, st);
-    if (D.B <= 16) lin_launch<1, 1, 8, LE_F32>(z, st, D.Hh);
-    else lin_launch<4, 1, 4, LE_F32>(z, st, D.Hh);
+    hipLaunchKernelGGL(dtype ? k_continue<bf16_t> : k_continue<float>, dim3(nseq), dim3(256), 0, st, D, s, seq0, prefill_mode, ignore_eos, select ? 1 : 0);
+    if (dtype) {
+        auto ahead = [&](const void* a, const void* b) { return D.Hh > 1 ? (size_t)((const char*)b - (const char*)a) : 0; };
+        const DraftW &d0 = draft[0], &d1 = draft[D.Hh > 1 ? 1 : 0];
+        LinArgs a{};
+        a.X = (const bf16_t*)s.hbest; a.W = (const uint4*)d0.W1; a.bias = d0.b1; a.nks = D.d >> 5; a.N = D.d; a.NT = D.d >> 4; a.R = D.B;
+        a.out = (bf16_t*)s.rdraft; a.z_w = ahead(d0.W1, d1.W1); a.z_b = ahead(d0.b1, d1.b1); a.z_out = s.draft_stride;
+        clock_point(s, H + TP_COMMIT, st);
+        if (D.B <= 16) lin_launch<1, 1, 8, LE_SILU>(a, st, D.Hh);
+        else lin_launch<4, 1, 4, LE_SILU>(a, st, D.Hh);
+        LinArgs z{};
+        z.X = (const bf16_t*)s.rdraft; z.W = (const uint4*)d0.W2; z.nks = D.d >> 5; z.N = D.V1; z.NT = cdiv(D.V1, 16); z.R = D.B;
+        z.outf = s.zdraft; z.z_w = ahead(d0.W2, d1.W2); z.z_x = s.draft_stride; z.z_out = (size_t)D.Bmax * D.V1;
+        clock_point(s, H + TP_DRAFT2, st);
+        if (D.B <= 16) lin_launch<1, 1, 8, LE_F32>(z, st, D.Hh);
+        else lin_launch<4, 1, 4, LE_F32>(z, st, D.Hh);
+    } else {
+        launch_draft32(D, s, draft, seq0, nseq, st);
+    }
     clock_point(s, H + TP_TOPK, st);
     const int lists = D.V1 > 4096 ? 0 : D.Hh * D.B, per_layer = cdiv(D.nH, 4) * nseq;
     const int layers = std::min(D.Ly, std::max(1, cdiv(D.Ly * per_layer, 256)));   // (layers per workgroup: one round of the 256 compute units)
     const int commits = prefill_mode ? 0 : cdiv(D.Ly, layers) * per_layer;
-    if (lists + commits > 0) hipLaunchKernelGGL(k_lists_commit, dim3(lists + commits), dim3(256), 0, st, D, s, lists, seq0, nseq, layers);
+    if (lists + commits > 0) hipLaunchKernelGGL(dtype ? k_lists_commit<bf16_t> : k_lists_commit<float>, dim3(lists + commits), dim3(256), 0, st, D, s, lists, seq0, nseq, layers);
     if (lists == 0) launch_topk(D, s, seq0, nseq, st);
 }
