@@ -71,7 +71,8 @@ typedef struct {
     int32_t dtype;          /* 0: fp32 weights/activations, 1: bf16 storage with fp32 accumulation */
     int32_t ignore_eos;     /* 1: EOS is an ordinary token (fixed-length benchmarks) */
     int32_t prefill_chunk;  /* rows of a sequence that one pass of vadusa_prefill runs through the decoder:
-                               0 = max_tree_nodes, else 1..VADUSA_MAX_PREFILL_CHUNK (longer passes turn the
+                               0 = max_tree_nodes, or more (up to VADUSA_MAX_TREE_NODES) while max_batch of
+                               them stay within 2048 rows; else 1..VADUSA_MAX_PREFILL_CHUNK (longer passes turn the
                                prompt's linear maps into many-row products; the arena grows with
                                max_batch * prefill_chunk rows of activations) */
 } vadusa_config;

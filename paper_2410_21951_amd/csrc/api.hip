@@ -40,7 +40,12 @@ static int fail(vadusa_ctx* c, int code, const char* fmt, ...) {
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // rows of one sequence in one pass of the prefill, and the most rows one sequence ever has in a forward
-static int prefill_rows(const vadusa_config& c) { return c.prefill_chunk > 0 ? c.prefill_chunk : c.max_tree_nodes; }
+// (prefill_chunk = 0: as many rows as a tree may ever have while the whole pass stays within 2048 rows, which fill the GPU
+// already; a launch costs the same few microseconds whatever its rows)
+static int prefill_rows(const vadusa_config& c) {
+    if (c.prefill_chunk > 0) return c.prefill_chunk;
+    return std::max(c.max_tree_nodes, std::min(VADUSA_MAX_TREE_NODES, std::max(1, 2048 / c.max_batch) / 16 * 16));
+}
 static int seq_rows_cap(const vadusa_config& c) { return std::max(c.max_tree_nodes, prefill_rows(c)); }
 static int pad16(int n) { return (n + 15) / 16 * 16; }
 
