@@ -513,11 +513,16 @@ __global__ __launch_bounds__(256, OCC) void k_big(LinArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Tree-masked attention (Sec. 2.1): one (sequence, head) and 16 query rows per workgroup.  Keys: cache positions
-// [0, L) and the rows of this forward at L + m where the query's mask bit m is set (CAUSAL: rows 0 .. n of a prompt
-// pass, which may have more rows than the mask table).  The four waves take 32-key blocks round-robin with a private
-// online softmax (S^T = K Q^T, O^T += V^T P^T on MFMA) and merge through LDS.  The cache keeps K and V^T in blocks of
-// 32 keys, each already in the layout of the MFMA operands (kc_off / vc_off in common.h).
+// Tree-masked attention (Sec. 2.1): one (sequence, head) and QT tiles of 16 query rows per workgroup.  Keys: cache
+// positions [0, L) and the rows of this forward at L + m where the query's mask bit m is set (CAUSAL: rows 0 .. n of a
+// prompt pass, which may have more rows than the mask table).  The four waves take 32-key blocks round-robin with a
+// private online softmax (S^T = K Q^T, O^T += V^T P^T on MFMA) and merge through LDS.  The cache keeps K and V^T in blocks
+// of 32 keys, each already in the layout of the MFMA operands (kc_off / vc_off in common.h).
+// QT = 2 where there are workgroups enough for every compute unit: a key block is then fetched once for 32 queries.
+// (64 sequences of 32 nodes, ~330 keys: 25 us a layer instead of 34; with 64 workgroups instead of 128 for one sequence
+// it takes 6.1 instead of 4.5.)  Measured and not kept: the key blocks split over up to four workgroups with the last
+// to arrive merging (2000 keys, 64 queries: 8.6 instead of 9.7, 1000 keys: 8.2 instead of 6.9); two blocks per step
+// (2000 keys: 9.3, 320 keys: 5.2 instead of 4.5).
 // ---------------------------------------------------------------------------
 struct AttnArgs {
     const bf16_t* q;
@@ -527,28 +532,37 @@ struct AttnArgs {
     const uint32_t* mask;
     int B, M, nH, d, maxpos;
 };
-template <bool CAUSAL>
+template <bool CAUSAL, int QT>
 __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
     constexpr int SO = 17;   // floats per row of the merge buffer: the merge reads a dimension's 16 queries' worth 64 rows apart
-    __shared__ float sm_o[4 * 64 * SO], sm_m[64], sm_l[64];
-    const int bh = blockIdx.x, qt = blockIdx.y;
+    __shared__ float sm_o[QT][4 * 64 * SO], sm_m[QT][64], sm_l[QT][64];
+    const int bh = blockIdx.x, qt0 = blockIdx.y * QT;
     if (bh >= a.B * a.nH) return;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, gq = lane >> 4, c = lane & 15;
     const int b = bh / a.nH, h = bh - b * a.nH;
     const int n_rows = ldg(a.n_rows + b), L = ldg(a.L + b);
-    const int node = min(qt * 16 + c, a.M - 1);
-    const bf16x8_t Q0 = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(b * a.M + node, h * 64 + 8 * gq, a.d >> 5)));
-    const bf16x8_t Q1 = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(b * a.M + node, h * 64 + 32 + 8 * gq, a.d >> 5)));
-    uint4 mw = make_uint4(0, 0, 0, 0);
-    if constexpr (!CAUSAL) mw = ldg4(a.mask + (size_t)node * MASK_WORDS);
-    const int q_out = tid >> 4, d_out = (tid & 15) * 4, nd_out = qt * 16 + q_out;   // the merge's outputs of this thread
-    bf16_t* const dst = a.att + toff(b * a.M + min(nd_out, a.M - 1), h * 64 + d_out, a.d >> 5);
+    int node[QT];
+    bf16x8_t Q0[QT], Q1[QT];
+    uint4 mw[QT];
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+        node[t] = min((qt0 + t) * 16 + c, a.M - 1);
+        Q0[t] = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(b * a.M + node[t], h * 64 + 8 * gq, a.d >> 5)));
+        Q1[t] = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(b * a.M + node[t], h * 64 + 32 + 8 * gq, a.d >> 5)));
+        mw[t] = make_uint4(0, 0, 0, 0);
+        if constexpr (!CAUSAL) mw[t] = ldg4(a.mask + (size_t)node[t] * MASK_WORDS);
+    }
+    const int q_out = tid >> 4, d_out = (tid & 15) * 4;   // the merge's outputs of this thread, per tile
     if (n_rows == 0) {
-        if (nd_out < a.M) *(uint2*)dst = make_uint2(0, 0);
+#pragma unroll
+        for (int t = 0; t < QT; ++t) {
+            const int nd = (qt0 + t) * 16 + q_out;
+            if (nd < a.M) *(uint2*)(a.att + toff(b * a.M + nd, h * 64 + d_out, a.d >> 5)) = make_uint2(0, 0);
+        }
         return;
     }
-    // (a causal pass: no query of the tile sees keys behind its last row)
-    const int T = min(CAUSAL ? L + min(qt * 16 + 16, a.M) : L + a.M, a.maxpos);
+    // (a causal pass: no query of the workgroup sees keys behind its last row)
+    const int T = min(CAUSAL ? L + min((qt0 + QT) * 16, a.M) : L + a.M, a.maxpos);
     const size_t hb = ((size_t)b * a.nH + h) * kv_cap(a.maxpos) * 64;
     const bf16_t *Kh = a.Kc + hb + lane * 8, *Vh = a.Vc + hb + lane * 8;
     const int nblk = (T + 31) >> 5;
@@ -557,10 +571,15 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) { kvb[i] = ldg4(Kh + off + i * 512); kvb[4 + i] = ldg4(Vh + off + i * 512); }
     };
-    float m_run = -1e30f, l_run = 0.f;
-    f32x4_t O[4];
+    float m_run[QT], l_run[QT];
+    f32x4_t O[QT][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) O[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < QT; ++t) {
+        m_run[t] = -1e30f;
+        l_run[t] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) O[t][i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    }
     constexpr int NB = 3;   // two blocks in flight behind the one being computed
     uint4 buf[NB][8];
     if (wave < nblk) {
@@ -569,61 +588,64 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
     }
     auto process = [&](const int blk, const uint4 (&cur)[8]) {
         const int p0 = blk << 5, v0 = p0 + 8 * gq;
-        f32x4_t sa = (f32x4_t){0.f, 0.f, 0.f, 0.f}, sb = sa;
-        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[0]), Q0, sa, 0, 0, 0);
-        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[1]), Q1, sa, 0, 0, 0);
-        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[2]), Q0, sb, 0, 0, 0);
-        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[3]), Q1, sb, 0, 0, 0);
-        // this lane: query c, keys v0 + 0..3 (sa) and v0 + 4..7 (sb).  Instantiated twice: blocks inside the committed
-        // cache need no mask tests.
-        uint32_t pk[4];
-        float m_new, corr, psum = 0.f;
-        auto softmax_block = [&](const unsigned okm) {
-            float sc[8];
-            float mx = -1e30f;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float sv = (j < 4 ? sa[j] : sb[j - 4]) * 0.125f;
-                sc[j] = (okm >> j) & 1u ? sv : -1e30f;
-                mx = fmaxf(mx, sc[j]);
-            }
-            mx = rows_max(mx);
-            m_new = fmaxf(m_run, mx);
-            corr = __expf(m_run - m_new);
+        for (int t = 0; t < QT; ++t) {
+            f32x4_t sa = (f32x4_t){0.f, 0.f, 0.f, 0.f}, sb = sa;
+            sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[0]), Q0[t], sa, 0, 0, 0);
+            sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[1]), Q1[t], sa, 0, 0, 0);
+            sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[2]), Q0[t], sb, 0, 0, 0);
+            sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[3]), Q1[t], sb, 0, 0, 0);
+            // this lane: query c, keys v0 + 0..3 (sa) and v0 + 4..7 (sb).  Instantiated twice: blocks inside the committed
+            // cache need no mask tests.
+            uint32_t pk[4];
+            float m_new, corr, psum = 0.f;
+            auto softmax_block = [&](const unsigned okm) {
+                float sc[8];
+                float mx = -1e30f;
 #pragma unroll
-            for (int j = 0; j < 8; j += 2) {
-                const float p0f = (okm >> j) & 1u ? __expf(sc[j] - m_new) : 0.f;
-                const float p1f = (okm >> (j + 1)) & 1u ? __expf(sc[j + 1] - m_new) : 0.f;
-                psum += p0f + p1f;
-                pk[j >> 1] = pack_bf16(p0f, p1f);
-            }
-        };
-        if (p0 + 32 > L) {   // the block reaches into this forward's rows (same for the whole wave)
-            unsigned okm = 0;   // which of the lane's 8 keys the query may see
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int key = v0 + j, mm = key - L;
-                bool okj = key < L;
-                if (!okj && key < T) {
-                    if constexpr (CAUSAL) okj = mm <= node;
-                    else {
-                        const uint32_t w = mm < 32 ? mw.x : mm < 64 ? mw.y : mm < 96 ? mw.z : mw.w;
-                        okj = (w >> (mm & 31)) & 1u;
-                    }
+                for (int j = 0; j < 8; ++j) {
+                    const float sv = (j < 4 ? sa[j] : sb[j - 4]) * 0.125f;
+                    sc[j] = (okm >> j) & 1u ? sv : -1e30f;
+                    mx = fmaxf(mx, sc[j]);
                 }
-                okm |= okj ? (1u << j) : 0u;
-            }
-            softmax_block(okm);
-        } else {
-            softmax_block(0xffu);
-        }
-        l_run = l_run * corr + psum;
-        m_run = m_new;
-        const bf16x8_t pfrag = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+                mx = rows_max(mx);
+                m_new = fmaxf(m_run[t], mx);
+                corr = __expf(m_run[t] - m_new);
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-            O[dt] *= corr;
-            O[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[4 + dt]), pfrag, O[dt], 0, 0, 0);
+                for (int j = 0; j < 8; j += 2) {
+                    const float p0f = (okm >> j) & 1u ? __expf(sc[j] - m_new) : 0.f;
+                    const float p1f = (okm >> (j + 1)) & 1u ? __expf(sc[j + 1] - m_new) : 0.f;
+                    psum += p0f + p1f;
+                    pk[j >> 1] = pack_bf16(p0f, p1f);
+                }
+            };
+            if (p0 + 32 > L) {   // the block reaches into this forward's rows (same for the whole wave)
+                unsigned okm = 0;   // which of the lane's 8 keys the query may see
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int key = v0 + j, mm = key - L;
+                    bool okj = key < L;
+                    if (!okj && key < T) {
+                        if constexpr (CAUSAL) okj = mm <= node[t];
+                        else {
+                            const uint32_t w = mm < 32 ? mw[t].x : mm < 64 ? mw[t].y : mm < 96 ? mw[t].z : mw[t].w;
+                            okj = (w >> (mm & 31)) & 1u;
+                        }
+                    }
+                    okm |= okj ? (1u << j) : 0u;
+                }
+                softmax_block(okm);
+            } else {
+                softmax_block(0xffu);
+            }
+            l_run[t] = l_run[t] * corr + psum;
+            m_run[t] = m_new;
+            const bf16x8_t pfrag = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) {
+                O[t][dt] *= corr;
+                O[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[4 + dt]), pfrag, O[t][dt], 0, 0, 0);
+            }
         }
     };
     for (int blk = wave; blk < nblk; blk += 4 * NB) {
@@ -636,29 +658,34 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
             }
         }
     }
-    l_run = rows_sum(l_run);
-    if (gq == 0) { sm_m[wave * 16 + c] = m_run; sm_l[wave * 16 + c] = l_run; }
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int t = 0; t < QT; ++t) {
+        l_run[t] = rows_sum(l_run[t]);
+        if (gq == 0) { sm_m[t][wave * 16 + c] = m_run[t]; sm_l[t][wave * 16 + c] = l_run[t]; }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sm_o[(wave * 64 + dt * 16 + 4 * gq + i) * SO + c] = O[dt][i];
-    __syncthreads();
-    float mstar = sm_m[q_out];
+        for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-    for (int w = 1; w < 4; ++w) mstar = fmaxf(mstar, sm_m[w * 16 + q_out]);
-    float f[4], lsum = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) { f[w] = __expf(sm_m[w * 16 + q_out] - mstar); lsum += f[w] * sm_l[w * 16 + q_out]; }
-    const float inv = 1.f / lsum;
-    float o[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float s = 0.f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) s += f[w] * sm_o[(w * 64 + d_out + j) * SO + q_out];
-        o[j] = s * inv;
+            for (int i = 0; i < 4; ++i) sm_o[t][(wave * 64 + dt * 16 + 4 * gq + i) * SO + c] = O[t][dt][i];
     }
-    if (nd_out < a.M) *(uint2*)dst = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+        const int nd = (qt0 + t) * 16 + q_out;
+        float mstar = sm_m[t][q_out];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) mstar = fmaxf(mstar, sm_m[t][w * 16 + q_out]);
+        float f[4], lsum = 0.f, o[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) { f[w] = __expf(sm_m[t][w * 16 + q_out] - mstar); lsum += f[w] * sm_l[t][w * 16 + q_out]; }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            o[j] = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) o[j] += f[w] * sm_o[t][(w * 64 + d_out + j) * SO + q_out];
+        }
+        const float inv = 1.f / lsum;
+        if (nd < a.M) *(uint2*)(a.att + toff(b * a.M + nd, h * 64 + d_out, a.d >> 5)) = make_uint2(pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv));
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -807,6 +834,18 @@ static void clock_point(const DevState& s, int ph, hipStream_t st) {
 #endif
 }
 
+template <int QT>
+static void attn_launch(const AttnArgs& t, bool causal, hipStream_t st) {
+    const dim3 grid(pad8(t.B * t.nH), cdiv(cdiv(t.M, 16), QT));
+    if (causal) hipLaunchKernelGGL((k_attn<true, QT>), grid, dim3(256), 0, st, t);
+    else hipLaunchKernelGGL((k_attn<false, QT>), grid, dim3(256), 0, st, t);
+}
+static void attn(const AttnArgs& t, bool causal, hipStream_t st) {
+    const int qt = cdiv(t.M, 16);
+    if (qt > 1 && t.B * t.nH * cdiv(qt, 2) >= 512) attn_launch<2>(t, causal, st);   // two workgroups per compute unit
+    else attn_launch<1>(t, causal, st);
+}
+
 void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st) {
     const int R = D.B * D.M, d = D.d;
     const size_t kv_layer = (size_t)D.Bmax * D.nH * kv_cap(D.maxpos) * 64;
@@ -825,9 +864,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         lin<LE_QKV>(a, big_min, st);
         AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos};
         clock_point(s, 2 + 5 * l, st);
-        const dim3 ga(pad8(D.B * D.nH), cdiv(D.M, 16));
-        if (table == 1) hipLaunchKernelGGL(k_attn<true>, ga, dim3(256), 0, st, t);
-        else hipLaunchKernelGGL(k_attn<false>, ga, dim3(256), 0, st, t);
+        attn(t, table == 1, st);
         LinArgs o = base;
         o.X = (const bf16_t*)s.att; o.W = (const uint4*)w.Wo; o.bias = w.bo; o.nks = d >> 5; o.N = d; o.NT = d >> 4;
         o.out = s.xb; o.outf = s.x; o.stats_out = (float2*)s.stats;
