@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "common.h"
@@ -48,6 +49,45 @@ static int prefill_rows(const vadusa_config& c) {
 }
 static int seq_rows_cap(const vadusa_config& c) { return std::max(c.max_tree_nodes, prefill_rows(c)); }
 static int pad16(int n) { return (n + 15) / 16 * 16; }
+
+static size_t result_words(const vadusa_config& c) { return 4 + (size_t)c.max_batch * (3 + VADUSA_MAX_DRAFT_HEADS + 1); }
+
+// ---------------------------------------------------------------------------
+// Pinned host memory that results are written into by the last kernel of a call.  A copy to pageable memory costs a step
+// some 30 to 40 us more.  A context takes one block when it is created and hands it back when it is destroyed, which
+// makes no HIP call: blocks stay in a list for later contexts, so that there are never more of them than there have been
+// contexts alive at once.  Without one (nullptr) a call copies to ordinary memory.
+// ---------------------------------------------------------------------------
+struct PinnedBlock { int32_t* p; size_t words; };
+struct PinnedList { std::mutex m; std::vector<PinnedBlock> free; };
+static PinnedList& pinned_list() {
+    static PinnedList* l = new PinnedList;   // (never destroyed: a context may be freed while the process ends)
+    return *l;
+}
+static PinnedBlock pinned_take(size_t words) {
+    {
+        PinnedList& l = pinned_list();
+        std::lock_guard<std::mutex> lock(l.m);
+        for (size_t i = 0; i < l.free.size(); ++i)
+            if (l.free[i].words >= words) {
+                const PinnedBlock b = l.free[i];
+                l.free.erase(l.free.begin() + (long)i);
+                return b;
+            }
+    }
+    void* p = nullptr;
+    words = (words + 1023) / 1024 * 1024;
+#if defined(__HIPCC__)
+    if (hipHostMalloc(&p, words * 4, hipHostMallocPortable) != hipSuccess) { (void)hipGetLastError(); p = nullptr; }
+#endif
+    return PinnedBlock{(int32_t*)p, p ? words : 0};
+}
+static void pinned_give(const PinnedBlock& b) {
+    if (!b.p) return;
+    PinnedList& l = pinned_list();
+    std::lock_guard<std::mutex> lock(l.m);
+    l.free.push_back(b);
+}
 
 extern "C" int vadusa_config_check(const vadusa_config* c, char* msg, size_t n) {
     if (!c) { set_msg(msg, n, "config is null"); return VADUSA_EINVAL; }
@@ -257,10 +297,10 @@ static size_t layout(const vadusa_config& c, char* base, DevState* s, std::vecto
     st.zdraft = (float*)cv.take(Hh * B * V1 * 4);
     auto ints = [&](size_t n) { return (int32_t*)cv.take(n * 4); };
     // What a step hands back to the host sits in one block, so that one copy fetches it: the error word (4 words),
-    // accepted lengths, committed lengths, accepted tokens (result_block_words)
-    int32_t* res = ints(4 + 2 * B + B * (VADUSA_MAX_DRAFT_HEADS + 1));
-    st.kerr = res; st.acc_len = res + 4; st.L = res + 4 + B; st.acc_tok = res + 4 + 2 * B;
-    st.root = ints(B); st.finished = ints(B);
+    // accepted lengths, committed lengths, roots, accepted tokens (result_words)
+    int32_t* res = ints(result_words(c));
+    st.kerr = res; st.acc_len = res + 4; st.L = res + 4 + B; st.root = res + 4 + 2 * B; st.acc_tok = res + 4 + 3 * B;
+    st.finished = ints(B);
     st.draft_topk = ints(B * Hh * VADUSA_MAX_TOPK);
     st.tok = ints(R); st.n_rows = ints(B); st.edge_ok = ints(R);
     st.path = ints(B * (VADUSA_MAX_DRAFT_HEADS + 2));
@@ -369,6 +409,12 @@ extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena
     if (e == hipSuccess) e = hipMemcpy(c->s.t_rank[1], rk.data(), Mm * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->s.t_mask[1], mask.data(), mask.size() * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) { delete c; return VADUSA_EHIP; }
+    c->pinned = nullptr;
+    {
+        const PinnedBlock b = pinned_take(std::max(result_words(*cfg), (size_t)5 + cfg->max_positions));
+        c->pinned = b.p;
+        c->pinned_words = b.words;
+    }
     *out = c;
     return VADUSA_OK;
 }
@@ -379,6 +425,7 @@ extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena
 // The caller drains its stream before it frees the arena.
 extern "C" void vadusa_destroy(vadusa_ctx* c) {
     if (!c) return;
+    pinned_give(PinnedBlock{c->pinned, c->pinned_words});
     delete c;
 }
 
@@ -457,6 +504,26 @@ static int kerr_seen(vadusa_ctx* c, int32_t k) {
     }
     return VADUSA_OK;
 }
+// Everything a call hands to the host, in one piece: na words from a, nb from b and nc from c2, behind everything the
+// stream holds.  *out is valid until the next fetch.
+static int fetch(vadusa_ctx* c, const int32_t* a, size_t na, const int32_t* b, size_t nb, const int32_t* c2, size_t nc, const int32_t** out) {
+    const size_t n = na + nb + nc;
+    if (c->pinned && n <= c->pinned_words) {
+        launch_gather(a, (int)na, b, (int)nb, c2, (int)nc, c->pinned, c->stream);
+        { int rc = launched(c); if (rc) return rc; }
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        *out = c->pinned;
+        return VADUSA_OK;
+    }
+    c->unpinned.resize(n);
+    if (na) HIP_TRY(c, hipMemcpyAsync(c->unpinned.data(), a, na * 4, hipMemcpyDeviceToHost, c->stream));
+    if (nb) HIP_TRY(c, hipMemcpyAsync(c->unpinned.data() + na, b, nb * 4, hipMemcpyDeviceToHost, c->stream));
+    if (nc) HIP_TRY(c, hipMemcpyAsync(c->unpinned.data() + na + nb, c2, nc * 4, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    *out = c->unpinned.data();
+    return VADUSA_OK;
+}
+
 static int check_kerr(vadusa_ctx* c) {
     if (!c->cfg.dtype) return VADUSA_OK;
     int32_t k = 0;
@@ -561,10 +628,10 @@ extern "C" int vadusa_prefill(vadusa_ctx* c, int32_t batch, const int32_t* text_
     }
     launch_continue(D, s, c->draft, 0, batch, 1, c->cfg.ignore_eos, false, c->cfg.dtype, c->stream);
     { int rc = launched(c); if (rc) return rc; }
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    HIP_TRY(c, hipGetLastError());
-    { int rc = check_kerr(c); if (rc) return rc; }
-    if (first_root) HIP_TRY(c, hipMemcpy(first_root, s.root, B * 4, hipMemcpyDeviceToHost));
+    const int32_t* res = nullptr;
+    { int rc = fetch(c, s.kerr, 4, s.root, B, nullptr, 0, &res); if (rc) return rc; }
+    { int rc = kerr_seen(c, c->cfg.dtype ? res[0] : 0); if (rc) return rc; }
+    if (first_root) memcpy(first_root, res + 4, B * 4);
     c->batch = batch;
     c->state = 2;
     for (int b = 0; b < batch; ++b) { c->L_ub[b] = (int)seqs[b].size(); c->pending[b] = 0; }
@@ -735,15 +802,14 @@ static int step_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau, c
     if (rc) return rc;
     if (accepted_tok) {
         const int B = c->batch, W = VADUSA_MAX_DRAFT_HEADS + 1, Hh1 = c->cfg.n_draft_heads + 1;
-        // one copy for everything the host reads after a step (every separate copy is a trip of tens of microseconds)
-        std::vector<int32_t> blk(4 + 2 * (size_t)c->cfg.max_batch + (size_t)c->cfg.max_batch * W);
-        HIP_TRY(c, hipMemcpyAsync(blk.data(), c->s.kerr, blk.size() * 4, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        const int32_t* blk = nullptr;
+        rc = fetch(c, c->s.kerr, result_words(c->cfg), nullptr, 0, nullptr, 0, &blk);
+        if (rc) return rc;
         rc = kerr_seen(c, c->cfg.dtype ? blk[0] : 0);
         if (rc) return rc;
-        const int32_t* len = blk.data() + 4;
+        const int32_t* len = blk + 4;
         const int32_t* L = len + c->cfg.max_batch;
-        const int32_t* tok = L + c->cfg.max_batch;
+        const int32_t* tok = L + 2 * (size_t)c->cfg.max_batch;
         for (int b = 0; b < B; ++b) {
             accepted_len[b] = len[b];
             for (int j = 0; j < Hh1; ++j) accepted_tok[(size_t)b * Hh1 + j] = j < len[b] ? tok[(size_t)b * W + j] : -1;
@@ -772,15 +838,13 @@ extern "C" int vadusa_read_output(vadusa_ctx* c, int32_t seq, int32_t* tok, int3
     { int rc = refuse_errored(c); if (rc) return rc; }
     if (c->state < 2) return fail(c, VADUSA_ESTATE, "prefill first");
     if (seq < 0 || seq >= c->batch || !n_out) return fail(c, VADUSA_EINVAL, "bad seq or null n_out");
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    { int rc = check_kerr(c); if (rc) return rc; }
-    int32_t n = 0;
-    HIP_TRY(c, hipMemcpy(&n, c->s.n_out + seq, 4, hipMemcpyDeviceToHost));
+    const int room = tok ? std::max(0, std::min(capacity, c->cfg.max_positions)) : 0;
+    const int32_t* res = nullptr;
+    { int rc = fetch(c, c->s.kerr, 4, c->s.n_out + seq, 1, c->s.out_tok + (size_t)seq * c->cfg.max_positions, room, &res); if (rc) return rc; }
+    { int rc = kerr_seen(c, c->cfg.dtype ? res[0] : 0); if (rc) return rc; }
+    const int32_t n = res[4];
     *n_out = n;
-    if (tok) {
-        const int m = std::min(n, capacity);
-        if (m > 0) HIP_TRY(c, hipMemcpy(tok, c->s.out_tok + (size_t)seq * c->cfg.max_positions, (size_t)m * 4, hipMemcpyDeviceToHost));
-    }
+    for (int i = 0; i < std::min(n, room); ++i) tok[i] = res[5 + i];
     return VADUSA_OK;
 }
 

@@ -259,6 +259,9 @@ struct vadusa_ctx {
     float* scores;               // same shape: perturbed scores that replace the logits in such a step
     int sampled;                 // the pending / last verification was a stochastic one
     int big_min;                 // many-row maps: k_big's tiles from this many on (environment VADUSA_BIG_MIN_UNITS, for tests of small shapes); 0: the rule
+    int32_t* pinned;             // host memory that the last kernel of a call writes results into (null: none)
+    size_t pinned_words;
+    std::vector<int32_t> unpinned;   // its stand-in
     int errored;                 // the error word was raised: every call but vadusa_prefill refuses until that resets the context
     std::string err;
 };
@@ -313,6 +316,8 @@ void launch_topk(const Dims& D, const DevState& s, int seq0, int nseq, hipStream
 void launch_perturb(const float* logits, const float* u, float* scores, int rows, int V1, float temperature,
                     float top_p, int tau, hipStream_t st);
 void launch_convert(const float* src, void* dst, size_t n, int dtype, hipStream_t st);
+// na words from a, nb from b, nc from c, one behind the other, into host memory the GPU can write
+void launch_gather(const int32_t* a, int na, const int32_t* b, int nb, const int32_t* c, int nc, int32_t* host, hipStream_t st);
 void launch_advance(const DevState& s, int B, hipStream_t st);
 void launch_read_kv(const Dims& D, const void* cache_layer, int seq, int which, int pos0, int npos, float* out, int dtype, hipStream_t st);
 void launch_to_float(const void* src, float* dst, size_t n, int dtype, hipStream_t st);

@@ -113,6 +113,13 @@ void launch_advance(const DevState& s, int B, hipStream_t st) {
     hipLaunchKernelGGL(k_advance, dim3((B + 63) / 64), dim3(64), 0, st, s, B);
 }
 
+__global__ __launch_bounds__(256) void k_gather(const int32_t* a, int na, const int32_t* b, int nb, const int32_t* c, int nc, int32_t* host) {
+    for (int i = threadIdx.x; i < na + nb + nc; i += 256) host[i] = i < na ? a[i] : i < na + nb ? b[i - na] : c[i - na - nb];
+}
+void launch_gather(const int32_t* a, int na, const int32_t* b, int nb, const int32_t* c, int nc, int32_t* host, hipStream_t st) {
+    hipLaunchKernelGGL(k_gather, dim3(1), dim3(256), 0, st, a, na, b, nb, c, nc, host);
+}
+
 // out[p][head*64 + dim] = K or V of (seq, head, position pos0 + p, dim)
 template <class T>
 __global__ void k_read_kv(Dims D, const T* __restrict__ cache, int seq, int which, int pos0, int npos, float* out) {
