@@ -1,0 +1,66 @@
+"""The kernels of the decoder layers at the sizes where they can go wrong: remainders of row and column tiles, reductions
+whose stages leave a remainder, the change from one tile shape to the next, an odd number of query tiles, and
+the row statistics of the fp32 maps on both sides of what they keep in registers.  Against the CPU oracle, with the
+tolerances of tests/parity.py (logits relative L2: 1e-4 in fp32, 1e-2 in bf16)."""
+import numpy as np
+import pytest
+
+from synth import ModelConfig, make_weights, make_tree
+from test_gpu_parity import rand_tokens
+
+pytestmark = pytest.mark.gpu
+
+# Weight scale.  The harness takes a decision for an error when its margin exceeds 1e-2, an absolute logit gap stated for a
+# logit spread of 0.57 to 0.64 (weight std x sqrt(d)).  bf16 logits are off by some 5e-3 of their spread, so the gap of two by
+# 7e-3: a spread of 0.9 (std 0.05 at d = 320) has gaps of 1.5e-2 decided either way.  The scale keeps the spread at 0.57.
+def _std(cfg):
+    return 0.08 if cfg.dtype == "fp32" else 0.57 / cfg.d_model ** 0.5
+
+
+def _run(cfg, batch, nodes, caps, taus, seed, prompt_lo, prompt_hi, compared=1):
+    from parity import Lockstep
+    W = make_weights(cfg, seed, std=_std(cfg), ln_jitter=0.1)
+    rng = np.random.default_rng(seed)
+    text, prompt = rand_tokens(cfg, rng, batch, (2, 6), (prompt_lo, prompt_hi))
+    ls = Lockstep(cfg, W, text, prompt, nodes)
+    tree = make_tree(nodes, caps)
+    for tau in taus:
+        ls.step(tree, tau)
+    ls.check_kv(layers=[0, cfg.n_layers - 1])
+    s = ls.stats
+    print(f"d {cfg.d_model} rows {batch * nodes}: compared {s.compared}/{s.steps} logit err {s.max_logit_err:.2e}", flush=True)
+    assert s.compared >= compared
+
+
+def _cfg(dtype, d, V, layers=2, heads=2, ffn=None, maxpos=192):
+    return ModelConfig(n_layers=layers, d_model=d, n_heads=d // 64, head_dim=64, d_ffn=ffn or 3 * d, speech_vocab=V, text_vocab=40,
+                       n_draft_heads=heads, max_positions=maxpos, dtype=dtype)
+
+
+# d: one, three, five and eight stages of 64; rows just below, at and above a 64-row tile; V + 1 logits: ragged column tiles
+@pytest.mark.parametrize("d,nodes,batch,V", [(64, 63, 1, 127), (192, 32, 2, 128), (320, 65, 1, 257), (512, 43, 3, 300)])
+def test_many_row_tiles_at_their_edges(monkeypatch, d, nodes, batch, V):
+    monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", "1")
+    _run(_cfg("bf16", d, V), batch, nodes, (9, 9), (2, 1), 300 + d, 20, 70)
+
+
+# rows at which the small-tile kernel changes its shape (16, 32, 64, 128, 192 rows and one more)
+@pytest.mark.parametrize("rows", [1, 16, 17, 33, 64, 97, 128, 193])
+def test_small_tile_shapes(rows):
+    batch = 1 if rows <= 100 else 2 if rows % 2 == 0 else 1
+    nodes = rows // batch if rows // batch <= 128 else 0
+    if not nodes:
+        batch, nodes = 2, 97    # 194 rows
+    caps = () if nodes == 1 else (10, 10, 10)
+    _run(_cfg("bf16", 256, 301, heads=3, maxpos=224), batch, nodes, caps, (1, 2), 400 + rows, 30, 80)
+
+
+def test_two_query_tiles_per_workgroup_with_an_odd_number_of_tiles():
+    # 40 nodes: three tiles of 16 queries, the last one ragged; 32 sequences x 8 heads
+    _run(_cfg("bf16", 512, 90, layers=1, ffn=256, maxpos=128), 32, 40, (7, 7), (2,), 511, 10, 60)
+
+
+# 384 values of a row stay in registers, more are read again; 15 and 17 rows: one row tile, two
+@pytest.mark.parametrize("d,nodes,V", [(64, 15, 70), (384, 17, 200), (448, 33, 129)])
+def test_fp32_maps_at_their_edges(d, nodes, V):
+    _run(_cfg("fp32", d, V), 2, nodes, (6, 6), (1, 3), 600 + d, 20, 60)
