@@ -50,7 +50,7 @@ def measured_traffic(workload):
     """HBM bytes per step from the rocprofv3 --pmc runs (FETCH_SIZE + WRITE_SIZE, scaled by a
     copy kernel of known size); the summary under profiles/ carries the figure on a `traffic_bytes_per_launch:`
     line.  None when no such measurement exists for the workload."""
-    path = os.path.join(ROOT, "profiles", f"k_step_{workload}_pmc.md")
+    path = os.path.join(ROOT, "profiles", f"step_{workload}_pmc.md")
     try:
         for line in open(path):
             if line.startswith("traffic_bytes_per_launch:"):
