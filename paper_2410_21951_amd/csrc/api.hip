@@ -50,6 +50,10 @@ static int prefill_rows(const vadusa_config& c) {
 static int seq_rows_cap(const vadusa_config& c) { return std::max(c.max_tree_nodes, prefill_rows(c)); }
 static int pad16(int n) { return (n + 15) / 16 * 16; }
 
+// bytes of the K cache, and of the V cache: positions are stored in whole blocks (kv_cap)
+static size_t kv_bytes(const vadusa_config& c) {
+    return (size_t)c.n_layers * c.max_batch * c.n_heads * kv_cap(c.max_positions) * 64 * (c.dtype ? 2 : 4);
+}
 static size_t result_words(const vadusa_config& c) { return 4 + (size_t)c.max_batch * (3 + VADUSA_MAX_DRAFT_HEADS + 1); }
 
 // ---------------------------------------------------------------------------
@@ -278,9 +282,8 @@ static size_t layout(const vadusa_config& c, char* base, DevState* s, std::vecto
     for (size_t i = 0; i < Hh; ++i) {
         mat(&dw[i].W1, d, d); vec(&dw[i].b1, d); mat(&dw[i].W2, V1, d);
     }
-    const size_t kv = (size_t)c.n_layers * B * c.n_heads * kv_cap((int)P) * 64 * e;
-    st.Kc = cv.take(kv);
-    st.Vc = cv.take(kv);
+    st.Kc = cv.take(kv_bytes(c));
+    st.Vc = cv.take(kv_bytes(c));
     st.x = (float*)cv.take(R * d * 4);
     const size_t Rp = (R + 15) / 16 * 16, Bp = (B + 15) / 16 * 16;   // tiled activation buffers hold whole row tiles
     st.draft_stride = Bp * d;
@@ -388,8 +391,9 @@ extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena
     c->errored = 0;
     c->big_min = getenv("VADUSA_BIG_MIN_UNITS") ? std::max(1, atoi(getenv("VADUSA_BIG_MIN_UNITS"))) : 0;
     {
-        // the error flag starts at zero; an unwritten KV row must never hold NaN bits
-        const size_t kv = (size_t)cfg->n_layers * cfg->max_batch * cfg->n_heads * cfg->max_positions * 64 * c->elem;
+        // the error flag starts at zero; an unwritten KV row must never hold NaN bits (a masked key enters the attention as
+        // 0 x its value), the rows that fill the last block of 32 included
+        const size_t kv = kv_bytes(*cfg);
         hipError_t e0 = hipMemset(c->s.tprof, 0, 1024 * 8);
         if (e0 == hipSuccess) e0 = hipMemset(c->s.kerr, 0, 16);
         if (e0 == hipSuccess) e0 = hipMemset(c->s.Kc, 0, kv);

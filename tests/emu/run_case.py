@@ -8,7 +8,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, HERE)
 sys.path.insert(0, os.path.dirname(HERE))
 import emulate
-emulate.install(sys.argv[1])
+# nanfill: the arena arrives holding NaN bits (0xFFFF is a NaN in bf16, 0xFFFFFFFF in fp32)
+emulate.install(sys.argv[1], fill=0xFF if sys.argv[2].endswith("-nanfill") else 0xAB)
 import numpy as np
 from synth import ModelConfig, make_weights, make_tree, make_uniforms
 from parity import Lockstep
@@ -110,6 +111,23 @@ if dtype == "bf16-giveup":
     assert codes == [-5, -4, -4], codes
     assert run() == want
     print("emulated give-up path: reported, refused, recovered", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
+if dtype.endswith("-nanfill"):
+    # A cache of 72 positions is stored as 96 (whole blocks of 32 keys), and a masked or unwritten key enters the
+    # attention as 0 x its value: whatever the caller's memory held, a context starts with zeros in all of it.
+    cfg = ModelConfig(n_layers=1, d_model=64, n_heads=1, head_dim=64, d_ffn=128, speech_vocab=70, text_vocab=20,
+                      n_draft_heads=2, max_positions=72, dtype=dtype[:4])
+    W = make_weights(cfg, 71, std=0.08)
+    rng = np.random.default_rng(75)
+    text = [rng.integers(0, cfg.text_vocab, 2 + b).astype(np.int32) for b in range(4)]
+    prompt = [rng.integers(0, cfg.speech_vocab, 9 - b).astype(np.int32) for b in range(4)]
+    ls = Lockstep(cfg, W, text, prompt, 8)
+    ls.step(make_tree(8, (3, 2)), 2)
+    ls.check_kv(layers=[0])
+    s = ls.stats
+    print(f"emulated {dtype}: compared {s.compared}/{s.steps} logit err {s.max_logit_err:.2e}", flush=True)
+    assert s.compared >= 1
     sys.stdout.flush()
     os._exit(0)
 if dtype in ("bf16-nan", "fp32-nan"):
