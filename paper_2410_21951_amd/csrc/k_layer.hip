@@ -344,16 +344,19 @@ __global__ __launch_bounds__(256, OCC) void k_big(LinArgs a) {
         Xp[j] = (const char*)((const uint4*)a.X + ((size_t)min(rb * NRT + (T >> 1), last_rt) * a.nks + (T & 1)) * 64);
     }
     const int second = (lane >> 4) & 1, piece = (lane & 15) + 16 * (lane >> 5);   // operand lane -> tile of the pair, piece of the tile's first half
+    // Tiles by a 64-bit base of the wave and a 32-bit distance from it: a map may hold more than 4 GiB.
+    const int wt_first = min(wt0, a.NT - 1);
+    const char* Wp = (const char*)a.W + (size_t)wt_first * a.nks * 1024;
     uint32_t woff[NC2];
 #pragma unroll
-    for (int c = 0; c < NC2; ++c) woff[c] = (uint32_t)min(wt0 + 2 * c + second, a.NT - 1) * (uint32_t)a.nks * 1024u + (uint32_t)piece * 16u;
+    for (int c = 0; c < NC2; ++c) woff[c] = (uint32_t)(min(wt0 + 2 * c + second, a.NT - 1) - wt_first) * (uint32_t)a.nks * 1024u + (uint32_t)piece * 16u;
     auto loadA = [&](int c, uint4 (&x)[NA]) {
         const uint32_t off = (uint32_t)min(c, nst - 1) * 2048u + (uint32_t)lane * 16u;
 #pragma unroll
         for (int j = 0; j < NA; ++j) x[j] = ldg4(Xp[j] + off);
     };
     auto loadW = [&](int c, uint4 (&w)[4][NC2]) {   // the four operand halves (k-step, half) of the stage
-        const char* base = (const char*)a.W + (uint32_t)min(c, nst - 1) * 2048u;
+        const char* base = Wp + (uint32_t)min(c, nst - 1) * 2048u;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll

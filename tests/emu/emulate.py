@@ -35,6 +35,8 @@ def build(out_dir, extra_flags=()):
         text = text.replace("extern __shared__ float s_s[];", "float* s_s = (float*)emu_dyn_lds;")
         text = "\n".join(l for l in text.split("\n") if "s_waitcnt" not in l)
         text = re.sub(r"hipLaunchCooperativeKernel\(\(const void\*\)(\w+), (.*), st\);", r"emu_launch_coop(\1, \2);", text)
+        if name == "k_layer.hip":
+            text += open(os.path.join(HERE, "layer_exports.inc")).read()
         dst = os.path.join(gen, name[:-4] + ".cpp" if name.endswith(".hip") else name)
         open(dst, "w").write(text)
         if dst.endswith(".cpp"):

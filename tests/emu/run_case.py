@@ -113,6 +113,38 @@ if dtype == "bf16-giveup":
     print("emulated give-up path: reported, refused, recovered", flush=True)
     sys.stdout.flush()
     os._exit(0)
+if dtype == "bf16-4gib-map":
+    # One linear map of more than 4 GiB (K = 4096): 64 x 128 workgroups at its start and on both sides of the 4 GiB mark.
+    # The weights are address space that is never touched but for the tiles of these workgroups, all values of tile t
+    # being t's value; X is all ones, its statistics mean 0 and variance 1.
+    import ctypes as C
+    import mmap
+    import paper_2410_21951_amd.vadusa as V
+    nks, R = 128, 2
+    tile = nks * 1024                                     # bytes of a column tile
+    first = (1 << 32) // tile                             # first tile behind the mark
+    NT = first + 8
+    space = mmap.mmap(-1, NT * tile, flags=mmap.MAP_PRIVATE | mmap.MAP_ANONYMOUS | 0x4000)   # MAP_NORESERVE
+    Wt = np.frombuffer(space, np.uint16)
+    value = lambda t: 0x3c00 + (t % 8) * 8 + (256 if t >= first else 128 if t >= 8 else 0)   # bits of a bf16
+    groups = (0, first // 8 - 1, first // 8)
+    for g in groups:
+        for t in range(8 * g, 8 * g + 8):
+            Wt[t * tile // 2:(t + 1) * tile // 2] = value(t)
+    X = np.full(nks * 512, 0x3f80, np.uint16)
+    zero = np.zeros(NT * 16, np.float32)
+    stats = np.tile(np.array([0, 16], np.float32), R * nks * 2)
+    out = np.full((R, NT * 16), np.nan, np.float32)
+    p = lambda a: a.ctypes.data_as(C.c_void_p)
+    for g in groups:
+        V._lib.emu_big_logits(p(X), p(Wt), p(zero), p(zero), p(stats), p(out), nks, NT, R, C.c_uint(g))
+        for t in range(8 * g, 8 * g + 8):
+            want = 32 * nks * np.array([value(t) << 16], np.uint32).view(np.float32)[0] / np.sqrt(1 + 1e-5)
+            got = out[:, 16 * t:16 * t + 16]
+            assert np.abs(got / want - 1).max() < 1e-5, (g, t, got[0, 0], want)   # (4096 equal terms: sums exact but for a few roundings)
+    print("emulated 4 GiB map: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype.endswith("-nanfill"):
     # A cache of 72 positions is stored as 96 (whole blocks of 32 keys), and a masked or unwritten key enters the
     # attention as 0 x its value: whatever the caller's memory held, a context starts with zeros in all of it.
