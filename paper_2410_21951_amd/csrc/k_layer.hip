@@ -766,10 +766,11 @@ __global__ __launch_bounds__(256) void k_continue(Dims D, DevState s, int seq0, 
 }
 
 // Workgroups below `lists`: one draft head's list of one sequence; the others: four heads (a wave each) of one
-// sequence's cache over `layers` layers.
+// sequence's cache over `layers` layers.  Sequences seq0 .. seq0 + nseq - 1 only: the lists of a sequence whose verification
+// is still pending stay what that verification used.
 template <class T>
 __global__ __launch_bounds__(256) void k_lists_commit(Dims D, DevState s, int lists, int seq0, int nseq, int layers) {
-    if ((int)blockIdx.x < lists) { dev_topk(D, s, blockIdx.x / D.B, blockIdx.x % D.B); return; }
+    if ((int)blockIdx.x < lists) { dev_topk(D, s, blockIdx.x / nseq, seq0 + blockIdx.x % nseq); return; }
     const int u = (int)blockIdx.x - lists, hq = cdiv(D.nH, 4);
     const int head = (u % hq) * 4 + (int)(threadIdx.x >> 6), b = (u / hq) % nseq, layer0 = u / (hq * nseq) * layers;
     if (head < D.nH) dev_commit_kv_layers<T>(D, s, layer0, min(layers, D.Ly - layer0), seq0 + b, head, threadIdx.x & 63);
@@ -924,7 +925,7 @@ void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>
         launch_draft32(D, s, draft, seq0, nseq, st);
     }
     clock_point(s, H + TP_TOPK, st);
-    const int lists = D.V1 > 4096 ? 0 : D.Hh * D.B, per_layer = cdiv(D.nH, 4) * nseq;
+    const int lists = D.V1 > 4096 ? 0 : D.Hh * nseq, per_layer = cdiv(D.nH, 4) * nseq;
     const int layers = std::min(D.Ly, std::max(1, cdiv(D.Ly * per_layer, 256)));   // (layers per workgroup: one round of the 256 compute units)
     const int commits = prefill_mode ? 0 : cdiv(D.Ly, layers) * per_layer;
     if (lists + commits > 0) hipLaunchKernelGGL(dtype ? k_lists_commit<bf16_t> : k_lists_commit<float>, dim3(lists + commits), dim3(256), 0, st, D, s, lists, seq0, nseq, layers);

@@ -113,6 +113,34 @@ if dtype == "bf16-giveup":
     print("emulated give-up path: reported, refused, recovered", flush=True)
     sys.stdout.flush()
     os._exit(0)
+if dtype.endswith("-partial"):
+    # kv_compact of one sequence of two with planted lists: the other one's verification is still pending, and its
+    # lists stay the planted ones until its own compaction.
+    from paper_2410_21951_amd import Vadusa, TreeArrays, DBG
+    cfg = ModelConfig(n_layers=1, d_model=64, n_heads=1, head_dim=64, d_ffn=128, speech_vocab=70, text_vocab=20,
+                      n_draft_heads=2, max_positions=64, dtype=dtype[:4])
+    W = make_weights(cfg, 71, std=0.08)
+    rng = np.random.default_rng(76)
+    text = [rng.integers(0, cfg.text_vocab, 3).astype(np.int32) for _ in range(2)]
+    prompt = [rng.integers(0, cfg.speech_vocab, 5).astype(np.int32) for _ in range(2)]
+    t = make_tree(8, (3, 2))
+    dev = Vadusa(cfg, max_batch=2, max_tree_nodes=8, ignore_eos=True)
+    dev.load_weights(W)
+    dev.prefill(text, prompt)
+    planted = np.stack([[rng.permutation(70)[:16] for _ in range(2)] for _ in range(2)]).astype(np.int32)
+    dev.verify(TreeArrays(t.parent, t.rank), 1, override=planted)
+    dev.kv_compact(0)
+    lists = dev.debug(DBG.DRAFT_TOPK)
+    assert np.array_equal(lists[1], planted[1]) and not np.array_equal(lists[0], planted[0]), lists
+    dev.kv_compact(1)
+    lists = dev.debug(DBG.DRAFT_TOPK)
+    z = dev.debug(DBG.DRAFT_LOGITS)
+    for b in range(2):
+        for i in range(2):
+            assert np.array_equal(lists[b, i], np.lexsort((np.arange(71), -z[b, i]))[:16]), (b, i)
+    print("emulated partial compaction: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype == "bf16-4gib-map":
     # One linear map of more than 4 GiB (K = 4096): 64 x 128 workgroups at its start and on both sides of the 4 GiB mark.
     # The weights are address space that is never touched but for the tiles of these workgroups, all values of tile t
