@@ -22,8 +22,11 @@ static void set_msg(char* msg, size_t n, const char* fmt, ...) {
     va_end(ap);
 }
 
+thread_local hipError_t launch_status = hipSuccess;
+
 static int fail(vadusa_ctx* c, int code, const char* fmt, ...) {
     char buf[512];
+    launch_status = hipSuccess;   // (a call that fails reports one thing)
     va_list ap;
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
@@ -38,6 +41,14 @@ static int fail(vadusa_ctx* c, int code, const char* fmt, ...) {
         if (e_ != hipSuccess)                                                              \
             return fail((c), VADUSA_EHIP, "%s failed: %s", #call, hipGetErrorString(e_)); \
     } while (0)
+
+// After launches: was one of them refused?
+static int launched(vadusa_ctx* c) {
+    if (launch_status == hipSuccess) return VADUSA_OK;
+    const hipError_t e = launch_status;
+    (void)hipGetLastError();   // it is reported here
+    return fail(c, VADUSA_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
+}
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // rows of one sequence in one pass of the prefill, and the most rows one sequence ever has in a forward
@@ -489,14 +500,9 @@ extern "C" int vadusa_load_weights(vadusa_ctx* c, const float* blob, size_t n_fl
             if (w.gamma && w.bias) launch_add_vec(w.tvec, w.bias, (int)w.rows, c->stream);
     }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    HIP_TRY(c, hipGetLastError());
+    { int rc = launched(c); if (rc) return rc; }
     c->state = 1;
     return VADUSA_OK;
-}
-
-static int launched(vadusa_ctx* c) {
-    const hipError_t e = hipGetLastError();
-    return e == hipSuccess ? VADUSA_OK : fail(c, VADUSA_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
 }
 
 // After a synchronisation: was the error word raised?
@@ -888,6 +894,7 @@ extern "C" int vadusa_debug_read(vadusa_ctx* c, int32_t what, void* host, size_t
         // no kernel keeps the node states: recompute them from the residual stream
         launch_layernorm(s.x, s.lnf_g, s.lnf_b, s.hn, (int)(B * M), (int)d, c->cfg.dtype, c->stream);
         launch_to_float(s.hn, s.staging, B * M * d, c->cfg.dtype, c->stream);
+        { int rc = launched(c); if (rc) return rc; }
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         HIP_TRY(c, hipMemcpy(host, s.staging, need, hipMemcpyDeviceToHost));
         return VADUSA_OK;
@@ -932,6 +939,7 @@ extern "C" int vadusa_debug_read_kv(vadusa_ctx* c, int32_t layer, int32_t seq, i
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     { int rc = check_kerr(c); if (rc) return rc; }
     launch_read_kv(D, base, seq, which, pos0, npos, c->s.staging, c->cfg.dtype, c->stream);
+    { int rc = launched(c); if (rc) return rc; }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipMemcpy(host, c->s.staging, (size_t)npos * D.d * 4, hipMemcpyDeviceToHost));
     return VADUSA_OK;
@@ -982,6 +990,7 @@ extern "C" int vadusa_debug_read_kv_static(vadusa_ctx* c, int32_t layer, int32_t
     { int rc = check_kerr(c); if (rc) return rc; }
     // every float of rows 0..npos-1 is overwritten by the kernel: nothing of the previous call's contents is read
     launch_read_kv(D, base, seq, which, pos0, npos, stage, c->cfg.dtype, c->stream);
+    { int rc = launched(c); if (rc) return rc; }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipMemcpy(host, stage, (size_t)npos * D.d * 4, hipMemcpyDeviceToHost));
     return VADUSA_OK;

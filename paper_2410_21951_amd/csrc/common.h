@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 #include <string>
+#include <tuple>
+#include <utility>
 #include <vector>
 
 #include "vadusa.h"
@@ -265,6 +267,23 @@ struct vadusa_ctx {
     int errored;                 // the error word was raised: every call but vadusa_prefill refuses until that resets the context
     std::string err;
 };
+
+// Launches a kernel and keeps the first failure of this thread until launched() or fail() in api.hip takes it.  The launch's
+// own status and not hipGetLastError: that also returns what any other library's call on the thread left behind.
+extern thread_local hipError_t launch_status;
+template <class... P, class... A>
+void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, A&&... args) {
+#if defined(__HIPCC__)
+    std::tuple<P...> values(std::forward<A>(args)...);
+    const hipError_t e = std::apply([&](auto&... v) {
+        void* p[] = {(void*)&v...};
+        return hipLaunchKernel((const void*)kernel, grid, block, p, lds, st);
+    }, values);
+#else   // host emulation of the kernels
+    const hipError_t e = hipLaunchKernelGGL(kernel, grid, block, lds, st, std::forward<A>(args)...);
+#endif
+    if (e != hipSuccess && launch_status == hipSuccess) launch_status = e;
+}
 
 // Epilogues of the fp32 model's linear map.
 enum {

@@ -44,7 +44,7 @@ __global__ void k_embed32(Dims D, DevState s, int prefill_mode, int table) {
 }
 
 void launch_embed32(const Dims& D, const DevState& s, int prefill_mode, int table, hipStream_t st) {
-    hipLaunchKernelGGL(k_embed32, dim3(D.B * D.M), dim3(256), 0, st, D, s, prefill_mode, table);
+    launch(k_embed32, dim3(D.B * D.M), dim3(256), 0, st, D, s, prefill_mode, table);
 }
 
 // ---------------------------------------------------------------------------
@@ -69,8 +69,8 @@ __global__ void k_layernorm(const float* __restrict__ x, const float* __restrict
 
 void launch_layernorm(const float* x, const float* g, const float* b, void* out, int R, int d, int dtype, hipStream_t st) {
     dim3 grid((R + 3) / 4), blk(256);
-    if (dtype) hipLaunchKernelGGL(k_layernorm<bf16_t>, grid, blk, 0, st, x, g, b, (bf16_t*)out, R, d);
-    else hipLaunchKernelGGL(k_layernorm<float>, grid, blk, 0, st, x, g, b, (float*)out, R, d);
+    if (dtype) launch(k_layernorm<bf16_t>, grid, blk, 0, st, x, g, b, (bf16_t*)out, R, d);
+    else launch(k_layernorm<float>, grid, blk, 0, st, x, g, b, (float*)out, R, d);
 }
 
 // ---------------------------------------------------------------------------
@@ -87,8 +87,8 @@ void launch_convert(const float* src, void* dst, size_t n, int dtype, hipStream_
     int blocks = (int)((n + 255) / 256);
     if (blocks > 4096) blocks = 4096;
     if (blocks < 1) blocks = 1;
-    if (dtype) hipLaunchKernelGGL(k_convert<bf16_t>, dim3(blocks), dim3(256), 0, st, src, (bf16_t*)dst, n);
-    else hipLaunchKernelGGL(k_convert<float>, dim3(blocks), dim3(256), 0, st, src, (float*)dst, n);
+    if (dtype) launch(k_convert<bf16_t>, dim3(blocks), dim3(256), 0, st, src, (bf16_t*)dst, n);
+    else launch(k_convert<float>, dim3(blocks), dim3(256), 0, st, src, (float*)dst, n);
 }
 
 template <class T>
@@ -101,8 +101,8 @@ void launch_to_float(const void* src, float* dst, size_t n, int dtype, hipStream
     int blocks = (int)((n + 255) / 256);
     if (blocks > 4096) blocks = 4096;
     if (blocks < 1) blocks = 1;
-    if (dtype) hipLaunchKernelGGL(k_to_float<bf16_t>, dim3(blocks), dim3(256), 0, st, (const bf16_t*)src, dst, n);
-    else hipLaunchKernelGGL(k_to_float<float>, dim3(blocks), dim3(256), 0, st, (const float*)src, dst, n);
+    if (dtype) launch(k_to_float<bf16_t>, dim3(blocks), dim3(256), 0, st, (const bf16_t*)src, dst, n);
+    else launch(k_to_float<float>, dim3(blocks), dim3(256), 0, st, (const float*)src, dst, n);
 }
 
 __global__ void k_advance(DevState s, int B) {
@@ -110,14 +110,14 @@ __global__ void k_advance(DevState s, int B) {
     if (b < B) s.L[b] += s.n_rows[b];
 }
 void launch_advance(const DevState& s, int B, hipStream_t st) {
-    hipLaunchKernelGGL(k_advance, dim3((B + 63) / 64), dim3(64), 0, st, s, B);
+    launch(k_advance, dim3((B + 63) / 64), dim3(64), 0, st, s, B);
 }
 
 __global__ __launch_bounds__(256) void k_gather(const int32_t* a, int na, const int32_t* b, int nb, const int32_t* c, int nc, int32_t* host) {
     for (int i = threadIdx.x; i < na + nb + nc; i += 256) host[i] = i < na ? a[i] : i < na + nb ? b[i - na] : c[i - na - nb];
 }
 void launch_gather(const int32_t* a, int na, const int32_t* b, int nb, const int32_t* c, int nc, int32_t* host, hipStream_t st) {
-    hipLaunchKernelGGL(k_gather, dim3(1), dim3(256), 0, st, a, na, b, nb, c, nc, host);
+    launch(k_gather, dim3(1), dim3(256), 0, st, a, na, b, nb, c, nc, host);
 }
 
 // out[p][head*64 + dim] = K or V of (seq, head, position pos0 + p, dim)
@@ -131,6 +131,6 @@ __global__ void k_read_kv(Dims D, const T* __restrict__ cache, int seq, int whic
     }
 }
 void launch_read_kv(const Dims& D, const void* cache_layer, int seq, int which, int pos0, int npos, float* out, int dtype, hipStream_t st) {
-    if (dtype) hipLaunchKernelGGL(k_read_kv<bf16_t>, dim3(npos), dim3(256), 0, st, D, (const bf16_t*)cache_layer, seq, which, pos0, npos, out);
-    else hipLaunchKernelGGL(k_read_kv<float>, dim3(npos), dim3(256), 0, st, D, (const float*)cache_layer, seq, which, pos0, npos, out);
+    if (dtype) launch(k_read_kv<bf16_t>, dim3(npos), dim3(256), 0, st, D, (const bf16_t*)cache_layer, seq, which, pos0, npos, out);
+    else launch(k_read_kv<float>, dim3(npos), dim3(256), 0, st, D, (const float*)cache_layer, seq, which, pos0, npos, out);
 }

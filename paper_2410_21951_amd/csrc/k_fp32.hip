@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void k_lin32(GemmArgs a) {
 }
 
 static void lin32(const GemmArgs& a, hipStream_t st, int nz = 1) {
-    hipLaunchKernelGGL(k_lin32, dim3(cdiv(a.N, 16), cdiv(a.R, 16), nz), dim3(256), 0, st, a);
+    launch(k_lin32, dim3(cdiv(a.N, 16), cdiv(a.R, 16), nz), dim3(256), 0, st, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -230,7 +230,7 @@ void launch_layers32(const Dims& D, const DevState& s, const std::vector<LayerW>
         a.X = s.x; a.ln_g = w.ln1_g; a.ln_b = w.ln1_b; a.W = w.Wqkv; a.bias = w.bqkv; a.K = D.d; a.N = 3 * D.d; a.epi = EPI_QKV;
         a.out = s.q; a.Kc = (float*)s.Kc + l * kv_layer; a.Vc = (float*)s.Vc + l * kv_layer;
         lin32(a, st);
-        hipLaunchKernelGGL(k_attn32, dim3(D.M, D.nH, D.B), dim3(256), 0, st, D, s, l, table);
+        launch(k_attn32, dim3(D.M, D.nH, D.B), dim3(256), 0, st, D, s, l, table);
         GemmArgs o = base;
         o.X = s.att; o.W = w.Wo; o.bias = w.bo; o.K = D.d; o.N = D.d; o.epi = EPI_RESID; o.outf = s.x;
         lin32(o, st);

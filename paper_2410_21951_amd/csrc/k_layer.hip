@@ -800,11 +800,11 @@ static LinShape lin_shape(int R, int NT) {
 
 template <int RT, int CT, int CH, int EPI>
 static void lin_launch(const LinArgs& a, hipStream_t st, int nz = 1) {
-    hipLaunchKernelGGL((k_lin<RT, CT, CH, EPI>), dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(256), 0, st, a);
+    launch((k_lin<RT, CT, CH, EPI>), dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(256), 0, st, a);
 }
 template <int NRT, int NCT, int DEPTH, int OCC, int EPI>
 static void big_launch(const LinArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL((k_big<NRT, NCT, DEPTH, OCC, EPI>), dim3(pad8(cdiv(a.NT, 4 * NCT)), cdiv(a.R, NRT * 16)), dim3(256), 0, st, a);
+    launch((k_big<NRT, NCT, DEPTH, OCC, EPI>), dim3(pad8(cdiv(a.NT, 4 * NCT)), cdiv(a.R, NRT * 16)), dim3(256), 0, st, a);
 }
 // k_big's 64 x 128 tiles from one tile per eight K values on (129 tiles at K = 1024): fewer leave compute units idle for
 // a whole reduction, where k_lin's smaller tiles split it over four waves.  Measured, K = 1024: 4096 columns, 320 rows
@@ -832,7 +832,7 @@ static void lin(const LinArgs& a, int big_min, hipStream_t st) {
 // -DVADUSA_CLOCK_BUILD, where each is a launch of its own.
 static void clock_point(const DevState& s, int ph, hipStream_t st) {
 #ifdef VADUSA_CLOCK_BUILD
-    if (ph < 128) hipLaunchKernelGGL(k_clock, dim3(1), dim3(1), 0, st, s, ph);
+    if (ph < 128) launch(k_clock, dim3(1), dim3(1), 0, st, s, ph);
 #else
     (void)s; (void)ph; (void)st;
 #endif
@@ -841,8 +841,8 @@ static void clock_point(const DevState& s, int ph, hipStream_t st) {
 template <int QT>
 static void attn_launch(const AttnArgs& t, bool causal, hipStream_t st) {
     const dim3 grid(pad8(t.B * t.nH), cdiv(cdiv(t.M, 16), QT));
-    if (causal) hipLaunchKernelGGL((k_attn<true, QT>), grid, dim3(256), 0, st, t);
-    else hipLaunchKernelGGL((k_attn<false, QT>), grid, dim3(256), 0, st, t);
+    if (causal) launch((k_attn<true, QT>), grid, dim3(256), 0, st, t);
+    else launch((k_attn<false, QT>), grid, dim3(256), 0, st, t);
 }
 static void attn(const AttnArgs& t, bool causal, hipStream_t st) {
     const int qt = cdiv(t.M, 16);
@@ -854,7 +854,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
     const int R = D.B * D.M, d = D.d;
     const size_t kv_layer = (size_t)D.Bmax * D.nH * kv_cap(D.maxpos) * 64;
     clock_point(s, 0, st);
-    hipLaunchKernelGGL(k_embed_rows, dim3(R), dim3(256), 0, st, D, s, prefill_mode, table);
+    launch(k_embed_rows, dim3(R), dim3(256), 0, st, D, s, prefill_mode, table);
     LinArgs base{};
     base.R = R; base.L = s.L; base.n_rows = s.n_rows; base.M = D.M; base.nH = D.nH; base.maxpos = D.maxpos; base.d = d;
     base.stats = (const float2*)s.stats;
@@ -896,8 +896,8 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
 
 void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eos, bool select, hipStream_t st) {
     clock_point(s, 1 + 5 * D.Ly + TP_EDGES, st);
-    hipLaunchKernelGGL(k_edges, dim3(cdiv(D.B * D.M, 4)), dim3(256), 0, st, D, s, tau);
-    if (select) hipLaunchKernelGGL(k_select, dim3(D.B), dim3(256), 0, st, D, s, 0, ignore_eos);
+    launch(k_edges, dim3(cdiv(D.B * D.M, 4)), dim3(256), 0, st, D, s, tau);
+    if (select) launch(k_select, dim3(D.B), dim3(256), 0, st, D, s, 0, ignore_eos);
 }
 
 // Rows of more than 4096 logits: the draft lists come from the stand-alone top-k kernel (it takes such rows slice by
@@ -905,7 +905,7 @@ void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eo
 void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, int dtype, hipStream_t st) {
     const int H = 1 + 5 * D.Ly;
     clock_point(s, H + TP_FINAL, st);
-    hipLaunchKernelGGL(dtype ? k_continue<bf16_t> : k_continue<float>, dim3(nseq), dim3(256), 0, st, D, s, seq0, prefill_mode, ignore_eos, select ? 1 : 0);
+    launch(dtype ? k_continue<bf16_t> : k_continue<float>, dim3(nseq), dim3(256), 0, st, D, s, seq0, prefill_mode, ignore_eos, select ? 1 : 0);
     if (dtype) {
         auto ahead = [&](const void* a, const void* b) { return D.Hh > 1 ? (size_t)((const char*)b - (const char*)a) : 0; };
         const DraftW &d0 = draft[0], &d1 = draft[D.Hh > 1 ? 1 : 0];
@@ -928,6 +928,6 @@ void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>
     const int lists = D.V1 > 4096 ? 0 : D.Hh * nseq, per_layer = cdiv(D.nH, 4) * nseq;
     const int layers = std::min(D.Ly, std::max(1, cdiv(D.Ly * per_layer, 256)));   // (layers per workgroup: one round of the 256 compute units)
     const int commits = prefill_mode ? 0 : cdiv(D.Ly, layers) * per_layer;
-    if (lists + commits > 0) hipLaunchKernelGGL(dtype ? k_lists_commit<bf16_t> : k_lists_commit<float>, dim3(lists + commits), dim3(256), 0, st, D, s, lists, seq0, nseq, layers);
+    if (lists + commits > 0) launch(dtype ? k_lists_commit<bf16_t> : k_lists_commit<float>, dim3(lists + commits), dim3(256), 0, st, D, s, lists, seq0, nseq, layers);
     if (lists == 0) launch_topk(D, s, seq0, nseq, st);
 }

@@ -57,17 +57,17 @@ __global__ void k_add_vec(float* __restrict__ dst, const float* __restrict__ src
 void launch_pack_w(const float* src, void* dst, int N, int K, hipStream_t st) {
     const size_t total = (size_t)((N + 15) / 16) * (K >> 5) * 64;
     const int blocks = (int)std::min<size_t>((total + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_pack_w, dim3(blocks), dim3(256), 0, st, src, (const float*)nullptr, (uint4*)dst, N, K);
+    launch(k_pack_w, dim3(blocks), dim3(256), 0, st, src, (const float*)nullptr, (uint4*)dst, N, K);
 }
 
 void launch_pack_w_ln(const float* src, const float* gamma, const float* beta, void* dst, float* colsum,
                       float* tvec, int N, int K, hipStream_t st) {
     const size_t total = (size_t)((N + 15) / 16) * (K >> 5) * 64;
     const int blocks = (int)std::min<size_t>((total + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_pack_w, dim3(blocks), dim3(256), 0, st, src, gamma, (uint4*)dst, N, K);
-    hipLaunchKernelGGL(k_fold_vectors, dim3((N + 3) / 4), dim3(256), 0, st, src, gamma, beta, colsum, tvec, N, K);
+    launch(k_pack_w, dim3(blocks), dim3(256), 0, st, src, gamma, (uint4*)dst, N, K);
+    launch(k_fold_vectors, dim3((N + 3) / 4), dim3(256), 0, st, src, gamma, beta, colsum, tvec, N, K);
 }
 
 void launch_add_vec(float* dst, const float* src, int n, hipStream_t st) {
-    hipLaunchKernelGGL(k_add_vec, dim3((n + 255) / 256), dim3(256), 0, st, dst, src, n);
+    launch(k_add_vec, dim3((n + 255) / 256), dim3(256), 0, st, dst, src, n);
 }

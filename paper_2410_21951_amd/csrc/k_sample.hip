@@ -212,9 +212,9 @@ __global__ __launch_bounds__(64) void k_perturb_wave(const float* __restrict__ l
 
 void launch_perturb(const float* logits, const float* u, float* scores, int rows, int V1, float temperature,
                     float top_p, int tau, hipStream_t st) {
-    if (V1 <= 1280) hipLaunchKernelGGL(k_perturb_wave<5>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
-    else if (V1 <= 2304) hipLaunchKernelGGL(k_perturb_wave<9>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
-    else if (V1 <= 4096) hipLaunchKernelGGL(k_perturb_wave<16>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
-    else hipLaunchKernelGGL(k_perturb, dim3(rows), dim3(256), (size_t)V1 * sizeof(float), st, logits, u, scores, V1,
+    if (V1 <= 1280) launch(k_perturb_wave<5>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
+    else if (V1 <= 2304) launch(k_perturb_wave<9>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
+    else if (V1 <= 4096) launch(k_perturb_wave<16>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
+    else launch(k_perturb, dim3(rows), dim3(256), (size_t)V1 * sizeof(float), st, logits, u, scores, V1,
                             temperature, top_p, tau);
 }

@@ -113,6 +113,38 @@ if dtype == "bf16-giveup":
     print("emulated give-up path: reported, refused, recovered", flush=True)
     sys.stdout.flush()
     os._exit(0)
+if dtype.endswith("-errors"):
+    # An error that another library's HIP call left behind is not this library's: every call works as without it.  A launch
+    # of its own that is refused is reported by the call that made it, and by no later one.
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    from paper_2410_21951_amd import Vadusa, TreeArrays, VadusaError, DBG
+    cfg = ModelConfig(n_layers=1, d_model=64, n_heads=1, head_dim=64, d_ffn=128, speech_vocab=70, text_vocab=20,
+                      n_draft_heads=2, max_positions=64, dtype=dtype[:4])
+    W = make_weights(cfg, 71, std=0.08)
+    text, prompt = [np.arange(3, dtype=np.int32)], [np.arange(5, dtype=np.int32)]
+    t = make_tree(8, (3, 2))
+    tree = TreeArrays(t.parent, t.rank)
+    dev = Vadusa(cfg, max_batch=1, max_tree_nodes=8, ignore_eos=True)
+    left, refuse = C.c_int.in_dll(V._lib, "emu_last_error"), C.c_int.in_dll(V._lib, "emu_fail_launch")
+    calls = [lambda: dev.load_weights(W), lambda: dev.prefill(text, prompt), lambda: dev.step(tree, 1),
+             lambda: dev.step(tree, 2, sync=False), lambda: dev.read_output(0), lambda: (dev.verify(tree, 1), dev.kv_compact()),
+             lambda: dev.debug(DBG.H_NODES), lambda: dev.read_kv(0, 0, 0, 0, 4), lambda: dev.read_kv(0, 0, 0, 0, 4, static=True)]
+    for call in calls:
+        left.value = 101
+        call()
+    left.value = 0
+    for i in (1, 2, 6, 7, 0):
+        refuse.value = 1
+        try:
+            calls[i]()
+            raise AssertionError(f"call {i}: a refused launch went unreported")
+        except VadusaError as e:
+            assert e.code == -5, (i, e)
+        calls[1 if i else 0]()
+    print("emulated errors: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype.endswith("-partial"):
     # kv_compact of one sequence of two with planted lists: the other one's verification is still pending, and its
     # lists stay the planted ones until its own compaction.

@@ -51,7 +51,9 @@ static inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMem
 static inline hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return 0; }
 static inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { memset(d, v, n); return 0; }
 static inline hipError_t hipStreamSynchronize(hipStream_t) { return 0; }
-static inline hipError_t hipGetLastError() { return 0; }
+extern "C" int emu_last_error;     // what another library's failed call left behind (0: nothing)
+extern "C" int emu_fail_launch;    // n > 0: the n-th launch from now on is refused
+static inline hipError_t hipGetLastError() { const int e = emu_last_error; emu_last_error = 0; return e; }
 static inline const char* hipGetErrorString(hipError_t) { return "emu"; }
 static inline hipError_t hipGetDevice(int* d) { *d = 0; return 0; }
 #ifndef __align__
@@ -72,9 +74,11 @@ static inline hipError_t hipFuncSetAttribute(const void*, int, int) { return 0; 
 // ---- launch ----
 void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t shmem, bool coop);
 template <class... KA, class... A>
-void hipLaunchKernelGGL(void (*k)(KA...), dim3 grid, dim3 block, size_t shmem, hipStream_t, A&&... a) {
+hipError_t hipLaunchKernelGGL(void (*k)(KA...), dim3 grid, dim3 block, size_t shmem, hipStream_t, A&&... a) {
+    if (emu_fail_launch > 0 && --emu_fail_launch == 0) return hipErrorUnknown;
     std::tuple<KA...> args(std::forward<A>(a)...);
     emu_launch([=]() { std::apply(k, args); }, grid, block, shmem, false);
+    return hipSuccess;
 }
 template <class P>
 hipError_t emu_launch_coop(void (*k)(P), dim3 grid, dim3 block, void** args, size_t shmem) {

@@ -167,6 +167,33 @@ def test_a_kernel_that_gave_up_is_reported_and_prefill_recovers():
     dev.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_an_error_left_by_another_call_is_not_the_librarys(dtype):
+    """A HIP call of somebody else that the runtime refused leaves its code with hipGetLastError: the library's calls
+    work as without it (they report the status of their own launches)."""
+    import ctypes as C
+    import dataclasses
+    from paper_2410_21951_amd import DBG
+    print("errors of other calls", dtype, flush=True)
+    cfg = dataclasses.replace(CFG, dtype=dtype)
+    W = make_weights(cfg, 4, std=0.08)
+    text, prompt = _inputs(np.random.default_rng(2))
+    tree = _tree(make_tree(16, (4, 2, 2)))
+    dev = _dev(cfg, max_batch=2, max_tree_nodes=16, ignore_eos=True)
+    hip = C.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))
+    calls = [lambda: dev.load_weights(W), lambda: dev.prefill(text, prompt), lambda: dev.step(tree, 1),
+             lambda: dev.step(tree, 2, sync=False), lambda: dev.read_output(0), lambda: (dev.verify(tree, 1), dev.kv_compact()),
+             lambda: dev.debug(DBG.H_NODES), lambda: dev.read_kv(0, 0, 0, 0, 4)]
+    try:
+        for call in calls:
+            assert hip.hipSetDevice(9999) != 0            # refused by the runtime on the host
+            call()
+        assert hip.hipGetLastError() != 0                 # and still there for whoever made the mistake
+    finally:
+        hip.hipGetLastError()
+        dev.close()
+
+
 def test_stochastic_entry_points():
     """vadusa_step_sampled = vadusa_verify_sampled + vadusa_kv_compact; uniforms from host or
     device memory give the same stream; argument errors are reported, not run."""
