@@ -74,7 +74,7 @@ typedef struct {
                                0 = max_tree_nodes, or more (up to VADUSA_MAX_TREE_NODES) while max_batch of
                                them stay within 2048 rows; else 1..VADUSA_MAX_PREFILL_CHUNK (longer passes turn the
                                prompt's linear maps into many-row products; the arena grows with
-                               max_batch * prefill_chunk rows of activations) */
+                               max_batch rows of such a pass: activations and V+1 logits each) */
 } vadusa_config;
 
 /*

@@ -246,11 +246,12 @@ static size_t layout(const vadusa_config& c, char* base, DevState* s, std::vecto
     const size_t e = c.dtype ? 2 : 4;
     const size_t d = c.d_model, F = c.d_ffn, V1 = c.speech_vocab + 1, Hh = c.n_draft_heads;
     const size_t R = (size_t)c.max_batch * seq_rows_cap(c), B = c.max_batch, P = c.max_positions;
+    const size_t Rt = B * c.max_tree_nodes;   // rows of a step: what only a verification fills or the readers show
     DevState st{};
     std::vector<LayerW> lw(c.n_layers);
     std::vector<DraftW> dw(Hh);
     std::vector<WeightSlot> sl;
-    size_t biggest = std::max(R * std::max(d, V1), P * d);
+    size_t biggest = std::max(Rt, P) * d;   // staging: a weight, the node states or one sequence's cache rows as floats
     auto mat = [&](const void** dst, size_t rows, size_t cols, int kind = 2) {
         *dst = cv.take((size_t)pad16((int)rows) * cols * e);
         sl.push_back({(void*)*dst, rows, cols, kind, nullptr, nullptr, nullptr, nullptr, nullptr});
@@ -304,7 +305,7 @@ static size_t layout(const vadusa_config& c, char* base, DevState* s, std::vecto
     st.q = cv.take(Rp * d * e);
     st.att = cv.take(Rp * d * e);
     st.hid = cv.take(Rp * F * e);
-    st.hn = cv.take(R * d * e);
+    st.hn = cv.take(Rt * d * e);
     st.logits = (float*)cv.take(R * V1 * 4);
     st.hbest = cv.take(Bp * d * e);
     st.rdraft = cv.take(Hh * Bp * d * e);
@@ -328,8 +329,8 @@ static size_t layout(const vadusa_config& c, char* base, DevState* s, std::vecto
         st.t_mask[t] = (uint32_t*)cv.take(VADUSA_MAX_TREE_NODES * MASK_WORDS * 4);
     }
     st.staging = (float*)cv.take(biggest * 4);
-    float* un = (float*)cv.take(R * V1 * 4);
-    float* sc = (float*)cv.take(R * V1 * 4);
+    float* un = (float*)cv.take(Rt * V1 * 4);
+    float* sc = (float*)cv.take(Rt * V1 * 4);
     if (uniforms) *uniforms = un;
     if (scores) *scores = sc;
     if (s) *s = st;

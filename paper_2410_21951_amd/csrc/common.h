@@ -224,7 +224,7 @@ struct DevState {
     void* q;         // [R][d]
     void* att;       // [R][d]
     void* hid;       // [R][F]
-    void* hn;        // [R][d]  final-LayerNorm'd node states
+    void* hn;        // [rows of a step][d]  final-LayerNorm'd node states (inspection)
     float* logits;   // [R][V1]
     void* hbest;     // [Bmax][d]
     void* rdraft;    // [Hh][Bmax][d]
@@ -238,7 +238,7 @@ struct DevState {
     // tree tables (index 0: current tree, 1: causal chunk used by prefill)
     int32_t *t_parent[2], *t_depth[2], *t_rank[2];
     uint32_t* t_mask[2];   // [Mmax][MASK_WORDS]
-    float* staging;        // weight conversion staging
+    float* staging;        // floats on their way in (weights) or out (readers)
 };
 
 struct vadusa_ctx {

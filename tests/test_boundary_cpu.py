@@ -72,6 +72,21 @@ def test_config_check_and_sizes(lib):
     assert lib.vadusa_arena_bytes(C.byref(_cfg(m, head_dim=32))) == 0
 
 
+@pytest.mark.parametrize("batch,nodes", [(16, 1), (16, 27), (1, 64)])
+def test_arena_holds_rows_of_logits_only_where_they_are_used(lib, batch, nodes):
+    """What a larger vocabulary adds to the arena: weights, one buffer of logits for the rows of a prompt pass, and random
+    numbers and scores for the rows of a tree (not of a prompt pass); the staging area is the largest weight's."""
+    from dataclasses import replace
+    m = PRESETS["valle_b1"].model
+    V0, V1 = 4000, 16000
+    small, large = (lib.vadusa_arena_bytes(C.byref(_cfg(replace(m, speech_vocab=v), max_batch=batch, max_tree_nodes=nodes))) for v in (V0, V1))
+    rows = batch * 128                                                    # default prompt passes at these batches
+    weights = (2 + m.n_draft_heads) * m.d_model * 2 + 8                   # bf16 tables and maps, folded LayerNorm
+    per_unit = weights + 4 * (rows + 2 * batch * nodes + m.n_draft_heads * batch)
+    staging = 4 * (V1 + 1) * m.d_model
+    assert large - small <= (V1 - V0) * per_unit + staging + (1 << 16)
+
+
 def _check(lib, cfg, parent, rank):
     t = V.TreeArrays(parent, rank)
     msg = C.create_string_buffer(256)
