@@ -27,6 +27,11 @@
  *  - The library allocates no device memory: the caller passes one device
  *    arena of vadusa_arena_bytes() bytes (256-byte aligned) that the context
  *    carves up and owns until vadusa_destroy(); the caller frees it afterwards.
+ *    vadusa_create() takes one block of pinned host memory (hipHostMalloc) per
+ *    context for the results of its calls, 4 * max(max_positions + 5,
+ *    12 * max_batch + 4) bytes in steps of 4 KiB.  vadusa_destroy() hands the
+ *    block to the next vadusa_create() of the process, which frees those it does
+ *    not use.  Where there is none to be had, results take an ordinary copy.
  *  - All kernels are enqueued on the HIP stream given to vadusa_create().
  *  - Speech token ids are 0..V-1, the end-of-sequence id is V (= speech_vocab);
  *    logits have V+1 entries.

@@ -69,39 +69,42 @@ static size_t result_words(const vadusa_config& c) { return 4 + (size_t)c.max_ba
 
 // ---------------------------------------------------------------------------
 // Pinned host memory that results are written into by the last kernel of a call.  A copy to pageable memory costs a step
-// some 30 to 40 us more.  A context takes one block when it is created and hands it back when it is destroyed, which
-// makes no HIP call: blocks stay in a list for later contexts, so that there are never more of them than there have been
-// contexts alive at once.  Without one (nullptr) a call copies to ordinary memory.
+// some 30 to 40 us more.  A context takes one block when it is created.  vadusa_destroy may make no HIP call (see there), so it
+// only puts the block in a list; the next vadusa_create takes the smallest that fits from the list, or allocates one, and
+// frees the rest: no block outlives two contexts in the list, and there are never more than contexts alive at once.
+// Without one (nullptr) a call copies to ordinary memory.
 // ---------------------------------------------------------------------------
 struct PinnedBlock { int32_t* p; size_t words; };
-struct PinnedList { std::mutex m; std::vector<PinnedBlock> free; };
+struct PinnedList { std::mutex m; std::vector<PinnedBlock> free; size_t handed_out = 0; };
 static PinnedList& pinned_list() {
     static PinnedList* l = new PinnedList;   // (never destroyed: a context may be freed while the process ends)
     return *l;
 }
 static PinnedBlock pinned_take(size_t words) {
+    PinnedList& l = pinned_list();
+    std::vector<PinnedBlock> rest;
+    PinnedBlock b{nullptr, 0};
     {
-        PinnedList& l = pinned_list();
         std::lock_guard<std::mutex> lock(l.m);
-        for (size_t i = 0; i < l.free.size(); ++i)
-            if (l.free[i].words >= words) {
-                const PinnedBlock b = l.free[i];
-                l.free.erase(l.free.begin() + (long)i);
-                return b;
-            }
+        rest.swap(l.free);
+        l.free.reserve(l.handed_out + 1);   // (vadusa_destroy allocates nothing)
+        ++l.handed_out;
     }
+    for (PinnedBlock& r : rest)
+        if (r.words >= words && (!b.p || r.words < b.words)) std::swap(r, b);
+    for (const PinnedBlock& r : rest)
+        if (r.p && hipHostFree(r.p) != hipSuccess) (void)hipGetLastError();
+    if (b.p) return b;
     void* p = nullptr;
     words = (words + 1023) / 1024 * 1024;
-#if defined(__HIPCC__)
     if (hipHostMalloc(&p, words * 4, hipHostMallocPortable) != hipSuccess) { (void)hipGetLastError(); p = nullptr; }
-#endif
     return PinnedBlock{(int32_t*)p, p ? words : 0};
 }
 static void pinned_give(const PinnedBlock& b) {
-    if (!b.p) return;
     PinnedList& l = pinned_list();
     std::lock_guard<std::mutex> lock(l.m);
-    l.free.push_back(b);
+    --l.handed_out;
+    if (b.p) l.free.push_back(b);
 }
 
 extern "C" int vadusa_config_check(const vadusa_config* c, char* msg, size_t n) {
@@ -427,9 +430,11 @@ extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena
     if (e != hipSuccess) { delete c; return VADUSA_EHIP; }
     c->pinned = nullptr;
     {
-        const PinnedBlock b = pinned_take(std::max(result_words(*cfg), (size_t)5 + cfg->max_positions));
+        const size_t words = std::max(result_words(*cfg), (size_t)5 + cfg->max_positions);
+        const PinnedBlock b = pinned_take(words);
         c->pinned = b.p;
         c->pinned_words = b.words;
+        if (!c->pinned) c->unpinned.resize(words);
     }
     *out = c;
     return VADUSA_OK;
@@ -519,14 +524,13 @@ static int kerr_seen(vadusa_ctx* c, int32_t k) {
 // stream holds.  *out is valid until the next fetch.
 static int fetch(vadusa_ctx* c, const int32_t* a, size_t na, const int32_t* b, size_t nb, const int32_t* c2, size_t nc, const int32_t** out) {
     const size_t n = na + nb + nc;
-    if (c->pinned && n <= c->pinned_words) {
+    if (c->pinned) {   // (vadusa_create took room for every call's results)
         launch_gather(a, (int)na, b, (int)nb, c2, (int)nc, c->pinned, c->stream);
         { int rc = launched(c); if (rc) return rc; }
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         *out = c->pinned;
         return VADUSA_OK;
     }
-    c->unpinned.resize(n);
     if (na) HIP_TRY(c, hipMemcpyAsync(c->unpinned.data(), a, na * 4, hipMemcpyDeviceToHost, c->stream));
     if (nb) HIP_TRY(c, hipMemcpyAsync(c->unpinned.data() + na, b, nb * 4, hipMemcpyDeviceToHost, c->stream));
     if (nc) HIP_TRY(c, hipMemcpyAsync(c->unpinned.data() + na + nb, c2, nc * 4, hipMemcpyDeviceToHost, c->stream));

@@ -19,7 +19,7 @@ thread_local const char* emu_where = "";
 thread_local int emu_line = 0;
 alignas(64) static char g_lds[160 * 1024];
 char* emu_dyn_lds = g_lds;
-extern "C" { int emu_last_error = 0, emu_fail_launch = 0; }
+extern "C" { int emu_last_error = 0, emu_fail_launch = 0, emu_host_blocks = 0; }
 
 constexpr int MAXT = 256;
 static thread_local int t_id = -1;   // index in the pool, -1: host thread

@@ -54,6 +54,15 @@ static inline hipError_t hipStreamSynchronize(hipStream_t) { return 0; }
 extern "C" int emu_last_error;     // what another library's failed call left behind (0: nothing)
 extern "C" int emu_fail_launch;    // n > 0: the n-th launch from now on is refused
 static inline hipError_t hipGetLastError() { const int e = emu_last_error; emu_last_error = 0; return e; }
+extern "C" int emu_host_blocks;    // pinned blocks alive; -1: none to be had
+enum { hipHostMallocPortable = 1 };
+static inline hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+    if (emu_host_blocks < 0) return hipErrorUnknown;
+    ++emu_host_blocks;
+    *p = malloc(n);
+    return hipSuccess;
+}
+static inline hipError_t hipHostFree(void* p) { --emu_host_blocks; free(p); return hipSuccess; }
 static inline const char* hipGetErrorString(hipError_t) { return "emu"; }
 static inline hipError_t hipGetDevice(int* d) { *d = 0; return 0; }
 #ifndef __align__
