@@ -140,8 +140,9 @@ int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena_bytes,
  *   VADUSA_PHASE_CLOCK          the binding loads libvadusa_clock.so (built with -DVADUSA_CLOCK_BUILD), which records
  *                               the timing points of VADUSA_DBG_PHASE_CLOCK
  *   VADUSA_BIG_MIN_UNITS=n      read by vadusa_create: a linear map of the bf16 model takes 64 x 128 output tiles
- *                               from n such tiles on, whatever its size; lets tests reach that kernel with
- *                               small shapes
+ *                               from n such tiles on, whatever its size, and its attention takes two tiles of
+ *                               16 queries per workgroup from n such workgroups on; lets tests reach these
+ *                               kernels with small shapes
  * A step is one launch per map, so VADUSA_PHASE_LAUNCHES and VADUSA_COOPERATIVE_LAUNCH of earlier versions have no
  * effect. */
 

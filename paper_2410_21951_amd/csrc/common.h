@@ -260,7 +260,7 @@ struct vadusa_ctx {
     float* uniforms;             // [max_batch * max_tree_nodes][V+1]: the caller's random numbers of a stochastic step
     float* scores;               // same shape: perturbed scores that replace the logits in such a step
     int sampled;                 // the pending / last verification was a stochastic one
-    int big_min;                 // many-row maps: k_big's tiles from this many on (environment VADUSA_BIG_MIN_UNITS, for tests of small shapes); 0: the rule
+    int big_min;                 // k_big's tiles, and attention workgroups of two query tiles, from this many on (environment VADUSA_BIG_MIN_UNITS, for tests of small shapes); 0: the rules
     int32_t* pinned;             // host memory that the last kernel of a call writes results into (null: none)
     size_t pinned_words;
     std::vector<int32_t> unpinned;   // its stand-in

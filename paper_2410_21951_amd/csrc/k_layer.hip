@@ -844,9 +844,10 @@ static void attn_launch(const AttnArgs& t, bool causal, hipStream_t st) {
     if (causal) launch((k_attn<true, QT>), grid, dim3(256), 0, st, t);
     else launch((k_attn<false, QT>), grid, dim3(256), 0, st, t);
 }
-static void attn(const AttnArgs& t, bool causal, hipStream_t st) {
+static void attn(const AttnArgs& t, bool causal, int big_min, hipStream_t st) {
     const int qt = cdiv(t.M, 16);
-    if (qt > 1 && t.B * t.nH * cdiv(qt, 2) >= 512) attn_launch<2>(t, causal, st);   // two workgroups per compute unit
+    // from two workgroups per compute unit on
+    if (qt > 1 && t.B * t.nH * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512)) attn_launch<2>(t, causal, st);
     else attn_launch<1>(t, causal, st);
 }
 
@@ -868,7 +869,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         lin<LE_QKV>(a, big_min, st);
         AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos};
         clock_point(s, 2 + 5 * l, st);
-        attn(t, table == 1, st);
+        attn(t, table == 1, big_min, st);
         LinArgs o = base;
         o.X = (const bf16_t*)s.att; o.W = (const uint4*)w.Wo; o.bias = w.bo; o.nks = d >> 5; o.N = d; o.NT = d >> 4;
         o.out = s.xb; o.outf = s.x; o.stats_out = (float2*)s.stats;

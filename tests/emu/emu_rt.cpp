@@ -106,7 +106,7 @@ static void worker(int id) {
     }
 }
 
-void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t shmem, bool coop) {
+void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t shmem) {
     static bool once = false;
     if (!once) {
         once = true;
@@ -124,7 +124,6 @@ void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t
     const int nt = (int)(block.x * block.y * block.z);
     if (nt > MAXT || nt % 64) { fprintf(stderr, "[emu] unsupported block size %d\n", nt); abort(); }
     if (shmem > sizeof g_lds) { fprintf(stderr, "[emu] dynamic LDS too large\n"); abort(); }
-    if (coop && grid.x * grid.y * grid.z != 1) { fprintf(stderr, "[emu] cooperative launches: one block only\n"); abort(); }
     if (grid.x * grid.y * grid.z == 0) return;
     g_body = body;
     gridDim = grid;

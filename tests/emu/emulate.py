@@ -7,11 +7,10 @@ the bf16 MFMA) are rendezvous between the 64 lanes, and the "device" arena sits 
 inaccessible guard pages.  The same C ABI is then driven through the ordinary Python binding, so
 the kernels' index arithmetic and control flow can be checked against the oracle (and under
 host sanitizers) without a GPU.  It says nothing about timing, caches or memory ordering across
-workgroups: a persistent launch is emulated with a single workgroup.
+workgroups.
 """
 import ctypes as C
 import os
-import re
 import subprocess
 import sys
 
@@ -30,11 +29,9 @@ def build(out_dir, extra_flags=()):
         if not name.endswith((".hip", ".h")):
             continue
         text = open(os.path.join(CSRC, name)).read()
-        # dynamic LDS, the one inline-asm wait, and the cooperative launch have host stand-ins
-        text = text.replace("extern __shared__ uint4 smem[];", "uint4* smem = (uint4*)emu_dyn_lds;")
+        # dynamic LDS and the inline-asm wait have host stand-ins
         text = text.replace("extern __shared__ float s_s[];", "float* s_s = (float*)emu_dyn_lds;")
         text = "\n".join(l for l in text.split("\n") if "s_waitcnt" not in l)
-        text = re.sub(r"hipLaunchCooperativeKernel\(\(const void\*\)(\w+), (.*), st\);", r"emu_launch_coop(\1, \2);", text)
         if name == "k_layer.hip":
             text += open(os.path.join(HERE, "layer_exports.inc")).read()
         dst = os.path.join(gen, name[:-4] + ".cpp" if name.endswith(".hip") else name)

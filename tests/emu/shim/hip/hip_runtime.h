@@ -44,8 +44,6 @@ typedef void* hipStream_t;
 typedef int hipError_t;
 enum { hipSuccess = 0, hipErrorUnknown = 999 };
 enum hipMemcpyKind { hipMemcpyHostToDevice, hipMemcpyDeviceToHost, hipMemcpyDeviceToDevice, hipMemcpyDefault };
-enum { hipFuncAttributeMaxDynamicSharedMemorySize = 8 };
-struct hipDeviceProp_t { int multiProcessorCount; int cooperativeLaunch; };
 static inline hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return 0; }
 static inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return 0; }
 static inline hipError_t hipMemset(void* d, int v, size_t n) { memset(d, v, n); return 0; }
@@ -70,32 +68,16 @@ static inline hipError_t hipGetDevice(int* d) { *d = 0; return 0; }
 #endif
 #define HIP_SYMBOL(x) (&(x))
 static inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = (void*)sym; return 0; }
-static inline hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) {
-    const char* e = getenv("EMU_CUS");
-    p->multiProcessorCount = e ? atoi(e) : 1;
-    p->cooperativeLaunch = 1;
-    return 0;
-}
-enum { hipErrorCooperativeLaunchTooLarge = 720 };
-template <class F> static inline hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, F, int, size_t) { *n = 1; return 0; }
-static inline hipError_t hipFuncSetAttribute(const void*, int, int) { return 0; }
 
 // ---- launch ----
-void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t shmem, bool coop);
+void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t shmem);
 template <class... KA, class... A>
 hipError_t hipLaunchKernelGGL(void (*k)(KA...), dim3 grid, dim3 block, size_t shmem, hipStream_t, A&&... a) {
     if (emu_fail_launch > 0 && --emu_fail_launch == 0) return hipErrorUnknown;
     std::tuple<KA...> args(std::forward<A>(a)...);
-    emu_launch([=]() { std::apply(k, args); }, grid, block, shmem, false);
+    emu_launch([=]() { std::apply(k, args); }, grid, block, shmem);
     return hipSuccess;
 }
-template <class P>
-hipError_t emu_launch_coop(void (*k)(P), dim3 grid, dim3 block, void** args, size_t shmem) {
-    P p = *(P*)args[0];
-    emu_launch([=]() { k(p); }, grid, block, shmem, true);
-    return 0;
-}
-
 // ---- block / wave collectives ----
 void emu_syncthreads();
 uint32_t emu_shfl_xor32(uint32_t v, int mask);

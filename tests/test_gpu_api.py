@@ -126,10 +126,9 @@ def test_step_equals_verify_plus_compact_and_async_and_reproducible():
 
 
 def test_a_kernel_that_gave_up_is_reported_and_prefill_recovers():
-    """The failure path of the persistent kernel without disturbing any kernel: the host sets the error word a
-    workgroup raises when its bounded barrier wait runs out.  The next synchronising call reports VADUSA_EHIP,
-    every later call (the debug readers included) refuses with VADUSA_ESTATE, vadusa_prefill resets the barrier
-    state, and the context then decodes the same tokens as a fresh one."""
+    """The error word, raised from the host (no kernel raises it today).  The next synchronising call reports
+    VADUSA_EHIP, every later call (the debug readers included) refuses with VADUSA_ESTATE, vadusa_prefill resets the
+    context, and it then decodes the same tokens as a fresh one."""
     from paper_2410_21951_amd import VadusaError, DBG
     print("give-up path", flush=True)
     W = make_weights(CFG, 4, std=0.08)

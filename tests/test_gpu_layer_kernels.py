@@ -56,8 +56,35 @@ def test_small_tile_shapes(rows):
 
 
 def test_two_query_tiles_per_workgroup_with_an_odd_number_of_tiles():
-    # 40 nodes: three tiles of 16 queries, the last one ragged; 32 sequences x 8 heads
+    # by the rule: 32 sequences x 8 heads x two workgroups.  40 nodes: three tiles of 16 queries, the last one ragged
     _run(_cfg("bf16", 512, 90, layers=1, ffn=256, maxpos=128), 32, 40, (7, 7), (2,), 511, 10, 60)
+
+
+@pytest.mark.parametrize("nodes,caps", [(40, (7, 7)), (17, (5, 4))])
+def test_two_query_tiles_beside_a_finished_sequence(monkeypatch, nodes, caps):
+    """Forced on for three sequences: an odd number of query tiles (three), or two with one query in the second; the
+    prompt's passes likewise; after the first step sequence 0 has ended with EOS and has no rows."""
+    from parity import Lockstep
+    from oracle import vadusa_oracle as O
+    monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", "1")
+    cfg = _cfg("bf16", 128, 90)
+    W = make_weights(cfg, 521, std=_std(cfg), ln_jitter=0.1)
+    W["W_out"] = W["W_out"].copy()
+    W["W_out"][cfg.speech_vocab] = 0    # EOS (logit 0, the largest of the other 90 is near 2.4 standard deviations) comes from the plan alone
+    rng = np.random.default_rng(521)
+    text, prompt = rand_tokens(cfg, rng, 3, (2, 6), (30, 60))
+    ls = Lockstep(cfg, W, text, prompt, nodes, ignore_eos=False)
+    tree = make_tree(nodes, caps)
+    need = O.topk_needed(tree.depth, tree.rank, cfg.n_draft_heads)
+    lists = [[rng.permutation(cfg.speech_vocab)[:k] for k in need] for _ in range(3)]
+    lists[0][0][0] = cfg.speech_vocab
+    for _ in range(2):    # every edge passes (tau above the vocabulary): the paths are the planted ones
+        r = ls.step(tree, cfg.n_logits, override=lists)
+        assert ls.sts[0].finished and not ls.sts[1].finished and not ls.sts[2].finished
+    assert [len(x["accepted"]) for x in r] == [0, 3, 3]
+    ls.check_kv(layers=[0, 1])
+    print(f"{nodes} nodes: compared {ls.stats.compared}/{ls.stats.steps} logit err {ls.stats.max_logit_err:.2e}", flush=True)
+    assert ls.stats.compared == 2
 
 
 # 384 values of a row stay in registers, more are read again; 15 and 17 rows: one row tile, two

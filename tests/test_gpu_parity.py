@@ -410,10 +410,10 @@ def test_large_vocabulary_16k():
 
 
 def test_many_row_unit_kinds_on_ragged_shapes(monkeypatch):
-    """The many-row kernel's 128 x 128 linear-map units and whole-head attention units, which the
+    """The 64 x 128 tiles of the linear maps and the attention with two query tiles per workgroup, which the
     library only picks for maps and batches that fill the GPU, forced on for a small batch with
-    ragged shapes (280 rows: a partial 128-row block; 56-node tree: a partial query tile;
-    vocabulary 301: a partial column group)."""
+    ragged shapes (280 rows: a partial 64-row block; 56-node tree: a partial query tile;
+    301 logits: a partial column group)."""
     monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", "1")     # read when the context is created
     cfg = small_cfg("bf16", layers=2, d=128, heads=3, V=300, maxpos=256)
     _say("many-row unit kinds, ragged shapes")
@@ -432,9 +432,9 @@ def test_many_row_unit_kinds_on_ragged_shapes(monkeypatch):
 
 @pytest.mark.parametrize("nodes,caps,batch", [(32, (6, 6, 6), 9), (12, (4, 3, 2), 24)])
 def test_many_row_attention_units_of_several_pairs(monkeypatch, nodes, caps, batch):
-    """Whole-head attention units of the many-row kernel for trees of one or two query tiles: a unit takes four or
-    two (sequence, head) pairs, a wave per query tile.  Forced on for a small batch whose pair count (27, 72 with
-    three attention heads) leaves the last unit short of pairs (27 = 13 x 2 + 1) or not (72 = 18 x 4)."""
+    """Attention over several (sequence, head) pairs, 27 and 72 of them with three heads (the grid is padded to a
+    multiple of eight), with the rule for two query tiles per workgroup forced on: a tree of 32 nodes has two tiles and
+    takes it, one of 12 nodes has one and may not."""
     monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", "1")
     cfg = small_cfg("bf16", layers=2, d=192, heads=3, V=300, maxpos=160)
     _say(f"many-row attention units of several pairs, {nodes}-node tree, batch {batch}")
@@ -454,8 +454,7 @@ def test_many_row_attention_units_of_several_pairs(monkeypatch, nodes, caps, bat
 @pytest.mark.parametrize("dtype,chunk", [("fp32", 160), ("bf16", 160), ("bf16", 512)])
 def test_prefill_in_long_passes(dtype, chunk):
     """vadusa_config.prefill_chunk: the prompt runs through the decoder in passes of up to that many
-    rows per sequence (more than the 128 rows a tree can have; from 256 rows on in the many-row
-    kernel), ragged batch, then ordinary steps."""
+    rows per sequence (more than the 128 rows a tree can have), ragged batch, then ordinary steps."""
     cfg = small_cfg(dtype, maxpos=512)
     _say(f"prefill passes of {chunk} rows, {dtype}")
     W = make_weights(cfg, 23, std=STD[dtype], ln_jitter=0.1)
@@ -473,8 +472,7 @@ def test_prefill_in_long_passes(dtype, chunk):
 
 
 def test_valle_b1_prefill_in_one_pass(valle):
-    """Configuration 2 at full size with prefill_chunk = 512: the 289-token prompt is one pass of the
-    many-row kernel; then steps as usual."""
+    """Configuration 2 at full size with prefill_chunk = 512: the 289-token prompt is one pass; then steps as usual."""
     wl, W = valle
     text, prompt = make_tokens(wl)
     tree = make_tree(wl.tree_nodes, wl.topk_caps)
@@ -489,8 +487,8 @@ def test_valle_b1_prefill_in_one_pass(valle):
 
 
 def test_many_row_kernel_with_128_node_tree(monkeypatch):
-    """A 128-node tree has eight query tiles per head: the whole-head attention unit (four waves, one
-    query tile each) must not be picked for it even where every other condition holds."""
+    """A 128-node tree, the largest: eight query tiles per head in four workgroups of two, every word of the mask, and
+    64 x 128 tiles of 256 rows."""
     monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", "1")
     cfg = small_cfg("bf16", layers=2, d=128, heads=4, V=300, maxpos=384)
     _say("many-row kernel, 128-node tree")
