@@ -47,10 +47,6 @@ __device__ __forceinline__ uint2 ldg2(const void* p) {
     const vadusa_u32x2 v = *(const VADUSA_GLOBAL vadusa_u32x2*)p;
     return make_uint2(v.x, v.y);
 }
-__device__ __forceinline__ float2 ldgf2(const void* p) {
-    const vadusa_u32x2 v = *(const VADUSA_GLOBAL vadusa_u32x2*)p;
-    return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
-}
 
 // Stores / loads that are coherent across the whole GPU without cache maintenance
 // (write-through to / read from the memory side), for values that a workgroup reads back through memory.
@@ -114,11 +110,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
@@ -138,7 +129,6 @@ __device__ __forceinline__ float quad_sum(float v) {
     v += __int_as_float(dpp_perm<0x4E>(__float_as_int(v)));
     return v;
 }
-__device__ __forceinline__ float pair_sum(float v) { return v + __int_as_float(dpp_perm<0xB1>(__float_as_int(v))); }
 __device__ __forceinline__ float row16_sum(float v) {
     v = quad_sum(v);
     v += __int_as_float(dpp_perm<0x141>(__float_as_int(v)));

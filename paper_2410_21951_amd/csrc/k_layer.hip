@@ -322,9 +322,12 @@ __device__ __forceinline__ f32x16_t mfma_32x32(uint4 a, uint4 b, f32x16_t c) {
 #endif
 }
 
-template <int NRT, int NCT, int DEPTH, int OCC, int EPI>
-__global__ __launch_bounds__(256, OCC) void k_big(LinArgs a) {
+constexpr int BIG_RT = 4, BIG_CT = 2;   // row tiles of a workgroup, column tiles of a wave
+template <int EPI>
+__global__ __launch_bounds__(256, 3) void k_big(LinArgs a) {
     constexpr bool LN = EPI <= LE_LOGITS;
+    constexpr int NRT = BIG_RT, NCT = BIG_CT, DEPTH = 2;   // DEPTH: stages in registers
+    static_assert(4 % DEPTH == 0, "stage c uses register set c mod DEPTH by c mod 4");
     constexpr int ROWS = NRT * 16, NA = NRT / 2, NR2 = NRT / 2, NC2 = NCT / 2;   // NA: activation tiles a wave fetches per stage
     __shared__ uint4 sA[4][NRT * 2 * 64];
     __shared__ float s_mean[ROWS], s_rstd[ROWS];
@@ -802,9 +805,9 @@ template <int RT, int CT, int CH, int EPI>
 static void lin_launch(const LinArgs& a, hipStream_t st, int nz = 1) {
     launch((k_lin<RT, CT, CH, EPI>), dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(256), 0, st, a);
 }
-template <int NRT, int NCT, int DEPTH, int OCC, int EPI>
+template <int EPI>
 static void big_launch(const LinArgs& a, hipStream_t st) {
-    launch((k_big<NRT, NCT, DEPTH, OCC, EPI>), dim3(pad8(cdiv(a.NT, 4 * NCT)), cdiv(a.R, NRT * 16)), dim3(256), 0, st, a);
+    launch(k_big<EPI>, dim3(pad8(cdiv(a.NT, 4 * BIG_CT)), cdiv(a.R, BIG_RT * 16)), dim3(256), 0, st, a);
 }
 // k_big's 64 x 128 tiles from one tile per eight K values on (129 tiles at K = 1024): fewer leave compute units idle for
 // a whole reduction, where k_lin's smaller tiles split it over four waves.  Measured, K = 1024: 4096 columns, 320 rows
@@ -813,17 +816,19 @@ static void big_launch(const LinArgs& a, hipStream_t st) {
 // rows 67 against 72.
 template <int EPI>
 static void lin(const LinArgs& a, int big_min, hipStream_t st) {
-    const long tiles = (long)cdiv(a.R, 64) * cdiv(a.NT, 8);
-    if (big_min > 0 ? tiles >= big_min : tiles > 4 * a.nks) { big_launch<4, 2, 2, 3, EPI>(a, st); return; }
+    const long tiles = (long)cdiv(a.R, 16 * BIG_RT) * cdiv(a.NT, 4 * BIG_CT);
+    if (big_min > 0 ? tiles >= big_min : tiles > 4 * a.nks) { big_launch<EPI>(a, st); return; }
     const LinShape s = lin_shape(a.R, a.NT);
+    if constexpr (EPI == LE_LOGITS) {   // (with a multiple of four column tiles 1 x 2 and 2 x 4 never take more workgroups than these)
+        if (s.rt == 2 && s.ct == 1) { lin_launch<2, 1, 8, EPI>(a, st); return; }
+        if (s.rt == 4 && s.ct == 2) { lin_launch<4, 2, 4, EPI>(a, st); return; }
+    }
     switch (s.rt * 8 + s.ct) {
     case 1 * 8 + 1: lin_launch<1, 1, 8, EPI>(a, st); break;
     case 1 * 8 + 2: lin_launch<1, 2, 8, EPI>(a, st); break;
-    case 2 * 8 + 1: lin_launch<2, 1, 8, EPI>(a, st); break;
     case 2 * 8 + 2: lin_launch<2, 2, EPI == LE_RESID ? 4 : 8, EPI>(a, st); break;
     case 2 * 8 + 4: lin_launch<2, 4, 4, EPI>(a, st); break;
     case 3 * 8 + 4: lin_launch<3, 4, 4, EPI>(a, st); break;
-    case 4 * 8 + 2: lin_launch<4, 2, 4, EPI>(a, st); break;
     default: lin_launch<4, 4, 2, EPI>(a, st); break;
     }
 }

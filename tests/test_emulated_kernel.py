@@ -34,3 +34,21 @@ def test_emulated_step_matches_oracle(emu_lib, dtype):
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=600, text=True)
     assert r.returncode == 0, r.stdout[-3000:]
     assert ("recovered" if dtype == "bf16-giveup" else "stayed in bounds" if dtype.endswith("-nan") else "compared") in r.stdout
+
+
+def test_tile_shapes_of_the_gpu_tests(emu_lib):
+    """The shapes that the GPU tests of k_lin name are those that the library picks, and each shape is among them."""
+    import ctypes as C
+    from test_gpu_layer_kernels import TILE_SHAPES
+    pick = C.CDLL(emu_lib).emu_lin_shape
+    seen = set()
+    for d, ffn, nodes, batch, V, shapes in TILE_SHAPES:
+        rows = nodes * batch
+        assert rows % 16, "the last row tile is ragged"
+        got = [pick(rows, -(-n // 16)) for n in (3 * d, d, ffn, V + 1)]
+        assert " ".join(f"{s // 16}x{s % 16}" for s in got) == shapes, (d, ffn, rows, V)
+        seen |= {(kind, s) for kind, s in zip(("qkv", "residual", "ffn1", "logits"), shapes.split())}
+    every = ("1x1", "1x2", "2x2", "2x4", "3x4", "4x4")
+    assert seen == {(kind, s) for kind in ("qkv", "residual", "ffn1", "logits") for s in every} | {("logits", "2x1"), ("logits", "4x2")}
+    # maps whose columns are a multiple of 64 never pick 2x1 or 4x2, which are built for the vocabulary map alone
+    assert {pick(16 * rt, nt) for rt in range(1, 129) for nt in range(4, 1025, 4)} <= {16 * int(s[0]) + int(s[2]) for s in every}

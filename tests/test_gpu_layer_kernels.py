@@ -44,7 +44,7 @@ def test_many_row_tiles_at_their_edges(monkeypatch, d, nodes, batch, V):
     _run(_cfg("bf16", d, V), batch, nodes, (9, 9), (2, 1), 300 + d, 20, 70)
 
 
-# rows at which the small-tile kernel changes its shape (16, 32, 64, 128, 192 rows and one more)
+# rows below, at and above whole tiles; at this width all maps run in tiles of one or two by one or two
 @pytest.mark.parametrize("rows", [1, 16, 17, 33, 64, 97, 128, 193])
 def test_small_tile_shapes(rows):
     batch = 1 if rows <= 100 else 2 if rows % 2 == 0 else 1
@@ -53,6 +53,35 @@ def test_small_tile_shapes(rows):
         batch, nodes = 2, 97    # 194 rows
     caps = () if nodes == 1 else (10, 10, 10)
     _run(_cfg("bf16", 256, 301, heads=3, maxpos=224), batch, nodes, caps, (1, 2), 400 + rows, 30, 80)
+
+
+# Every tile shape of k_lin with a ragged last row tile (and, in the vocabulary map, a ragged last column tile and a column
+# count that the shape does not divide): d, ffn, nodes, batch, V, and the shapes (row tiles x column tiles) that the rule picks
+# for QKV, out-projection and FFN2, FFN1, vocabulary map.  tests/test_emulated_kernel.py holds the rule to this table.
+TILE_SHAPES = [
+    (64, 4096, 17, 1, 1349, "1x1 1x1 1x2 1x1"),
+    (64, 4096, 33, 1, 2060, "1x1 1x1 2x2 1x2"),
+    (64, 4096, 65, 1, 4110, "1x1 1x1 2x4 2x4"),
+    (64, 4096, 43, 3, 1610, "1x1 1x1 3x4 2x2"),
+    (64, 4096, 97, 2, 300, "1x1 1x1 4x4 1x1"),
+    (64, 256, 85, 1, 1349, "1x1 1x1 1x1 2x1"),
+    (64, 256, 17, 17, 1610, "1x1 1x1 1x2 4x2"),
+    (64, 64, 33, 1, 8205, "1x1 1x1 1x1 3x4"),
+    (64, 64, 49, 1, 8300, "1x1 1x1 1x1 4x4"),
+    (64, 128, 26, 13, 77, "1x2 1x1 1x1 1x1"),
+    (64, 128, 27, 25, 300, "2x2 1x1 1x2 2x2"),
+    (128, 128, 27, 25, 77, "2x4 1x2 1x2 1x1"),
+    (192, 192, 23, 39, 77, "3x4 2x2 2x2 1x2"),
+    (512, 512, 27, 19, 77, "4x4 2x4 2x4 1x1"),
+    (512, 512, 41, 25, 77, "4x4 3x4 3x4 1x2"),
+    (512, 512, 53, 29, 77, "4x4 4x4 4x4 2x1"),
+]
+
+
+@pytest.mark.parametrize("d,ffn,nodes,batch,V,shapes", TILE_SHAPES)
+def test_every_small_tile_shape(monkeypatch, d, ffn, nodes, batch, V, shapes):
+    monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", "1000000")   # k_big never
+    _run(_cfg("bf16", d, V, layers=1, ffn=ffn, maxpos=160), batch, nodes, (16, 16), (2,), 700 + d + nodes, 4, 20)
 
 
 def test_two_query_tiles_per_workgroup_with_an_odd_number_of_tiles():
