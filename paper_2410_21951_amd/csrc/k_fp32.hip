@@ -33,9 +33,12 @@ __device__ __forceinline__ float silu_f(float v) { return v / (1.f + __expf(-v))
 // Y = X W^T (+ bias) with the epilogues of common.h, X = LayerNorm(x) where GemmArgs::ln_g is given.  One workgroup per
 // 16 rows x 16 columns, the four waves split the reduction in steps of 16 (a lane's four consecutive values of a row are
 // four matrix instructions' operands; both operands take the same order, so no value moves between lanes), eight steps
-// requested at a time; the partial sums are added in wave order through LDS.
+// requested at a time.  A wave keeps 16 accumulators, which makes 64 partial sums of K / 64 products, added pairwise, in the
+// wave and then through LDS: with one chain of K / 4 per wave a model's logits were twice as far from 64-bit arithmetic (two
+// and three layers: 4.4e-7 and 5.2e-7 against 2.4e-7 and 2.5e-7) and a step took 1 to 3 % less (two layers, d = 256, 16 rows:
+// 94 us against 96).  Launch bounds of two: the accumulators stay where additions can read them (2.5 % of a step).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_lin32(GemmArgs a) {
+__global__ __launch_bounds__(256, 2) void k_lin32(GemmArgs a) {
     constexpr int CH = 8;
     __shared__ f32x4_t red[4 * 64];
     __shared__ float s_mean[16], s_rstd[16];
@@ -83,7 +86,9 @@ __global__ __launch_bounds__(256) void k_lin32(GemmArgs a) {
         load(lo);
     }
     const float mu = a.ln_g ? s_mean[lc] : 0.f, rstd = a.ln_g ? s_rstd[lc] : 1.f;
-    f32x4_t acc = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc[4][4];   // [step mod 4][which of a lane's four values]
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i >> 2][i & 3] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     for (int s = lo; s < hi; s += CH) {
         if (s > lo) load(s);
 #pragma unroll
@@ -94,18 +99,19 @@ __global__ __launch_bounds__(256) void k_lin32(GemmArgs a) {
                 const float4 g = lg[i], b = lb[i];
                 v = make_float4((v.x - mu) * rstd * g.x + b.x, (v.y - mu) * rstd * g.y + b.y, (v.z - mu) * rstd * g.z + b.z, (v.w - mu) * rstd * g.w + b.w);
             }
-            acc = mfma_16x16x4(w[i].x, v.x, acc);   // weights first: a lane then holds four consecutive columns of one row
-            acc = mfma_16x16x4(w[i].y, v.y, acc);
-            acc = mfma_16x16x4(w[i].z, v.z, acc);
-            acc = mfma_16x16x4(w[i].w, v.w, acc);
+            f32x4_t(&a4)[4] = acc[i & 3];
+            a4[0] = mfma_16x16x4(w[i].x, v.x, a4[0]);   // weights first: a lane then holds four consecutive columns of one row
+            a4[1] = mfma_16x16x4(w[i].y, v.y, a4[1]);
+            a4[2] = mfma_16x16x4(w[i].z, v.z, a4[2]);
+            a4[3] = mfma_16x16x4(w[i].w, v.w, a4[3]);
         }
     }
-    red[tid] = acc;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i][0] = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+    red[tid] = (acc[0][0] + acc[1][0]) + (acc[2][0] + acc[3][0]);
     __syncthreads();
     if (wave) return;
-    f32x4_t s = red[lane];
-#pragma unroll
-    for (int v = 1; v < 4; ++v) s += red[v * 64 + lane];
+    const f32x4_t s = (red[lane] + red[64 + lane]) + (red[128 + lane] + red[192 + lane]);
     const int r = r0 + lc;
     if (r >= a.R) return;
 #pragma unroll

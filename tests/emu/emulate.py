@@ -32,8 +32,9 @@ def build(out_dir, extra_flags=()):
         # dynamic LDS and the inline-asm wait have host stand-ins
         text = text.replace("extern __shared__ float s_s[];", "float* s_s = (float*)emu_dyn_lds;")
         text = "\n".join(l for l in text.split("\n") if "s_waitcnt" not in l)
-        if name == "k_layer.hip":
-            text += open(os.path.join(HERE, "layer_exports.inc")).read()
+        extra = os.path.join(HERE, name[:-4] + "_exports.inc")      # single kernels for tests that call them alone
+        if os.path.exists(extra):
+            text += open(extra).read()
         dst = os.path.join(gen, name[:-4] + ".cpp" if name.endswith(".hip") else name)
         open(dst, "w").write(text)
         if dst.endswith(".cpp"):

@@ -204,6 +204,31 @@ if dtype.endswith("-partial"):
     print("emulated partial compaction: compared", flush=True)
     sys.stdout.flush()
     os._exit(0)
+if dtype == "fp32-sums":
+    # The linear map of the fp32 model against 64-bit arithmetic: no further off than 64 partial sums of K / 64 products each
+    # (fused multiply-add), added pairwise, are on the same operands.
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    rng = np.random.default_rng(77)
+    f = np.float32
+    for K in (64, 256, 320, 1024):
+        X, Wm = rng.standard_normal((16, K)).astype(f), rng.standard_normal((48, K)).astype(f)
+        out = np.zeros((16, 48), f)
+        p = lambda a: a.ctypes.data_as(C.c_void_p)
+        V._lib.emu_lin32(p(X), p(Wm), p(out), 16, K, 48)
+        prod = X.astype(np.float64)[:, None, :] * Wm.astype(np.float64)[None]      # exact
+        part = np.zeros((16, 48, 64), f)
+        for k in range(0, K, 64):
+            part = (part + prod[:, :, k:k + 64]).astype(f)
+        while part.shape[2] > 1:
+            part = (part[:, :, ::2] + part[:, :, 1::2]).astype(f)
+        want = prod.sum(axis=2)
+        err = lambda a: float(np.sqrt(np.mean((a - want) ** 2) / np.mean(want ** 2)))
+        print(f"K {K}: kernel {err(out):.2e}, pairwise sums {err(part[:, :, 0]):.2e}", flush=True)
+        assert err(out) < 1.1 * err(part[:, :, 0]), K       # (768 results: the two root mean squares scatter by some 4 % each)
+    print("emulated fp32 sums: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype == "bf16-4gib-map":
     # One linear map of more than 4 GiB (K = 4096): 64 x 128 workgroups at its start and on both sides of the 4 GiB mark.
     # The weights are address space that is never touched but for the tiles of these workgroups, all values of tile t
