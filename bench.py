@@ -262,9 +262,8 @@ def main():
     del src, dst
     out["roofline"]["copy_kernel_gbs"] = copy_gbs
     out["roofline"]["hbm_gbs_over_copy_kernel"] = achieved / copy_gbs
-    # Prefill (the call synchronises, so host time is the measure): in passes of max_tree_nodes rows
-    # (the default) and in passes of up to 512 rows per sequence (vadusa_config.prefill_chunk), which
-    # run in the many-row kernel from 256 rows on.
+    # Prefill (the call synchronises, so host time is the measure): in passes of the default length (up to 128
+    # rows per sequence) and of up to 512 rows per sequence (vadusa_config.prefill_chunk).
     def prefill_ms(d, reps=5):
         d.prefill(text, prompt)
         t0 = time.perf_counter()
@@ -277,7 +276,7 @@ def main():
     dev512.load_weights(W)
     ms_big = prefill_ms(dev512)
     dev512.close()
-    out["prefill"] = {"prompt_tokens": n_prompt, "ms_passes_of_tree_size": ms_small, "ms_passes_of_512": ms_big,
+    out["prefill"] = {"prompt_tokens": n_prompt, "ms_default_passes": ms_small, "ms_passes_of_512": ms_big,
                       "tokens_per_s_passes_of_512": n_prompt / (ms_big * 1e-3)}
     # The stochastic form of Algorithm 1 (temperature 0.9, top_p 0.9 as in Sec. 3.1.2's sampling runs):
     # the same step with the perturbed-score kernel between the base head and the acceptance; the

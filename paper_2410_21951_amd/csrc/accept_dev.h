@@ -476,7 +476,7 @@ __device__ inline void dev_topk(const Dims& D, const DevState& s, int i, int b) 
         } else {
             rescan = true;   // n is the same for every thread
         }
-        __syncthreads();     // the LDS arrays are free for the next unit
+        __syncthreads();     // the LDS arrays are free again
     }
     if (rescan) {
         float pv = INFINITY;

@@ -691,7 +691,7 @@ static void mark_compacted(vadusa_ctx* c, int seq0, int nseq, int n_forced) {
 }
 
 // Verification; with fuse_compact the compaction of every sequence's chosen path and the
-// draft heads follow in the same launch (bf16 model) or right behind (fp32 model).
+// draft heads follow at once.
 static int verify_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau, const int32_t* draft_override,
                        bool fuse_compact, const vadusa_sampling* sp = nullptr) {
     if (!c) return VADUSA_EINVAL;

@@ -67,7 +67,7 @@ __device__ __forceinline__ size_t toff(int r, int k, int nks) {
     return ((size_t)((r >> 4) * nks + (k >> 5)) * 64 + (r & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
 }
 // KV cache of one (layer, sequence, head): kv_cap(max_positions) positions (whole blocks of 32) x 64 dimensions,
-// kept in the operand tiles of the attention units, so that every operand of a 32-key block is one contiguous KiB
+// kept in the operand tiles of the attention, so that every operand of a 32-key block is one contiguous KiB
 // per wave load (a row-major cache makes such a load touch 16 cache lines and use half of each):
 //   K: [block of 32 keys][key tile t][k-step s][lane][8]: key k = pos & 31 sits in tile t = (k >> 2) & 1 (tile 0:
 //      keys 0-3, 8-11, 16-19, 24-27 of the block; tile 1: the others) at row c = ((k >> 3) << 2) | (k & 3); k-step
@@ -202,7 +202,7 @@ struct DevState {
     const float *lnf_g, *lnf_b;
     const void* W_out;
     float *cs_out, *t_out;          // bf16 model: folded final LayerNorm for the vocabulary map
-    // KV cache, element type = dtype: K [Ly][Bmax][nH][maxpos][64], V [Ly][Bmax][nH][64][maxpos]
+    // KV cache, element type = dtype: [Ly][Bmax][nH] times kv_cap(maxpos) positions x 64 dimensions in the order of kc_off / vc_off
     void *Kc, *Vc;
     // activations
     float* x;        // [R][d]  residual stream

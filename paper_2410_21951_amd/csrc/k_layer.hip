@@ -287,18 +287,21 @@ __global__ __launch_bounds__(256) void k_lin(LinArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Linear map of many rows: one workgroup per 16 NRT rows x 64 NCT columns, wave w taking all rows and columns
-// 16 NCT w .. of them.  Activations pass through LDS (all four waves need all of them), weights go straight into the
+// Linear map of many rows: one workgroup per 64 rows x 128 columns, wave w taking all rows and the columns 32 w .. 32 w + 31
+// of them.  Activations pass through LDS (all four waves need all of them), weights go straight into the
 // registers of the one wave that needs them.  v_mfma_f32_32x32x16_bf16: with one wave per SIMD it reaches 2.26 PFLOP/s
 // where the 16 x 16 x 32 form reaches 1.4 (register operands, 256 workgroups); two row tiles (column tiles) and half
 // of their k-step make one operand, which is a permutation of the 16-byte pieces of the stored tiles.
 // The reduction runs in stages of two k-steps of 32.  A stage's activation tiles are fetched into registers by the four
-// waves (NRT / 2 tiles each), written to LDS two stages before they are multiplied, and four stages of activations and
-// three of weights are on their way behind the one being multiplied.
-// What bounds it: at 128 x 256 the compute unit pulls 24 KB and reads and writes 40 KB of LDS per k-step of 512
-// matrix-core clocks (48 B and 80 B per clock; 47 to 57 B per clock is what a compute unit gets through L2 when all
-// 256 pull).  With both operands through LDS and 64 x 64 per wave the LDS traffic alone would exceed the matrix cores'
-// time.
+// waves (two tiles each) four stages before they are multiplied and written to LDS two stages before; weights are
+// fetched two stages ahead.  Two stages in registers and 144 vector registers let three workgroups share a compute unit;
+// tile, depth and occupancy were measured together (FFN1 at 2048 rows, K = 1024, us): 128 x 256, one workgroup per compute
+// unit 28.7; 128 x 128, two, 24.7; 64 x 256, two, 25.3; 64 x 128 with four stages, two, 27.5, with two stages, three, 26.0, four,
+// 31.  64 x 128 is the best of them at 1024 rows and for narrow maps (QKV 14.1 against 16.2 for 128 x 128, FFN1 15.7 against 16.5).
+// What bounds it: no single unit.  FFN1 of 2048 rows takes 28.5 us in a step; its products keep a SIMD's matrix core busy
+// for 6.8 us of them, 69 MB cross between the L2s and memory (2.4 TB/s), and a compute unit pulls 1.6 MB through L2 (23 B
+// per clock of the 47 to 57 it can).  1024 workgroups are 1.33 rounds of the 768 that fit, each with its statistics,
+// 16 stages with a barrier, GELU and stores one behind the other.
 // ---------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 // D = A B + C, A 32 x 16 (lane: row lane & 31, k 8 (lane >> 5) ..), B 16 x 32 alike; lane l, element i of D: column
@@ -391,8 +394,8 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a) {
                 for (int c = 0; c < NC2; ++c)   // weights first: a lane then holds groups of four consecutive columns of one row
                     acc[c][r] = mfma_32x32(h ? w1[c] : w0[c], x[h][r], acc[c][r]);
     };
-    // Stage c reads LDS buffer c mod 4 and weight set c mod 4; set (c + 2) mod 4 of the activation registers holds stage
-    // c + 2, which goes into buffer (c + 2) mod 4, last read in stage c - 2.  The first k-step's operands of stage c are
+    // Stage c reads LDS buffer c mod 4 and weight set c mod 2; set c mod 2 of the activation registers holds stage
+    // c + 2, which goes into buffer (c + 2) mod 4, last read in stage c - 2, and then takes stage c + 4.  The first k-step's operands of stage c are
     // read at the end of stage c - 1, so that no multiplication waits for LDS; the scheduling fences keep the compiler
     // from moving the reads next to their uses.  Every load, copy and read is unconditional, so that the waits count exactly
     // the loads issued since: past the end the last stage is fetched again (from L2) and never multiplied.
@@ -786,8 +789,10 @@ __global__ void k_clock(DevState s, int ph) { s.tprof[ph * 8] = wall_clock64(); 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// Tile shape of a map.  k_lin's time is what a compute unit has to pull in through L2: a workgroup reads its rows and its
-// columns of K values, and the 256 compute units get cdiv(workgroups, 256) of them each.
+// Tile shape of a map.  The rule counts what a compute unit has to pull in through L2: a workgroup reads its rows and its
+// columns of K values, and the 256 compute units get cdiv(workgroups, 256) of them each.  (Not counted, and what bounds
+// the maps of many rows and long reductions: an XCD has an eighth of the columns and all rows, so that the activations cross
+// into the L2s eight times.  FFN2 of 2048 rows, K = 4096: 160 MB fetched in 33.4 us = 4.8 TB/s, what a large copy reaches.)
 struct LinShape { int rt, ct; };
 static LinShape lin_shape(int R, int NT) {
     static const LinShape shapes[] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 4}, {3, 4}, {4, 2}, {4, 4}};
@@ -813,7 +818,10 @@ static void big_launch(const LinArgs& a, hipStream_t st) {
 // a whole reduction, where k_lin's smaller tiles split it over four waves.  Measured, K = 1024: 4096 columns, 320 rows
 // (160 tiles) 10.8 us against 12.2 in k_lin, 512 rows 11.0 against 14.6; 1024 columns, 1024 rows (128 tiles) 8.9 against
 // 7.8, 2048 rows 12.5 against 14.6.  K = 4096, 1024 columns: 1024 rows 26.8 against 17.0, 2048 rows 32 against 32, 4480
-// rows 67 against 72.
+// rows 67 against 72.  Whole steps of six layers, all maps by the rule against all in k_lin: d = 512, 1024 rows 283 against
+// 316, 2048 rows 430 against 483, 8192 rows 1310 against 1667; d = 256, 2048 rows 314 against 336, 8192 rows 776 against 962.
+// Below that the line lies too low for short reductions: d = 512, 512 rows 248 against 228; d = 256, 512 rows 198 against
+// 170, 1024 rows 224 against 215; d = 128, 2048 rows 251 against 226.
 template <int EPI>
 static void lin(const LinArgs& a, int big_min, hipStream_t st) {
     const long tiles = (long)cdiv(a.R, 16 * BIG_RT) * cdiv(a.NT, 4 * BIG_CT);

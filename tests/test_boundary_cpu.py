@@ -28,7 +28,7 @@ def test_every_declared_symbol_is_exported(lib):
 
 
 def test_the_library_with_timing_points_exports_the_same_symbols():
-    """libvadusa_clock.so (the step kernel's timing points compiled in; the binding loads it when
+    """libvadusa_clock.so (timing points compiled in; the binding loads it when
     VADUSA_PHASE_CLOCK is set) is the same library otherwise."""
     path = V._LIB_CLOCK_PATH
     assert os.path.exists(path), "build it with `python -m paper_2410_21951_amd.build`"
