@@ -404,7 +404,7 @@ extern "C" int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena
     c->L_ub.assign(cfg->max_batch, 0);
     c->pending.assign(cfg->max_batch, 0);
     c->errored = 0;
-    c->big_min = getenv("VADUSA_BIG_MIN_UNITS") ? std::max(1, atoi(getenv("VADUSA_BIG_MIN_UNITS"))) : 0;
+    c->big_min = getenv("VADUSA_BIG_MIN_UNITS") ? atoi(getenv("VADUSA_BIG_MIN_UNITS")) : 0;
     {
         // the error flag starts at zero; an unwritten KV row must never hold NaN bits (a masked key enters the attention as
         // 0 x its value), the rows that fill the last block of 32 included

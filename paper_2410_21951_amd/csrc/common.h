@@ -92,17 +92,16 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_cvt));
 }
 
-// GELU with the exact (erf) definition; erf by the rational approximation 7.1.26 of Abramowitz &
+// GELU with the exact (erf) definition, v Phi(v); erfc by the rational approximation 7.1.26 of Abramowitz &
 // Stegun (absolute error below 1.5e-7, the size of an fp32 rounding of the result, which is then
 // stored as bf16): one exponential, one reciprocal and a fifth-degree polynomial instead of the
-// library routine's two branches.
+// library routine's two branches.  Its constants are scaled for |v| in place of |v| / sqrt 2, powers of two and erfc / 2 = Phi(-|v|).
 __device__ __forceinline__ float gelu_s(float v) {
-    const float x = fabsf(v) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(1.f + 0.3275911f * x);   // one instruction, 1 ulp: far below the approximation's own error
-    const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-    const float erfc_x = poly * __expf(-x * x);            // 1 - erf(|x|)
-    const float one_plus_erf = v < 0.f ? erfc_x : 2.f - erfc_x;
-    return 0.5f * v * one_plus_erf;
+    const float t = __builtin_amdgcn_rcpf(1.f + 0.23164190f * fabsf(v));   // one instruction, 1 ulp: far below the approximation's own error
+    const float poly = t * (0.127414796f + t * (-0.142248368f + t * (0.7107068705f + t * (-0.7265760135f + t * 0.5307027145f))));
+    const float u = v * 0.84932180f;                                        // 2^-(u u) = exp(-v^2 / 2)
+    const float tail = poly * __builtin_amdgcn_exp2f(-(u * u));
+    return v * (v < 0.f ? tail : 1.f - tail);
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -250,7 +249,8 @@ struct vadusa_ctx {
     float* uniforms;             // [max_batch * max_tree_nodes][V+1]: the caller's random numbers of a stochastic step
     float* scores;               // same shape: perturbed scores that replace the logits in such a step
     int sampled;                 // the pending / last verification was a stochastic one
-    int big_min;                 // k_big's tiles, and attention workgroups of two query tiles, from this many on (environment VADUSA_BIG_MIN_UNITS, for tests of small shapes); 0: the rules
+    int big_min;                 // k_big's tiles, and attention workgroups of two query tiles, from this many on; -1, -2: k_tile of 256 x 128, 128 x 64 outputs for every
+                                 // map (environment VADUSA_BIG_MIN_UNITS, for tests of small shapes); 0: the rules
     int32_t* pinned;             // host memory that the last kernel of a call writes results into (null: none)
     size_t pinned_words;
     std::vector<int32_t> unpinned;   // its stand-in

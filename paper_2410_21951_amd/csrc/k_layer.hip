@@ -38,11 +38,12 @@ struct LinArgs {
     const bf16_t* X;        // [R][K] operand tiles
     const uint4* W;         // [N][K] operand tiles
     const float *bias, *colsum;
-    const float2* stats;    // [R][K / 16] statistics of X's rows (LayerNorm-folded maps)
+    const float2* stats;    // [R][K >> sg] statistics of X's rows (LayerNorm-folded maps)
     int nks, NT, R, N;      // K / 32, column tiles, rows, columns
+    int sg, sg_out;         // log2 of the columns that an entry of stats (stats_out) describes: 4 to 6; a row's entries are an even number
     bf16_t* out;            // operand tiles of the next map: q, hidden layer or the residual stream's bf16 copy
     float* outf;            // logits, or the residual stream (LE_RESID)
-    float2* stats_out;      // [R][N / 16] (LE_RESID)
+    float2* stats_out;      // [R][N >> sg_out] (LE_RESID)
     bf16_t *Kc, *Vc;        // LE_QKV: this layer's cache
     const int32_t *L, *n_rows;
     int M, nH, maxpos, d;
@@ -63,17 +64,18 @@ struct RowStats {
     float c0[PASS];
     uint4 v[PASS][NV];
     __device__ __forceinline__ void request(const LinArgs& a, int row0) {
-        const int tiles = a.nks * 2, part = threadIdx.x % TPR;
+        const int tiles = a.nks * 32 >> a.sg, part = threadIdx.x % TPR;
 #pragma unroll
         for (int p = 0; p < PASS; ++p) {
             sp[p] = a.stats + (size_t)min(row0 + p * (256 / TPR) + (int)threadIdx.x / TPR, a.R - 1) * tiles;
             c0[p] = ldg(&sp[p]->x);
 #pragma unroll
-            for (int j = 0; j < NV; ++j) v[p][j] = ldg4(sp[p] + (2 * (part + j * TPR) < tiles ? 2 * (part + j * TPR) : 0));
+            for (int j = 0; j < NV; ++j)
+                if (j == 0 || 2 * j * TPR < tiles) v[p][j] = ldg4(sp[p] + (2 * (part + j * TPR) < tiles ? 2 * (part + j * TPR) : 0));
         }
     }
     __device__ __forceinline__ void merge(const LinArgs& a, float* s_mean, float* s_rstd) {
-        const int tiles = a.nks * 2, part = threadIdx.x % TPR;
+        const int tiles = a.nks * 32 >> a.sg, part = threadIdx.x % TPR;
 #pragma unroll
         for (int p = 0; p < PASS; ++p) {
             float s1 = 0.f, s2 = 0.f, s3 = 0.f;   // sums of the tile means' distances from c0, of the tiles' squared deviations, of the squared distances
@@ -98,9 +100,9 @@ struct RowStats {
             s3 = sum(s3);
             if (part == 0) {
                 const int r = p * (256 / TPR) + (int)threadIdx.x / TPR;
-                const float m2 = s2 + 16.f * fmaxf(s3 - s1 * s1 / tiles, 0.f);
+                const float m2 = s2 + (float)(1 << a.sg) * fmaxf(s3 - s1 * s1 / tiles, 0.f);
                 s_mean[r] = c0[p] + s1 / tiles;
-                s_rstd[r] = rsqrtf(m2 / (16 * tiles) + LN_EPS);
+                s_rstd[r] = rsqrtf(m2 / (a.nks * 32) + LN_EPS);
             }
         }
     }
@@ -298,10 +300,13 @@ __global__ __launch_bounds__(256) void k_lin(LinArgs a) {
 // tile, depth and occupancy were measured together (FFN1 at 2048 rows, K = 1024, us): 128 x 256, one workgroup per compute
 // unit 28.7; 128 x 128, two, 24.7; 64 x 256, two, 25.3; 64 x 128 with four stages, two, 27.5, with two stages, three, 26.0, four,
 // 31.  64 x 128 is the best of them at 1024 rows and for narrow maps (QKV 14.1 against 16.2 for 128 x 128, FFN1 15.7 against 16.5).
-// What bounds it: no single unit.  FFN1 of 2048 rows takes 28.5 us in a step; its products keep a SIMD's matrix core busy
-// for 6.8 us of them, 69 MB cross between the L2s and memory (2.4 TB/s), and a compute unit pulls 1.6 MB through L2 (23 B
-// per clock of the 47 to 57 it can).  1024 workgroups are 1.33 rounds of the 768 that fit, each with its statistics,
-// 16 stages with a barrier, GELU and stores one behind the other.
+// What bounds it: no single unit.  FFN1 of 1024 rows takes 17 us in a step; its products keep a SIMD's matrix core busy
+// for 3.4 us of them, and a compute unit pulls 0.8 MB through L2.  512 workgroups are 0.67 rounds of the 768 that fit, each with its
+// statistics, 16 stages with a barrier, GELU and stores one behind the other.
+// Tiles numbered in blocks per XCD (a column of tiles per XCD before: eight times all activations into the L2s), results stored as whole
+// 16-byte pieces, statistics per 32 columns, values of a piece of the cache in one store (us, before and after, weights from HBM):
+// out-projection of 2048 rows 15.0 -> 13.5, FFN2 of 3200 rows 46.3 -> 42.2, of 4352 rows 68.6 -> 62.4, QKV of 3200 rows 37.9 -> 36.0, FFN1 of
+// 2048 rows 31.6 -> 30.5.
 // ---------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 // D = A B + C, A 32 x 16 (lane: row lane & 31, k 8 (lane >> 5) ..), B 16 x 32 alike; lane l, element i of D: column
@@ -310,7 +315,7 @@ __device__ __forceinline__ f32x16_t mfma_32x32(uint4 a, uint4 b, f32x16_t c) {
 #if defined(__HIP_DEVICE_COMPILE__)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 #else   // host emulation of the kernels: the wave's operands meet in an array, between two lane exchanges
-    __shared__ uint4 ops[4][2][64];
+    __shared__ uint4 ops[8][2][64];
     const int w = (int)(threadIdx.x >> 6), l = (int)(threadIdx.x & 63);
     ops[w][0][l] = a;
     ops[w][1][l] = b;
@@ -325,17 +330,112 @@ __device__ __forceinline__ f32x16_t mfma_32x32(uint4 a, uint4 b, f32x16_t c) {
 #endif
 }
 
+// Stores 16 outputs of one row, columns n0 .. n0 + 15, held by lanes l and l + 32 (hi): columns 4 hi .. + 3 and 8 + 4 hi .. + 3.
+// bf16 results change places between the two lanes first, so that each has eight consecutive columns, a whole piece of an
+// operand tile: with half pieces every cache line is written in two parts.
+template <int EPI>
+__device__ __forceinline__ void store16(const LinArgs& a, int r, int n0, int hi, float (&v)[8], const KvRow& kv, uint4* v_row) {
+    const bool live = r < a.R;
+    if constexpr (EPI == LE_LOGITS) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int n = n0 + 4 * hi + (j & 3) + 2 * (j & 4);
+            if (live && n < a.N) a.outf[(size_t)r * a.N + n] = v[j];
+        }
+        return;
+    }
+    if constexpr (EPI == LE_RESID) {
+        if (live) {
+            *(float4*)(a.outf + (size_t)r * a.N + n0 + 4 * hi) = make_float4(v[0], v[1], v[2], v[3]);
+            *(float4*)(a.outf + (size_t)r * a.N + n0 + 8 + 4 * hi) = make_float4(v[4], v[5], v[6], v[7]);
+        }
+    }
+    if constexpr (EPI == LE_GELU)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = gelu_s(v[j]);
+    const vadusa_u32x2 p = __builtin_amdgcn_permlane32_swap(pack_bf16(v[0], v[1]), pack_bf16(v[4], v[5]), false, false);
+    const vadusa_u32x2 q = __builtin_amdgcn_permlane32_swap(pack_bf16(v[2], v[3]), pack_bf16(v[6], v[7]), false, false);
+    const uint4 pk = make_uint4(p.x, q.x, p.y, q.y);   // columns n .. n + 7
+    const int n = n0 + 8 * hi;
+    if constexpr (EPI == LE_QKV) {
+        if (n < a.d) {
+            if (live) *(uint4*)(a.out + toff(r, n, a.d >> 5)) = pk;
+        } else if (n < 2 * a.d) {
+            const int head = (n - a.d) >> 6, dim = (n - a.d) & 63;
+            if (kv.pos >= 0) *(uint4*)(a.Kc + kv.base + (size_t)head * kv_cap(a.maxpos) * 64 + kc_off(kv.pos, dim)) = pk;   // eight dimensions of one key: a lane's piece
+        } else {
+            v_row[hi] = pk;
+        }
+    } else {
+        if (live) *(uint4*)(a.out + toff(r, n, a.N >> 5)) = pk;
+    }
+}
+
+// The wave's LDS writes so far come before its LDS reads from here on.
+__device__ __forceinline__ void wave_sync() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_wave_barrier();
+#else
+    (void)__shfl(0u, 0, 64);
+#endif
+}
+
+// The values of ROWS rows from `first` on and COLS columns of one head (from value column `col` on), which the wave has left in
+// LDS, into the cache.  The cache keeps eight consecutive positions of a dimension side by side: a lane becomes a dimension and takes the rows
+// of one sequence that share such a piece, one store of 16 bytes where there are eight of them.  (From the lanes that hold rows it
+// takes eight stores of two bytes, each to ten lines.)
+template <int ROWS, int COLS>
+__device__ __forceinline__ void store_values(const LinArgs& a, int first, int col, const uint16_t* values, int lane) {
+    constexpr int STRIDE = COLS + 8;   // a row's columns and room for eight more: the rows start in different banks
+    const int head = col >> 6, dim = (col & 63) + lane, rows = min(ROWS, a.R - first);
+    const uint16_t* mine = values + lane % COLS;
+    wave_sync();
+    for (int j = 0; j < rows;) {
+        const int b = (first + j) / a.M, m0 = first + j - b * a.M, end = min(j + a.M - m0, rows), L = ldg(a.L + b);
+        const bool live = ldg(a.n_rows + b) > 0 && lane < COLS;
+        bf16_t* to = a.Vc + ((size_t)b * a.nH + head) * kv_cap(a.maxpos) * 64;
+        for (int pos = L + m0; j < end;) {
+            const int n = min(8 - (pos & 7), end - j);   // rows that share the piece
+            uint32_t e[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) e[k] = mine[min(j + k, ROWS - 1) * STRIDE];
+            if (live) {
+                bf16_t* p = to + vc_off(pos, dim);
+                if (n == 8 && pos + 8 <= a.maxpos) {
+                    *(uint4*)p = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        if (k < n && pos + k < a.maxpos) p[k] = (bf16_t)e[k];
+                }
+            }
+            j += n;
+            pos += n;
+        }
+    }
+}
+
+// Which tile a workgroup takes.  Workgroup i runs on XCD i mod 8: every XCD gets an eighth of the tiles, consecutive in
+// strips of `strip` column tiles, so that the rows and columns which its L2 fetches are about the same number.
+struct TileGrid { int gr, gc, strip; };
+
 constexpr int BIG_RT = 4, BIG_CT = 2;   // row tiles of a workgroup, column tiles of a wave
 template <int EPI>
-__global__ __launch_bounds__(256, 3) void k_big(LinArgs a) {
+__global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
     constexpr bool LN = EPI <= LE_LOGITS;
     constexpr int NRT = BIG_RT, NCT = BIG_CT, DEPTH = 2;   // DEPTH: stages in registers
     static_assert(4 % DEPTH == 0, "stage c uses register set c mod DEPTH by c mod 4");
     constexpr int ROWS = NRT * 16, NA = NRT / 2, NR2 = NRT / 2, NC2 = NCT / 2;   // NA: activation tiles a wave fetches per stage
     __shared__ uint4 sA[4][NRT * 2 * 64];
     __shared__ float s_mean[ROWS], s_rstd[ROWS];
-    const int ct0 = blockIdx.x * 4 * NCT, rb = blockIdx.y;
-    if (ct0 >= a.NT) return;   // padding of the XCD-aware numbering
+    int rb, ct0;   // row tile of 64, first column tile
+    {
+        const int n = g.gr * g.gc, xcd = blockIdx.x & 7, lo = (n * xcd) >> 3, i = lo + (int)(blockIdx.x >> 3);
+        if (i >= (n * (xcd + 1)) >> 3) return;
+        const int s = i / (g.gr * g.strip), in = i - s * g.gr * g.strip, w = min(g.strip, g.gc - s * g.strip);
+        rb = in / w;
+        ct0 = (s * g.strip + in % w) * 4 * NCT;
+    }
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int row0 = rb * ROWS, last_rt = (a.R - 1) >> 4;
     const int wt0 = ct0 + wave * NCT;      // this wave's first column tile
@@ -449,6 +549,9 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a) {
     }
     // Everything the epilogue reads arrives before its first store: a wait between the stores would wait for them too
     // (loads and stores share one counter).
+    constexpr int VS = 2 * NCT + 1;   // (QKV) pieces of a row of the wave's values, for store_values
+    uint4* values = &sA[0][0] + wave * ROWS * VS;
+    if constexpr (EPI == LE_QKV) __syncthreads();   // (every wave has its operands)
     const int lr = lane & 31, hi = lane >> 5;   // the lane's row of a 32-row block; its columns of a block: 8 q + 4 hi .. + 3, q = 0 .. 3
     KvRow kv[NR2];
     float mean[NR2], rstd[NR2];
@@ -486,38 +589,339 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a) {
 #pragma unroll
             for (int ri = 0; ri < NR2; ++ri) ARRIVED(kv[ri].pos);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int tile = wt0 + 2 * ci + t;
-            if (tile >= a.NT) break;
+        for (int ri = 0; ri < NR2; ++ri) {
+            const int r = row0 + ri * 32 + lr;
+            float v[2][8];
 #pragma unroll
-            for (int ri = 0; ri < NR2; ++ri) {
-                const int r = row0 + ri * 32 + lr;
-                float v[2][4];
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int g = 0; g < 2; ++g)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int q = 2 * t + g;
-                        float y = acc[ci][ri][4 * q + j];
-                        if (LN) y = rstd[ri] * (y - mean[ri] * cs[q][j]);
-                        v[g][j] = y + bias[q][j];
-                        if (EPI == LE_RESID) v[g][j] += xr[ri][q][j];
-                    }
-                if constexpr (EPI == LE_RESID) {
-                    // statistics of the tile's 16 columns: eight here, eight in the lane 32 further on
-                    const float mu = half_sum(((v[0][0] + v[0][1]) + (v[0][2] + v[0][3])) + ((v[1][0] + v[1][1]) + (v[1][2] + v[1][3]))) * (1.f / 16.f);
-                    float sq = 0.f;
-#pragma unroll
-                    for (int g = 0; g < 2; ++g)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) sq += (v[g][j] - mu) * (v[g][j] - mu);
-                    sq = half_sum(sq);
-                    if (r < a.R && hi == 0) a.stats_out[(size_t)r * (a.N >> 4) + tile] = make_float2(mu, sq);
+                for (int e = 0; e < 8; ++e) {
+                    const int q = 2 * t + (e >> 2), j = e & 3;
+                    float y = acc[ci][ri][8 * t + e];
+                    if (LN) y = rstd[ri] * (y - mean[ri] * cs[q][j]);
+                    v[t][e] = y + bias[q][j];
+                    if (EPI == LE_RESID) v[t][e] += xr[ri][q][j];
                 }
+            if constexpr (EPI == LE_RESID) {
+                // statistics of 32 columns: sixteen here, sixteen in the lane 32 further on
+                float sum = 0.f, sq = 0.f;
 #pragma unroll
-                for (int g = 0; g < 2; ++g) store4<EPI>(a, r, tile * 16 + 8 * g + 4 * hi, r < a.R, v[g], kv[ri]);
+                for (int t = 0; t < 2; ++t) sum += ((v[t][0] + v[t][1]) + (v[t][2] + v[t][3])) + ((v[t][4] + v[t][5]) + (v[t][6] + v[t][7]));
+                const float mu = half_sum(sum) * (1.f / 32.f);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) sq += (v[t][e] - mu) * (v[t][e] - mu);
+                sq = half_sum(sq);
+                if (r < a.R && hi == 0 && wt0 + 2 * ci < a.NT) a.stats_out[(size_t)r * (a.N >> 5) + ((wt0 + 2 * ci) >> 1)] = make_float2(mu, sq);
             }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                if (wt0 + 2 * ci + t < a.NT) store16<EPI>(a, r, (wt0 + 2 * ci + t) * 16, hi, v[t], kv[ri], values + (ri * 32 + lr) * VS + 2 * (2 * ci + t));
         }
+    }
+    if constexpr (EPI == LE_QKV)
+        if (wt0 < a.NT && wt0 * 16 >= 2 * a.d) store_values<ROWS, 16 * NCT>(a, row0, wt0 * 16 - 2 * a.d, (const uint16_t*)values, lane);
+}
+
+// ---------------------------------------------------------------------------
+// Linear map of many rows where its rounds of workgroups are nearly full: one workgroup per 64 RG rows x 64 CG columns and compute
+// unit, eight waves of 64 x 64 outputs each; where the workgroup has fewer than eight such blocks the waves share a block's reduction
+// (KSP waves per block).  Both operands pass through a ring of LDS stages, filled by loads that go straight into LDS (a stored operand
+// tile is the contiguous KiB that such a load writes): up to 144 KiB are in flight per compute unit and cost no registers.  Half the bytes of
+// k_big per product cross from L2.
+// What bounds it (2048 rows, FFN1, 256 x 128 outputs, 24.8 us in a step): launch 2.5 us, the first stage 2.5, products 13 (LDS: 128 KB of
+// operand reads and 48 KB of arrivals per stage at 128 B per clock against 1024 clocks of matrix instructions; and the clock, which
+// falls from 2.4 to 1.6 GHz while every matrix core is busy), epilogue 5 (GELU: 70 clocks per value and SIMD) with nothing beside it.  Measured
+// and not kept: 128 x 64 outputs per wave and four waves, which reads a quarter less from LDS but leaves one wave per SIMD (27.8 instead of 24.2 us);
+// a stage's loads in one piece behind the barrier (24.9); the row statistics asked for in the middle of the reduction (+1.5); a ninth wave
+// that reads the weights' lines ahead of the ring (K = 4096: products 21.5 -> 20.2 us and a clock 0.3 GHz lower, 29.1 -> 30.6).
+// ---------------------------------------------------------------------------
+// One KiB from memory into LDS, 16 bytes per lane; counts as one load of the wave.  No register receives it and the
+// compiler does not know of it: landed() is what says that it has arrived.
+__device__ __forceinline__ void fill_lds(uint4* lds, const char* src, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"((uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)lds), "v"(lane * 16), "s"(src) : "memory");
+#else
+    lds[lane] = ldg4(src + lane * 16);
+#endif
+}
+// All but the wave's N youngest loads have arrived and its LDS reads are done; then every wave of the workgroup is here.
+template <int N>
+__device__ __forceinline__ void landed() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+#else
+    __syncthreads();
+#endif
+}
+
+template <int RG, int CG> struct TileShape {
+    static constexpr int NB = RG * CG, KSP = 8 / NB;              // blocks of 64 x 64, waves per block
+    static constexpr int KB = KSP >= 4 ? 4 : 2;                   // k-steps of 32 per stage
+    static constexpr int TILES = 4 * (RG + CG), KIB = TILES * KB; // operand tiles, KiB of a stage
+    static constexpr int NS = 144 / KIB;                          // stages in the ring
+    static constexpr int LPW = KIB / 8, SPW = 2 * KB / KSP;       // loads and half k-steps of a wave per stage
+};
+
+template <int RG, int CG, int EPI>
+__global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
+    using S = TileShape<RG, CG>;
+    constexpr bool LN = EPI <= LE_LOGITS;
+    constexpr int NB = S::NB, KSP = S::KSP, KB = S::KB, NS = S::NS, LPW = S::LPW, SPW = S::SPW, ROWS = 64 * RG;
+    static_assert(SPW % 2 == 0, "a stage starts with the first of the two operand sets");
+    __shared__ uint4 ring[NS * S::KIB * 64];
+    __shared__ float s_mean[ROWS], s_rstd[ROWS];
+    __shared__ float4 s_bias[16 * CG], s_cs[16 * CG];
+    int row0, ct0;   // first row and column tile
+    {
+        const int n = t.gr * t.gc, xcd = blockIdx.x & 7, lo = (n * xcd) >> 3, i = lo + (int)(blockIdx.x >> 3);
+        if (i >= (n * (xcd + 1)) >> 3) return;
+        const int s = i / (t.gr * t.strip), in = i - s * t.gr * t.strip, w = min(t.strip, t.gc - s * t.strip);
+        row0 = in / w * ROWS;
+        ct0 = (s * t.strip + in % w) * 4 * CG;
+    }
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int rg = wave / CG % RG, cg = wave % CG, kq = wave / NB;   // the wave's block and its share of the reduction
+    const int nst = (a.nks + KB - 1) / KB;
+    // row statistics: TPR threads of a row read two groups at a time, NV such pieces asked for here
+    constexpr int TPR = 512 / ROWS, NV = TPR < 8 ? 8 : 4;
+    const int groups = (a.nks * 32) >> a.sg;
+    const float2* sp = nullptr;
+    float c0 = 0.f;
+    uint4 sv[NV];
+    if constexpr (LN) {
+        sp = a.stats + (size_t)min(row0 + tid / TPR, a.R - 1) * groups;
+        c0 = ldg(&sp->x);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) sv[j] = ldg4(sp + (2 * (tid % TPR + j * TPR) < groups ? 2 * (tid % TPR + j * TPR) : 0));
+    }
+    float bias_in = 0.f, cs_in = 0.f;   // one column's per thread of the first waves
+    if (tid < 64 * CG) {
+        const int n = min(ct0 * 16 + tid, a.NT * 16 - 1);
+        bias_in = ldg(a.bias + n);
+        if constexpr (LN) cs_in = ldg(a.colsum + n);
+    }
+    SCHED_FENCE();
+    // Tiles beyond the map's last row or column re-read a valid one and only reach accumulators that are never stored; k-steps
+    // beyond the last re-read the last and are not multiplied.
+    const char* base[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        const int T = (wave + 8 * i) / KB;
+        base[i] = T < 4 * RG ? (const char*)a.X + (size_t)min((row0 >> 4) + T, (a.R - 1) >> 4) * a.nks * 1024
+                             : (const char*)a.W + (size_t)min(ct0 + T - 4 * RG, a.NT - 1) * a.nks * 1024;
+    }
+    auto fetch = [&](int s, int buf, int i0, int i1) {   // loads i0 .. i1 - 1 of stage s
+#pragma unroll
+        for (int i = 0; i < LPW; ++i)
+            if (i >= i0 && i < i1) {
+                const int j = wave + 8 * i;
+                fill_lds(ring + (buf * S::KIB + j) * 64, base[i] + (uint32_t)min(s * KB + j % KB, a.nks - 1) * 1024u, lane);
+            }
+    };
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+        if (s < nst) fetch(s, s, 0, LPW);
+    f32x16_t acc[2][2];   // [block of 32 columns][block of 32 rows]
+#pragma unroll
+    for (int i = 0; i < 64; ++i) acc[i >> 5][(i >> 4) & 1][i & 15] = 0.f;
+    // an operand: two tiles' rows, one half of their k-step
+    const int second = (lane >> 4) & 1, piece = (lane & 15) + 16 * (lane >> 5);
+    const uint4* xl = ring + (rg * 4 + second) * KB * 64 + piece;
+    const uint4* wl = ring + ((RG + cg) * 4 + second) * KB * 64 + piece;
+    uint4 x[2][2], w[2][2];
+    auto read = [&](int buf, int sl, uint4 (&x)[2], uint4 (&w)[2]) {
+        const int q = kq * SPW + sl, at = buf * S::KIB * 64 + (q >> 1) * 64 + (q & 1) * 32;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { x[i] = xl[at + 2 * i * KB * 64]; w[i] = wl[at + 2 * i * KB * 64]; }
+    };
+    auto mul = [&](const uint4 (&x)[2], const uint4 (&w)[2]) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) acc[c][r] = mfma_32x32(w[c], x[r], acc[c][r]);   // weights first: a lane then holds groups of four consecutive columns of one row
+    };
+    // Stage s is multiplied while the stages behind it arrive; behind it, one slice after the other, go the loads of stage
+    // s + NS - 1 into the place that stage s - 1 left.
+    int buf = 0;
+    if (nst >= NS - 1) landed<(NS - 2) * LPW>();
+    else landed<0>();
+    read(0, 0, x[0], w[0]);
+    auto stage = [&](int s, auto final) {
+        const int next = buf + 1 == NS ? 0 : buf + 1, left = buf ? buf - 1 : NS - 1;
+#pragma unroll
+        for (int sl = 0; sl < SPW; ++sl) {
+            if (sl + 1 < SPW) read(buf, sl + 1, x[(sl + 1) & 1], w[(sl + 1) & 1]);
+            if constexpr (!decltype(final)::value) {
+                if (sl + 1 < SPW) {
+                    if (s + NS - 1 < nst) fetch(s + NS - 1, left, LPW * sl / (SPW - 1), LPW * (sl + 1) / (SPW - 1));
+                } else {
+                    if (s + NS <= nst) landed<(NS - 2) * LPW>();      // stages s + 2 .. s + NS - 1 may be on their way
+                    else if (NS > 3 && s + NS - 1 == nst) landed<(NS > 3 ? NS - 3 : 0) * LPW>();
+                    else landed<0>();
+                    read(next, 0, x[0], w[0]);
+                }
+            }
+            SCHED_FENCE();
+            if (KB == 2 || s * KB + (kq * SPW + sl) / 2 < a.nks) mul(x[sl & 1], w[sl & 1]);
+            SCHED_FENCE();
+        }
+        buf = next;
+    };
+    for (int s = 0; s + 1 < nst; ++s) stage(s, std::false_type{});
+    // What the epilogue adds is asked for ahead of the last stage's products.
+    constexpr int RB = KSP == 1 ? 2 : 1, TB = KSP <= 2 ? 4 : 8 / KSP;
+    const int lr = lane & 31, hi = lane >> 5, rb0 = KSP == 1 ? 0 : kq * 2 / KSP, tb0 = KSP <= 2 ? 0 : kq * TB % 4, tile0 = ct0 + 4 * cg + tb0;
+    int r[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) r[i] = row0 + (rg * 2 + rb0 + i) * 32 + lr;
+    uint4 xr[RB][TB][2];
+    if constexpr (EPI == LE_RESID)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int tt = 0; tt < TB; ++tt)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) xr[i][tt][h] = ldg4(a.outf + (size_t)min(r[i], a.R - 1) * a.N + min(tile0 + tt, a.NT - 1) * 16 + 8 * h + 4 * hi);
+    KvRow kv[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        kv[i] = KvRow{0, -1};
+        if (EPI == LE_QKV && (tile0 + TB) * 16 > a.d) kv[i] = kv_row(a, r[i]);
+    }
+    SCHED_FENCE();
+    stage(nst - 1, std::true_type{});
+    if constexpr (LN) {
+        float s1 = 0.f, s2 = 0.f, s3 = 0.f;   // sums of the group means' distances from c0, of the groups' squared deviations, of the squared distances
+        auto add = [&](const uint4& g) {
+            const float d0 = __uint_as_float(g.x) - c0, d1 = __uint_as_float(g.z) - c0;
+            s1 += d0 + d1;
+            s2 += __uint_as_float(g.y) + __uint_as_float(g.w);
+            s3 += d0 * d0 + d1 * d1;
+        };
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            ARRIVED(sv[j].x);
+            if (2 * (tid % TPR + j * TPR) < groups) add(sv[j]);
+        }
+        for (int g = 2 * (tid % TPR + NV * TPR); g < groups; g += 2 * TPR) add(ldg4(sp + g));
+        auto sum = [](float v) {
+            if (TPR >= 2) v += __int_as_float(dpp_perm<0xB1>(__float_as_int(v)));
+            if (TPR >= 4) v += __int_as_float(dpp_perm<0x4E>(__float_as_int(v)));
+            if (TPR >= 8) v += __int_as_float(dpp_perm<0x141>(__float_as_int(v)));
+            return v;
+        };
+        s1 = sum(s1);
+        s2 = sum(s2);
+        s3 = sum(s3);
+        if (tid % TPR == 0) {
+            const float m2 = s2 + (float)(1 << a.sg) * fmaxf(s3 - s1 * s1 / groups, 0.f);
+            s_mean[tid / TPR] = c0 + s1 / groups;
+            s_rstd[tid / TPR] = rsqrtf(m2 / (a.nks * 32) + LN_EPS);
+        }
+    }
+    // The block's outputs: piece u of 32 rows x 16 columns, u = 4 (row block) + column tile; a lane holds eight values of one
+    // row, columns 4 hi .. + 3 of each eight.  Waves that share a block add their sums through LDS and take 8 / KSP pieces each.
+    float y[RB][TB][8];
+    ARRIVED(bias_in);
+    if (tid < 64 * CG) {
+        ((float*)s_bias)[tid] = bias_in;
+        if constexpr (LN) ((float*)s_cs)[tid] = cs_in;
+    }
+    if constexpr (KSP == 1) {
+#pragma unroll
+        for (int i = 0; i < 64; ++i) y[i >> 5][(i >> 3) & 3][i & 7] = acc[(i >> 4) & 1][i >> 5][8 * ((i >> 3) & 1) + (i & 7)];
+        __syncthreads();
+    } else {
+        float4* part = (float4*)ring;   // [wave][piece][half][lane]; 
+        __syncthreads();                // (the last stage has been read)
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x16_t& v = acc[(u >> 1) & 1][u >> 2];
+                const int e = 8 * (u & 1) + 4 * h;
+                part[((wave * 8 + u) * 2 + h) * 64 + lane] = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int tt = 0; tt < TB; ++tt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int k = 0; k < KSP; ++k) {
+                    const float4 p = part[(((k * NB + rg * CG + cg) * 8 + rb0 * 4 + tb0 + tt) * 2 + h) * 64 + lane];
+                    v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+                }
+                y[0][tt][4 * h] = v.x; y[0][tt][4 * h + 1] = v.y; y[0][tt][4 * h + 2] = v.z; y[0][tt][4 * h + 3] = v.w;
+            }
+    }
+    constexpr int VS = 2 * TB + 1;   // (QKV) pieces of a row of the wave's values, for store_values
+    uint4* values = ring + wave * 32 * RB * VS;
+    if constexpr (EPI == LE_QKV && KSP > 1) __syncthreads();   // (every wave has its sums)
+    // Everything the epilogue reads has arrived before its first store: a wait between the stores would wait for them too
+    // (loads and stores share one counter).
+    if (tile0 >= a.NT) return;
+    if constexpr (EPI == LE_RESID)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int tt = 0; tt < TB; ++tt) { ARRIVED(xr[i][tt][0].x); ARRIVED(xr[i][tt][1].x); }
+    if constexpr (EPI == LE_QKV)
+#pragma unroll
+        for (int i = 0; i < RB; ++i) ARRIVED(kv[i].pos);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        const int rl = (rg * 2 + rb0 + i) * 32 + lr;
+        const float mean = LN ? s_mean[rl] : 0.f, rstd = LN ? s_rstd[rl] : 1.f;
+#pragma unroll
+        for (int tt = 0; tt < TB; ++tt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int at = (4 * cg + tb0 + tt) * 4 + 2 * h + hi;
+                const float4 b4 = s_bias[at], c4 = LN ? s_cs[at] : make_float4(0.f, 0.f, 0.f, 0.f);
+                const float b[4] = {b4.x, b4.y, b4.z, b4.w}, c[4] = {c4.x, c4.y, c4.z, c4.w};
+                const uint4 x4 = EPI == LE_RESID ? xr[i][tt][h] : make_uint4(0, 0, 0, 0);
+                const float x[4] = {__uint_as_float(x4.x), __uint_as_float(x4.y), __uint_as_float(x4.z), __uint_as_float(x4.w)};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float v = y[i][tt][4 * h + e];
+                    if constexpr (LN) v = rstd * (v - mean * c[e]);
+                    v += b[e];
+                    if constexpr (EPI == LE_RESID) v += x[e];
+                    y[i][tt][4 * h + e] = v;
+                }
+            }
+        if constexpr (EPI == LE_RESID) {
+            // statistics of the wave's 16 TB columns (a.sg_out) or of each 16: eight values here, eight in the lane 32 further on
+            auto stats = [&](int t0, int nt, int at) {
+                float mu = 0.f, sq = 0.f;
+#pragma unroll
+                for (int tt = 0; tt < TB; ++tt)
+                    if (tt >= t0 && tt < t0 + nt)
+                        mu += ((y[i][tt][0] + y[i][tt][1]) + (y[i][tt][2] + y[i][tt][3])) + ((y[i][tt][4] + y[i][tt][5]) + (y[i][tt][6] + y[i][tt][7]));
+                mu = half_sum(mu) / (16 * nt);
+#pragma unroll
+                for (int tt = 0; tt < TB; ++tt)
+                    if (tt >= t0 && tt < t0 + nt)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) sq += (y[i][tt][e] - mu) * (y[i][tt][e] - mu);
+                sq = half_sum(sq);
+                if (r[i] < a.R && hi == 0) a.stats_out[(size_t)r[i] * (a.N >> a.sg_out) + at] = make_float2(mu, sq);
+            };
+            if (a.sg_out > 4) stats(0, TB, (tile0 * 16) >> a.sg_out);
+            else
+#pragma unroll
+                for (int tt = 0; tt < TB; ++tt) stats(tt, 1, tile0 + tt);
+        }
+#pragma unroll
+        for (int tt = 0; tt < TB; ++tt)
+            if (tile0 + tt < a.NT) store16<EPI>(a, r[i], (tile0 + tt) * 16, hi, y[i][tt], kv[i], values + (i * 32 + lr) * VS + 2 * tt);
+    }
+    if constexpr (EPI == LE_QKV) {
+        if (tile0 * 16 >= 2 * a.d) store_values<32 * RB, 16 * TB>(a, row0 + (rg * 2 + rb0) * 32, tile0 * 16 - 2 * a.d, (const uint16_t*)values, lane);
     }
 }
 
@@ -789,20 +1193,17 @@ __global__ void k_clock(DevState s, int ph) { s.tprof[ph * 8] = wall_clock64(); 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// Tile shape of a map.  The rule counts what a compute unit has to pull in through L2: a workgroup reads its rows and its
-// columns of K values, and the 256 compute units get cdiv(workgroups, 256) of them each.  (Not counted, and what bounds
-// the maps of many rows and long reductions: an XCD has an eighth of the columns and all rows, so that the activations cross
-// into the L2s eight times.  FFN2 of 2048 rows, K = 4096: 160 MB fetched in 33.4 us = 4.8 TB/s, what a large copy reaches.)
+// Tile shape of a map in k_lin.  The rule counts what a compute unit has to pull in through L2: a workgroup reads its rows and
+// its columns of K values, and the 256 compute units get cdiv(workgroups, 256) of them each.
 struct LinShape { int rt, ct; };
+static int lin_rounds(int RT, int NT, const LinShape& s) { return cdiv(cdiv(RT, s.rt) * cdiv(NT, s.ct), 256); }
 static LinShape lin_shape(int R, int NT) {
     static const LinShape shapes[] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 4}, {3, 4}, {4, 2}, {4, 4}};
     const int RT = cdiv(R, 16);
+    auto cost = [&](const LinShape& s) { return lin_rounds(RT, NT, s) * (s.rt + s.ct); };
     LinShape best = shapes[0];
-    long cost = -1;
-    for (const LinShape& s : shapes) {
-        const long c = (long)cdiv(cdiv(RT, s.rt) * cdiv(NT, s.ct), 256) * (s.rt + s.ct);
-        if (cost < 0 || c < cost) { cost = c; best = s; }
-    }
+    for (const LinShape& s : shapes)
+        if (cost(s) < cost(best)) best = s;
     return best;
 }
 
@@ -810,22 +1211,52 @@ template <int RT, int CT, int CH, int EPI>
 static void lin_launch(const LinArgs& a, hipStream_t st, int nz = 1) {
     launch((k_lin<RT, CT, CH, EPI>), dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(256), 0, st, a);
 }
-template <int EPI>
-static void big_launch(const LinArgs& a, hipStream_t st) {
-    launch(k_big<EPI>, dim3(pad8(cdiv(a.NT, 4 * BIG_CT)), cdiv(a.R, BIG_RT * 16)), dim3(256), 0, st, a);
+// The tiles of `rows` rows x 16 `ct` columns; an XCD's eighth of them: about as many columns as rows.
+static TileGrid tile_grid(const LinArgs& a, int rows, int ct) {
+    TileGrid g{cdiv(a.R, rows), cdiv(a.NT, ct), 1};
+    while (g.strip < g.gc && (long)g.strip * g.strip * ct * 16 * 8 < (long)g.gr * g.gc * rows) ++g.strip;
+    return g;
 }
-// k_big's 64 x 128 tiles from one tile per eight K values on (129 tiles at K = 1024): fewer leave compute units idle for
-// a whole reduction, where k_lin's smaller tiles split it over four waves.  Measured, K = 1024: 4096 columns, 320 rows
-// (160 tiles) 10.8 us against 12.2 in k_lin, 512 rows 11.0 against 14.6; 1024 columns, 1024 rows (128 tiles) 8.9 against
-// 7.8, 2048 rows 12.5 against 14.6.  K = 4096, 1024 columns: 1024 rows 26.8 against 17.0, 2048 rows 32 against 32, 4480
-// rows 67 against 72.  Whole steps of six layers, all maps by the rule against all in k_lin: d = 512, 1024 rows 283 against
-// 316, 2048 rows 430 against 483, 8192 rows 1310 against 1667; d = 256, 2048 rows 314 against 336, 8192 rows 776 against 962.
-// Below that the line lies too low for short reductions: d = 512, 512 rows 248 against 228; d = 256, 512 rows 198 against
-// 170, 1024 rows 224 against 215; d = 128, 2048 rows 251 against 226.
 template <int EPI>
-static void lin(const LinArgs& a, int big_min, hipStream_t st) {
-    const long tiles = (long)cdiv(a.R, 16 * BIG_RT) * cdiv(a.NT, 4 * BIG_CT);
-    if (big_min > 0 ? tiles >= big_min : tiles > 4 * a.nks) { big_launch<EPI>(a, st); return; }
+static void big_launch(LinArgs& a, hipStream_t st) {
+    const TileGrid g = tile_grid(a, BIG_RT * 16, 4 * BIG_CT);
+    a.sg_out = 5;
+    launch(k_big<EPI>, dim3(8 * cdiv(g.gr * g.gc, 8)), dim3(256), 0, st, a, g);
+}
+template <int RG, int CG, int EPI>
+static void tile_launch(LinArgs& a, hipStream_t st) {
+    const TileGrid g = tile_grid(a, 64 * RG, 4 * CG);
+    a.sg_out = TileShape<RG, CG>::KSP > 2 ? 5 : a.N % 128 ? 4 : 6;   // (a wave's columns as one entry where that leaves a row an even number)
+    launch((k_tile<RG, CG, EPI>), dim3(8 * cdiv(g.gr * g.gc, 8)), dim3(512), 0, st, a, g);
+}
+// Which kernel: the one that is estimated to take least.  n: workgroups of the fullest of the 256 compute units; us without the launch,
+// from chains of launches whose weights come from HBM (K = 1024 | 4096, launch included):
+//   k_lin 64 x 64            n = 1   8.4 | 19    n = 2  15.5 | 33
+//   k_big 64 x 128           n = 1  12.5 | 33    n = 2  17.8 | 42    n = 3  25.9 | 62    n = 4  30.5    n = 7  46.6    n = 9  57.2
+//   k_tile 128 x 64          n = 1  12.9 | 29    n = 2  22
+//   k_tile 256 x 128         n = 1  24.4 | 52    n = 2  48
+// What that decides at d = 1024 (us, the choice first): 304 rows FFN1 k_tile 9.9, k_big 11.7, k_lin 12.6; 1024 rows QKV k_big 16.7, k_lin 22, FFN1 k_big 18.1,
+// k_lin 26, out-projection k_lin 8.4, k_big 11.6, FFN2 k_lin 19, k_tile 27; 2048 rows out-projection k_tile 12.9, k_big 13.5, k_lin 15.6, FFN1 k_tile 26.9,
+// k_big 30.5, FFN2 k_tile 29.1, k_lin 33, k_big 34; 3200 rows FFN2 k_big 42, k_lin 58, k_tile 47; 4352 rows FFN1 k_big 57, k_tile 66.
+enum { MAP_LIN = 0, MAP_BIG, MAP_TILE_256, MAP_TILE_128 };
+static int map_kernel(int R, int NT, int nks) {
+    const LinShape s = lin_shape(R, NT);
+    auto n = [&](int rows, int ct) { return cdiv(cdiv(R, rows) * cdiv(NT, ct), 256); };
+    const int nb = n(64, 8);
+    const float us[4] = {lin_rounds(cdiv(R, 16), NT, s) * (2.4f + 0.0135f * nks * (s.rt + s.ct)), 2.5f + 2.3f * nb + nks * std::max(0.21f, 0.115f * nb),
+                         n(256, 8) * (12.f + 0.31f * nks), n(128, 4) * (5.f + 0.17f * nks)};
+    return (int)(std::min_element(us, us + 4) - us);
+}
+// big_min (tests): k_big from that many of its tiles on; -1, -2: k_tile for every map.
+template <int EPI>
+static void lin(LinArgs& a, int big_min, hipStream_t st) {
+    a.sg_out = 4;
+    const int kernel = big_min < 0 ? (big_min == -1 ? MAP_TILE_256 : MAP_TILE_128)
+                       : big_min > 0 ? ((long)cdiv(a.R, 16 * BIG_RT) * cdiv(a.NT, 4 * BIG_CT) >= big_min ? MAP_BIG : MAP_LIN)
+                                     : map_kernel(a.R, a.NT, a.nks);
+    if (kernel == MAP_BIG) { big_launch<EPI>(a, st); return; }
+    if (kernel == MAP_TILE_256) { tile_launch<4, 2, EPI>(a, st); return; }
+    if (kernel == MAP_TILE_128) { tile_launch<2, 1, EPI>(a, st); return; }
     const LinShape s = lin_shape(a.R, a.NT);
     if constexpr (EPI == LE_LOGITS) {   // (with a multiple of four column tiles 1 x 2 and 2 x 4 never take more workgroups than these)
         if (s.rt == 2 && s.ct == 1) { lin_launch<2, 1, 8, EPI>(a, st); return; }
@@ -871,7 +1302,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
     launch(k_embed_rows, dim3(R), dim3(256), 0, st, D, s, prefill_mode, table);
     LinArgs base{};
     base.R = R; base.L = s.L; base.n_rows = s.n_rows; base.M = D.M; base.nH = D.nH; base.maxpos = D.maxpos; base.d = d;
-    base.stats = (const float2*)s.stats;
+    base.stats = (const float2*)s.stats; base.sg = 4;   // (k_embed_rows)
     for (int l = 0; l < D.Ly; ++l) {
         const LayerW& w = layers[l];
         bf16_t *Kc = (bf16_t*)s.Kc + l * kv_layer, *Vc = (bf16_t*)s.Vc + l * kv_layer;
@@ -888,6 +1319,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         o.out = s.xb; o.outf = s.x; o.stats_out = (float2*)s.stats;
         clock_point(s, 3 + 5 * l, st);
         lin<LE_RESID>(o, big_min, st);
+        base.sg = o.sg_out;
         LinArgs f = base;
         f.X = s.xb; f.W = (const uint4*)w.W1; f.bias = w.t_w1; f.colsum = w.cs_w1; f.nks = d >> 5; f.N = D.F; f.NT = D.F >> 4;
         f.out = (bf16_t*)s.hid;
@@ -898,6 +1330,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         g.out = s.xb; g.outf = s.x; g.stats_out = (float2*)s.stats;
         clock_point(s, 5 + 5 * l, st);
         lin<LE_RESID>(g, big_min, st);
+        base.sg = g.sg_out;
     }
     if (head) {
         LinArgs a = base;

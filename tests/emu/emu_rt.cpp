@@ -1,4 +1,4 @@
-// Runtime of the CPU emulation: a pool of 256 OS threads plays the threads of one block;
+// Runtime of the CPU emulation: a pool of 512 OS threads plays the threads of one block;
 // blocks of a launch run one after another.
 #include <hip/hip_runtime.h>
 
@@ -21,7 +21,7 @@ alignas(64) static char g_lds[160 * 1024];
 char* emu_dyn_lds = g_lds;
 extern "C" { int emu_last_error = 0, emu_fail_launch = 0, emu_host_blocks = 0; }
 
-constexpr int MAXT = 256;
+constexpr int MAXT = 512;
 static thread_local int t_id = -1;   // index in the pool, -1: host thread
 static const char* g_where[MAXT];
 static int g_wline[MAXT];
@@ -72,7 +72,7 @@ struct Barrier {
 };
 
 static Barrier &b_start = *new Barrier, &b_done = *new Barrier, &b_blk = *new Barrier, &b_sync = *new Barrier;
-static Barrier* const b_wave = new Barrier[4];   // never destroyed: idle workers sleep on them at exit
+static Barrier* const b_wave = new Barrier[MAXT / 64];   // never destroyed: idle workers sleep on them at exit
 static std::function<void()> g_body;
 static int g_nthreads = 0;
 static std::vector<std::thread>& g_pool = *new std::vector<std::thread>;
@@ -131,7 +131,7 @@ void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t
     g_nthreads = nt;
     b_blk.init(nt);
     b_sync.init(nt);
-    for (int w = 0; w < 4; ++w) b_wave[w].init(64);
+    for (int w = 0; w < MAXT / 64; ++w) b_wave[w].init(64);
     b_start.wait("start");
     b_done.wait("done");
 }

@@ -52,3 +52,16 @@ def test_tile_shapes_of_the_gpu_tests(emu_lib):
     assert seen == {(kind, s) for kind in ("qkv", "residual", "ffn1", "logits") for s in every} | {("logits", "2x1"), ("logits", "4x2")}
     # maps whose columns are a multiple of 64 never pick 2x1 or 4x2, which are built for the vocabulary map alone
     assert {pick(16 * rt, nt) for rt in range(1, 129) for nt in range(4, 1025, 4)} <= {16 * int(s[0]) + int(s[2]) for s in every}
+
+
+def test_kernels_of_the_mixed_gpu_tests(emu_lib):
+    """The kernels that the GPU test of mixed maps names are those that the rule picks."""
+    import ctypes as C
+    sys.path.insert(0, HERE)
+    from test_gpu_layer_kernels import MIXED
+    pick = C.CDLL(emu_lib).emu_map_kernel
+    names = ("lin", "big", "tile256", "tile128")
+    for d, ffn, nodes, batch, kernels in MIXED:
+        rows = nodes * batch
+        got = [pick(rows, n // 16, k // 32) for n, k in ((3 * d, d), (d, d), (ffn, d), (d, ffn))]
+        assert " ".join(names[g] for g in got) == kernels, (d, ffn, rows)

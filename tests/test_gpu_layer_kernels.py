@@ -44,6 +44,26 @@ def test_many_row_tiles_at_their_edges(monkeypatch, d, nodes, batch, V):
     _run(_cfg("bf16", d, V), batch, nodes, (9, 9), (2, 1), 300 + d, 20, 70)
 
 
+# Both shapes of k_tile (256 x 128 and 128 x 64 outputs) for every map: fewer stages than the ring has and more, an odd number of them,
+# a last stage that is half empty (K = 64, 192, 320), rows and columns that end inside a tile or leave whole blocks of it
+# empty, row statistics of 16, 32 and 64 columns, values whose rows share a piece of the cache with those of no, one or two passes
+@pytest.mark.parametrize("shape", [1, 2])
+@pytest.mark.parametrize("d,nodes,batch,V", [(64, 65, 1, 127), (192, 43, 3, 300), (320, 126, 2, 257), (512, 64, 5, 128), (128, 5, 61, 90)])
+def test_many_row_tile_shapes(monkeypatch, shape, d, nodes, batch, V):
+    monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", str(-shape))
+    _run(_cfg("bf16", d, V), batch, nodes, (4, 3) if nodes == 5 else (11, 11), (2, 1), 800 + d, 20, 70)
+
+
+# By the rule one model mixes the kernels, and with them statistics of 16 and of 32 columns (tests/test_emulated_kernel.py holds the
+# rule to this: QKV, out-projection, FFN1, FFN2)
+MIXED = [(256, 4096, 100, 4, "lin lin tile128 lin"), (256, 4096, 127, 5, "lin lin big lin"), (128, 16384, 127, 4, "lin lin tile256 lin")]
+
+
+@pytest.mark.parametrize("d,ffn,nodes,batch,kernels", MIXED)
+def test_kernels_mixed_by_the_rule(d, ffn, nodes, batch, kernels):
+    _run(_cfg("bf16", d, 90, layers=1, ffn=ffn, maxpos=192), batch, nodes, (11, 11), (2, 1), 830 + batch, 4, 40)
+
+
 # rows below, at and above whole tiles; at this width all maps run in tiles of one or two by one or two
 @pytest.mark.parametrize("rows", [1, 16, 17, 33, 64, 97, 128, 193])
 def test_small_tile_shapes(rows):
