@@ -365,7 +365,7 @@ static Dims make_dims(const vadusa_ctx* c, int B, int M) {
     Dims D;
     D.Ly = c->cfg.n_layers; D.d = c->cfg.d_model; D.nH = c->cfg.n_heads; D.F = c->cfg.d_ffn;
     D.V1 = c->cfg.speech_vocab + 1; D.Hh = c->cfg.n_draft_heads; D.maxpos = c->cfg.max_positions;
-    D.Bmax = c->cfg.max_batch; D.Mmax = c->cfg.max_tree_nodes; D.B = B; D.M = M;
+    D.Bmax = c->cfg.max_batch; D.Mmax = c->cfg.max_tree_nodes; D.B = B; D.M = M; D.keys = D.maxpos;
     return D;
 }
 
@@ -615,7 +615,7 @@ extern "C" int vadusa_prefill(vadusa_ctx* c, int32_t batch, const int32_t* text_
     HIP_TRY(c, hipMemsetAsync(s.finished, 0, B * 4, c->stream));
     HIP_TRY(c, hipMemsetAsync(s.n_out, 0, B * 4, c->stream));
     HIP_TRY(c, hipMemsetAsync(s.path, 0, B * (VADUSA_MAX_DRAFT_HEADS + 2) * 4, c->stream));
-    const Dims D = make_dims(c, batch, Mc);
+    Dims D = make_dims(c, batch, Mc);
     // chunks are right-aligned so that every sequence ends in the last chunk
     std::vector<std::vector<int32_t>> keep;   // host buffers stay alive until the final sync
     for (int ch = 0; ch < max_chunks; ++ch) {
@@ -638,6 +638,7 @@ extern "C" int vadusa_prefill(vadusa_ctx* c, int32_t batch, const int32_t* text_
         HIP_TRY(c, hipMemcpyAsync(s.n_rows, rows.data(), rows.size() * 4, hipMemcpyHostToDevice, c->stream));
         const bool last = ch == max_chunks - 1;
         // the chunk is a causal "tree"; the last one also runs the vocabulary map, the continuation and the draft heads
+        D.keys = std::min((ch + 1) * Mc, D.maxpos);
         forward(c, D, 1, 1, last);
         if (!last) launch_advance(s, batch, c->stream);
     }
@@ -736,7 +737,8 @@ static int verify_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau,
                                   hipMemcpyHostToDevice, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));   // the caller's buffer is not kept
     }
-    const Dims D = make_dims(c, B, M);
+    Dims D = make_dims(c, B, M);
+    D.keys = std::min(*std::max_element(c->L_ub.begin(), c->L_ub.begin() + B) + M, D.maxpos);
     c->M = M;
     c->sampled = sp != nullptr;
     if (sp) {

@@ -181,6 +181,7 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 struct Dims {
     int Ly, d, nH, F, V1, Hh, maxpos, Bmax, Mmax;   // model / capacity
     int B, M;                                        // current batch, rows per sequence
+    int keys;                                        // no sequence attends to more keys than this (for the choice of kernels)
 };
 
 // Pointers to one layer's parameters on the device.

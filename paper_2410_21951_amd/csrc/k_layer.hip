@@ -932,8 +932,14 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 // private online softmax (S^T = K Q^T, O^T += V^T P^T on MFMA) and merge through LDS.  The cache keeps K and V^T in blocks
 // of 32 keys, each already in the layout of the MFMA operands (kc_off / vc_off in common.h).
 // QT = 2 where there are workgroups enough for every compute unit: a key block is then fetched once for 32 queries.
-// (64 sequences of 32 nodes, ~330 keys: 25 us a layer instead of 34; with 64 workgroups instead of 128 for one sequence
-// it takes 6.1 instead of 4.5.)  Measured and not kept: the key blocks split over up to four workgroups with the last
+// (64 sequences of 32 nodes, ~330 keys: 24 us a layer instead of 34; with 64 workgroups instead of 128 for one sequence
+// it takes 6.1 instead of 4.5.)
+// NW waves take the key blocks of a workgroup in turn.  What bounds it with few workgroups: a wave's chain of blocks (load, scores,
+// maximum, exponentials), then the 50 bytes per clock that a compute unit pulls through L2 (2000 keys: 512 KB, 4.3 us), so many waves where
+// there are blocks for them and workgroups do not fill the chip (us, four waves -> NW; 64 queries 360 keys 6.0 -> 5.6 with 8;
+// 128 queries, 2000 keys 14.0 -> 12.4 with 16, of 1500 12.0 -> 10.8; 1024 causal queries of 1500 keys 22.0 -> 19 with 8); with a block or two per
+// wave the merge costs more than it gives (270 keys, QT = 2: 11.7 -> 13.4 with 8).
+// Measured and not kept: the key blocks split over up to four workgroups with the last
 // to arrive merging (2000 keys, 64 queries: 8.6 instead of 9.7, 1000 keys: 8.2 instead of 6.9); two blocks per step
 // (2000 keys: 9.3, 320 keys: 5.2 instead of 4.5).
 // ---------------------------------------------------------------------------
@@ -945,11 +951,17 @@ struct AttnArgs {
     const uint32_t* mask;
     int B, M, nH, d, maxpos;
 };
-template <bool CAUSAL, int QT>
-__global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
+template <bool CAUSAL, int QT, int NW>
+__global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(AttnArgs a) {
     constexpr int SO = 17;   // floats per row of the merge buffer: the merge reads a dimension's 16 queries' worth 64 rows apart
-    __shared__ float sm_o[QT][4 * 64 * SO], sm_m[QT][64], sm_l[QT][64];
-    const int bh = blockIdx.x, qt0 = blockIdx.y * QT;
+    __shared__ float sm_o[QT][NW * 64 * SO], sm_m[QT][NW * 16], sm_l[QT][NW * 16];
+    const int bh = blockIdx.x;
+    int qt0 = blockIdx.y * QT;
+    if constexpr (CAUSAL) {
+        // Later queries see more keys.  Workgroups i and i + 256 share a compute unit: heavy ones first, in rounds of 256 that run to and fro.
+        const int per = max(1, 256 / (int)gridDim.x), round = blockIdx.y / per, at = blockIdx.y - round * per, left = min(per, (int)gridDim.y - round * per);
+        qt0 = ((int)gridDim.y - 1 - (round * per + (round & 1 ? left - 1 - at : at))) * QT;
+    }
     if (bh >= a.B * a.nH) return;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, gq = lane >> 4, c = lane & 15;
     const int b = bh / a.nH, h = bh - b * a.nH;
@@ -965,12 +977,20 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
         mw[t] = make_uint4(0, 0, 0, 0);
         if constexpr (!CAUSAL) mw[t] = ldg4(a.mask + (size_t)node[t] * MASK_WORDS);
     }
-    const int q_out = tid >> 4, d_out = (tid & 15) * 4;   // the merge's outputs of this thread, per tile
+    constexpr int DT = NW > 4 ? 2 : 4;   // the merge's outputs of a thread, per tile: dimensions d_out .. of query q_out
+    const int q_out = tid / (64 / DT), d_out = tid % (64 / DT) * DT;
+    const bool merges = q_out < 16;
+    auto put = [&](int nd, const float (&o)[DT]) {
+        if (!merges || nd >= a.M) return;
+        bf16_t* to = a.att + toff(b * a.M + nd, h * 64 + d_out, a.d >> 5);
+        if constexpr (DT == 4) *(uint2*)to = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+        else *(uint32_t*)to = pack_bf16(o[0], o[1]);
+    };
     if (n_rows == 0) {
 #pragma unroll
         for (int t = 0; t < QT; ++t) {
-            const int nd = (qt0 + t) * 16 + q_out;
-            if (nd < a.M) *(uint2*)(a.att + toff(b * a.M + nd, h * 64 + d_out, a.d >> 5)) = make_uint2(0, 0);
+            const float zero[DT] = {};
+            put((qt0 + t) * 16 + q_out, zero);
         }
         return;
     }
@@ -984,6 +1004,7 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) { kvb[i] = ldg4(Kh + off + i * 512); kvb[4 + i] = ldg4(Vh + off + i * 512); }
     };
+    constexpr float SCALE = 0.125f * 1.44269504088896340736f;   // head dim 64; powers of two
     float m_run[QT], l_run[QT];
     f32x4_t O[QT][4];
 #pragma unroll
@@ -993,14 +1014,16 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) O[t][i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     }
-    constexpr int NB = 3;   // two blocks in flight behind the one being computed
+    constexpr int NB = NW > 4 ? 2 : 3;   // one block, or with few waves two, in flight behind the one being computed
     uint4 buf[NB][8];
     if (wave < nblk) {
 #pragma unroll
-        for (int j = 0; j < NB - 1; ++j) load_block(wave + 4 * j, buf[j]);
+        for (int j = 0; j < NB - 1; ++j) load_block(wave + NW * j, buf[j]);
     }
     auto process = [&](const int blk, const uint4 (&cur)[8]) {
         const int p0 = blk << 5, v0 = p0 + 8 * gq;
+        uint32_t pk[QT][4];
+        float m_new[QT], psum[QT];
 #pragma unroll
         for (int t = 0; t < QT; ++t) {
             f32x4_t sa = (f32x4_t){0.f, 0.f, 0.f, 0.f}, sb = sa;
@@ -1009,30 +1032,23 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
             sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[2]), Q0[t], sb, 0, 0, 0);
             sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[3]), Q1[t], sb, 0, 0, 0);
             // this lane: query c, keys v0 + 0..3 (sa) and v0 + 4..7 (sb).  Instantiated twice: blocks inside the committed
-            // cache need no mask tests.
-            uint32_t pk[4];
-            float m_new, corr, psum = 0.f;
+            // cache need no mask tests.  The running maximum is of the unscaled scores; exp((s - m) / 8) = 2^(s c - m c).
             auto softmax_block = [&](const unsigned okm) {
-                float sc[8];
                 float mx = -1e30f;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float sv = (j < 4 ? sa[j] : sb[j - 4]) * 0.125f;
-                    sc[j] = (okm >> j) & 1u ? sv : -1e30f;
-                    mx = fmaxf(mx, sc[j]);
-                }
-                mx = rows_max(mx);
-                m_new = fmaxf(m_run[t], mx);
-                corr = __expf(m_run[t] - m_new);
+                for (int j = 0; j < 8; ++j) mx = fmaxf(mx, (okm >> j) & 1u ? (j < 4 ? sa[j] : sb[j - 4]) : -1e30f);
+                m_new[t] = fmaxf(m_run[t], rows_max(mx));
+                const float mc = m_new[t] * SCALE;
+                psum[t] = 0.f;
 #pragma unroll
                 for (int j = 0; j < 8; j += 2) {
-                    const float p0f = (okm >> j) & 1u ? __expf(sc[j] - m_new) : 0.f;
-                    const float p1f = (okm >> (j + 1)) & 1u ? __expf(sc[j + 1] - m_new) : 0.f;
-                    psum += p0f + p1f;
-                    pk[j >> 1] = pack_bf16(p0f, p1f);
+                    const float p0f = (okm >> j) & 1u ? __builtin_amdgcn_exp2f(__builtin_fmaf(j < 4 ? sa[j] : sb[j - 4], SCALE, -mc)) : 0.f;
+                    const float p1f = (okm >> (j + 1)) & 1u ? __builtin_amdgcn_exp2f(__builtin_fmaf(j < 4 ? sa[j + 1] : sb[j - 3], SCALE, -mc)) : 0.f;
+                    psum[t] += p0f + p1f;
+                    pk[t][j >> 1] = pack_bf16(p0f, p1f);
                 }
             };
-            if (p0 + 32 > L) {   // the block reaches into this forward's rows (same for the whole wave)
+            if (p0 + 32 > L + (CAUSAL ? min((qt0 + t) * 16, a.M - 1) + 1 : 0)) {   // the block reaches into this forward's rows, behind the tile's first query (same for the whole wave)
                 unsigned okm = 0;   // which of the lane's 8 keys the query may see
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
@@ -1051,22 +1067,35 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
             } else {
                 softmax_block(0xffu);
             }
-            l_run[t] = l_run[t] * corr + psum;
-            m_run[t] = m_new;
-            const bf16x8_t pfrag = __builtin_bit_cast(bf16x8_t, make_uint4(pk[0], pk[1], pk[2], pk[3]));
+        }
+        bool moved = false;
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt) {
-                O[t][dt] *= corr;
-                O[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[4 + dt]), pfrag, O[t][dt], 0, 0, 0);
+        for (int t = 0; t < QT; ++t) moved |= m_new[t] != m_run[t];
+        if (!__all(!moved)) {   // (after the first blocks the maxima rarely move)
+#pragma unroll
+            for (int t = 0; t < QT; ++t) {
+                const float corr = __builtin_amdgcn_exp2f((m_run[t] - m_new[t]) * SCALE);
+                l_run[t] *= corr;
+                m_run[t] = m_new[t];
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt) O[t][dt] *= corr;
             }
         }
+#pragma unroll
+        for (int t = 0; t < QT; ++t) {
+            l_run[t] += psum[t];
+            const bf16x8_t pfrag = __builtin_bit_cast(bf16x8_t, make_uint4(pk[t][0], pk[t][1], pk[t][2], pk[t][3]));
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+                O[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur[4 + dt]), pfrag, O[t][dt], 0, 0, 0);
+        }
     };
-    for (int blk = wave; blk < nblk; blk += 4 * NB) {
+    for (int blk = wave; blk < nblk; blk += NW * NB) {
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const int bi = blk + 4 * i;
+            const int bi = blk + NW * i;
             if (bi < nblk) {
-                load_block(bi + 4 * (NB - 1), buf[(i + NB - 1) % NB]);
+                load_block(bi + NW * (NB - 1), buf[(i + NB - 1) % NB]);
                 process(bi, buf[i]);
             }
         }
@@ -1081,23 +1110,24 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
             for (int i = 0; i < 4; ++i) sm_o[t][(wave * 64 + dt * 16 + 4 * gq + i) * SO + c] = O[t][dt][i];
     }
     __syncthreads();
+    if (!merges) return;
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-        const int nd = (qt0 + t) * 16 + q_out;
         float mstar = sm_m[t][q_out];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) mstar = fmaxf(mstar, sm_m[t][w * 16 + q_out]);
-        float f[4], lsum = 0.f, o[4];
+        for (int w = 1; w < NW; ++w) mstar = fmaxf(mstar, sm_m[t][w * 16 + q_out]);
+        float lsum = 0.f, o[DT] = {};
 #pragma unroll
-        for (int w = 0; w < 4; ++w) { f[w] = __expf(sm_m[t][w * 16 + q_out] - mstar); lsum += f[w] * sm_l[t][w * 16 + q_out]; }
+        for (int w = 0; w < NW; ++w) {
+            const float f = __builtin_amdgcn_exp2f((sm_m[t][w * 16 + q_out] - mstar) * SCALE);
+            lsum += f * sm_l[t][w * 16 + q_out];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            o[j] = 0.f;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) o[j] += f[w] * sm_o[t][(w * 64 + d_out + j) * SO + q_out];
+            for (int j = 0; j < DT; ++j) o[j] += f * sm_o[t][(w * 64 + d_out + j) * SO + q_out];
         }
         const float inv = 1.f / lsum;
-        if (nd < a.M) *(uint2*)(a.att + toff(b * a.M + nd, h * 64 + d_out, a.d >> 5)) = make_uint2(pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv));
+#pragma unroll
+        for (int j = 0; j < DT; ++j) o[j] *= inv;
+        put((qt0 + t) * 16 + q_out, o);
     }
 }
 
@@ -1282,17 +1312,23 @@ static void clock_point(const DevState& s, int ph, hipStream_t st) {
 #endif
 }
 
-template <int QT>
+template <int QT, int NW>
 static void attn_launch(const AttnArgs& t, bool causal, hipStream_t st) {
     const dim3 grid(pad8(t.B * t.nH), cdiv(cdiv(t.M, 16), QT));
-    if (causal) launch((k_attn<true, QT>), grid, dim3(256), 0, st, t);
-    else launch((k_attn<false, QT>), grid, dim3(256), 0, st, t);
+    if (causal) launch((k_attn<true, QT, NW>), grid, dim3(64 * NW), 0, st, t);
+    else launch((k_attn<false, QT, NW>), grid, dim3(64 * NW), 0, st, t);
 }
-static void attn(const AttnArgs& t, bool causal, int big_min, hipStream_t st) {
-    const int qt = cdiv(t.M, 16);
-    // from two workgroups per compute unit on
-    if (qt > 1 && t.B * t.nH * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512)) attn_launch<2>(t, causal, st);
-    else attn_launch<1>(t, causal, st);
+// keys: an upper bound of the longest sequence's keys.
+static void attn(const AttnArgs& t, bool causal, int keys, int big_min, hipStream_t st) {
+    const int qt = cdiv(t.M, 16), blocks = cdiv(keys, 32);
+    // two query tiles from two workgroups per compute unit on; waves: every one with a key block to take, up to four per SIMD
+    const bool two = qt > 1 && t.B * t.nH * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512);
+    const int wgs = t.B * t.nH * (two ? cdiv(qt, 2) : qt);
+    if (two && blocks >= 32 && wgs <= 512) attn_launch<2, 8>(t, causal, st);
+    else if (two) attn_launch<2, 4>(t, causal, st);
+    else if (blocks >= 32 && wgs <= 256) attn_launch<1, 16>(t, causal, st);
+    else if (blocks >= 10 && wgs <= 512) attn_launch<1, 8>(t, causal, st);
+    else attn_launch<1, 4>(t, causal, st);
 }
 
 void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st) {
@@ -1313,7 +1349,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         lin<LE_QKV>(a, big_min, st);
         AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos};
         clock_point(s, 2 + 5 * l, st);
-        attn(t, table == 1, big_min, st);
+        attn(t, table == 1, D.keys, big_min, st);
         LinArgs o = base;
         o.X = (const bf16_t*)s.att; o.W = (const uint4*)w.Wo; o.bias = w.bo; o.nks = d >> 5; o.N = d; o.NT = d >> 4;
         o.out = s.xb; o.outf = s.x; o.stats_out = (float2*)s.stats;

@@ -109,6 +109,24 @@ def test_two_query_tiles_per_workgroup_with_an_odd_number_of_tiles():
     _run(_cfg("bf16", 512, 90, layers=1, ffn=256, maxpos=128), 32, 40, (7, 7), (2,), 511, 10, 60)
 
 
+# Attention with 16 waves per workgroup (512 keys and more: 17 to 19 blocks, so that some waves take two and the last block is ragged),
+# with eight (one query tile and two), prompts in one pass and in passes of the tree's rows; the keys' bound moves with the steps
+@pytest.mark.parametrize("d,batch,nodes,prompt,chunk", [(128, 1, 40, 520, 0), (64, 2, 17, 590, 0), (128, 3, 33, 300, 0), (512, 32, 40, 240, 0), (64, 1, 1, 511, 0), (128, 2, 24, 560, 576)])
+def test_attention_waves(d, batch, nodes, prompt, chunk):
+    from parity import Lockstep
+    cfg = _cfg("bf16", d, 90, layers=1, ffn=128, maxpos=704)
+    W = make_weights(cfg, 900 + d, std=_std(cfg), ln_jitter=0.1)
+    rng = np.random.default_rng(900 + prompt)
+    text, tokens = rand_tokens(cfg, rng, batch, (2, 6), (prompt, prompt + 9))
+    ls = Lockstep(cfg, W, text, tokens, nodes, prefill_chunk=chunk)
+    tree = make_tree(nodes, () if nodes == 1 else (7, 7))
+    for tau in (2, 1):
+        ls.step(tree, tau)
+    ls.check_kv(layers=[0])
+    print(f"keys {prompt}: compared {ls.stats.compared}/{ls.stats.steps} logit err {ls.stats.max_logit_err:.2e}", flush=True)
+    assert ls.stats.compared >= 1
+
+
 @pytest.mark.parametrize("nodes,caps", [(40, (7, 7)), (17, (5, 4))])
 def test_two_query_tiles_beside_a_finished_sequence(monkeypatch, nodes, caps):
     """Forced on for three sequences: an odd number of query tiles (three), or two with one query in the second; the
