@@ -168,7 +168,7 @@ __device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int
     if (threadIdx.x == 0) stwi(s.acc_len + b, prefill_mode ? 0 : cnt);
     if (cnt <= 0) return;
     const int32_t* tok = s.tok + (size_t)b * D.M;
-    const int r = b * D.M + last;
+    const int r = prefill_mode && D.last_only ? b : (prefill_mode && s.row0 ? ldg(s.row0 + b) : b * D.M) + last;
     const int root = block_argbest(s.logits + (size_t)r * D.V1, D.V1, INFINITY, -1, nullptr);
     auto store = [&](int i, float a, float c) {
         if constexpr (sizeof(T) == 4) *(float2*)((float*)s.hbest + (size_t)b * D.d + i) = make_float2(a, c);

@@ -323,7 +323,7 @@ static size_t layout(const vadusa_config& c, char* base, DevState* s, std::vecto
     st.tok = ints(R); st.n_rows = ints(B); st.edge_ok = ints(R);
     st.path = ints(B * (VADUSA_MAX_DRAFT_HEADS + 2));
     st.out_tok = ints(B * P); st.n_out = ints(B);
-    st.chunk_tok = ints(R);
+    st.pass_tables = ints(4 * B * (P + 16));   // two numbers per row and two per sequence and pass (fp32: rows are padded, passes of up to 16 more than the longest sequence)
     st.override_topk = ints(B * Hh * VADUSA_MAX_TOPK);
     for (int t = 0; t < 2; ++t) {
         st.t_parent[t] = ints(VADUSA_MAX_TREE_NODES);
@@ -365,7 +365,7 @@ static Dims make_dims(const vadusa_ctx* c, int B, int M) {
     Dims D;
     D.Ly = c->cfg.n_layers; D.d = c->cfg.d_model; D.nH = c->cfg.n_heads; D.F = c->cfg.d_ffn;
     D.V1 = c->cfg.speech_vocab + 1; D.Hh = c->cfg.n_draft_heads; D.maxpos = c->cfg.max_positions;
-    D.Bmax = c->cfg.max_batch; D.Mmax = c->cfg.max_tree_nodes; D.B = B; D.M = M; D.keys = D.maxpos;
+    D.Bmax = c->cfg.max_batch; D.Mmax = c->cfg.max_tree_nodes; D.B = B; D.M = M; D.R = B * M; D.keys = D.maxpos; D.last_only = 0;
     return D;
 }
 
@@ -564,9 +564,9 @@ static int recover(vadusa_ctx* c) {
 }
 
 // Forward of B x M rows through the decoder (Sec. 2.1 tree attention; the prefill uses it with a causal pass as the "tree").
-static void forward(vadusa_ctx* c, const Dims& D, int table, int prefill_mode, bool want_logits) {
-    if (c->cfg.dtype) launch_layers(D, c->s, c->layers, table, prefill_mode, want_logits, c->big_min, c->stream);
-    else launch_layers32(D, c->s, c->layers, table, prefill_mode, want_logits, c->stream);
+static void forward(vadusa_ctx* c, const Dims& D, const DevState& s, int table, int prefill_mode, bool want_logits) {
+    if (c->cfg.dtype) launch_layers(D, s, c->layers, table, prefill_mode, want_logits, c->big_min, c->stream);
+    else launch_layers32(D, s, c->layers, table, prefill_mode, want_logits, c->stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -610,39 +610,53 @@ extern "C" int vadusa_prefill(vadusa_ctx* c, int32_t batch, const int32_t* text_
     }
     const DevState& s = c->s;
     const size_t B = batch;
-    // reset the decoding state
-    HIP_TRY(c, hipMemsetAsync(s.L, 0, B * 4, c->stream));
-    HIP_TRY(c, hipMemsetAsync(s.finished, 0, B * 4, c->stream));
-    HIP_TRY(c, hipMemsetAsync(s.n_out, 0, B * 4, c->stream));
-    HIP_TRY(c, hipMemsetAsync(s.path, 0, B * (VADUSA_MAX_DRAFT_HEADS + 2) * 4, c->stream));
-    Dims D = make_dims(c, batch, Mc);
-    // chunks are right-aligned so that every sequence ends in the last chunk
-    std::vector<std::vector<int32_t>> keep;   // host buffers stay alive until the final sync
+    // Passes are right-aligned so that every sequence ends in the last one, and ragged: the rows of a pass are the tokens it has, one
+    // sequence behind the other (the fp32 model's kernels take Mc rows per sequence instead).  The tables of all passes go up in one copy.
+    // With Mc rows per sequence and pass a fourth to a half of the rows had no token (16 prompts of 120 to 280 tokens: 4.3 ms, now 3.7; a prompt
+    // of 1564 in passes of 540 and 1024 rows, first step included: 2.6 ms, now 2.3).
+    const bool ragged = c->cfg.dtype;
+    std::vector<int32_t> tables;   // per pass: n_rows[B], row0[B], tokens[R], sequences of the rows[R]; alive until the final synchronisation
+    std::vector<Dims> dims;
+    std::vector<size_t> begin;
     for (int ch = 0; ch < max_chunks; ++ch) {
-        keep.emplace_back((size_t)batch * Mc, 0);
-        keep.emplace_back(batch, 0);
-        std::vector<int32_t>& ctok = keep[keep.size() - 2];
-        std::vector<int32_t>& rows = keep[keep.size() - 1];
+        std::vector<int32_t> n_rows(B, 0), row0(B, 0), tok, seq;
+        int longest = 0;
         for (int b = 0; b < batch; ++b) {
             const int total = (int)seqs[b].size();
             const int nch = (total + Mc - 1) / Mc;
             const int first = total - (nch - 1) * Mc;       // size of the sequence's first chunk
             const int k = ch - (max_chunks - nch);           // chunk index within the sequence
-            if (k < 0) continue;
-            const int begin = k == 0 ? 0 : first + (k - 1) * Mc;
-            const int cnt = k == 0 ? first : Mc;
-            rows[b] = cnt;
-            for (int i = 0; i < cnt; ++i) ctok[(size_t)b * Mc + i] = seqs[b][begin + i];
+            const int cnt = k < 0 ? 0 : k == 0 ? first : Mc, from = k <= 0 ? 0 : first + (k - 1) * Mc;
+            n_rows[b] = cnt;
+            row0[b] = (int)tok.size();
+            longest = std::max(longest, cnt);
+            tok.insert(tok.end(), seqs[b].begin() + from, seqs[b].begin() + from + cnt);
+            if (!ragged) tok.resize((size_t)(b + 1) * Mc, 0);
+            seq.resize(tok.size(), b);
         }
-        HIP_TRY(c, hipMemcpyAsync(s.chunk_tok, ctok.data(), ctok.size() * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(s.n_rows, rows.data(), rows.size() * 4, hipMemcpyHostToDevice, c->stream));
+        Dims D = make_dims(c, batch, ragged ? longest : Mc);
+        D.R = (int)tok.size();
+        D.keys = std::min((ch + 1) * Mc, D.maxpos);
+        // Behind the last layer's attention only the sequences' last rows matter.  The residual stream's last rows wait in the hidden layer's buffer.
+        D.last_only = ragged && ch == max_chunks - 1 && D.R > batch && (size_t)D.R * D.F >= 2 * B * (size_t)D.d;
+        dims.push_back(D);
+        begin.push_back(tables.size());
+        for (const auto* v : {&n_rows, &row0, &tok, &seq}) tables.insert(tables.end(), v->begin(), v->end());
+    }
+    launch_reset(s, batch, c->stream);
+    HIP_TRY(c, hipMemcpyAsync(s.pass_tables, tables.data(), tables.size() * 4, hipMemcpyHostToDevice, c->stream));
+    for (int ch = 0; ch < max_chunks; ++ch) {
+        const Dims& D = dims[ch];
+        DevState sp = s;
+        sp.n_rows = s.pass_tables + begin[ch];
+        sp.chunk_tok = sp.n_rows + 2 * B;
+        if (ragged) { sp.row0 = sp.n_rows + B; sp.row_seq = sp.chunk_tok + D.R; }
         const bool last = ch == max_chunks - 1;
         // the chunk is a causal "tree"; the last one also runs the vocabulary map, the continuation and the draft heads
-        D.keys = std::min((ch + 1) * Mc, D.maxpos);
-        forward(c, D, 1, 1, last);
-        if (!last) launch_advance(s, batch, c->stream);
+        forward(c, D, sp, 1, 1, last);
+        if (last) launch_continue(D, sp, c->draft, 0, batch, 1, c->cfg.ignore_eos, false, c->cfg.dtype, c->stream);
+        else launch_advance(sp, batch, c->stream);
     }
-    launch_continue(D, s, c->draft, 0, batch, 1, c->cfg.ignore_eos, false, c->cfg.dtype, c->stream);
     { int rc = launched(c); if (rc) return rc; }
     const int32_t* res = nullptr;
     { int rc = fetch(c, s.kerr, 4, s.root, B, nullptr, 0, &res); if (rc) return rc; }
@@ -751,7 +765,7 @@ static int verify_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau,
     // and acceptance, choice and continuation rank the scores in place of the logits.
     DevState sr = s;
     if (sp) sr.logits = c->scores;
-    forward(c, D, 0, 0, true);
+    forward(c, D, s, 0, 0, true);
     if (sp) launch_perturb(s.logits, c->uniforms, c->scores, B * M, D.V1, sp->temperature, sp->top_p, tau, c->stream);
     // the path is chosen beside the continuation where that follows at once
     launch_verify_tail(D, sr, tau, c->cfg.ignore_eos, !fuse_compact, c->stream);

@@ -180,7 +180,9 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 // Shapes that every kernel needs (passed by value).
 struct Dims {
     int Ly, d, nH, F, V1, Hh, maxpos, Bmax, Mmax;   // model / capacity
-    int B, M;                                        // current batch, rows per sequence
+    int B, M;                                        // current batch; rows per sequence (a ragged prompt pass: of the longest)
+    int R;                                           // rows of the forward: B * M, or the rows that a ragged prompt pass has
+    int last_only;                                   // the vocabulary map's rows are the sequences' last rows, one behind the other (else all rows)
     int keys;                                        // no sequence attends to more keys than this (for the choice of kernels)
 };
 
@@ -224,7 +226,10 @@ struct DevState {
     int32_t *tok /*[R]*/, *n_rows /*[Bmax]*/, *edge_ok /*[R]*/, *path /*[Bmax][MAX_DRAFT_HEADS+2]*/;
     int32_t *out_tok /*[Bmax][maxpos]*/, *n_out /*[Bmax]*/;
     int32_t *acc_tok /*[Bmax][MAX_DRAFT_HEADS+1]*/, *acc_len /*[Bmax]*/;
-    int32_t *chunk_tok /*[R]*/, *override_topk /*[Bmax][Hh][MAX_TOPK]*/;
+    int32_t *chunk_tok /*[R]*/;
+    int32_t *row_seq /*[R]*/, *row0 /*[Bmax]*/;   // ragged prompt pass: each row's sequence, each sequence's first row (null: sequence b has rows b * M ..)
+    int32_t *pass_tables;  // where vadusa_prefill puts n_rows, row0, chunk_tok and row_seq of all its passes
+    int32_t *override_topk /*[Bmax][Hh][MAX_TOPK]*/;
     // tree tables (index 0: current tree, 1: causal chunk used by prefill)
     int32_t *t_parent[2], *t_depth[2], *t_rank[2];
     uint32_t* t_mask[2];   // [Mmax][MASK_WORDS]
@@ -305,7 +310,8 @@ struct GemmArgs {
 // out-projection, FFN1, FFN2); then H + TP_*, H = 1 + 5 * n_layers.  TP_COMMIT: first map of the draft heads; TP_TOPK: draft
 // lists and, beside them, the compaction of the KV cache.
 enum { TP_HEAD = 0, TP_EDGES, TP_SELECT, TP_FINAL, TP_COMMIT, TP_DRAFT2, TP_TOPK, TP_COUNT };
-// bf16 model: embedding, decoder layers and (head) the vocabulary map (see k_layer.hip)
+// bf16 model: embedding, decoder layers and (head) the vocabulary map (see k_layer.hip).  Prompt passes (prefill_mode) are ragged; without
+// head the last layer ends with its keys and values, with it only the sequences' last rows go on behind its attention where D.last_only.
 void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st);
 // edge decisions, and (select) the path choice of every sequence
 void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eos, bool select, hipStream_t st);
@@ -329,5 +335,6 @@ void launch_convert(const float* src, void* dst, size_t n, int dtype, hipStream_
 // na words from a, nb from b, nc from c, one behind the other, into host memory the GPU can write
 void launch_gather(const int32_t* a, int na, const int32_t* b, int nb, const int32_t* c, int nc, int32_t* host, hipStream_t st);
 void launch_advance(const DevState& s, int B, hipStream_t st);
+void launch_reset(const DevState& s, int B, hipStream_t st);   // committed lengths, finished, outputs and paths back to zero
 void launch_read_kv(const Dims& D, const void* cache_layer, int seq, int which, int pos0, int npos, float* out, int dtype, hipStream_t st);
 void launch_to_float(const void* src, float* dst, size_t n, int dtype, hipStream_t st);

@@ -109,6 +109,14 @@ __global__ void k_advance(DevState s, int B) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b < B) s.L[b] += s.n_rows[b];
 }
+__global__ __launch_bounds__(256) void k_reset(DevState s, int B) {
+    constexpr int W = VADUSA_MAX_DRAFT_HEADS + 2;
+    for (int i = threadIdx.x; i < B * W; i += 256) {
+        s.path[i] = 0;
+        if (i < B) s.L[i] = s.finished[i] = s.n_out[i] = 0;
+    }
+}
+void launch_reset(const DevState& s, int B, hipStream_t st) { launch(k_reset, dim3(1), dim3(256), 0, st, s, B); }
 void launch_advance(const DevState& s, int B, hipStream_t st) {
     launch(k_advance, dim3((B + 63) / 64), dim3(64), 0, st, s, B);
 }

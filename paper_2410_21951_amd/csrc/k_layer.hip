@@ -42,10 +42,11 @@ struct LinArgs {
     int nks, NT, R, N;      // K / 32, column tiles, rows, columns
     int sg, sg_out;         // log2 of the columns that an entry of stats (stats_out) describes: 4 to 6; a row's entries are an even number
     bf16_t* out;            // operand tiles of the next map: q, hidden layer or the residual stream's bf16 copy
-    float* outf;            // logits, or the residual stream (LE_RESID)
+    float* outf;            // logits, or the new residual stream (LE_RESID)
     float2* stats_out;      // [R][N >> sg_out] (LE_RESID)
     bf16_t *Kc, *Vc;        // LE_QKV: this layer's cache
-    const int32_t *L, *n_rows;
+    const int32_t *L, *n_rows, *row_seq, *row0;   // row_seq, row0: of a ragged prompt pass (null: sequence b has rows b * M ..)
+    const float* resid;     // LE_RESID: what the map's result is added to
     int M, nH, maxpos, d;
     size_t z_w, z_b, z_x, z_out;   // LE_SILU, LE_F32: what a draft head's weights, bias (bytes), X and result (elements) are ahead of the previous head's
 };
@@ -114,7 +115,7 @@ struct KvRow { size_t base; int pos; };
 __device__ __forceinline__ KvRow kv_row(const LinArgs& a, int r) {
     KvRow k{0, -1};
     if (r >= a.R) return k;
-    const int b = r / a.M, pos = ldg(a.L + b) + (r - b * a.M);
+    const int b = a.row_seq ? ldg(a.row_seq + r) : r / a.M, pos = ldg(a.L + b) + (r - (a.row_seq ? ldg(a.row0 + b) : b * a.M));
     k.base = (size_t)b * a.nH * kv_cap(a.maxpos) * 64;
     if (pos < a.maxpos && ldg(a.n_rows + b) > 0) k.pos = pos;
     return k;
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(256) void k_lin(LinArgs a) {
         if (have) {
             if (EPI != LE_F32) b4 = ldg4(a.bias + n0);
             if (LN) c4 = ldg4(a.colsum + n0);
-            if (EPI == LE_RESID) x4 = ldg4(a.outf + (size_t)(r < a.R ? r : 0) * a.N + n0);
+            if (EPI == LE_RESID) x4 = ldg4(a.resid + (size_t)(r < a.R ? r : 0) * a.N + n0);
             if (EPI == LE_QKV && n0 >= a.d) kv[p] = kv_row(a, r);
         }
         bias[p][0] = __uint_as_float(b4.x); bias[p][1] = __uint_as_float(b4.y); bias[p][2] = __uint_as_float(b4.z); bias[p][3] = __uint_as_float(b4.w);
@@ -391,8 +392,9 @@ __device__ __forceinline__ void store_values(const LinArgs& a, int first, int co
     const uint16_t* mine = values + lane % COLS;
     wave_sync();
     for (int j = 0; j < rows;) {
-        const int b = (first + j) / a.M, m0 = first + j - b * a.M, end = min(j + a.M - m0, rows), L = ldg(a.L + b);
-        const bool live = ldg(a.n_rows + b) > 0 && lane < COLS;
+        const int b = a.row_seq ? ldg(a.row_seq + first + j) : (first + j) / a.M, m0 = first + j - (a.row_seq ? ldg(a.row0 + b) : b * a.M);
+        const int have = ldg(a.n_rows + b), end = min(j + (a.row_seq ? have : a.M) - m0, rows), L = ldg(a.L + b);
+        const bool live = have > 0 && lane < COLS;
         bf16_t* to = a.Vc + ((size_t)b * a.nH + head) * kv_cap(a.maxpos) * 64;
         for (int pos = L + m0; j < end;) {
             const int n = min(8 - (pos & 7), end - j);   // rows that share the piece
@@ -574,7 +576,7 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
             if constexpr (EPI == LE_RESID)
 #pragma unroll
                 for (int ri = 0; ri < NR2; ++ri) {
-                    const uint4 x4 = ldg4(a.outf + (size_t)min(row0 + ri * 32 + lr, a.R - 1) * a.N + n0);
+                    const uint4 x4 = ldg4(a.resid + (size_t)min(row0 + ri * 32 + lr, a.R - 1) * a.N + n0);
                     xr[ri][q][0] = __uint_as_float(x4.x); xr[ri][q][1] = __uint_as_float(x4.y); xr[ri][q][2] = __uint_as_float(x4.z); xr[ri][q][3] = __uint_as_float(x4.w);
                 }
         }
@@ -783,7 +785,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 #pragma unroll
             for (int tt = 0; tt < TB; ++tt)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) xr[i][tt][h] = ldg4(a.outf + (size_t)min(r[i], a.R - 1) * a.N + min(tile0 + tt, a.NT - 1) * 16 + 8 * h + 4 * hi);
+                for (int h = 0; h < 2; ++h) xr[i][tt][h] = ldg4(a.resid + (size_t)min(r[i], a.R - 1) * a.N + min(tile0 + tt, a.NT - 1) * 16 + 8 * h + 4 * hi);
     KvRow kv[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
@@ -950,6 +952,9 @@ struct AttnArgs {
     const int32_t *L, *n_rows;
     const uint32_t* mask;
     int B, M, nH, d, maxpos;
+    const int32_t* row0;     // causal pass: each sequence's first row (its rows are n_rows many)
+    const float* x;          // causal pass, where only the sequences' last rows go on: the residual stream, and
+    float* x_last;           // where its last rows go, one behind the other like the attention's results (null: all rows go on)
 };
 template <bool CAUSAL, int QT, int NW>
 __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(AttnArgs a) {
@@ -966,14 +971,23 @@ __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(Att
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, gq = lane >> 4, c = lane & 15;
     const int b = bh / a.nH, h = bh - b * a.nH;
     const int n_rows = ldg(a.n_rows + b), L = ldg(a.L + b);
+    const int M = CAUSAL ? n_rows : a.M, row0 = CAUSAL ? ldg(a.row0 + b) : b * a.M;   // the sequence's rows
+    const bool last_only = CAUSAL && a.x_last;
+    if constexpr (CAUSAL) {
+        if (last_only) {
+            qt0 = (M - 1) >> 4;
+            if (tid < 16) *(float4*)(a.x_last + (size_t)b * a.d + h * 64 + 4 * tid) = *(const float4*)(a.x + (size_t)(row0 + M - 1) * a.d + h * 64 + 4 * tid);
+        }
+        if (qt0 * 16 >= M) return;
+    }
     int node[QT];
     bf16x8_t Q0[QT], Q1[QT];
     uint4 mw[QT];
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-        node[t] = min((qt0 + t) * 16 + c, a.M - 1);
-        Q0[t] = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(b * a.M + node[t], h * 64 + 8 * gq, a.d >> 5)));
-        Q1[t] = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(b * a.M + node[t], h * 64 + 32 + 8 * gq, a.d >> 5)));
+        node[t] = min((qt0 + t) * 16 + c, M - 1);
+        Q0[t] = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(row0 + node[t], h * 64 + 8 * gq, a.d >> 5)));
+        Q1[t] = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(row0 + node[t], h * 64 + 32 + 8 * gq, a.d >> 5)));
         mw[t] = make_uint4(0, 0, 0, 0);
         if constexpr (!CAUSAL) mw[t] = ldg4(a.mask + (size_t)node[t] * MASK_WORDS);
     }
@@ -981,12 +995,12 @@ __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(Att
     const int q_out = tid / (64 / DT), d_out = tid % (64 / DT) * DT;
     const bool merges = q_out < 16;
     auto put = [&](int nd, const float (&o)[DT]) {
-        if (!merges || nd >= a.M) return;
-        bf16_t* to = a.att + toff(b * a.M + nd, h * 64 + d_out, a.d >> 5);
+        if (!merges || nd >= M || (last_only && nd != M - 1)) return;
+        bf16_t* to = a.att + toff(last_only ? b : row0 + nd, h * 64 + d_out, a.d >> 5);
         if constexpr (DT == 4) *(uint2*)to = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
         else *(uint32_t*)to = pack_bf16(o[0], o[1]);
     };
-    if (n_rows == 0) {
+    if (!CAUSAL && n_rows == 0) {   // a finished sequence
 #pragma unroll
         for (int t = 0; t < QT; ++t) {
             const float zero[DT] = {};
@@ -995,7 +1009,7 @@ __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(Att
         return;
     }
     // (a causal pass: no query of the workgroup sees keys behind its last row)
-    const int T = min(CAUSAL ? L + min((qt0 + QT) * 16, a.M) : L + a.M, a.maxpos);
+    const int T = min(CAUSAL ? L + min((qt0 + QT) * 16, M) : L + M, a.maxpos);
     const size_t hb = ((size_t)b * a.nH + h) * kv_cap(a.maxpos) * 64;
     const bf16_t *Kh = a.Kc + hb + lane * 8, *Vh = a.Vc + hb + lane * 8;
     const int nblk = (T + 31) >> 5;
@@ -1048,7 +1062,7 @@ __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(Att
                     pk[t][j >> 1] = pack_bf16(p0f, p1f);
                 }
             };
-            if (p0 + 32 > L + (CAUSAL ? min((qt0 + t) * 16, a.M - 1) + 1 : 0)) {   // the block reaches into this forward's rows, behind the tile's first query (same for the whole wave)
+            if (p0 + 32 > L + (CAUSAL ? min((qt0 + t) * 16, M - 1) + 1 : 0)) {   // the block reaches into this forward's rows, behind the tile's first query (same for the whole wave)
                 unsigned okm = 0;   // which of the lane's 8 keys the query may see
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
@@ -1137,10 +1151,8 @@ __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(Att
 // passed as -(id + 1), speech ids as they are.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_embed_rows(Dims D, DevState s, int prefill_mode, int table) {
-    const int r = blockIdx.x, b = r / D.M, n = r - b * D.M, tid = threadIdx.x;
-    int rows;
-    if (prefill_mode) rows = ldg(s.n_rows + b);
-    else rows = ldg(s.finished + b) ? 0 : D.M;
+    const int r = blockIdx.x, tid = threadIdx.x, b = prefill_mode ? ldg(s.row_seq + r) : r / D.M, n = r - (prefill_mode ? ldg(s.row0 + b) : b * D.M);
+    const int rows = prefill_mode ? ldg(s.n_rows + b) : ldg(s.finished + b) ? 0 : D.M;
     if (!prefill_mode && n == 0 && tid == 0) s.n_rows[b] = rows;
     const bool valid = n < rows;
     int tok = 0, pos = 0;
@@ -1314,13 +1326,13 @@ static void clock_point(const DevState& s, int ph, hipStream_t st) {
 
 template <int QT, int NW>
 static void attn_launch(const AttnArgs& t, bool causal, hipStream_t st) {
-    const dim3 grid(pad8(t.B * t.nH), cdiv(cdiv(t.M, 16), QT));
+    const dim3 grid(pad8(t.B * t.nH), t.x_last ? 1 : cdiv(cdiv(t.M, 16), QT));
     if (causal) launch((k_attn<true, QT, NW>), grid, dim3(64 * NW), 0, st, t);
     else launch((k_attn<false, QT, NW>), grid, dim3(64 * NW), 0, st, t);
 }
 // keys: an upper bound of the longest sequence's keys.
 static void attn(const AttnArgs& t, bool causal, int keys, int big_min, hipStream_t st) {
-    const int qt = cdiv(t.M, 16), blocks = cdiv(keys, 32);
+    const int qt = t.x_last ? 1 : cdiv(t.M, 16), blocks = cdiv(keys, 32);
     // two query tiles from two workgroups per compute unit on; waves: every one with a key block to take, up to four per SIMD
     const bool two = qt > 1 && t.B * t.nH * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512);
     const int wgs = t.B * t.nH * (two ? cdiv(qt, 2) : qt);
@@ -1332,12 +1344,13 @@ static void attn(const AttnArgs& t, bool causal, int keys, int big_min, hipStrea
 }
 
 void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st) {
-    const int R = D.B * D.M, d = D.d;
+    int R = D.R;
+    const int d = D.d;
     const size_t kv_layer = (size_t)D.Bmax * D.nH * kv_cap(D.maxpos) * 64;
     clock_point(s, 0, st);
     launch(k_embed_rows, dim3(R), dim3(256), 0, st, D, s, prefill_mode, table);
     LinArgs base{};
-    base.R = R; base.L = s.L; base.n_rows = s.n_rows; base.M = D.M; base.nH = D.nH; base.maxpos = D.maxpos; base.d = d;
+    base.R = R; base.L = s.L; base.n_rows = s.n_rows; base.row_seq = s.row_seq; base.row0 = s.row0; base.M = D.M; base.nH = D.nH; base.maxpos = D.maxpos; base.d = d;
     base.stats = (const float2*)s.stats; base.sg = 4;   // (k_embed_rows)
     for (int l = 0; l < D.Ly; ++l) {
         const LayerW& w = layers[l];
@@ -1347,12 +1360,18 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         a.out = (bf16_t*)s.q; a.Kc = Kc; a.Vc = Vc;
         clock_point(s, 1 + 5 * l, st);
         lin<LE_QKV>(a, big_min, st);
-        AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos};
+        const bool end = l + 1 == D.Ly;
+        if (end && prefill_mode && !head) break;   // what follows the last layer's keys and values is for the vocabulary map
+        AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos, s.row0, s.x, nullptr};
+        float* x = s.x;
+        if (end && D.last_only) x = t.x_last = (float*)s.hid;   // (free until FFN1)
         clock_point(s, 2 + 5 * l, st);
         attn(t, table == 1, D.keys, big_min, st);
         LinArgs o = base;
         o.X = (const bf16_t*)s.att; o.W = (const uint4*)w.Wo; o.bias = w.bo; o.nks = d >> 5; o.N = d; o.NT = d >> 4;
         o.out = s.xb; o.outf = s.x; o.stats_out = (float2*)s.stats;
+        if (end && D.last_only) base.R = R = o.R = D.B;
+        o.resid = x;
         clock_point(s, 3 + 5 * l, st);
         lin<LE_RESID>(o, big_min, st);
         base.sg = o.sg_out;
@@ -1363,7 +1382,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         lin<LE_GELU>(f, big_min, st);
         LinArgs g = base;
         g.X = (const bf16_t*)s.hid; g.W = (const uint4*)w.W2; g.bias = w.b2; g.nks = D.F >> 5; g.N = d; g.NT = d >> 4;
-        g.out = s.xb; g.outf = s.x; g.stats_out = (float2*)s.stats;
+        g.out = s.xb; g.outf = s.x; g.resid = s.x; g.stats_out = (float2*)s.stats;
         clock_point(s, 5 + 5 * l, st);
         lin<LE_RESID>(g, big_min, st);
         base.sg = g.sg_out;

@@ -109,6 +109,29 @@ def test_two_query_tiles_per_workgroup_with_an_odd_number_of_tiles():
     _run(_cfg("bf16", 512, 90, layers=1, ffn=256, maxpos=128), 32, 40, (7, 7), (2,), 511, 10, 60)
 
 
+# Prompt passes have the rows of the tokens they hold: sequences without rows in the first passes, of one token, that end at and beside
+# a tile of 16; a pass whose sequences have a row each; behind the last layer's attention only the sequences' last rows (a
+# hidden layer of 64 leaves no room for that with fewer than 16 rows per sequence); one sequence alone; every kernel of the maps
+@pytest.mark.parametrize("big_min", [0, 1, -1, -2])
+@pytest.mark.parametrize("lens,chunk,d,ffn", [((1, 17, 70), 16, 128, 256), ((33, 1, 1, 2, 16), 0, 192, 64), ((5, 9, 3), 0, 512, 64), ((97,), 32, 64, 128),
+                                              ((1, 1), 64, 128, 128), ((129, 64, 100, 31), 64, 256, 512)])
+def test_ragged_prompt_passes(monkeypatch, big_min, lens, chunk, d, ffn):
+    from parity import Lockstep
+    monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", str(big_min))
+    cfg = _cfg("bf16", d, 90, ffn=ffn, maxpos=192)
+    W = make_weights(cfg, 940 + d, std=_std(cfg), ln_jitter=0.1)
+    rng = np.random.default_rng(940 + len(lens))
+    text = [rng.integers(0, cfg.text_vocab, n // 3).astype(np.int32) for n in lens]
+    tokens = [rng.integers(0, cfg.speech_vocab, n - n // 3).astype(np.int32) for n in lens]
+    ls = Lockstep(cfg, W, text, tokens, 16, prefill_chunk=chunk)
+    ls.check_kv(layers=[0, 1])    # beside the draft lists' logits and the first root, which the harness compares
+    tree = make_tree(16, (4, 4))
+    for tau in (2, 1):
+        ls.step(tree, tau)
+    print(f"{lens}: compared {ls.stats.compared}/{ls.stats.steps} logit err {ls.stats.max_logit_err:.2e} kv {ls.stats.max_kv_err:.2e}", flush=True)
+    assert ls.stats.compared >= 1
+
+
 # Attention with 16 waves per workgroup (512 keys and more: 17 to 19 blocks, so that some waves take two and the last block is ragged),
 # with eight (one query tile and two), prompts in one pass and in passes of the tree's rows; the keys' bound moves with the steps
 @pytest.mark.parametrize("d,batch,nodes,prompt,chunk", [(128, 1, 40, 520, 0), (64, 2, 17, 590, 0), (128, 3, 33, 300, 0), (512, 32, 40, 240, 0), (64, 1, 1, 511, 0), (128, 2, 24, 560, 576)])
