@@ -46,6 +46,7 @@ struct LinArgs {
     float2* stats_out;      // [R][N >> sg_out] (LE_RESID)
     bf16_t *Kc, *Vc;        // LE_QKV: this layer's cache
     const int32_t *L, *n_rows, *row_seq, *row0;   // row_seq, row0: of a ragged prompt pass (null: sequence b has rows b * M ..)
+    int per_block;          // k_lin: 65536 / row blocks where these start at different k-steps, else 0
     const float* resid;     // LE_RESID: what the map's result is added to
     int M, nH, maxpos, d;
     size_t z_w, z_b, z_x, z_out;   // LE_SILU, LE_F32: what a draft head's weights, bias (bytes), X and result (elements) are ahead of the previous head's
@@ -162,8 +163,8 @@ __device__ __forceinline__ void store4(const LinArgs& a, int r, int n0, bool liv
 // load) straight into registers, CH k-steps at a time with the next chunk's loads ahead of the current chunk's MFMAs;
 // the four partial sums are added in wave order through LDS.
 // ---------------------------------------------------------------------------
-template <int RT, int CT, int CH, int EPI>
-__global__ __launch_bounds__(256) void k_lin(LinArgs a) {
+template <int RT, int CT, int CH, int EPI, int NW>
+__global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
     constexpr bool LN = EPI <= LE_LOGITS;
     if constexpr (EPI == LE_SILU || EPI == LE_F32) {
         const size_t z = blockIdx.z;
@@ -173,31 +174,36 @@ __global__ __launch_bounds__(256) void k_lin(LinArgs a) {
         a.out += z * a.z_out;
         a.outf += z * a.z_out;
     }
-    constexpr int T = RT * CT, NPW = (T + 3) / 4;   // output tiles, tiles per wave in the epilogue
+    constexpr int T = RT * CT, NPW = (T + NW - 1) / NW;   // output tiles, tiles per wave in the epilogue
+    static_assert(!LN || NW == 4, "the row statistics are merged by 256 threads");
     constexpr int ROWS = RT == 3 ? 64 : RT * 16;   // rows whose statistics are merged
-    __shared__ f32x4_t red[4 * T * 64];
+    __shared__ f32x4_t red[NW * T * 64];
     __shared__ float s_mean[ROWS], s_rstd[ROWS];
     const int g = blockIdx.x, rb = blockIdx.y;
     if (g * CT >= a.NT) return;   // padding of the XCD-aware numbering
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int lc = lane & 15, gq = lane >> 4, row0 = rb * RT * 16, last_rt = (a.R - 1) >> 4;
-    const int ks_lo = (a.nks * wave) >> 2, ks_hi = (a.nks * (wave + 1)) >> 2;
+    const int ks_lo = a.nks * wave / NW, ks_hi = a.nks * (wave + 1) / NW;
     // epilogue inputs of this thread's tiles, and the row statistics: asked for first, needed last
     float bias[NPW][4], cs[NPW][4], xr[NPW][4];
-    KvRow kv[NPW];
+    int seq[NPW], pos[NPW], rows[NPW];   // LE_QKV: sequence, first position and rows of the row's sequence, for kv_row
     RowStats<ROWS> st;
     if constexpr (LN) st.request(a, row0);
 #pragma unroll
     for (int p = 0; p < NPW; ++p) {
-        const int t = wave + 4 * p, n0 = (g * CT + t % CT) * 16 + 4 * gq, r = row0 + (t / CT) * 16 + lc;
+        const int t = wave + NW * p, n0 = (g * CT + t % CT) * 16 + 4 * gq, r = row0 + (t / CT) * 16 + lc;
         const bool have = t < T && g * CT + t % CT < a.NT;
         uint4 b4 = make_uint4(0, 0, 0, 0), c4 = b4, x4 = b4;
-        kv[p] = KvRow{0, -1};
         if (have) {
             if (EPI != LE_F32) b4 = ldg4(a.bias + n0);
             if (LN) c4 = ldg4(a.colsum + n0);
             if (EPI == LE_RESID) x4 = ldg4(a.resid + (size_t)(r < a.R ? r : 0) * a.N + n0);
-            if (EPI == LE_QKV && n0 >= a.d) kv[p] = kv_row(a, r);
+        }
+        if constexpr (EPI == LE_QKV) {   // nothing waits for these before the operands are on their way
+            const int rr = min(r, a.R - 1);
+            seq[p] = a.row_seq ? ldg(a.row_seq + rr) : rr / a.M;
+            pos[p] = ldg(a.L + seq[p]) + rr - (a.row_seq ? ldg(a.row0 + seq[p]) : seq[p] * a.M);
+            rows[p] = ldg(a.n_rows + seq[p]);
         }
         bias[p][0] = __uint_as_float(b4.x); bias[p][1] = __uint_as_float(b4.y); bias[p][2] = __uint_as_float(b4.z); bias[p][3] = __uint_as_float(b4.w);
         cs[p][0] = __uint_as_float(c4.x); cs[p][1] = __uint_as_float(c4.y); cs[p][2] = __uint_as_float(c4.z); cs[p][3] = __uint_as_float(c4.w);
@@ -207,6 +213,8 @@ __global__ __launch_bounds__(256) void k_lin(LinArgs a) {
             xr[p][0] = bf2f((bf16_t)h.x); xr[p][1] = bf2f((bf16_t)(h.x >> 16)); xr[p][2] = bf2f((bf16_t)h.y); xr[p][3] = bf2f((bf16_t)(h.y >> 16));
         }
     }
+    // (one row tile: rows beyond the map's last read the last one's pieces, which are fewer lines: one row, QKV 4.3 -> 3.9 us, FFN2 6.8 -> 5.9)
+    const uint32_t xl = RT > 1 ? (uint32_t)lane * 16u : (uint32_t)(min(lc, a.R - 1 - min(rb, last_rt) * 16) + 16 * gq) * 16u;
     const char *Wp[CT], *Xp[RT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) Wp[c] = (const char*)(a.W + (size_t)min(g * CT + c, a.NT - 1) * a.nks * 64);
@@ -217,17 +225,24 @@ __global__ __launch_bounds__(256) void k_lin(LinArgs a) {
     for (int c = 0; c < CT; ++c)
 #pragma unroll
         for (int r = 0; r < RT; ++r) acc[c][r] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    // Workgroups on the same columns start at different k-steps: side by side they would all wait for the same lines from HBM, and a
+    // compute unit has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
+    // (FFN2, K = 4096, us: 128 rows 8.6 -> 7.0, 135 rows 9.3 -> 8.7, 320 rows 12.8 -> 11.7; beyond what an L2 holds they
+    // drive each other out of it: 1024 rows 18.4 -> 20.3, k_tile and k_big likewise.  Not the LayerNorm-folded maps of K = 1024,
+    // whose operands are all on their way at once: 64 rows FFN1 5.0 -> 5.4.)
+    const int turn = EPI == LE_RESID ? (ks_hi - ks_lo) * rb * a.per_block >> 16 : 0;
     // Loads are unconditional: a tile beyond the map's last row or column re-reads a valid one and only reaches
     // accumulators that are never stored; a k-step beyond the last re-reads the last and is not multiplied.
     uint4 wA[CH][CT], xA[CH][RT], wB[CH][CT], xB[CH][RT];
     auto load = [&](int kb, uint4 (&w)[CH][CT], uint4 (&x)[CH][RT]) {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            const uint32_t off = (uint32_t)min(kb + i, a.nks - 1) * 1024u + (uint32_t)lane * 16u;
+            const int k = kb + i + turn;
+            const uint32_t off = (uint32_t)min(EPI == LE_RESID && k >= ks_hi ? k - (ks_hi - ks_lo) : k, a.nks - 1) * 1024u;
 #pragma unroll
-            for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + off);
+            for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + (off + (uint32_t)lane * 16u));
 #pragma unroll
-            for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + off);
+            for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + (off + xl));
         }
     };
     auto mul = [&](int n, const uint4 (&w)[CH][CT], const uint4 (&x)[CH][RT]) {
@@ -264,13 +279,13 @@ __global__ __launch_bounds__(256) void k_lin(LinArgs a) {
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < NPW; ++p) {
-        const int t = wave + 4 * p;
+        const int t = wave + NW * p;
         if (t >= T) break;
         const int c = t % CT, rl = (t / CT) * 16 + lc, r = row0 + rl, tile = g * CT + c, n0 = tile * 16 + 4 * gq;
         if (tile >= a.NT) continue;
         f32x4_t s = red[t * 64 + lane];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) s += red[(w * T + t) * 64 + lane];
+        for (int w = 1; w < NW; ++w) s += red[(w * T + t) * 64 + lane];
         float v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -285,7 +300,12 @@ __global__ __launch_bounds__(256) void k_lin(LinArgs a) {
             const float m2 = rows_sum((v[0] - mean) * (v[0] - mean) + (v[1] - mean) * (v[1] - mean) + (v[2] - mean) * (v[2] - mean) + (v[3] - mean) * (v[3] - mean));
             if (r < a.R && gq == 0) a.stats_out[(size_t)r * (a.N >> 4) + tile] = make_float2(mean, m2);
         }
-        store4<EPI>(a, r, n0, r < a.R, v, kv[p]);
+        KvRow kv{0, -1};
+        if constexpr (EPI == LE_QKV) {
+            kv.base = (size_t)seq[p] * a.nH * kv_cap(a.maxpos) * 64;
+            if (r < a.R && pos[p] < a.maxpos && rows[p] > 0) kv.pos = pos[p];
+        }
+        store4<EPI>(a, r, n0, r < a.R, v, kv);
     }
 }
 
@@ -936,11 +956,11 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 // QT = 2 where there are workgroups enough for every compute unit: a key block is then fetched once for 32 queries.
 // (64 sequences of 32 nodes, ~330 keys: 24 us a layer instead of 34; with 64 workgroups instead of 128 for one sequence
 // it takes 6.1 instead of 4.5.)
-// NW waves take the key blocks of a workgroup in turn.  What bounds it with few workgroups: a wave's chain of blocks (load, scores,
-// maximum, exponentials), then the 50 bytes per clock that a compute unit pulls through L2 (2000 keys: 512 KB, 4.3 us), so many waves where
-// there are blocks for them and workgroups do not fill the chip (us, four waves -> NW; 64 queries 360 keys 6.0 -> 5.6 with 8;
-// 128 queries, 2000 keys 14.0 -> 12.4 with 16, of 1500 12.0 -> 10.8; 1024 causal queries of 1500 keys 22.0 -> 19 with 8); with a block or two per
-// wave the merge costs more than it gives (270 keys, QT = 2: 11.7 -> 13.4 with 8).
+// NW waves take the key blocks of a workgroup in turn.  What bounds it with few workgroups: misses (a compute unit has no more than some
+// 64 KB on their way; 512 KB of keys and values took 9 us), so the workgroups of a head start at different blocks (128 queries, 2000 keys
+// 12.4 -> 10.3 us a layer, 64 queries, 360 keys 5.7 -> 5.3), and eight waves instead of four where there are blocks for them and the
+// workgroups do not fill the chip (14.0 -> 12.4, 6.0 -> 5.6; 1024 causal queries of 1500 keys 22.0 -> 17.4; sixteen waves 10.7, eight with
+// five buffers 11.7 instead of 10.3); with a block or two per wave the merge costs more than it gives (270 keys, QT = 2: 11.7 -> 13.4).
 // Measured and not kept: the key blocks split over up to four workgroups with the last
 // to arrive merging (2000 keys, 64 queries: 8.6 instead of 9.7, 1000 keys: 8.2 instead of 6.9); two blocks per step
 // (2000 keys: 9.3, 320 keys: 5.2 instead of 4.5).
@@ -956,8 +976,8 @@ struct AttnArgs {
     const float* x;          // causal pass, where only the sequences' last rows go on: the residual stream, and
     float* x_last;           // where its last rows go, one behind the other like the attention's results (null: all rows go on)
 };
-template <bool CAUSAL, int QT, int NW>
-__global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(AttnArgs a) {
+template <bool CAUSAL, int QT, int NW, int NB>   // NB: buffers of a wave, all but one of them in flight
+__global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : QT == 1 ? 4 : 2) void k_attn(AttnArgs a) {
     constexpr int SO = 17;   // floats per row of the merge buffer: the merge reads a dimension's 16 queries' worth 64 rows apart
     __shared__ float sm_o[QT][NW * 64 * SO], sm_m[QT][NW * 16], sm_l[QT][NW * 16];
     const int bh = blockIdx.x;
@@ -1011,12 +1031,18 @@ __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(Att
     // (a causal pass: no query of the workgroup sees keys behind its last row)
     const int T = min(CAUSAL ? L + min((qt0 + QT) * 16, M) : L + M, a.maxpos);
     const size_t hb = ((size_t)b * a.nH + h) * kv_cap(a.maxpos) * 64;
-    const bf16_t *Kh = a.Kc + hb + lane * 8, *Vh = a.Vc + hb + lane * 8;
+    const bf16_t *Kh = a.Kc + hb, *Vh = a.Vc + hb;
     const int nblk = (T + 31) >> 5;
+    // The workgroups of a head start at different blocks: side by side they would all wait for the same lines from HBM, and a compute unit
+    // has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
+    const int turn = nblk * (int)blockIdx.y / (int)gridDim.y;
+    auto at_turn = [&](int i) { return i + turn < nblk ? i + turn : i + turn - nblk; };
+    // Loads are unconditional, so that the waits count exactly the loads behind: past the last block every lane reads the same
+    // 16 bytes, which is one line.
     auto load_block = [&](int blk, uint4 (&kvb)[8]) {
-        const uint32_t off = (uint32_t)min(blk, nblk - 1) * 2048u;
+        const uint32_t off = blk < nblk ? (uint32_t)at_turn(blk) * 2048u + lane * 8u : 0u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { kvb[i] = ldg4(Kh + off + i * 512); kvb[4 + i] = ldg4(Vh + off + i * 512); }
+        for (int i = 0; i < 4; ++i) { kvb[i] = ldg4(Kh + (off + i * 512)); kvb[4 + i] = ldg4(Vh + (off + i * 512)); }
     };
     constexpr float SCALE = 0.125f * 1.44269504088896340736f;   // head dim 64; powers of two
     float m_run[QT], l_run[QT];
@@ -1028,14 +1054,23 @@ __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(Att
 #pragma unroll
         for (int i = 0; i < 4; ++i) O[t][i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     }
-    constexpr int NB = NW > 4 ? 2 : 3;   // one block, or with few waves two, in flight behind the one being computed
     uint4 buf[NB][8];
     if (wave < nblk) {
 #pragma unroll
         for (int j = 0; j < NB - 1; ++j) load_block(wave + NW * j, buf[j]);
     }
+    // Which of the eight keys m .. m + 7 of this forward (negative: committed ones) the lane's query sees, without a branch: bits of its
+    // mask row, or in a causal pass keys up to its own.
+    auto visible = [&](int t, int m) -> unsigned {
+        if constexpr (CAUSAL) return (1u << max(0, min(8, node[t] + 1 - m))) - 1u;
+        const int at = max(m, 0), w = at >> 5, sh = at & 31, before = min(8, at - m);
+        const uint32_t lo = w == 0 ? mw[t].x : w == 1 ? mw[t].y : w == 2 ? mw[t].z : w == 3 ? mw[t].w : 0u;
+        const uint32_t hi = w == 0 ? mw[t].y : w == 1 ? mw[t].z : w == 2 ? mw[t].w : 0u;
+        const uint32_t bits = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 0xffu;
+        return ((bits << before) | ((1u << before) - 1u)) & 0xffu;
+    };
     auto process = [&](const int blk, const uint4 (&cur)[8]) {
-        const int p0 = blk << 5, v0 = p0 + 8 * gq;
+        const int p0 = at_turn(blk) << 5, v0 = p0 + 8 * gq;
         uint32_t pk[QT][4];
         float m_new[QT], psum[QT];
 #pragma unroll
@@ -1063,21 +1098,7 @@ __global__ __launch_bounds__(64 * NW, NW > 4 && QT == 1 ? 4 : 1) void k_attn(Att
                 }
             };
             if (p0 + 32 > L + (CAUSAL ? min((qt0 + t) * 16, M - 1) + 1 : 0)) {   // the block reaches into this forward's rows, behind the tile's first query (same for the whole wave)
-                unsigned okm = 0;   // which of the lane's 8 keys the query may see
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int key = v0 + j, mm = key - L;
-                    bool okj = key < L;
-                    if (!okj && key < T) {
-                        if constexpr (CAUSAL) okj = mm <= node[t];
-                        else {
-                            const uint32_t w = mm < 32 ? mw[t].x : mm < 64 ? mw[t].y : mm < 96 ? mw[t].z : mw[t].w;
-                            okj = (w >> (mm & 31)) & 1u;
-                        }
-                    }
-                    okm |= okj ? (1u << j) : 0u;
-                }
-                softmax_block(okm);
+                softmax_block(visible(t, v0 - L));
             } else {
                 softmax_block(0xffu);
             }
@@ -1249,9 +1270,10 @@ static LinShape lin_shape(int R, int NT) {
     return best;
 }
 
-template <int RT, int CT, int CH, int EPI>
-static void lin_launch(const LinArgs& a, hipStream_t st, int nz = 1) {
-    launch((k_lin<RT, CT, CH, EPI>), dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(256), 0, st, a);
+template <int RT, int CT, int CH, int EPI, int NW = 4>
+static void lin_launch(LinArgs a, hipStream_t st, int nz = 1) {
+    a.per_block = (size_t)a.R * a.nks * 64 <= (3u << 20) ? 65536 / cdiv(a.R, RT * 16) : 0;   // (while an L2 of 4 MiB holds what its workgroups read)
+    launch((k_lin<RT, CT, CH, EPI, NW>), dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(64 * NW), 0, st, a);
 }
 // The tiles of `rows` rows x 16 `ct` columns; an XCD's eighth of them: about as many columns as rows.
 static TileGrid tile_grid(const LinArgs& a, int rows, int ct) {
@@ -1304,6 +1326,19 @@ static void lin(LinArgs& a, int big_min, hipStream_t st) {
         if (s.rt == 2 && s.ct == 1) { lin_launch<2, 1, 8, EPI>(a, st); return; }
         if (s.rt == 4 && s.ct == 2) { lin_launch<4, 2, 4, EPI>(a, st); return; }
     }
+    if constexpr (EPI == LE_RESID) {
+        // Long reductions: eight waves, so that a compute unit's 128 to 256 KB are all in flight instead of half of them (K = 4096, us:
+        // 64 rows 6.7 -> 6.5, 135 rows 10.0 -> 9.3, 320 rows 13.2 -> 12.8, 512 rows 13.6 -> 13.1; sixteen spill).
+        if (a.nks >= 64) {
+            switch (s.rt * 8 + s.ct) {
+            case 1 * 8 + 1: lin_launch<1, 1, 8, EPI, 8>(a, st); return;
+            case 1 * 8 + 2: lin_launch<1, 2, 4, EPI, 8>(a, st); return;
+            case 2 * 8 + 2: lin_launch<2, 2, 4, EPI, 8>(a, st); return;
+            case 2 * 8 + 4: lin_launch<2, 4, 2, EPI, 8>(a, st); return;
+            default: break;
+            }
+        }
+    }
     switch (s.rt * 8 + s.ct) {
     case 1 * 8 + 1: lin_launch<1, 1, 8, EPI>(a, st); break;
     case 1 * 8 + 2: lin_launch<1, 2, 8, EPI>(a, st); break;
@@ -1324,11 +1359,11 @@ static void clock_point(const DevState& s, int ph, hipStream_t st) {
 #endif
 }
 
-template <int QT, int NW>
+template <int QT, int NW, int NB>
 static void attn_launch(const AttnArgs& t, bool causal, hipStream_t st) {
     const dim3 grid(pad8(t.B * t.nH), t.x_last ? 1 : cdiv(cdiv(t.M, 16), QT));
-    if (causal) launch((k_attn<true, QT, NW>), grid, dim3(64 * NW), 0, st, t);
-    else launch((k_attn<false, QT, NW>), grid, dim3(64 * NW), 0, st, t);
+    if (causal) launch((k_attn<true, QT, NW, NB>), grid, dim3(64 * NW), 0, st, t);
+    else launch((k_attn<false, QT, NW, NB>), grid, dim3(64 * NW), 0, st, t);
 }
 // keys: an upper bound of the longest sequence's keys.
 static void attn(const AttnArgs& t, bool causal, int keys, int big_min, hipStream_t st) {
@@ -1336,11 +1371,11 @@ static void attn(const AttnArgs& t, bool causal, int keys, int big_min, hipStrea
     // two query tiles from two workgroups per compute unit on; waves: every one with a key block to take, up to four per SIMD
     const bool two = qt > 1 && t.B * t.nH * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512);
     const int wgs = t.B * t.nH * (two ? cdiv(qt, 2) : qt);
-    if (two && blocks >= 32 && wgs <= 512) attn_launch<2, 8>(t, causal, st);
-    else if (two) attn_launch<2, 4>(t, causal, st);
-    else if (blocks >= 32 && wgs <= 256) attn_launch<1, 16>(t, causal, st);
-    else if (blocks >= 10 && wgs <= 512) attn_launch<1, 8>(t, causal, st);
-    else attn_launch<1, 4>(t, causal, st);
+    if (two && blocks >= 32 && wgs <= 512) attn_launch<2, 8, 2>(t, causal, st);
+    else if (two) attn_launch<2, 4, 3>(t, causal, st);
+    else if (blocks >= 32 && wgs <= 256) attn_launch<1, 8, 3>(t, causal, st);
+    else if (blocks >= 10 && wgs <= 512) attn_launch<1, 8, 2>(t, causal, st);
+    else attn_launch<1, 4, 3>(t, causal, st);
 }
 
 void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st) {
