@@ -90,163 +90,170 @@ __device__ inline int dev_edge(const Dims& D, const DevState& s, int b, int n, i
     return wave_sum_i_dpp(cnt) < tau;
 }
 
-// Sec. 2.3's choice from the edge decisions in s_edge (LDS, complete and visible on entry):
-// path_ok[n] = every edge from the root to n accepted; the chosen node is the deepest such
-// node, smallest index among equals (canonical order = leftmost).
-// Output: path[b] = {count, node indices...}; the count is cut after the first EOS.
-__device__ inline void dev_choose(const Dims& D, const DevState& s, int b, int ignore_eos, const int* s_edge, int* s_ok) {
-    int32_t* path = s.path + (size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2);
-    const int32_t* parent = s.t_parent[0];
-    const int32_t* depth = s.t_depth[0];
-    const int32_t* tok = s.tok + (size_t)b * D.M;
-    // the tree tables go to LDS once: the walks below would otherwise pay a memory latency per hop
-    __shared__ int s_par[VADUSA_MAX_TREE_NODES];
-    __shared__ int s_key[VADUSA_MAX_TREE_NODES];
-    for (int n = threadIdx.x; n < D.M; n += 256) s_par[n] = ldg(parent + n);
-    __syncthreads();
-    for (int n = threadIdx.x; n < D.M; n += 256) {
-        int ok = 1, m = n;
-        while (m > 0) { ok &= s_edge[m]; m = s_par[m]; }
-        s_ok[n] = ok;
-        // deepest accepted node, smallest index among equals: largest depth * 256 + (255 - n)
-        s_key[n] = ok ? ldg(depth + n) * 256 + (255 - n) : -1;
+// An accepted path in LDS: number of nodes, the nodes and their tokens.
+struct PathLds { int cnt, node[VADUSA_MAX_DRAFT_HEADS + 1], tok[VADUSA_MAX_DRAFT_HEADS + 1]; };
+
+// Sec. 2.3's choice for sequence b from the edge decisions in edge_ok (dev_edge): a node is accepted iff every edge from the root to
+// it is; the chosen one is the deepest, smallest index among equals (canonical order = leftmost).  Cut after the first EOS.
+// Output: p, and path[b] = {count, node indices...} in memory for the compaction.  256 threads; everything it reads from memory is
+// asked for at once, and what the walks need sits in LDS (a step's chain of dependent loads is what bounds it).
+__device__ inline void dev_select(const Dims& D, const DevState& s, int b, int ignore_eos, PathLds& p) {
+    __shared__ int s_par[VADUSA_MAX_TREE_NODES], s_edge[VADUSA_MAX_TREE_NODES], s_tok[VADUSA_MAX_TREE_NODES], s_key[2];
+    const int n = threadIdx.x;
+    const bool node = n < D.M;
+    const int fin = ldg(s.finished + b);
+    int par = 0, dep = 0, edge = 0, tok = 0;
+    if (node) {
+        par = ldg(s.t_parent[0] + n);
+        dep = ldg(s.t_depth[0] + n);
+        tok = ldg(s.tok + (size_t)b * D.M + n);
+        edge = D.M > 1 ? ldg(s.edge_ok + (size_t)b * D.M + n) : !fin;   // (a tree of the root alone has no edge to test)
+        if (D.M == 1) s.edge_ok[b] = edge;
+        s_par[n] = par;
+        s_edge[n] = edge;
+        s_tok[n] = tok;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int key = -1;
-        for (int n0 = 0; n0 < D.M; n0 += 8) {
-            int kq[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) kq[q] = s_key[(n0 + q) & (VADUSA_MAX_TREE_NODES - 1)];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) if (n0 + q < D.M && kq[q] > key) key = kq[q];
-        }
-        const int best = key < 0 ? 0 : 255 - (key & 255);
-        int cnt = (key < 0 ? 0 : key >> 8) + 1;
-        int m = best;
-        int nodes[VADUSA_MAX_DRAFT_HEADS + 1];
-        for (int j = cnt - 1; j >= 0; --j) { nodes[j] = m; m = s_par[m]; }
+    int key = -1;   // deepest accepted node, smallest index among equals: largest depth * 256 + (255 - n)
+    if (node) {
+        int ok = 1, m = n;
+        while (m > 0) { ok &= s_edge[m]; m = s_par[m]; }
+        if (ok) key = dep * 256 + (255 - n);
+    }
+    if (n < VADUSA_MAX_TREE_NODES) {   // (two waves)
+        key = max(key, dpp_perm<0xB1>(key));
+        key = max(key, dpp_perm<0x4E>(key));
+        key = max(key, dpp_perm<0x141>(key));
+        key = max(key, dpp_perm<0x140>(key));
+        key = max(max(__builtin_amdgcn_readlane(key, 0), __builtin_amdgcn_readlane(key, 16)), max(__builtin_amdgcn_readlane(key, 32), __builtin_amdgcn_readlane(key, 48)));
+        if ((n & 63) == 0) s_key[n >> 6] = key;
+    }
+    __syncthreads();
+    if (n == 0) {
+        key = max(s_key[0], s_key[1]);
+        int32_t* path = s.path + (size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2);
+        int cnt = fin ? 0 : (key < 0 ? 0 : key >> 8) + 1, m = key < 0 ? 0 : 255 - (key & 255);
+        for (int j = cnt - 1; j >= 0; --j) { p.node[j] = m; p.tok[j] = s_tok[m]; m = s_par[m]; }
         if (!ignore_eos)
             for (int j = 0; j < cnt; ++j)
-                if (ldg(tok + nodes[j]) == D.V1 - 1) { cnt = j + 1; break; }
-        for (int j = 0; j < cnt; ++j) stwi(path + 1 + j, nodes[j]);
-        stwi(path, cnt);
+                if (p.tok[j] == D.V1 - 1) { cnt = j + 1; break; }
+        for (int j = 0; j < cnt; ++j) path[1 + j] = p.node[j];
+        path[0] = cnt;
+        p.cnt = cnt;
     }
     __syncthreads();
 }
 
-// Sec. 2.3's choice for sequence b from the edge decisions in edge_ok (dev_edge).
-__device__ inline void dev_select(const Dims& D, const DevState& s, int b, int ignore_eos) {
-    __shared__ int s_edge[VADUSA_MAX_TREE_NODES];
-    __shared__ int s_ok[VADUSA_MAX_TREE_NODES];
-    if (s.finished[b]) {
-        if (threadIdx.x == 0) stwi(s.path + (size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2), 0);
-        return;
+// The path of sequence b that waits in memory (chosen earlier, or forced by the caller).
+__device__ inline void dev_load_path(const Dims& D, const DevState& s, int b, PathLds& p) {
+    const int32_t* path = s.path + (size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2);
+    const int j = threadIdx.x;
+    if (j <= VADUSA_MAX_DRAFT_HEADS) {
+        const int cnt = ldg(path), m = ldg(path + 1 + j);
+        if (j < cnt) { p.node[j] = m; p.tok[j] = ldg(s.tok + (size_t)b * D.M + m); }
+        if (j == 0) p.cnt = cnt;
     }
-    for (int n = threadIdx.x; n < D.M; n += 256) s_edge[n] = s.edge_ok[b * D.M + n];
     __syncthreads();
-    dev_choose(D, s, b, ignore_eos, s_edge, s_ok);
 }
 
 // Continue from the last accepted node (Sec. 2.1): advance L, append the
 // accepted tokens to the output, next root = best logit of that node's row, and
 // its final-LayerNorm'd hidden state for the draft heads (operand tiles in the bf16 model).  acc_len[b] keeps the number
 // of committed rows for the compaction that follows.  In prefill mode the
-// "path" is the chunk's last row and nothing is emitted.
+// "path" is the chunk's last row and nothing is emitted (p is not read).  host (or null): where the caller wants the results, laid out like
+// the block that starts at kerr (after a prefill: the error word and the first roots).
 template <class T>
-__device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int prefill_mode, int ignore_eos) {
+__device__ inline void dev_finalize(const Dims& D, const DevState& s, int b, int prefill_mode, int ignore_eos, const PathLds& p, int32_t* host) {
     __shared__ float s_red[8];
-    int32_t* path = s.path + (size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2);
-    int cnt, last;
-    if (prefill_mode) {
-        cnt = s.n_rows[b];
-        last = cnt - 1;
-    } else {
-        cnt = ldci(path);
-        last = cnt > 0 ? ldci(path + cnt) : 0;
+    constexpr int W = VADUSA_MAX_DRAFT_HEADS + 1;
+    const int cnt = prefill_mode ? ldg(s.n_rows + b) : p.cnt;
+    const int L = ldg(s.L + b), no = prefill_mode ? 0 : ldg(s.n_out + b), old_root = ldg(s.root + b);
+    if (host && b == 0 && threadIdx.x < 4) host[threadIdx.x] = ldg(s.kerr + threadIdx.x);
+    if (threadIdx.x == 0) s.acc_len[b] = prefill_mode ? 0 : cnt;
+    if (cnt <= 0) {
+        if (host && !prefill_mode && threadIdx.x == 0) { host[4 + b] = 0; host[4 + D.Bmax + b] = L; host[4 + 2 * D.Bmax + b] = old_root; }
+        return;
     }
-    if (threadIdx.x == 0) stwi(s.acc_len + b, prefill_mode ? 0 : cnt);
-    if (cnt <= 0) return;
-    const int32_t* tok = s.tok + (size_t)b * D.M;
+    const int last = prefill_mode ? cnt - 1 : p.node[cnt - 1];
     const int r = prefill_mode && D.last_only ? b : (prefill_mode && s.row0 ? ldg(s.row0 + b) : b * D.M) + last;
+    // final LayerNorm of the accepted node's residual row: read once, into registers (up to 16 values per
+    // thread, d <= 4096; larger rows take the three-pass route below), ahead of the row of logits
+    const float* xr = s.x + (size_t)r * D.d;
+    float xv[16], gv[16], bv[16];
+    if (D.d <= 4096) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int i = threadIdx.x * 2 + 512 * j;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                xv[2 * j + q] = i < D.d ? ldg(xr + i + q) : 0.f;
+                gv[2 * j + q] = i < D.d ? ldg(s.lnf_g + i + q) : 0.f;
+                bv[2 * j + q] = i < D.d ? ldg(s.lnf_b + i + q) : 0.f;
+            }
+        }
+    }
     const int root = block_argbest(s.logits + (size_t)r * D.V1, D.V1, INFINITY, -1, nullptr);
+    if (threadIdx.x == 0) {
+        s.root[b] = root;
+        s.L[b] = L + cnt;
+        if (host && prefill_mode) host[4 + b] = root;
+        if (!prefill_mode) {
+            bool fin = false;
+            for (int j = 0; j < cnt; ++j) {
+                const int t = p.tok[j];
+                s.acc_tok[b * W + j] = t;
+                if (no + j < D.maxpos) s.out_tok[(size_t)b * D.maxpos + no + j] = t;
+                if (t == D.V1 - 1) fin = true;
+                if (host) host[4 + 3 * D.Bmax + b * W + j] = t;
+            }
+            s.n_out[b] = min(no + cnt, max(no, D.maxpos));
+            s.path[(size_t)b * (VADUSA_MAX_DRAFT_HEADS + 2)] = 0;   // consumed
+            if (fin && !ignore_eos) s.finished[b] = 1;
+            if (host) { host[4 + b] = cnt; host[4 + D.Bmax + b] = L + cnt; host[4 + 2 * D.Bmax + b] = root; }
+        }
+    }
     auto store = [&](int i, float a, float c) {
         if constexpr (sizeof(T) == 4) *(float2*)((float*)s.hbest + (size_t)b * D.d + i) = make_float2(a, c);
-        else stw32((bf16_t*)s.hbest + toff(b, i, D.d >> 5), pack_bf16(a, c));   // tiled for the draft maps
+        else *(uint32_t*)((bf16_t*)s.hbest + toff(b, i, D.d >> 5)) = pack_bf16(a, c);   // tiled for the draft maps
     };
-    {
-        // final LayerNorm of the accepted node's residual row: read once, into registers (up to 16 values per
-        // thread, d <= 4096; larger rows take the three-pass route below)
-        const float* xr = s.x + (size_t)r * D.d;
-        if (D.d <= 4096) {
-            float xv[16];
-            float sum = 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int i = threadIdx.x * 2 + 512 * j;
-                xv[2 * j] = i < D.d ? ldcf(xr + i) : 0.f;
-                xv[2 * j + 1] = i < D.d ? ldcf(xr + i + 1) : 0.f;
-                sum += xv[2 * j] + xv[2 * j + 1];
-            }
-            sum = wave_sum_dpp(sum);
-            if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = sum;
-            __syncthreads();
-            const float mu = (s_red[0] + s_red[1] + s_red[2] + s_red[3]) / D.d;
-            float sq = 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int i = threadIdx.x * 2 + 512 * j;
-                if (i < D.d) { const float t0 = xv[2 * j] - mu, t1 = xv[2 * j + 1] - mu; sq += t0 * t0 + t1 * t1; }
-            }
-            sq = wave_sum_dpp(sq);
-            if ((threadIdx.x & 63) == 0) s_red[4 + (threadIdx.x >> 6)] = sq;
-            __syncthreads();
-            const float rstd = rsqrtf((s_red[4] + s_red[5] + s_red[6] + s_red[7]) / D.d + LN_EPS);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int i = threadIdx.x * 2 + 512 * j;
-                if (i < D.d) {
-                    const float a = (xv[2 * j] - mu) * rstd * ldg(s.lnf_g + i) + ldg(s.lnf_b + i);
-                    const float c2 = (xv[2 * j + 1] - mu) * rstd * ldg(s.lnf_g + i + 1) + ldg(s.lnf_b + i + 1);
-                    store(i, a, c2);
-                }
-            }
-        } else {
+    if (D.d <= 4096) {
         float sum = 0.f;
-        for (int i = threadIdx.x; i < D.d; i += 256) sum += ldcf(xr + i);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum += xv[2 * j] + xv[2 * j + 1];
         sum = wave_sum_dpp(sum);
         if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = sum;
         __syncthreads();
         const float mu = (s_red[0] + s_red[1] + s_red[2] + s_red[3]) / D.d;
         float sq = 0.f;
-        for (int i = threadIdx.x; i < D.d; i += 256) { const float t = ldcf(xr + i) - mu; sq += t * t; }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int i = threadIdx.x * 2 + 512 * j;
+            if (i < D.d) { const float t0 = xv[2 * j] - mu, t1 = xv[2 * j + 1] - mu; sq += t0 * t0 + t1 * t1; }
+        }
         sq = wave_sum_dpp(sq);
         if ((threadIdx.x & 63) == 0) s_red[4 + (threadIdx.x >> 6)] = sq;
         __syncthreads();
         const float rstd = rsqrtf((s_red[4] + s_red[5] + s_red[6] + s_red[7]) / D.d + LN_EPS);
-        for (int i = threadIdx.x * 2; i < D.d; i += 512) {
-            const float a = (ldcf(xr + i) - mu) * rstd * s.lnf_g[i] + s.lnf_b[i];
-            const float c2 = (ldcf(xr + i + 1) - mu) * rstd * s.lnf_g[i + 1] + s.lnf_b[i + 1];
-            store(i, a, c2);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int i = threadIdx.x * 2 + 512 * j;
+            if (i < D.d) store(i, (xv[2 * j] - mu) * rstd * gv[2 * j] + bv[2 * j], (xv[2 * j + 1] - mu) * rstd * gv[2 * j + 1] + bv[2 * j + 1]);
         }
-        }
-    }
-    if (threadIdx.x == 0) {
-        stwi(s.root + b, root);
-        stwi(s.L + b, s.L[b] + cnt);
-        if (!prefill_mode) {
-            int no = s.n_out[b];
-            bool fin = false;
-            for (int j = 0; j < cnt; ++j) {
-                const int t = tok[ldci(path + 1 + j)];
-                stwi(s.acc_tok + b * (VADUSA_MAX_DRAFT_HEADS + 1) + j, t);
-                if (no < D.maxpos) stwi(s.out_tok + (size_t)b * D.maxpos + no++, t);
-                if (t == D.V1 - 1) fin = true;
-            }
-            stwi(s.n_out + b, no);
-            stwi(path, 0);   // consumed
-            if (fin && !ignore_eos) stwi(s.finished + b, 1);
-        }
+    } else {
+        float sum = 0.f;
+        for (int i = threadIdx.x; i < D.d; i += 256) sum += ldg(xr + i);
+        sum = wave_sum_dpp(sum);
+        if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = sum;
+        __syncthreads();
+        const float mu = (s_red[0] + s_red[1] + s_red[2] + s_red[3]) / D.d;
+        float sq = 0.f;
+        for (int i = threadIdx.x; i < D.d; i += 256) { const float t = ldg(xr + i) - mu; sq += t * t; }
+        sq = wave_sum_dpp(sq);
+        if ((threadIdx.x & 63) == 0) s_red[4 + (threadIdx.x >> 6)] = sq;
+        __syncthreads();
+        const float rstd = rsqrtf((s_red[4] + s_red[5] + s_red[6] + s_red[7]) / D.d + LN_EPS);
+        for (int i = threadIdx.x * 2; i < D.d; i += 512)
+            store(i, (ldg(xr + i) - mu) * rstd * s.lnf_g[i] + s.lnf_b[i], (ldg(xr + i + 1) - mu) * rstd * s.lnf_g[i + 1] + s.lnf_b[i + 1]);
     }
 }
 

@@ -539,6 +539,13 @@ static int fetch(vadusa_ctx* c, const int32_t* a, size_t na, const int32_t* b, s
     return VADUSA_OK;
 }
 
+// The results that the continuation has written into the pinned block.
+static int written(vadusa_ctx* c, const int32_t** out) {
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    *out = c->pinned;
+    return VADUSA_OK;
+}
+
 static int check_kerr(vadusa_ctx* c) {
     if (!c->cfg.dtype) return VADUSA_OK;
     int32_t k = 0;
@@ -654,12 +661,12 @@ extern "C" int vadusa_prefill(vadusa_ctx* c, int32_t batch, const int32_t* text_
         const bool last = ch == max_chunks - 1;
         // the chunk is a causal "tree"; the last one also runs the vocabulary map, the continuation and the draft heads
         forward(c, D, sp, 1, 1, last);
-        if (last) launch_continue(D, sp, c->draft, 0, batch, 1, c->cfg.ignore_eos, false, c->cfg.dtype, c->stream);
+        if (last) launch_continue(D, sp, c->draft, 0, batch, 1, c->cfg.ignore_eos, false, c->pinned, c->cfg.dtype, c->stream);
         else launch_advance(sp, batch, c->stream);
     }
     { int rc = launched(c); if (rc) return rc; }
     const int32_t* res = nullptr;
-    { int rc = fetch(c, s.kerr, 4, s.root, B, nullptr, 0, &res); if (rc) return rc; }
+    { int rc = c->pinned ? written(c, &res) : fetch(c, s.kerr, 4, s.root, B, nullptr, 0, &res); if (rc) return rc; }
     { int rc = kerr_seen(c, c->cfg.dtype ? res[0] : 0); if (rc) return rc; }
     if (first_root) memcpy(first_root, res + 4, B * 4);
     c->batch = batch;
@@ -708,7 +715,7 @@ static void mark_compacted(vadusa_ctx* c, int seq0, int nseq, int n_forced) {
 // Verification; with fuse_compact the compaction of every sequence's chosen path and the
 // draft heads follow at once.
 static int verify_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau, const int32_t* draft_override,
-                       bool fuse_compact, const vadusa_sampling* sp = nullptr) {
+                       bool fuse_compact, const vadusa_sampling* sp = nullptr, bool want_results = false) {
     if (!c) return VADUSA_EINVAL;
     { int rc = refuse_errored(c); if (rc) return rc; }
     if (c->state != 2) return fail(c, VADUSA_ESTATE, c->state == 3 ? "a verification is still waiting for vadusa_kv_compact" : "prefill first");
@@ -769,7 +776,7 @@ static int verify_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau,
     if (sp) launch_perturb(s.logits, c->uniforms, c->scores, B * M, D.V1, sp->temperature, sp->top_p, tau, c->stream);
     // the path is chosen beside the continuation where that follows at once
     launch_verify_tail(D, sr, tau, c->cfg.ignore_eos, !fuse_compact, c->stream);
-    if (fuse_compact) launch_continue(D, sr, c->draft, 0, B, 0, c->cfg.ignore_eos, true, c->cfg.dtype, c->stream);
+    if (fuse_compact) launch_continue(D, sr, c->draft, 0, B, 0, c->cfg.ignore_eos, true, want_results ? c->pinned : nullptr, c->cfg.dtype, c->stream);
     rc = launched(c);
     if (rc) return rc;
     c->state = 3;
@@ -819,7 +826,7 @@ extern "C" int vadusa_kv_compact(vadusa_ctx* c, int32_t seq, const int32_t* path
     }
     DevState sr = s;
     if (c->sampled) sr.logits = c->scores;   // the next root is the first draw at the last committed node
-    launch_continue(D, sr, c->draft, seq0, nseq, 0, c->cfg.ignore_eos, false, c->cfg.dtype, c->stream);
+    launch_continue(D, sr, c->draft, seq0, nseq, 0, c->cfg.ignore_eos, false, nullptr, c->cfg.dtype, c->stream);
     { int rc = launched(c); if (rc) return rc; }
     mark_compacted(c, seq0, nseq, path_nodes ? n : 0);
     return VADUSA_OK;
@@ -829,12 +836,12 @@ static int step_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau, c
                      const int32_t* draft_override, int32_t* accepted_tok, int32_t* accepted_len) {
     if ((accepted_tok == nullptr) != (accepted_len == nullptr))
         return fail(c, VADUSA_EINVAL, "accepted_tok and accepted_len must both be given or both be null");
-    int rc = verify_impl(c, tree, tau, draft_override, true, sp);
+    int rc = verify_impl(c, tree, tau, draft_override, true, sp, accepted_tok != nullptr);
     if (rc) return rc;
     if (accepted_tok) {
         const int B = c->batch, W = VADUSA_MAX_DRAFT_HEADS + 1, Hh1 = c->cfg.n_draft_heads + 1;
         const int32_t* blk = nullptr;
-        rc = fetch(c, c->s.kerr, result_words(c->cfg), nullptr, 0, nullptr, 0, &blk);
+        rc = c->pinned ? written(c, &blk) : fetch(c, c->s.kerr, result_words(c->cfg), nullptr, 0, nullptr, 0, &blk);
         if (rc) return rc;
         rc = kerr_seen(c, c->cfg.dtype ? blk[0] : 0);
         if (rc) return rc;

@@ -57,9 +57,6 @@ __device__ __forceinline__ void stwi(int32_t* p, int32_t v) { stw32(p, (uint32_t
 __device__ __forceinline__ int32_t ldci(const int32_t* p) {
     return __hip_atomic_load((const VADUSA_GLOBAL int32_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float ldcf(const float* p) {
-    return __uint_as_float(__hip_atomic_load((const VADUSA_GLOBAL uint32_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
 // Offset of element (r, k) of a bf16 activation matrix kept in MFMA-operand tiles:
 // [row tile of 16][k-step of 32][lane = (r & 15) + 16 * ((k & 31) >> 3)][k & 7], nks = K / 32.
 // A wave reads one (row tile, k-step) as the A operand with one contiguous KiB load.
@@ -315,8 +312,9 @@ enum { TP_HEAD = 0, TP_EDGES, TP_SELECT, TP_FINAL, TP_COMMIT, TP_DRAFT2, TP_TOPK
 void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st);
 // edge decisions, and (select) the path choice of every sequence
 void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eos, bool select, hipStream_t st);
-// (select: path choice,) continuation, draft heads, draft lists and KV compaction
-void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, int dtype, hipStream_t st);
+// (select: path choice,) continuation, draft heads, draft lists and KV compaction; host: memory the GPU can write that takes the results (see
+// dev_finalize), or null
+void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, int32_t* host, int dtype, hipStream_t st);
 void launch_pack_w_ln(const float* src, const float* gamma, const float* beta, void* dst, float* colsum,
                       float* tvec, int N, int K, hipStream_t st);
 void launch_add_vec(float* dst, const float* src, int n, hipStream_t st);
