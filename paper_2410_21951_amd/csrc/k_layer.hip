@@ -324,10 +324,10 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
 // What bounds it: no single unit.  FFN1 of 1024 rows takes 17 us in a step; its products keep a SIMD's matrix core busy
 // for 3.4 us of them, and a compute unit pulls 0.8 MB through L2.  512 workgroups are 0.67 rounds of the 768 that fit, each with its
 // statistics, 16 stages with a barrier, GELU and stores one behind the other.
-// Tiles numbered in blocks per XCD (a column of tiles per XCD before: eight times all activations into the L2s), results stored as whole
-// 16-byte pieces, statistics per 32 columns, values of a piece of the cache in one store (us, before and after, weights from HBM):
-// out-projection of 2048 rows 15.0 -> 13.5, FFN2 of 3200 rows 46.3 -> 42.2, of 4352 rows 68.6 -> 62.4, QKV of 3200 rows 37.9 -> 36.0, FFN1 of
-// 2048 rows 31.6 -> 30.5.
+// Residual maps: tiles numbered in blocks per XCD (with a column of tiles per XCD all activations go into every L2), statistics per
+// 32 columns; bf16 results as whole 16-byte pieces (us, before and after, weights from HBM): out-projection of 2048 rows 15.0 -> 13.2, FFN2 of
+// 3200 rows 46.4 -> 42.5, of 4352 rows 68.6 -> 62.4; FFN1 of 640 rows 15.4 -> 14.3, of 1024 rows 18.2 -> 17.4.  The other maps keep the column
+// numbering: their activations fit an L2, and finding the block costs more than it gives (QKV of 1024 rows 16.8 against 17.6).
 // ---------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 // D = A B + C, A 32 x 16 (lane: row lane & 31, k 8 (lane >> 5) ..), B 16 x 32 alike; lane l, element i of D: column
@@ -355,7 +355,7 @@ __device__ __forceinline__ f32x16_t mfma_32x32(uint4 a, uint4 b, f32x16_t c) {
 // bf16 results change places between the two lanes first, so that each has eight consecutive columns, a whole piece of an
 // operand tile: with half pieces every cache line is written in two parts.
 template <int EPI>
-__device__ __forceinline__ void store16(const LinArgs& a, int r, int n0, int hi, float (&v)[8], const KvRow& kv, uint4* v_row) {
+__device__ __forceinline__ void store16(const LinArgs& a, int r, int n0, int hi, float (&v)[8], const KvRow& kv) {
     const bool live = r < a.R;
     if constexpr (EPI == LE_LOGITS) {
 #pragma unroll
@@ -374,67 +374,19 @@ __device__ __forceinline__ void store16(const LinArgs& a, int r, int n0, int hi,
     if constexpr (EPI == LE_GELU)
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = gelu_s(v[j]);
+    if constexpr (EPI == LE_QKV) {
+        // (half pieces: a store of values wants the two lanes' dimensions four apart, in the same line; through LDS into whole pieces of eight
+        // positions it took 1 to 2 us more)
+        const float lo[4] = {v[0], v[1], v[2], v[3]}, up[4] = {v[4], v[5], v[6], v[7]};
+        store4<EPI>(a, r, n0 + 4 * hi, live, lo, kv);
+        store4<EPI>(a, r, n0 + 8 + 4 * hi, live, up, kv);
+        return;
+    }
     const vadusa_u32x2 p = __builtin_amdgcn_permlane32_swap(pack_bf16(v[0], v[1]), pack_bf16(v[4], v[5]), false, false);
     const vadusa_u32x2 q = __builtin_amdgcn_permlane32_swap(pack_bf16(v[2], v[3]), pack_bf16(v[6], v[7]), false, false);
     const uint4 pk = make_uint4(p.x, q.x, p.y, q.y);   // columns n .. n + 7
     const int n = n0 + 8 * hi;
-    if constexpr (EPI == LE_QKV) {
-        if (n < a.d) {
-            if (live) *(uint4*)(a.out + toff(r, n, a.d >> 5)) = pk;
-        } else if (n < 2 * a.d) {
-            const int head = (n - a.d) >> 6, dim = (n - a.d) & 63;
-            if (kv.pos >= 0) *(uint4*)(a.Kc + kv.base + (size_t)head * kv_cap(a.maxpos) * 64 + kc_off(kv.pos, dim)) = pk;   // eight dimensions of one key: a lane's piece
-        } else {
-            v_row[hi] = pk;
-        }
-    } else {
-        if (live) *(uint4*)(a.out + toff(r, n, a.N >> 5)) = pk;
-    }
-}
-
-// The wave's LDS writes so far come before its LDS reads from here on.
-__device__ __forceinline__ void wave_sync() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_wave_barrier();
-#else
-    (void)__shfl(0u, 0, 64);
-#endif
-}
-
-// The values of ROWS rows from `first` on and COLS columns of one head (from value column `col` on), which the wave has left in
-// LDS, into the cache.  The cache keeps eight consecutive positions of a dimension side by side: a lane becomes a dimension and takes the rows
-// of one sequence that share such a piece, one store of 16 bytes where there are eight of them.  (From the lanes that hold rows it
-// takes eight stores of two bytes, each to ten lines.)
-template <int ROWS, int COLS>
-__device__ __forceinline__ void store_values(const LinArgs& a, int first, int col, const uint16_t* values, int lane) {
-    constexpr int STRIDE = COLS + 8;   // a row's columns and room for eight more: the rows start in different banks
-    const int head = col >> 6, dim = (col & 63) + lane, rows = min(ROWS, a.R - first);
-    const uint16_t* mine = values + lane % COLS;
-    wave_sync();
-    for (int j = 0; j < rows;) {
-        const int b = a.row_seq ? ldg(a.row_seq + first + j) : (first + j) / a.M, m0 = first + j - (a.row_seq ? ldg(a.row0 + b) : b * a.M);
-        const int have = ldg(a.n_rows + b), end = min(j + (a.row_seq ? have : a.M) - m0, rows), L = ldg(a.L + b);
-        const bool live = have > 0 && lane < COLS;
-        bf16_t* to = a.Vc + ((size_t)b * a.nH + head) * kv_cap(a.maxpos) * 64;
-        for (int pos = L + m0; j < end;) {
-            const int n = min(8 - (pos & 7), end - j);   // rows that share the piece
-            uint32_t e[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) e[k] = mine[min(j + k, ROWS - 1) * STRIDE];
-            if (live) {
-                bf16_t* p = to + vc_off(pos, dim);
-                if (n == 8 && pos + 8 <= a.maxpos) {
-                    *(uint4*)p = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        if (k < n && pos + k < a.maxpos) p[k] = (bf16_t)e[k];
-                }
-            }
-            j += n;
-            pos += n;
-        }
-    }
+    if (live) *(uint4*)(a.out + toff(r, n, a.N >> 5)) = pk;
 }
 
 // Which tile a workgroup takes.  Workgroup i runs on XCD i mod 8: every XCD gets an eighth of the tiles, consecutive in
@@ -451,7 +403,12 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
     __shared__ uint4 sA[4][NRT * 2 * 64];
     __shared__ float s_mean[ROWS], s_rstd[ROWS];
     int rb, ct0;   // row tile of 64, first column tile
-    {
+    if constexpr (EPI != LE_RESID) {
+        // Workgroup i runs on XCD i mod 8: the XCD has an eighth of the columns, whose weights leave HBM once.
+        rb = blockIdx.y;
+        ct0 = blockIdx.x * 4 * NCT;
+        if (ct0 >= a.NT) return;   // padding of that numbering
+    } else {
         const int n = g.gr * g.gc, xcd = blockIdx.x & 7, lo = (n * xcd) >> 3, i = lo + (int)(blockIdx.x >> 3);
         if (i >= (n * (xcd + 1)) >> 3) return;
         const int s = i / (g.gr * g.strip), in = i - s * g.gr * g.strip, w = min(g.strip, g.gc - s * g.strip);
@@ -571,9 +528,6 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
     }
     // Everything the epilogue reads arrives before its first store: a wait between the stores would wait for them too
     // (loads and stores share one counter).
-    constexpr int VS = 2 * NCT + 1;   // (QKV) pieces of a row of the wave's values, for store_values
-    uint4* values = &sA[0][0] + wave * ROWS * VS;
-    if constexpr (EPI == LE_QKV) __syncthreads();   // (every wave has its operands)
     const int lr = lane & 31, hi = lane >> 5;   // the lane's row of a 32-row block; its columns of a block: 8 q + 4 hi .. + 3, q = 0 .. 3
     KvRow kv[NR2];
     float mean[NR2], rstd[NR2];
@@ -639,11 +593,9 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
             }
 #pragma unroll
             for (int t = 0; t < 2; ++t)
-                if (wt0 + 2 * ci + t < a.NT) store16<EPI>(a, r, (wt0 + 2 * ci + t) * 16, hi, v[t], kv[ri], values + (ri * 32 + lr) * VS + 2 * (2 * ci + t));
+                if (wt0 + 2 * ci + t < a.NT) store16<EPI>(a, r, (wt0 + 2 * ci + t) * 16, hi, v[t], kv[ri]);
         }
     }
-    if constexpr (EPI == LE_QKV)
-        if (wt0 < a.NT && wt0 * 16 >= 2 * a.d) store_values<ROWS, 16 * NCT>(a, row0, wt0 * 16 - 2 * a.d, (const uint16_t*)values, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -880,9 +832,6 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
                 y[0][tt][4 * h] = v.x; y[0][tt][4 * h + 1] = v.y; y[0][tt][4 * h + 2] = v.z; y[0][tt][4 * h + 3] = v.w;
             }
     }
-    constexpr int VS = 2 * TB + 1;   // (QKV) pieces of a row of the wave's values, for store_values
-    uint4* values = ring + wave * 32 * RB * VS;
-    if constexpr (EPI == LE_QKV && KSP > 1) __syncthreads();   // (every wave has its sums)
     // Everything the epilogue reads has arrived before its first store: a wait between the stores would wait for them too
     // (loads and stores share one counter).
     if (tile0 >= a.NT) return;
@@ -940,10 +889,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
         }
 #pragma unroll
         for (int tt = 0; tt < TB; ++tt)
-            if (tile0 + tt < a.NT) store16<EPI>(a, r[i], (tile0 + tt) * 16, hi, y[i][tt], kv[i], values + (i * 32 + lr) * VS + 2 * tt);
-    }
-    if constexpr (EPI == LE_QKV) {
-        if (tile0 * 16 >= 2 * a.d) store_values<32 * RB, 16 * TB>(a, row0 + (rg * 2 + rb0) * 32, tile0 * 16 - 2 * a.d, (const uint16_t*)values, lane);
+            if (tile0 + tt < a.NT) store16<EPI>(a, r[i], (tile0 + tt) * 16, hi, y[i][tt], kv[i]);
     }
 }
 
@@ -1289,7 +1235,7 @@ template <int EPI>
 static void big_launch(LinArgs& a, hipStream_t st) {
     const TileGrid g = tile_grid(a, BIG_RT * 16, 4 * BIG_CT);
     a.sg_out = 5;
-    launch(k_big<EPI>, dim3(8 * cdiv(g.gr * g.gc, 8)), dim3(256), 0, st, a, g);
+    launch(k_big<EPI>, EPI == LE_RESID ? dim3(8 * cdiv(g.gr * g.gc, 8)) : dim3(pad8(g.gc), g.gr), dim3(256), 0, st, a, g);
 }
 template <int RG, int CG, int EPI>
 static void tile_launch(LinArgs& a, hipStream_t st) {
