@@ -206,7 +206,7 @@ struct DevState {
     // activations
     float* x;        // [R][d]  residual stream
     bf16_t* xb;      // bf16 model: [R][d] copy of the residual stream, operand tiles (rows padded to a multiple of 16)
-    float* stats;    // bf16 model: [R][d/16][2] per 16-column tile: mean, sum of squared deviations
+    float* stats;    // bf16 model: [R][groups][2] per group of 16, 32 or 64 columns: mean, sum of squared deviations
     size_t draft_stride;   // elements from one draft head's rdraft to the next
     int32_t* kerr;   // [4] error flag that the next synchronising call reports
     long long* tprof; // [128][8] timing points (device clock, 100 MHz; -DVADUSA_CLOCK_BUILD)

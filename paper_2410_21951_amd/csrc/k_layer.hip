@@ -11,10 +11,10 @@
 // LayerNorm is folded into the map that follows it:
 //   LN(x) W^T = rstd * (x (g*W)^T - mu * colsum(g*W)) + (beta W^T + bias),
 // so a map reads the bf16 copy of the raw residual stream and applies the row statistics in its epilogue.  The
-// statistics come from whoever wrote the residual stream (exact fp32 values, per 16 columns, [row][column tile]) and
-// are merged by the consumer: mean of the tile means; squared deviations = the tiles' own plus 16 x the spread of the
-// tile means, summed as distances from the row's first tile mean.  No atomics combine data: results are
-// bit-reproducible.
+// statistics come from whoever wrote the residual stream (exact fp32 values, per group of 16, 32 or 64 columns,
+// [row][group]) and are merged by the consumer: mean of the group means; squared deviations = the groups' own plus
+// their columns x the spread of the group means, summed as distances from the row's first group mean.  No atomics
+// combine data: results are bit-reproducible.
 #include <algorithm>
 #include <type_traits>
 
