@@ -44,50 +44,57 @@ __device__ __forceinline__ void wave_argbest(float& bv, int& bi) {
 }
 
 // Block-wide arg-best under the order above, restricted to entries that come
-// strictly after (pv, pi).  Every thread returns the winner.  256 threads.
-__device__ inline int block_argbest(const float* __restrict__ z, int n, float pv, int pi, float* best_val) {
-    __shared__ float sv[4];
-    __shared__ int si[4];
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int v0 = threadIdx.x; v0 < n; v0 += 256 * 4) {
-        float zv[4];
+// strictly after (pv, pi).  Every thread returns the winner.  64 NW threads, each with PER loads on their way at once: a round
+// is one trip to the L2 (k_continue with four and with 16 loads per round, us per launch: 16 001 logits 12.3 -> 10.9; 1025 logits 6.4 either way).
+// Loads are unconditional; an index beyond the row re-reads its last entry and does not count.
+template <int NW, int PER>
+__device__ inline void argbest_scan(const float* __restrict__ z, int n, float pv, int pi, float& bv, int& bi) {
+    for (int v0 = threadIdx.x; v0 < n; v0 += 64 * NW * PER) {
+        float zv[PER];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) zv[j] = v0 + 256 * j < n ? z[v0 + 256 * j] : 0.f;
+        for (int j = 0; j < PER; ++j) zv[j] = ldg(z + min(v0 + 64 * NW * j, n - 1));
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int v = v0 + 256 * j;
+        for (int j = 0; j < PER; ++j) {
+            const int v = v0 + 64 * NW * j;
             if (v < n && before(pv, pi, zv[j], v) && before(zv[j], v, bv, bi)) { bv = zv[j]; bi = v; }
         }
     }
+}
+template <int NW = 4>
+__device__ inline int block_argbest(const float* __restrict__ z, int n, float pv, int pi, float* best_val) {
+    __shared__ float sv[NW];
+    __shared__ int si[NW];
+    float bv = -INFINITY;
+    int bi = 0x7fffffff;
+    if (n <= 64 * NW * 8) argbest_scan<NW, 8>(z, n, pv, pi, bv, bi);
+    else argbest_scan<NW, 16>(z, n, pv, pi, bv, bi);
     wave_argbest(bv, bi);
     __syncthreads();   // protects sv/si against the previous call's readers
     if ((threadIdx.x & 63) == 0) { sv[threadIdx.x >> 6] = bv; si[threadIdx.x >> 6] = bi; }
     __syncthreads();
     bv = sv[0]; bi = si[0];
-    for (int w = 1; w < 4; ++w) if (before(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
+    for (int w = 1; w < NW; ++w) if (before(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
     if (bi == 0x7fffffff) bi = 0;   // no entry qualifies (a row of NaN): still an index of the row
     if (best_val) *best_val = bv;
     return bi;
 }
 
 // Algorithm 1, one edge: node n of sequence b is accepted iff fewer than tau entries of its
-// parent's logit row rank before its token.  One wave; every lane returns the decision.
-__device__ inline int dev_edge(const Dims& D, const DevState& s, int b, int n, int tau) {
-    if (n == 0) return 1;
-    const int lane = threadIdx.x & 63;
+// parent's logit row rank before its token.  NW waves, of which this thread is number t0; returns this wave's count of such entries.
+template <int NW>
+__device__ inline int dev_edge_count(const Dims& D, const DevState& s, int b, int n, int t0) {
     const float* z = s.logits + ((size_t)b * D.M + s.t_parent[0][n]) * D.V1;
     const int t = s.tok[(size_t)b * D.M + n];
     const float zt = z[t];
     int cnt = 0;
-    for (int v0 = lane; v0 < D.V1; v0 += 64 * 17) {
+    for (int v0 = t0; v0 < D.V1; v0 += 64 * NW * 17) {
         float zv[17];
 #pragma unroll
-        for (int q = 0; q < 17; ++q) zv[q] = v0 + 64 * q < D.V1 ? z[v0 + 64 * q] : -INFINITY;
+        for (int q = 0; q < 17; ++q) zv[q] = v0 + 64 * NW * q < D.V1 ? z[v0 + 64 * NW * q] : -INFINITY;
 #pragma unroll
-        for (int q = 0; q < 17; ++q) cnt += (v0 + 64 * q < D.V1 && before(zv[q], v0 + 64 * q, zt, t)) ? 1 : 0;
+        for (int q = 0; q < 17; ++q) cnt += (v0 + 64 * NW * q < D.V1 && before(zv[q], v0 + 64 * NW * q, zt, t)) ? 1 : 0;
     }
-    return wave_sum_i_dpp(cnt) < tau;
+    return wave_sum_i_dpp(cnt);
 }
 
 // An accepted path in LDS: number of nodes, the nodes and their tokens.
@@ -316,11 +323,8 @@ __device__ inline void dev_commit_kv_layers(const Dims& D, const DevState& s, in
 // quad maxima are distinct entries of the row, so the row's 16th best entry is not after the
 // 16th best of them, T.  Every entry not after T is a candidate (two dozen for random logits);
 // each candidate counts the candidates before it, which is its place in the list.
-// More than 256 candidates (many equal or missing values), or more than 4096 logits: the
-// list is built one entry per round by re-scanning (block_argbest); with SLICED, rows of up to
-// 65536 logits first try the candidate scheme slice by slice (used by the stand-alone top-k
-// kernel, which serves large vocabularies).
-template <bool SLICED = false>
+// More than 256 candidates (many equal or missing values): the list is built one entry per round by
+// re-scanning (block_argbest).  Rows of more than 4096 logits are k_topk's.
 __device__ inline void dev_topk(const Dims& D, const DevState& s, int i, int b) {
     __shared__ float c_v[256];
     __shared__ int c_i[256];
@@ -332,76 +336,8 @@ __device__ inline void dev_topk(const Dims& D, const DevState& s, int i, int b) 
     const float* z = s.zdraft + ((size_t)i * D.Bmax + b) * D.V1;
     int32_t* out = s.draft_topk + ((size_t)b * D.Hh + i) * VADUSA_MAX_TOPK;
     const int kmax = D.V1 < VADUSA_MAX_TOPK ? D.V1 : VADUSA_MAX_TOPK;
-    bool rescan = D.V1 > 256 * 16;
-    if constexpr (SLICED) {
-        if (rescan) {
-            // More than 4096 logits: the same scheme over slices of 4096.  First pass: the 16 group
-            // maxima of every slice go to LDS (at most 256 of them: V1 <= 65536) and T is the 16th
-            // best of these, again an entry of the row with at least 15 others before it.  Second
-            // pass: every entry not after T is a candidate.
-            const int nsl = (D.V1 + 4095) / 4096;
-            if (nsl <= 16) {
-                for (int sl = 0; sl < nsl; ++sl) {
-                    float lv = -INFINITY;
-                    int li = 0x7fffffff;
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        const int v = sl * 4096 + (int)threadIdx.x + 256 * j;
-                        const float zv = v < D.V1 ? ldg(z + v) : -INFINITY;
-                        if (v < D.V1 && before(zv, v, lv, li)) { lv = zv; li = v; }
-                    }
-#pragma unroll
-                    for (int o = 1; o < 16; o <<= 1) {
-                        const float ov = __shfl_xor(lv, o, 64);
-                        const int oi = __shfl_xor(li, o, 64);
-                        if (before(ov, oi, lv, li)) { lv = ov; li = oi; }
-                    }
-                    if ((threadIdx.x & 15) == 0) { c_v[sl * 16 + (threadIdx.x >> 4)] = lv; c_i[sl * 16 + (threadIdx.x >> 4)] = li; }
-                }
-                if (threadIdx.x == 0) c_n = 0;
-                __syncthreads();
-                // thread t ranks maximum t among the nsl * 16 maxima; the one 15 are before is T
-                // (a slice tail without entries leaves (-inf, 0x7fffffff), which ranks last)
-                const int nm = nsl * 16;
-                if ((int)threadIdx.x < nm) {
-                    const float mv = c_v[threadIdx.x];
-                    const int mi = c_i[threadIdx.x];
-                    int r = 0;
-                    for (int t = 0; t < nm; ++t) r += before(c_v[t], c_i[t], mv, mi) ? 1 : 0;
-                    if (r == 15) { g_v[0] = mv; g_i[0] = mi; }
-                }
-                __syncthreads();
-                const float tv = g_v[0];
-                const int ti = g_i[0];
-                __syncthreads();   // every thread holds T: the candidate list may overwrite the maxima
-                for (int sl = 0; sl < nsl; ++sl) {
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        const int v = sl * 4096 + (int)threadIdx.x + 256 * j;
-                        const float zv = v < D.V1 ? ldg(z + v) : -INFINITY;
-                        if (v < D.V1 && !before(tv, ti, zv, v)) {
-                            const int slot = atomicAdd(&c_n, 1);
-                            if (slot < 256) { c_v[slot] = zv; c_i[slot] = v; }
-                        }
-                    }
-                }
-                __syncthreads();
-                const int n = c_n;
-                if (n <= 256) {
-                    rescan = false;
-                    if ((int)threadIdx.x < n) {
-                        const float mv = c_v[threadIdx.x];
-                        const int mi = c_i[threadIdx.x];
-                        int r = 0;
-                        for (int t = 0; t < n; ++t) r += before(c_v[t], c_i[t], mv, mi) ? 1 : 0;
-                        if (r < kmax) stwi(out + r, mi);
-                    }
-                }
-                __syncthreads();
-            }
-        }
-    }
-    if (D.V1 <= 256 * 16) {
+    bool rescan = false;
+    {
         float zr[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {

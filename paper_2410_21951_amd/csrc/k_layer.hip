@@ -1160,15 +1160,31 @@ __global__ __launch_bounds__(256) void k_embed_rows(Dims D, DevState s, int pref
 }
 
 // ---------------------------------------------------------------------------
-// After the vocabulary map: Algorithm 1 on every edge (one wave per edge), Sec. 2.3's path choice with the continuation
+// After the vocabulary map: Algorithm 1 on every edge (one wave per edge, eight for long rows), Sec. 2.3's path choice with the continuation
 // (one workgroup per sequence), and, after the draft heads' maps, their top-k lists beside the KV compaction.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_edges(Dims D, DevState s, int tau) {
     const int e = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
     if (e >= D.B * D.M) return;
     const int b = e / D.M, n = e - b * D.M;
-    const int fin = ldg(s.finished + b), ok = dev_edge(D, s, b, n, tau) && !fin;   // (one chain of loads, not two)
+    const int fin = ldg(s.finished + b), ok = (n == 0 || dev_edge_count<1>(D, s, b, n, threadIdx.x & 63) < tau) && !fin;   // (one chain of loads, not two)
     if ((threadIdx.x & 63) == 0) s.edge_ok[e] = ok;
+}
+
+// The same with eight waves per edge, for rows of more than 4096 logits: one wave goes to memory 15 times one after the other for
+// 16 001 logits, eight waves twice (64 edges, us per launch: 18.1 -> 5.4).  Up to 4096 one wave needs at most four trips.
+__global__ __launch_bounds__(512) void k_edges_wide(Dims D, DevState s, int tau) {
+    __shared__ int s_cnt[8];
+    const int e = blockIdx.x, b = e / D.M, n = e - b * D.M;
+    const int fin = ldg(s.finished + b);
+    const int cnt = n == 0 ? 0 : dev_edge_count<8>(D, s, b, n, threadIdx.x);
+    if ((threadIdx.x & 63) == 0) s_cnt[threadIdx.x >> 6] = cnt;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int sum = 0;
+        for (int w = 0; w < 8; ++w) sum += s_cnt[w];
+        s.edge_ok[e] = (n == 0 || sum < tau) && !fin;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_select(Dims D, DevState s, int seq0, int ignore_eos) {
@@ -1383,12 +1399,15 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
 
 void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eos, bool select, hipStream_t st) {
     clock_point(s, 1 + 5 * D.Ly + TP_EDGES, st);
-    if (D.M > 1) launch(k_edges, dim3(cdiv(D.B * D.M, 4)), dim3(256), 0, st, D, s, tau);
+    if (D.M > 1) {
+        if (D.V1 > 4096) launch(k_edges_wide, dim3(D.B * D.M), dim3(512), 0, st, D, s, tau);
+        else launch(k_edges, dim3(cdiv(D.B * D.M, 4)), dim3(256), 0, st, D, s, tau);
+    }
     if (select) launch(k_select, dim3(D.B), dim3(256), 0, st, D, s, 0, ignore_eos);
 }
 
-// Rows of more than 4096 logits: the draft lists come from the stand-alone top-k kernel (it takes such rows slice by
-// slice; dev_topk would re-scan the row once per list entry).
+// Rows of more than 4096 logits: the draft lists come from the stand-alone top-k kernel (1024 threads hold a row of 16 384; the 256
+// of dev_topk hold 4096).
 void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, int32_t* host, int dtype, hipStream_t st) {
     const int H = 1 + 5 * D.Ly;
     clock_point(s, H + TP_FINAL, st);

@@ -181,3 +181,50 @@ def test_two_query_tiles_beside_a_finished_sequence(monkeypatch, nodes, caps):
 @pytest.mark.parametrize("d,nodes,V", [(64, 15, 70), (384, 17, 200), (448, 33, 129)])
 def test_fp32_maps_at_their_edges(d, nodes, V):
     _run(_cfg("fp32", d, V), 2, nodes, (6, 6), (1, 3), 600 + d, 20, 60)
+
+
+# The lists, the edges and the roots of long rows, from the kernels' own logits: whole numbers, so the same.  V + 1 logits: the first row
+# beyond 4096; one slice of 16 384 full, and one entry in the next; four slices full, and beyond them (one entry per round);
+# odd ones between.  equal: all logits the same, more candidates than the list of them holds.
+@pytest.mark.parametrize("V,equal", [(4096, False), (8702, False), (16383, False), (16384, False), (40001, False), (65535, False), (65536, False), (5000, True), (20000, True)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_long_rows_are_ranked_as_by_sorting(V, equal, dtype):
+    from paper_2410_21951_amd import TreeArrays, Vadusa
+    from paper_2410_21951_amd.vadusa import DBG
+    cfg = _cfg(dtype, 64, V, layers=1, ffn=64, maxpos=96)
+    W = make_weights(cfg, 77, std=_std(cfg), ln_jitter=0.1)
+    if equal:
+        for name in ("W_out", "D0.W2", "D1.W2"):
+            W[name] = np.zeros_like(W[name])
+    rng = np.random.default_rng(V)
+    text, prompt = rand_tokens(cfg, rng, 2, (2, 6), (20, 30))
+    tree = make_tree(23, (8, 8))
+    dev = Vadusa(cfg, max_batch=2, max_tree_nodes=23)
+    dev.load_weights(W)
+    dev.prefill(text, prompt)
+
+    def lists_are_sorted():
+        z, got = dev.debug(DBG.DRAFT_LOGITS), dev.debug(DBG.DRAFT_TOPK)
+        for b in range(2):
+            for i in range(2):
+                want = np.argsort(-z[b, i], kind="stable")[:got.shape[2]]
+                assert np.array_equal(got[b, i], want), (V, b, i)
+
+    lists_are_sorted()
+    for tau in (1, V // 8, V // 3):
+        print(f"{V + 1} logits, {dtype}, tau {tau}", flush=True)
+        accepted = dev.step(TreeArrays(tree.parent, tree.rank), tau)
+        z, tok, ok, root = dev.debug(DBG.LOGITS), dev.debug(DBG.TREE_TOK), dev.debug(DBG.EDGE_OK), dev.debug(DBG.ROOT)
+        for b in range(2):
+            for n in range(1, 23):
+                row, t = z[b, tree.parent[n]], tok[b, n]
+                ahead = int((row > row[t]).sum() + (row[:t] == row[t]).sum())
+                assert ok[b, n] == (ahead < tau), (V, tau, b, n)
+            good = [True]
+            for n in range(1, 23):
+                good.append(bool(ok[b, n]) and good[tree.parent[n]])
+            last = max((n for n in range(23) if good[n]), key=lambda n: (tree.depth[n], -n))
+            assert len(accepted[b]) == tree.depth[last] + 1
+            assert root[b] == int(np.argmax(z[b, last])), (V, tau, b)
+        lists_are_sorted()
+    dev.close()
