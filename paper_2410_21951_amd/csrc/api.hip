@@ -726,7 +726,7 @@ static int verify_impl(vadusa_ctx* c, const vadusa_tree_spec* tree, int32_t tau,
         if (!(sp->top_p > 0.f)) return fail(c, VADUSA_EINVAL, "top_p must be positive");
         if (!sp->uniforms) return fail(c, VADUSA_EINVAL, "uniforms is null");
         if ((size_t)(c->cfg.speech_vocab + 1) * sizeof(float) > 65536)
-            return fail(c, VADUSA_ESHAPE, "stochastic verification keeps one row of V+1 floats in 64 KiB of LDS: vocabulary too large");
+            return fail(c, VADUSA_ESHAPE, "stochastic verification keeps a row of V+1 floats in one workgroup, at most 16384: vocabulary too large");
     }
     char msg[256];
     std::vector<int32_t> depth;

@@ -14,99 +14,11 @@ __device__ __forceinline__ uint32_t order_key(float f) {
     return b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u);
 }
 
-// One workgroup of 256 threads per row; the scaled row sits in LDS (V1 floats).
-// The kept set is {v : s_v >= s*}; s* is found by a 16-way interval search over the 32-bit keys
-// of the predicate "the tokens above this key hold less than top_p, or are fewer than tau",
-// which is monotone in the key and changes only at values that occur in the row.
-__global__ __launch_bounds__(256) void k_perturb(const float* __restrict__ logits, const float* __restrict__ u,
-                                                 float* __restrict__ scores, int V1, float temperature,
-                                                 float top_p, int tau) {
-    extern __shared__ float s_s[];
-    constexpr int NT = 15;
-    __shared__ float s_f[2][4][NT + 1];
-    __shared__ int s_i[2][4][NT + 1];
-    const size_t row = blockIdx.x;
-    const float* z = logits + row * V1;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    float m = -INFINITY;
-    for (int v = tid; v < V1; v += 256) {
-        const float s = z[v] / temperature + 0.f;   // -0 becomes +0: equal values, equal keys
-        s_s[v] = s;
-        m = fmaxf(m, s);
-    }
-    m = wave_max(m);
-    if (lane == 0) s_f[0][wave][0] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(s_f[0][0][0], s_f[0][1][0]), fmaxf(s_f[0][2][0], s_f[0][3][0]));
-    uint32_t kmin = 0;   // keep everything
-    if (top_p < 1.f) {
-        float zsum = 0.f;
-        for (int v = tid; v < V1; v += 256) zsum += expf(s_s[v] - m);
-        zsum = wave_sum(zsum);
-        if (lane == 0) s_f[1][wave][0] = zsum;
-        __syncthreads();
-        const float target = top_p * (s_f[1][0][0] + s_f[1][1][0] + s_f[1][2][0] + s_f[1][3][0]);
-        // Search for the smallest key at which the predicate holds.  It holds at hi (nothing lies
-        // above the largest key) and is monotone; each round tries NT keys that cut [lo, hi] into
-        // NT + 1 parts (their NT pairs of sums are reduced side by side, which costs little more
-        // than one pair), so the interval shrinks 16-fold per round.  Every thread sees the same
-        // sums, hence the same lo and hi: uniform control flow.
-        uint32_t lo = 0, hi = 0xffffffffu;
-        for (int it = 0; lo < hi; ++it) {
-            const uint64_t span = (uint64_t)hi - lo;
-            uint32_t mid[NT];
-            float a[NT];
-            int cnt[NT];
-#pragma unroll
-            for (int q = 0; q < NT; ++q) {
-                mid[q] = lo + (uint32_t)((span * (uint64_t)(q + 1)) / (NT + 1));   // lo <= mid[q] < hi, non-decreasing
-                a[q] = 0.f;
-                cnt[q] = 0;
-            }
-            for (int v = tid; v < V1; v += 256) {
-                const float s = s_s[v];
-                const float e = expf(s - m);
-                const uint32_t k = order_key(s);
-#pragma unroll
-                for (int q = 0; q < NT; ++q)
-                    if (k > mid[q]) { a[q] += e; ++cnt[q]; }
-            }
-#pragma unroll
-            for (int q = 0; q < NT; ++q) { a[q] = wave_sum_dpp(a[q]); cnt[q] = wave_sum_i_dpp(cnt[q]); }
-            if (lane == 0) {
-#pragma unroll
-                for (int q = 0; q < NT; ++q) { s_f[it & 1][wave][q] = a[q]; s_i[it & 1][wave][q] = cnt[q]; }
-            }
-            __syncthreads();
-            // the first key of the round at which the predicate holds bounds the answer from above,
-            // the key before it (where it fails) from below
-            uint32_t nlo = lo, nhi = hi;
-            bool found = false;
-#pragma unroll
-            for (int q = 0; q < NT; ++q) {
-                const float A = s_f[it & 1][0][q] + s_f[it & 1][1][q] + s_f[it & 1][2][q] + s_f[it & 1][3][q];
-                const int C = s_i[it & 1][0][q] + s_i[it & 1][1][q] + s_i[it & 1][2][q] + s_i[it & 1][3][q];
-                const bool holds = A < target || C < tau;
-                if (!found) {
-                    if (holds) { nhi = mid[q]; found = true; }
-                    else nlo = mid[q] + 1;
-                }
-            }
-            lo = nlo; hi = nhi;
-        }
-        kmin = hi;
-    }
-    float* y = scores + row * V1;
-    const float* ur = u + row * V1;
-    for (int v = tid; v < V1; v += 256) {
-        const float s = s_s[v];
-        y[v] = order_key(s) >= kmin ? s - logf(-logf(ur[v])) : -INFINITY;
-    }
-}
-
+// The kept set is {v : s_v >= s*}; s* is found by a search over the 32-bit keys of the predicate "the tokens above this key hold less
+// than top_p, or are fewer than tau", which is monotone in the key and changes only at values that occur in the row.
 
 // Rows of up to 4096 logits: one WAVE per row, the row in registers (values of lane l: l, l + 64, ...), no LDS
-// and no workgroup barrier.  The same search as in k_perturb, as a plain bisection over the 32-bit keys: a round is a
+// and no workgroup barrier.  A plain bisection over the 32-bit keys: a round is a
 // compare and two conditional adds per value and two wave sums by lane permutations.  The values are kept as their
 // keys (key_value gives a value back), entries beyond the row have key 0 (below every key) and mass 0.
 __device__ __forceinline__ float key_value(uint32_t k) { return __uint_as_float(k ^ ((k >> 31) ? 0x80000000u : 0xffffffffu)); }
@@ -117,6 +29,14 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
     v = fmaxf(v, __int_as_float(dpp_perm<0x140>(__float_as_int(v))));
     return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16))),
                  fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48))));
+}
+__device__ __forceinline__ uint32_t wave_umax_dpp(uint32_t v) {
+    v = max(v, (uint32_t)dpp_perm<0xB1>((int)v));
+    v = max(v, (uint32_t)dpp_perm<0x4E>((int)v));
+    v = max(v, (uint32_t)dpp_perm<0x141>((int)v));
+    v = max(v, (uint32_t)dpp_perm<0x140>((int)v));
+    return max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
+               max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
 }
 template <int GROUPS>   // groups of four 64-value chunks the row may have: GROUPS * 256 >= V1
 __global__ __launch_bounds__(64) void k_perturb_wave(const float* __restrict__ logits, const float* __restrict__ u,
@@ -210,11 +130,119 @@ __global__ __launch_bounds__(64) void k_perturb_wave(const float* __restrict__ l
         }
 }
 
+// Rows of more than 4096 logits: the same by a workgroup of 1024 threads per row, the row in registers (entries of thread t: t, t + 1024, ...;
+// PER of them), so up to 16 384 logits.  A round of the bisection is three instructions per value, a wave's two sums by lane
+// permutations, 16 pairs through LDS (two sets in turn: one barrier) and their sum in the same order by every thread, so that lo and
+// hi are the same everywhere.  The smallest and the largest key are taken as keys: with missing values among the logits the interval still
+// holds every key of the row.
+// What bounds it: some 17 rounds one after the other, each a reduction and a barrier, behind one trip to memory (64 rows of
+// 16 001, us per launch: 256 threads, the row in LDS, 15 keys per round and the exponentials anew in each 171; this 34).
+template <int PER>
+__global__ __launch_bounds__(1024) void k_perturb_block(const float* __restrict__ logits, const float* __restrict__ u,
+                                                        float* __restrict__ scores, int V1, float temperature, float top_p, int tau) {
+    constexpr int NW = 16;
+    __shared__ float s_f[2][NW];
+    __shared__ int s_i[2][NW];
+    __shared__ uint32_t s_lo[NW], s_hi[NW], s_last;
+    const size_t row = blockIdx.x;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const float* z = logits + row * V1;
+    const float* ur = u + row * V1;
+    float* y = scores + row * V1;
+    float gum[PER], e[PER];
+    uint32_t key[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {   // logits and uniforms together; an index beyond the row re-reads its last entry
+        e[j] = ldg(z + min(tid + 1024 * j, V1 - 1));
+        gum[j] = ldg(ur + min(tid + 1024 * j, V1 - 1));
+    }
+    float m = -INFINITY;
+    uint32_t lo = 0xffffffffu, hi = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const bool have = tid + 1024 * j < V1;
+        const float sv = have ? e[j] / temperature + 0.f : -INFINITY;   // -0 becomes +0: equal values, equal keys
+        gum[j] = logf(-logf(gum[j]));
+        key[j] = have ? order_key(sv) : 0u;   // (below every key, and no mass)
+        m = fmaxf(m, sv);
+        lo = min(lo, have ? key[j] : 0xffffffffu);
+        hi = max(hi, key[j]);
+    }
+    uint32_t kmin = 0;   // keep everything
+    if (top_p < 1.f) {
+        m = wave_max_dpp(m);
+        hi = wave_umax_dpp(hi);
+        lo = ~wave_umax_dpp(~lo);
+        if (lane == 0) { s_f[0][wave] = m; s_lo[wave] = lo; s_hi[wave] = hi; }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { m = fmaxf(m, s_f[0][w]); lo = min(lo, s_lo[w]); hi = max(hi, s_hi[w]); }
+        // sums over the row by every thread; `set` is not the one of the call before
+        auto block_sums = [&](int set, float a, int c, float& A, int& C) {
+            a = wave_sum_dpp(a);
+            c = wave_sum_i_dpp(c);
+            if (lane == 0) { s_f[set][wave] = a; s_i[set][wave] = c; }
+            __syncthreads();
+            float av[NW];
+            C = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) { av[w] = s_f[set][w]; C += s_i[set][w]; }
+#pragma unroll
+            for (int n = NW / 2; n; n >>= 1)
+#pragma unroll
+                for (int w = 0; w < n; ++w) av[w] += av[w + n];
+            A = av[0];
+        };
+        float zs[4] = {0.f, 0.f, 0.f, 0.f}, zsum;
+        int none;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            e[j] = tid + 1024 * j < V1 ? expf(key_value(key[j]) - m) : 0.f;
+            zs[j & 3] += e[j];
+        }
+        block_sums(1, (zs[0] + zs[1]) + (zs[2] + zs[3]), 0, zsum, none);
+        const float target = top_p * zsum;
+        // (the search and its early end: as in k_perturb_wave)
+        int c_lo = V1, c_hi = 0, set = 0;
+        bool failed = false;
+        while (lo < hi) {
+            const uint32_t mid = lo + ((hi - lo) >> 1);
+            float a4[4] = {0.f, 0.f, 0.f, 0.f}, A;
+            int c4[4] = {0, 0, 0, 0}, C;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const bool above = key[j] > mid;
+                a4[j & 3] += above ? e[j] : 0.f;
+                c4[j & 3] += above ? 1 : 0;
+            }
+            block_sums(set, (a4[0] + a4[1]) + (a4[2] + a4[3]), (c4[0] + c4[1]) + (c4[2] + c4[3]), A, C);
+            set ^= 1;
+            if (A < target || C < tau) { hi = mid; c_hi = C; }
+            else { lo = mid + 1; c_lo = C; failed = true; }
+            if (failed && c_lo - c_hi == 1) {   // one entry left: its key
+#pragma unroll
+                for (int j = 0; j < PER; ++j)
+                    if (tid + 1024 * j < V1 && key[j] >= lo && key[j] <= hi) s_last = key[j];
+                __syncthreads();
+                hi = s_last;
+                break;
+            }
+        }
+        kmin = hi;
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int v = tid + 1024 * j;
+        if (v < V1) y[v] = key[j] >= kmin ? key_value(key[j]) - gum[j] : -INFINITY;
+    }
+}
+
+// (V1 <= 16 384: vadusa_step and vadusa_verify refuse the stochastic rule for larger vocabularies)
 void launch_perturb(const float* logits, const float* u, float* scores, int rows, int V1, float temperature,
                     float top_p, int tau, hipStream_t st) {
     if (V1 <= 1280) launch(k_perturb_wave<5>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
     else if (V1 <= 2304) launch(k_perturb_wave<9>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
     else if (V1 <= 4096) launch(k_perturb_wave<16>, dim3(rows), dim3(64), 0, st, logits, u, scores, V1, temperature, top_p, tau);
-    else launch(k_perturb, dim3(rows), dim3(256), (size_t)V1 * sizeof(float), st, logits, u, scores, V1,
-                            temperature, top_p, tau);
+    else if (V1 <= 8192) launch(k_perturb_block<8>, dim3(rows), dim3(1024), 0, st, logits, u, scores, V1, temperature, top_p, tau);
+    else launch(k_perturb_block<16>, dim3(rows), dim3(1024), 0, st, logits, u, scores, V1, temperature, top_p, tau);
 }

@@ -228,3 +228,42 @@ def test_long_rows_are_ranked_as_by_sorting(V, equal, dtype):
             assert root[b] == int(np.argmax(z[b, last])), (V, tau, b)
         lists_are_sorted()
     dev.close()
+
+
+# Scores of the stochastic rule against 64 bits from the kernel's own logits, around the sizes where its kernels change (4096 and 8192
+# logits) and end (16 384).  A token may be kept or not where the mass above it is within 1e-5 of top_p: sums of 16 384 masses in
+# trees of some 30 additions (2e-6) of exponentials good to 1e-6.  Scores: two logarithms and a quotient, a few 2^-24 of each.
+@pytest.mark.parametrize("V1", [4096, 4097, 6000, 8192, 8193, 16001, 16384])
+def test_scores_of_long_rows(V1):
+    from paper_2410_21951_amd import TreeArrays, Vadusa
+    from paper_2410_21951_amd.vadusa import DBG
+    from synth import make_uniforms
+    cfg = _cfg("bf16", 64, V1 - 1, layers=1, ffn=64, maxpos=96)
+    W = make_weights(cfg, 78, std=_std(cfg), ln_jitter=0.1)
+    W["W_out"] = W["W_out"].copy() * 4     # logits of spread 2.3
+    W["W_out"][V1 - 9:] = W["W_out"][7]    # nine equal logits
+    rng = np.random.default_rng(V1)
+    text, prompt = rand_tokens(cfg, rng, 2, (2, 6), (20, 30))
+    tree = make_tree(13, (6, 6))
+    dev = Vadusa(cfg, max_batch=2, max_tree_nodes=13)
+    dev.load_weights(W)
+    dev.prefill(text, prompt)
+    for i, (tau, T, top_p) in enumerate([(1, 0.9, 0.9), (3, 1.0, 0.5), (40, 0.5, 1e-4), (1, 1.0, 1.0), (V1, 1.0, 0.3), (2, 0.7, 0.999)]):
+        print(f"{V1} logits, tau {tau}, temperature {T}, top_p {top_p}", flush=True)
+        u = make_uniforms(91, i, 2, 13, V1)
+        dev.step(TreeArrays(tree.parent, tree.rank), tau, sample=(T, top_p, u))
+        z, got = dev.debug(DBG.LOGITS).reshape(26, V1), dev.debug(DBG.SCORES).reshape(26, V1)
+        for row, y, ur in zip(z, got, np.asarray(u, np.float64).reshape(26, V1)):
+            s32 = row / np.float32(T)
+            s = s32.astype(np.float64)
+            of = np.unique(-s32, return_inverse=True)[1]     # rank of the value, largest first
+            count = np.bincount(of)
+            mass = np.bincount(of, np.exp(s - s.max()))
+            above, ahead = (np.cumsum(mass) - mass)[of] / mass.sum(), (np.cumsum(count) - count)[of]
+            kept = np.isfinite(y)
+            sure = (np.abs(above - top_p) > 1e-5) | (ahead < tau) | (top_p >= 1)
+            want = (above < top_p) | (ahead < tau) | (top_p >= 1)
+            assert np.array_equal(kept[sure], want[sure]), (V1, tau, top_p)
+            score = s - np.log(-np.log(ur))
+            assert np.allclose(y[kept], score[kept], rtol=1e-6, atol=1e-5)
+    dev.close()
