@@ -905,8 +905,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 // NW waves take the key blocks of a workgroup in turn.  What bounds it with few workgroups: misses (a compute unit has no more than some
 // 64 KB on their way; 512 KB of keys and values took 9 us), so the workgroups of a head start at different blocks (128 queries, 2000 keys
 // 12.4 -> 10.3 us a layer, 64 queries, 360 keys 5.7 -> 5.3), and eight waves instead of four where there are blocks for them and the
-// workgroups do not fill the chip (14.0 -> 12.4, 6.0 -> 5.6; 1024 causal queries of 1500 keys 22.0 -> 17.4; sixteen waves 10.7, eight with
-// five buffers 11.7 instead of 10.3); with a block or two per wave the merge costs more than it gives (270 keys, QT = 2: 11.7 -> 13.4).
+// workgroups do not fill the chip (attn_shape; sixteen waves were slower than eight, 10.7 instead of 10.3).
 // Measured and not kept: the key blocks split over up to four workgroups with the last
 // to arrive merging (2000 keys, 64 queries: 8.6 instead of 9.7, 1000 keys: 8.2 instead of 6.9); two blocks per step
 // (2000 keys: 9.3, 320 keys: 5.2 instead of 4.5).
@@ -923,7 +922,7 @@ struct AttnArgs {
     float* x_last;           // where its last rows go, one behind the other like the attention's results (null: all rows go on)
 };
 template <bool CAUSAL, int QT, int NW, int NB>   // NB: buffers of a wave, all but one of them in flight
-__global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : QT == 1 ? 4 : 2) void k_attn(AttnArgs a) {
+__global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
     constexpr int SO = 17;   // floats per row of the merge buffer: the merge reads a dimension's 16 queries' worth 64 rows apart
     __shared__ float sm_o[QT][NW * 64 * SO], sm_m[QT][NW * 16], sm_l[QT][NW * 16];
     const int bh = blockIdx.x;
@@ -1331,16 +1330,25 @@ static void attn_launch(const AttnArgs& t, bool causal, hipStream_t st) {
     if (causal) launch((k_attn<true, QT, NW, NB>), grid, dim3(64 * NW), 0, st, t);
     else launch((k_attn<false, QT, NW, NB>), grid, dim3(64 * NW), 0, st, t);
 }
-// keys: an upper bound of the longest sequence's keys.
+// Query tiles and waves of a workgroup for `heads` heads (of all sequences) of qt query tiles and up to `keys` keys (an upper bound of the longest
+// sequence's): two query tiles from two workgroups per compute unit on, else eight waves while every one has a key block to take and
+// the workgroups do not fill the chip.  Measured in steps and prompt passes (us: one tile and four waves, one and eight, two and four;
+// the choice in brackets):
+//   64 queries, 360 | 2000 keys, 64 workgroups of one tile    5.4 [5.1] 7.8 | 11.7 [9.7] 15.6
+//   64 queries of 8 sequences, 1100 keys, 512                 14.9 [14.0] 13.9
+//   64 queries of 16 sequences, 350 | 2000 keys, 1024         12.7 12.0 [10.8] | 66 82 [40]
+//   896 | 1024 causal queries, twice the keys, 896 | 1024     [16.8] 16.0 14.7 | 20.3 19.6 [16.8]
+// Two tiles with eight waves lose to four wherever two tiles are taken (512 workgroups, 1100 | 2000 keys 28.4 | 47.6 against 23.6 | 39.8; 1024
+// causal queries 18.0 against 16.8), three buffers for eight waves to two (128 queries, 1100 | 2000 | 3000 keys 7.6 | 10.1 | 12.8 against 7.2 | 9.3 | 12.6).
+struct AttnShape { int tiles, waves; };
+static AttnShape attn_shape(int heads, int qt, int keys, int big_min) {
+    if (qt > 1 && heads * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512)) return {2, 4};
+    return {1, cdiv(keys, 32) >= 10 && heads * qt <= 512 ? 8 : 4};
+}
 static void attn(const AttnArgs& t, bool causal, int keys, int big_min, hipStream_t st) {
-    const int qt = t.x_last ? 1 : cdiv(t.M, 16), blocks = cdiv(keys, 32);
-    // two query tiles from two workgroups per compute unit on; waves: every one with a key block to take, up to four per SIMD
-    const bool two = qt > 1 && t.B * t.nH * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512);
-    const int wgs = t.B * t.nH * (two ? cdiv(qt, 2) : qt);
-    if (two && blocks >= 32 && wgs <= 512) attn_launch<2, 8, 2>(t, causal, st);
-    else if (two) attn_launch<2, 4, 3>(t, causal, st);
-    else if (blocks >= 32 && wgs <= 256) attn_launch<1, 8, 3>(t, causal, st);
-    else if (blocks >= 10 && wgs <= 512) attn_launch<1, 8, 2>(t, causal, st);
+    const AttnShape s = attn_shape(t.B * t.nH, t.x_last ? 1 : cdiv(t.M, 16), keys, big_min);
+    if (s.tiles == 2) attn_launch<2, 4, 3>(t, causal, st);
+    else if (s.waves == 8) attn_launch<1, 8, 2>(t, causal, st);
     else attn_launch<1, 4, 3>(t, causal, st);
 }
 

@@ -65,3 +65,28 @@ def test_kernels_of_the_mixed_gpu_tests(emu_lib):
         rows = nodes * batch
         got = [pick(rows, n // 16, k // 32) for n, k in ((3 * d, d), (d, d), (ffn, d), (d, ffn))]
         assert " ".join(names[g] for g in got) == kernels, (d, ffn, rows)
+
+
+def test_attention_shapes(emu_lib):
+    """The attention's tiles and waves that the GPU test names are those that the rule picks; and no shape is taken at one number of
+    workgroups only: what 512 workgroups of two tiles take, 528 take too, and 16 heads fewer take what 256 and 512 of one tile take."""
+    import ctypes as C
+    sys.path.insert(0, HERE)
+    from test_gpu_layer_kernels import ATTENTION
+    pick = C.CDLL(emu_lib).emu_attn_shape
+    seen = set()
+    for d, batch, nodes, prompt, chunk, big_min, shapes in ATTENTION:
+        heads, lo, hi = batch * d // 64, prompt + 2, prompt + 16      # lengths of the prompts
+        name = lambda rows, keys: "{}x{}".format(*divmod(pick(heads, -(-rows // 16), keys, big_min), 16))
+        step = {name(nodes, n + nodes + 4 * i) for n in (lo, hi) for i in (0, 1)}
+        per = min(chunk or max(nodes, min(128, max(1, 2048 // batch) // 16 * 16)), -(-hi // 16) * 16)
+        # all passes but the first are full; the last layer's attention of the last pass has one tile
+        passes = sorted({name(min(per, n), min((i + 1) * per, 704 if prompt < 700 else 1104)) for n in (lo, hi) for i in range(-(-n // per))})
+        assert (" ".join(passes) + ", " + " ".join(sorted(step))) == shapes, (d, batch, nodes, prompt)
+        seen |= set(passes) | step
+    assert seen == {"1x4", "1x8", "2x4"}
+    for keys in range(32, 3328, 32):
+        for qt in (2, 4, 8, 64):
+            for heads, beside in ((512 // (qt // 2), 528 // (qt // 2)), (256 // qt, 240 // qt), (512 // qt, 496 // qt)):
+                if heads and beside:
+                    assert pick(heads, qt, keys, 0) == pick(beside, qt, keys, 0), (heads, qt, keys)

@@ -132,12 +132,28 @@ def test_ragged_prompt_passes(monkeypatch, big_min, lens, chunk, d, ffn):
     assert ls.stats.compared >= 1
 
 
-# Attention with 16 waves per workgroup (512 keys and more: 17 to 19 blocks, so that some waves take two and the last block is ragged),
-# with eight (one query tile and two), prompts in one pass and in passes of the tree's rows; the keys' bound moves with the steps
-@pytest.mark.parametrize("d,batch,nodes,prompt,chunk", [(128, 1, 40, 520, 0), (64, 2, 17, 590, 0), (128, 3, 33, 300, 0), (512, 32, 40, 240, 0), (64, 1, 1, 511, 0), (128, 2, 24, 560, 576)])
-def test_attention_waves(d, batch, nodes, prompt, chunk):
+# Attention: one query tile with four and with eight waves, two with four; 9 to 34 blocks of keys, so that some waves take one more than
+# others and the last block is ragged; prompts in one pass and in passes of the tree's rows; the keys' bound moves with the steps.  The
+# last column: query tiles x waves of the prompt's passes, then of the steps (tests/test_emulated_kernel.py holds the rule to it); big_min 1:
+# two tiles wherever there are two.
+ATTENTION = [
+    (128, 1, 40, 520, 0, 0, "1x4 1x8, 1x8"),
+    (64, 2, 17, 590, 0, 0, "1x4 1x8, 1x8"),
+    (128, 3, 33, 300, 0, 0, "1x4 1x8, 1x8"),
+    (512, 32, 40, 240, 0, 0, "2x4, 2x4"),
+    (64, 1, 1, 511, 0, 0, "1x4 1x8, 1x8"),
+    (128, 2, 24, 560, 576, 0, "1x8, 1x8"),
+    (128, 1, 33, 1010, 1024, 0, "1x8, 1x8"),
+    (128, 1, 33, 1010, 1024, 1, "2x4, 2x4"),
+    (64, 3, 16, 250, 0, 0, "1x4 1x8, 1x4"),
+]
+
+
+@pytest.mark.parametrize("d,batch,nodes,prompt,chunk,big_min,shapes", ATTENTION)
+def test_attention_waves(monkeypatch, d, batch, nodes, prompt, chunk, big_min, shapes):
     from parity import Lockstep
-    cfg = _cfg("bf16", d, 90, layers=1, ffn=128, maxpos=704)
+    monkeypatch.setenv("VADUSA_BIG_MIN_UNITS", str(big_min))
+    cfg = _cfg("bf16", d, 90, layers=1, ffn=128, maxpos=1104 if prompt > 700 else 704)
     W = make_weights(cfg, 900 + d, std=_std(cfg), ln_jitter=0.1)
     rng = np.random.default_rng(900 + prompt)
     text, tokens = rand_tokens(cfg, rng, batch, (2, 6), (prompt, prompt + 9))
