@@ -1258,22 +1258,30 @@ static void tile_launch(LinArgs& a, hipStream_t st) {
     a.sg_out = TileShape<RG, CG>::KSP > 2 ? 5 : a.N % 128 ? 4 : 6;   // (a wave's columns as one entry where that leaves a row an even number)
     launch((k_tile<RG, CG, EPI>), dim3(8 * cdiv(g.gr * g.gc, 8)), dim3(512), 0, st, a, g);
 }
-// Which kernel: the one that is estimated to take least.  n: workgroups of the fullest of the 256 compute units; us without the launch,
-// from chains of launches whose weights come from HBM (K = 1024 | 4096, launch included):
-//   k_lin 64 x 64            n = 1   8.4 | 19    n = 2  15.5 | 33
-//   k_big 64 x 128           n = 1  12.5 | 33    n = 2  17.8 | 42    n = 3  25.9 | 62    n = 4  30.5    n = 7  46.6    n = 9  57.2
-//   k_tile 128 x 64          n = 1  12.9 | 29    n = 2  22
-//   k_tile 256 x 128         n = 1  24.4 | 52    n = 2  48
-// What that decides at d = 1024 (us, the choice first): 304 rows FFN1 k_tile 9.9, k_big 11.7, k_lin 12.6; 1024 rows QKV k_big 16.7, k_lin 22, FFN1 k_big 18.1,
-// k_lin 26, out-projection k_lin 8.4, k_big 11.6, FFN2 k_lin 19, k_tile 27; 2048 rows out-projection k_tile 12.9, k_big 13.5, k_lin 15.6, FFN1 k_tile 26.9,
-// k_big 30.5, FFN2 k_tile 29.1, k_lin 33, k_big 34; 3200 rows FFN2 k_big 42, k_lin 58, k_tile 47; 4352 rows FFN1 k_big 57, k_tile 66.
+// Which kernel: the one that is estimated to take least.  us per launch, fitted to 1445 maps of whole steps, each run with all four kernels (widths
+// of 64 to 1024 with hidden layers of two and four times that, 64 to 16 384 rows, vocabulary maps of 1025 and 16 001 columns): the choice takes
+// 1.008 times the best of the four in the mean, 1.06 at the 95th percentile, 1.33 at most.  What the terms stand for: rounds of the fullest of the 256 compute units, where
+// a map numbered by columns gives an XCD whole column groups (18 of them: three for two of the XCDs, two for the others); k_lin's workgroups are
+// small and many, padding included, so that their number counts too; rows of logits are stored in pieces of four bytes.  An estimate fitted at K = 1024
+// and 4096 alone was up to 4.3 times the best (us, choice and best: width 256, 1536 rows QKV k_lin 11.0, k_big 7.0; 4096 rows out-projection 11.1, 8.5,
+// FFN2 19.0, 11.7; width 1024, 16 384 rows to 1025 logits k_big 151, k_tile 91).
+// What it decides at d = 1024 (us: k_lin, k_big, k_tile 256 x 128, k_tile 128 x 64; the choice in brackets):
+//   320 rows QKV [10.6] 13.1 22.7 12.5    FFN1 14.0 12.0 19.5 [11.7]    FFN2 [12.0] 32.1 49.5 24.7
+//   1024     QKV 23.9 [17.7] 25.0 23.2    FFN1 27.6 [17.5] 22.5 23.4    FFN2 [19.2] 33.1 53.0 27.9    out-projection [9.7] 12.7 22.5 12.2
+//   2048     QKV 43.5 [24.8] 27.3 33.7    FFN1 51.3 28.0 [25.5] 39.6    FFN2 34.4 35.6 54.2 [30.3]    out-projection 16.2 14.6 23.1 [13.6]
+//   3200     QKV 68.6 [37.2] 46.7 51.3    FFN1 80.1 42.8 [42.3] 64.4    FFN2 60.6 [44.1] 54.0 49.1    out-projection 27.5 [18.9] 23.9 20.7
 enum { MAP_LIN = 0, MAP_BIG, MAP_TILE_256, MAP_TILE_128 };
-static int map_kernel(int R, int NT, int nks) {
+static int map_kernel(int R, int NT, int nks, int epi) {
+    auto by_columns = [](int gr, int gc) { return cdiv(cdiv(gc, 8) * gr, 32); };
+    auto by_blocks = [](int gr, int gc) { return cdiv(gr * gc, 256); };
     const LinShape s = lin_shape(R, NT);
-    auto n = [&](int rows, int ct) { return cdiv(cdiv(R, rows) * cdiv(NT, ct), 256); };
-    const int nb = n(64, 8);
-    const float us[4] = {lin_rounds(cdiv(R, 16), NT, s) * (2.4f + 0.0135f * nks * (s.rt + s.ct)), 2.5f + 2.3f * nb + nks * std::max(0.21f, 0.115f * nb),
-                         n(256, 8) * (12.f + 0.31f * nks), n(128, 4) * (5.f + 0.17f * nks)};
+    const int gr = cdiv(cdiv(R, 16), s.rt), gc = cdiv(NT, s.ct), nl = by_columns(gr, gc);
+    const int nb = epi == LE_RESID ? by_blocks(cdiv(R, 64), cdiv(NT, 8)) : by_columns(cdiv(R, 64), cdiv(NT, 8));
+    const float logits = epi == LE_LOGITS ? 1.f : 0.f;
+    const float us[4] = {2.8f + 0.0014f * pad8(gc) * gr + nl * (0.188f * s.rt * s.ct + 0.0117f * nks * (s.rt + s.ct)),
+                         2.5f + nb * (2.4f + 1.7f * logits) + nks * std::max(0.213f, 0.15f * nb),
+                         1.9f + by_blocks(cdiv(R, 256), cdiv(NT, 8)) * (8.5f + 8.5f * logits + 0.43f * nks),
+                         1.6f + by_blocks(cdiv(R, 128), cdiv(NT, 4)) * (5.f + 3.f * logits + 0.157f * nks)};
     return (int)(std::min_element(us, us + 4) - us);
 }
 // big_min (tests): k_big from that many of its tiles on; -1, -2: k_tile for every map.
@@ -1282,7 +1290,7 @@ static void lin(LinArgs& a, int big_min, hipStream_t st) {
     a.sg_out = 4;
     const int kernel = big_min < 0 ? (big_min == -1 ? MAP_TILE_256 : MAP_TILE_128)
                        : big_min > 0 ? ((long)cdiv(a.R, 16 * BIG_RT) * cdiv(a.NT, 4 * BIG_CT) >= big_min ? MAP_BIG : MAP_LIN)
-                                     : map_kernel(a.R, a.NT, a.nks);
+                                     : map_kernel(a.R, a.NT, a.nks, EPI);
     if (kernel == MAP_BIG) { big_launch<EPI>(a, st); return; }
     if (kernel == MAP_TILE_256) { tile_launch<4, 2, EPI>(a, st); return; }
     if (kernel == MAP_TILE_128) { tile_launch<2, 1, EPI>(a, st); return; }

@@ -56,7 +56,8 @@ def test_many_row_tile_shapes(monkeypatch, shape, d, nodes, batch, V):
 
 # By the rule one model mixes the kernels, and with them statistics of 16 and of 32 columns (tests/test_emulated_kernel.py holds the
 # rule to this: QKV, out-projection, FFN1, FFN2)
-MIXED = [(256, 4096, 100, 4, "lin lin tile128 lin"), (256, 4096, 127, 5, "lin lin big lin"), (128, 16384, 127, 4, "lin lin tile256 lin")]
+MIXED = [(256, 4096, 100, 4, "lin lin big lin"), (256, 4096, 127, 5, "big lin big lin"), (128, 16384, 127, 4, "lin lin tile256 lin"),
+         (128, 1024, 77, 27, "tile128 big big tile128")]
 
 
 @pytest.mark.parametrize("d,ffn,nodes,batch,kernels", MIXED)
