@@ -1,4 +1,4 @@
-// Runtime of the CPU emulation: a pool of 512 OS threads plays the threads of one block;
+// Runtime of the CPU emulation: a pool of OS threads, as many as the largest block so far had, plays the threads of one block;
 // blocks of a launch run one after another.
 #include <hip/hip_runtime.h>
 
@@ -21,7 +21,7 @@ alignas(64) static char g_lds[160 * 1024];
 char* emu_dyn_lds = g_lds;
 extern "C" { int emu_last_error = 0, emu_fail_launch = 0, emu_host_blocks = 0; }
 
-constexpr int MAXT = 512;
+constexpr int MAXT = 1024;
 static thread_local int t_id = -1;   // index in the pool, -1: host thread
 static const char* g_where[MAXT];
 static int g_wline[MAXT];
@@ -45,6 +45,7 @@ struct Barrier {
     int count = 0, n = 0;
     uint64_t gen = 0;
     void init(int n_) { n = n_; count = 0; }
+    void grow(int n_) { std::unique_lock<std::mutex> lk(m); n = n_; }   // while the launching thread is not waiting: nobody is released
     void wait(const char* what) {
         note();
         std::unique_lock<std::mutex> lk(m);
@@ -116,15 +117,16 @@ void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t
         sa.sa_flags = SA_SIGINFO;
         sigaction(SIGSEGV, &sa, nullptr);
         sigaction(SIGBUS, &sa, nullptr);
-        b_start.init(MAXT + 1);
-        b_done.init(MAXT + 1);
-        for (int i = 0; i < MAXT; ++i) g_pool.emplace_back(worker, i);
-        for (auto& t : g_pool) t.detach();
     }
     const int nt = (int)(block.x * block.y * block.z);
     if (nt > MAXT || nt % 64) { fprintf(stderr, "[emu] unsupported block size %d\n", nt); abort(); }
     if (shmem > sizeof g_lds) { fprintf(stderr, "[emu] dynamic LDS too large\n"); abort(); }
     if (grid.x * grid.y * grid.z == 0) return;
+    if ((int)g_pool.size() < nt) {   // (idle workers take part in every launch's start and end: no more of them than needed)
+        b_start.grow(nt + 1);
+        b_done.grow(nt + 1);
+        while ((int)g_pool.size() < nt) { g_pool.emplace_back(worker, (int)g_pool.size()); g_pool.back().detach(); }
+    }
     g_body = body;
     gridDim = grid;
     blockDim = block;

@@ -36,8 +36,7 @@ if dtype == "bf16-40rows":
     sys.stdout.flush()
     os._exit(0)
 if dtype == "bf16-72rows":
-    # 72 rows: five row tiles, the last ragged, masks of three words.  The prompt of 70 tokens goes through one causal
-    # pass of 80 rows, the last ten of which no token has.
+    # 72 rows: five row tiles, the last ragged, masks of three words.  The prompt's 70 tokens are one causal pass of 70 rows.
     cfg = ModelConfig(n_layers=2, d_model=64, n_heads=1, head_dim=64, d_ffn=192, speech_vocab=71, text_vocab=20,
                       n_draft_heads=3, max_positions=224, dtype="bf16")
     W = make_weights(cfg, 81, std=0.05)
@@ -74,6 +73,90 @@ if dtype == "bf16-256rows":
     print(f"emulated {dtype}: compared {s.compared}/{s.steps} logit err {s.max_logit_err:.2e} "
           f"ties {s.tie_root}/{s.tie_list}/{s.tie_edge} in {time.time() - t0:.0f} s", flush=True)
     assert s.compared >= 1
+    sys.stdout.flush()
+    os._exit(0)
+if dtype in ("bf16-tile256", "bf16-tile128", "bf16-long-ffn", "bf16-long-keys"):
+    # tile256, tile128: every map by k_tile of 256 x 128 or 128 x 64 outputs (81 rows, 192 and 72 columns: blocks of a tile that are empty, a
+    # last stage that is half empty); long-ffn: a reduction of 2048 by eight waves; long-keys: 318 keys and more, eight waves per query tile.
+    long_ffn, long_keys = dtype == "bf16-long-ffn", dtype == "bf16-long-keys"
+    os.environ["VADUSA_BIG_MIN_UNITS"] = {"bf16-tile256": "-1", "bf16-tile128": "-2"}.get(dtype, "0")
+    cfg = ModelConfig(n_layers=1 if long_ffn or long_keys else 2, d_model=64, n_heads=1, head_dim=64, d_ffn=2048 if long_ffn else 64 if long_keys else 192,
+                      speech_vocab=71, text_vocab=20, n_draft_heads=2, max_positions=392 if long_keys else 96, dtype="bf16")
+    W = make_weights(cfg, 95, std=0.05)
+    rng = np.random.default_rng(96)
+    B, M = (1, 19) if long_ffn else (1, 17) if long_keys else (3, 27)
+    text = [rng.integers(0, cfg.text_vocab, 2 + b).astype(np.int32) for b in range(B)]
+    prompt = [rng.integers(0, cfg.speech_vocab, 315 if long_keys else 20 - 7 * b).astype(np.int32) for b in range(B)]
+    t0 = time.time()
+    ls = Lockstep(cfg, W, text, prompt, M, prefill_chunk=160 if long_keys else 0)
+    ls.step(make_tree(M, (6, 6)), 2)
+    ls.check_kv(layers=[0, cfg.n_layers - 1])
+    s = ls.stats
+    print(f"emulated {dtype}: compared {s.compared}/{s.steps} logit err {s.max_logit_err:.2e} in {time.time() - t0:.0f} s", flush=True)
+    assert s.compared >= 1
+    sys.stdout.flush()
+    os._exit(0)
+if dtype == "long-rows":
+    # The kernels of rows of more than 4096 logits alone, their rows up against the guard page: draft lists, edges and perturbed scores against sorting,
+    # counting and 64-bit sums.  Sizes where they change: one slice of 16 384 and the next entry, four slices and the next entry (one list entry per
+    # round, as with more than 256 equal candidates), 8192 and 16 384 values of a row in registers.  Rows of NaN stay inside the row.
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    lib, f32, i32 = V._lib, np.float32, np.int32
+
+    def guarded(a):
+        p = lib.emu_alloc(a.nbytes, 0xAB)
+        v = np.frombuffer((C.c_char * a.nbytes).from_address(p), a.dtype).reshape(a.shape)
+        v[...] = a
+        return v
+    ptr = lambda a: C.c_void_p(a.ctypes.data)
+    rng = np.random.default_rng(97)
+    for V1, kind in ((4097, ""), (16384, ""), (16385, ""), (40001, ""), (65536, ""), (65537, ""), (5001, "equal"), (4999, "nan"), (6001, "some nan"), (4098, "-inf")):
+        z = rng.standard_normal((2, V1)).astype(f32)
+        z[:, V1 - 5:] = z[:, :5]                                   # equal values at both ends
+        if kind == "equal": z[:] = 1.5
+        if kind == "nan": z[:] = np.nan
+        if kind == "some nan": z[:, ::7] = np.nan
+        if kind == "-inf": z[:, 10:] = -np.inf
+        lists = guarded(np.full((2, 16), -1, i32))
+        lib.emu_topk(ptr(guarded(z)), V1, 2, ptr(lists))
+        print(f"lists of {V1} logits {kind}", flush=True)
+        assert ((lists >= 0) & (lists < V1)).all()
+        if "nan" not in kind:
+            for row, got in zip(z, lists):
+                assert np.array_equal(got, np.argsort(-row, kind="stable")[:16]), (V1, kind)
+    for V1 in (4097, 16001):
+        B, M = 2, 4
+        parent, finished = guarded(np.array([-1, 0, 0, 1], i32)), guarded(np.array([0, 1], i32))
+        z, tok = rng.standard_normal((B, M, V1)).astype(f32), rng.integers(0, V1, (B, M)).astype(i32)
+        tok[0, 1] = V1 - 1
+        z[0, 0, 5:50] = z[0, 0, tok[0, 1]]
+        for tau in (1, V1 // 3, V1):
+            ok = guarded(np.full((B, M), -1, i32))
+            lib.emu_edges(ptr(guarded(z)), B, M, V1, ptr(parent), ptr(guarded(tok)), ptr(finished), tau, ptr(ok))
+            print(f"edges of {V1} logits, tau {tau}", flush=True)
+            for n in range(M):
+                row, t = z[0, max(parent[n], 0)], tok[0, n]
+                ahead = int((row > row[t]).sum() + (row[:t] == row[t]).sum())
+                assert ok[0, n] == (n == 0 or ahead < tau), (V1, tau, n)
+            assert not ok[1].any()
+    for V1, tau, T, top_p in ((4097, 1, 0.9, 0.9), (8192, 3, 1.0, 0.5), (8193, 40, 0.5, 1e-4), (16384, 2, 0.7, 0.999), (4100, 1, 1.0, 1.0)):
+        z, u = (2.3 * rng.standard_normal((1, V1))).astype(f32), np.clip(rng.random((1, V1)), 2.0 ** -24, 1 - 2.0 ** -24).astype(f32)
+        z[0, V1 - 9:] = z[0, 7]
+        y = guarded(np.zeros((1, V1), f32))
+        lib.emu_perturb(ptr(guarded(z)), ptr(guarded(u)), ptr(y), 1, V1, C.c_float(T), C.c_float(top_p), tau)
+        print(f"scores of {V1} logits", flush=True)
+        s = (z[0] / f32(T)).astype(np.float64)
+        of = np.unique(-s, return_inverse=True)[1]
+        count, mass = np.bincount(of), np.bincount(of, np.exp(s - s.max()))
+        above, ahead = (np.cumsum(mass) - mass)[of] / mass.sum(), (np.cumsum(count) - count)[of]
+        kept = np.isfinite(y[0])
+        sure = (np.abs(above - top_p) > 1e-5) | (ahead < tau) | (top_p >= 1)     # (fp32 sums of the masses)
+        assert np.array_equal(kept[sure], ((above < top_p) | (ahead < tau) | (top_p >= 1))[sure]), V1
+        assert np.allclose(y[0][kept], (s - np.log(-np.log(u[0].astype(np.float64))))[kept], rtol=1e-6, atol=1e-5)
+    z = np.full((1, 4500), np.nan, f32)
+    lib.emu_perturb(ptr(guarded(z)), ptr(guarded(np.full((1, 4500), 0.5, f32))), ptr(guarded(z.copy())), 1, 4500, C.c_float(1.0), C.c_float(0.9), 2)
+    print("emulated long rows: compared", flush=True)
     sys.stdout.flush()
     os._exit(0)
 if dtype == "bf16-giveup":
