@@ -96,6 +96,9 @@ TILE_SHAPES = [
     (512, 512, 27, 19, 77, "4x4 2x4 2x4 1x1"),
     (512, 512, 41, 25, 77, "4x4 3x4 3x4 1x2"),
     (512, 512, 53, 29, 77, "4x4 4x4 4x4 2x1"),
+    (512, 2048, 27, 5, 77, "2x2 1x2 2x4 1x1"),     # a reduction of 2048: eight waves in FFN2
+    (512, 2048, 41, 7, 77, "2x4 2x2 3x4 1x1"),
+    (512, 2048, 53, 12, 77, "4x4 2x4 3x4 1x1"),
 ]
 
 
