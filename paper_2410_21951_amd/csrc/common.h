@@ -106,11 +106,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 
 // The same sums without LDS traffic: DPP lane permutations inside each row of 16 lanes (swap
 // with the quad neighbour, the other pair of the quad, the mirrored half row, the mirrored row:

@@ -632,9 +632,10 @@ __device__ __forceinline__ void landed() {
 
 template <int RG, int CG> struct TileShape {
     static constexpr int NB = RG * CG, KSP = 8 / NB;              // blocks of 64 x 64, waves per block
-    static constexpr int KB = KSP >= 4 ? 4 : 2;                   // k-steps of 32 per stage
+    static constexpr int KB = KSP == 1 ? 2 : 4;                   // k-steps of 32 per stage
     static constexpr int TILES = 4 * (RG + CG), KIB = TILES * KB; // operand tiles, KiB of a stage
     static constexpr int NS = 144 / KIB;                          // stages in the ring
+    static_assert((KSP == 1 || KSP == 4) && NS == 3, "the waits and the epilogue are written for 256 x 128 and 128 x 64 outputs");
     static constexpr int LPW = KIB / 8, SPW = 2 * KB / KSP;       // loads and half k-steps of a wave per stage
 };
 
@@ -732,7 +733,6 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
                     if (s + NS - 1 < nst) fetch(s + NS - 1, left, LPW * sl / (SPW - 1), LPW * (sl + 1) / (SPW - 1));
                 } else {
                     if (s + NS <= nst) landed<(NS - 2) * LPW>();      // stages s + 2 .. s + NS - 1 may be on their way
-                    else if (NS > 3 && s + NS - 1 == nst) landed<(NS > 3 ? NS - 3 : 0) * LPW>();
                     else landed<0>();
                     read(next, 0, x[0], w[0]);
                 }
@@ -745,8 +745,8 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
     };
     for (int s = 0; s + 1 < nst; ++s) stage(s, std::false_type{});
     // What the epilogue adds is asked for ahead of the last stage's products.
-    constexpr int RB = KSP == 1 ? 2 : 1, TB = KSP <= 2 ? 4 : 8 / KSP;
-    const int lr = lane & 31, hi = lane >> 5, rb0 = KSP == 1 ? 0 : kq * 2 / KSP, tb0 = KSP <= 2 ? 0 : kq * TB % 4, tile0 = ct0 + 4 * cg + tb0;
+    constexpr int RB = KSP == 1 ? 2 : 1, TB = KSP == 1 ? 4 : 2;
+    const int lr = lane & 31, hi = lane >> 5, rb0 = KSP == 1 ? 0 : kq >> 1, tb0 = KSP == 1 ? 0 : 2 * (kq & 1), tile0 = ct0 + 4 * cg + tb0;
     int r[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) r[i] = row0 + (rg * 2 + rb0 + i) * 32 + lr;
@@ -896,7 +896,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 // ---------------------------------------------------------------------------
 // Tree-masked attention (Sec. 2.1): one (sequence, head) and QT tiles of 16 query rows per workgroup.  Keys: cache
 // positions [0, L) and the rows of this forward at L + m where the query's mask bit m is set (CAUSAL: rows 0 .. n of a
-// prompt pass, which may have more rows than the mask table).  The four waves take 32-key blocks round-robin with a
+// prompt pass, which may have more rows than the mask table).  The waves take 32-key blocks round-robin with a
 // private online softmax (S^T = K Q^T, O^T += V^T P^T on MFMA) and merge through LDS.  The cache keeps K and V^T in blocks
 // of 32 keys, each already in the layout of the MFMA operands (kc_off / vc_off in common.h).
 // QT = 2 where there are workgroups enough for every compute unit: a key block is then fetched once for 32 queries.
@@ -958,9 +958,8 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
     }
     constexpr int DT = NW > 4 ? 2 : 4;   // the merge's outputs of a thread, per tile: dimensions d_out .. of query q_out
     const int q_out = tid / (64 / DT), d_out = tid % (64 / DT) * DT;
-    const bool merges = q_out < 16;
     auto put = [&](int nd, const float (&o)[DT]) {
-        if (!merges || nd >= M || (last_only && nd != M - 1)) return;
+        if (nd >= M || (last_only && nd != M - 1)) return;
         bf16_t* to = a.att + toff(last_only ? b : row0 + nd, h * 64 + d_out, a.d >> 5);
         if constexpr (DT == 4) *(uint2*)to = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
         else *(uint32_t*)to = pack_bf16(o[0], o[1]);
@@ -1090,7 +1089,6 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
             for (int i = 0; i < 4; ++i) sm_o[t][(wave * 64 + dt * 16 + 4 * gq + i) * SO + c] = O[t][dt][i];
     }
     __syncthreads();
-    if (!merges) return;
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
         float mstar = sm_m[t][q_out];
@@ -1255,7 +1253,7 @@ static void big_launch(LinArgs& a, hipStream_t st) {
 template <int RG, int CG, int EPI>
 static void tile_launch(LinArgs& a, hipStream_t st) {
     const TileGrid g = tile_grid(a, 64 * RG, 4 * CG);
-    a.sg_out = TileShape<RG, CG>::KSP > 2 ? 5 : a.N % 128 ? 4 : 6;   // (a wave's columns as one entry where that leaves a row an even number)
+    a.sg_out = TileShape<RG, CG>::KSP > 1 ? 5 : a.N % 128 ? 4 : 6;   // (a wave's columns as one entry where that leaves a row an even number)
     launch((k_tile<RG, CG, EPI>), dim3(8 * cdiv(g.gr * g.gc, 8)), dim3(512), 0, st, a, g);
 }
 // Which kernel: the one that is estimated to take least.  us per launch, fitted to 1445 maps of whole steps, each run with all four kernels (widths
@@ -1361,8 +1359,7 @@ static void attn(const AttnArgs& t, bool causal, int keys, int big_min, hipStrea
 }
 
 void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st) {
-    int R = D.R;
-    const int d = D.d;
+    const int R = D.R, d = D.d;
     const size_t kv_layer = (size_t)D.Bmax * D.nH * kv_cap(D.maxpos) * 64;
     clock_point(s, 0, st);
     launch(k_embed_rows, dim3(R), dim3(256), 0, st, D, s, prefill_mode, table);
@@ -1387,7 +1384,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         LinArgs o = base;
         o.X = (const bf16_t*)s.att; o.W = (const uint4*)w.Wo; o.bias = w.bo; o.nks = d >> 5; o.N = d; o.NT = d >> 4;
         o.out = s.xb; o.outf = s.x; o.stats_out = (float2*)s.stats;
-        if (end && D.last_only) base.R = R = o.R = D.B;
+        if (end && D.last_only) base.R = o.R = D.B;
         o.resid = x;
         clock_point(s, 3 + 5 * l, st);
         lin<LE_RESID>(o, big_min, st);
