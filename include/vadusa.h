@@ -136,13 +136,14 @@ size_t vadusa_blob_floats(const vadusa_config* cfg);
  * stream).  *out receives the context (host object, freed by vadusa_destroy). */
 int vadusa_create(const vadusa_config* cfg, void* arena, size_t arena_bytes,
                   void* hip_stream, vadusa_ctx** out);
-/* Environment variables (debugging and test aids; none changes results):
+/* Environment variables (debugging and test aids; none changes results beyond the order of fp32 sums):
  *   VADUSA_PHASE_CLOCK          the binding loads libvadusa_clock.so (built with -DVADUSA_CLOCK_BUILD), which records
  *                               the timing points of VADUSA_DBG_PHASE_CLOCK
- *   VADUSA_BIG_MIN_UNITS=n      read by vadusa_create: a linear map of the bf16 model takes 64 x 128 output tiles
+ *   VADUSA_BIG_MIN_UNITS=n      read by vadusa_create; lets tests reach kernels with small shapes.  0, or not set: the
+ *                               library chooses.  n > 0: a linear map of the bf16 model takes 64 x 128 output tiles
  *                               from n such tiles on, whatever its size, and its attention takes two tiles of
- *                               16 queries per workgroup from n such workgroups on; lets tests reach these
- *                               kernels with small shapes
+ *                               16 queries per workgroup from n such workgroups on.  -1: every map of a decoder layer
+ *                               and of the vocabulary takes tiles of 256 x 128 outputs; below -1: of 128 x 64
  * A step is one launch per map, so VADUSA_PHASE_LAUNCHES and VADUSA_COOPERATIVE_LAUNCH of earlier versions have no
  * effect. */
 

@@ -100,7 +100,7 @@ __device__ inline int dev_edge_count(const Dims& D, const DevState& s, int b, in
 // An accepted path in LDS: number of nodes, the nodes and their tokens.
 struct PathLds { int cnt, node[VADUSA_MAX_DRAFT_HEADS + 1], tok[VADUSA_MAX_DRAFT_HEADS + 1]; };
 
-// Sec. 2.3's choice for sequence b from the edge decisions in edge_ok (dev_edge): a node is accepted iff every edge from the root to
+// Sec. 2.3's choice for sequence b from the edge decisions in edge_ok (k_edges, k_edges_wide): a node is accepted iff every edge from the root to
 // it is; the chosen one is the deepest, smallest index among equals (canonical order = leftmost).  Cut after the first EOS.
 // Output: p, and path[b] = {count, node indices...} in memory for the compaction.  256 threads; everything it reads from memory is
 // asked for at once, and what the walks need sits in LDS (a step's chain of dependent loads is what bounds it).

@@ -247,7 +247,7 @@ struct vadusa_ctx {
     float* uniforms;             // [max_batch * max_tree_nodes][V+1]: the caller's random numbers of a stochastic step
     float* scores;               // same shape: perturbed scores that replace the logits in such a step
     int sampled;                 // the pending / last verification was a stochastic one
-    int big_min;                 // k_big's tiles, and attention workgroups of two query tiles, from this many on; -1, -2: k_tile of 256 x 128, 128 x 64 outputs for every
+    int big_min;                 // k_big's tiles, and attention workgroups of two query tiles, from this many on; -1, below -1: k_tile of 256 x 128, 128 x 64 outputs for every
                                  // map (environment VADUSA_BIG_MIN_UNITS, for tests of small shapes); 0: the rules
     int32_t* pinned;             // host memory that the last kernel of a call writes results into (null: none)
     size_t pinned_words;

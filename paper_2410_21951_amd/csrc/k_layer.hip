@@ -325,9 +325,9 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
 // for 3.4 us of them, and a compute unit pulls 0.8 MB through L2.  512 workgroups are 0.67 rounds of the 768 that fit, each with its
 // statistics, 16 stages with a barrier, GELU and stores one behind the other.
 // Residual maps: tiles numbered in blocks per XCD (with a column of tiles per XCD all activations go into every L2), statistics per
-// 32 columns; bf16 results as whole 16-byte pieces (us, before and after, weights from HBM): out-projection of 2048 rows 15.0 -> 13.2, FFN2 of
-// 3200 rows 46.4 -> 42.5, of 4352 rows 68.6 -> 62.4; FFN1 of 640 rows 15.4 -> 14.3, of 1024 rows 18.2 -> 17.4.  The other maps keep the column
-// numbering: their activations fit an L2, and finding the block costs more than it gives (QKV of 1024 rows 16.8 against 17.6).
+// 32 columns (us, before and after, weights from HBM): out-projection of 2048 rows 15.0 -> 13.2, FFN2 of 3200 rows 46.4 -> 42.5, of 4352 rows
+// 68.6 -> 62.4.  The other maps keep the column numbering: their activations fit an L2, and finding the block costs more than it gives (QKV
+// of 1024 rows 16.8 against 17.6).  FFN1 stores its results as whole 16-byte pieces (640 rows 15.4 -> 14.3, 1024 rows 18.2 -> 17.4).
 // ---------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 // D = A B + C, A 32 x 16 (lane: row lane & 31, k 8 (lane >> 5) ..), B 16 x 32 alike; lane l, element i of D: column

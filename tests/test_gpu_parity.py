@@ -388,7 +388,7 @@ def test_valle_b1_stochastic_steps(valle):
 
 def test_large_vocabulary_16k():
     """A 16 000-entry speech vocabulary (16 001 logits per row: the draft lists come from the
-    re-scanning top-k, the stochastic rule holds a whole row in LDS) on a 3-layer d = 1024 model."""
+    top-k of 1024 threads, the stochastic rule holds a whole row in their registers) on a 3-layer d = 1024 model."""
     from synth import make_uniforms
     m = PRESETS["vocab16k_b1"].model
     cfg = dataclasses.replace(m, n_layers=3, max_positions=512)
