@@ -80,11 +80,11 @@ if dtype in ("bf16-tile256", "bf16-tile128", "bf16-long-ffn", "bf16-long-keys"):
     # last stage that is half empty); long-ffn: a reduction of 2048 by eight waves; long-keys: 318 keys and more, eight waves per query tile.
     long_ffn, long_keys = dtype == "bf16-long-ffn", dtype == "bf16-long-keys"
     os.environ["VADUSA_BIG_MIN_UNITS"] = {"bf16-tile256": "-1", "bf16-tile128": "-2"}.get(dtype, "0")
-    cfg = ModelConfig(n_layers=1 if long_ffn or long_keys else 2, d_model=64, n_heads=1, head_dim=64, d_ffn=2048 if long_ffn else 64 if long_keys else 192,
+    cfg = ModelConfig(n_layers=1, d_model=64, n_heads=1, head_dim=64, d_ffn=2048 if long_ffn else 64 if long_keys else 192,
                       speech_vocab=71, text_vocab=20, n_draft_heads=2, max_positions=392 if long_keys else 96, dtype="bf16")
     W = make_weights(cfg, 95, std=0.05)
     rng = np.random.default_rng(96)
-    B, M = (1, 19) if long_ffn else (1, 17) if long_keys else (3, 27)
+    B, M = (1, 17) if long_ffn or long_keys else (3, 27)
     text = [rng.integers(0, cfg.text_vocab, 2 + b).astype(np.int32) for b in range(B)]
     prompt = [rng.integers(0, cfg.speech_vocab, 315 if long_keys else 20 - 7 * b).astype(np.int32) for b in range(B)]
     t0 = time.time()
