@@ -46,7 +46,7 @@ struct LinArgs {
     float2* stats_out;      // [R][N >> sg_out] (LE_RESID)
     bf16_t *Kc, *Vc;        // LE_QKV: this layer's cache
     const int32_t *L, *n_rows, *row_seq, *row0;   // row_seq, row0: of a ragged prompt pass (null: sequence b has rows b * M ..)
-    int per_block;          // k_lin: 65536 / row blocks where these start at different k-steps, else 0
+    uint32_t m_magic;       // ceil(2^32 / M): r / M of a step's rows (0: M = 1)
     const float* resid;     // LE_RESID: what the map's result is added to
     int M, nH, maxpos, d;
     size_t z_w, z_b, z_x, z_out;   // LE_SILU, LE_F32: what a draft head's weights, bias (bytes), X and result (elements) are ahead of the previous head's
@@ -54,6 +54,7 @@ struct LinArgs {
 
 // Workgroup i runs on XCD i mod 8.  The first grid dimension counts column groups, padded to a multiple of 8, so that
 // the row blocks that share a weight tile share an XCD and its L2 and the tile leaves HBM once.
+__device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
 __host__ __device__ inline int pad8(int a) { return (a + 7) & ~7; }
 
 // Row statistics of the LayerNorm folded into a map, for the ROWS rows of a workgroup, in two steps: request (ahead of
@@ -162,87 +163,69 @@ __device__ __forceinline__ void store4(const LinArgs& a, int r, int n0, bool liv
 // operands (weights from HBM, activations from L2, both already in MFMA operand tiles: one contiguous KiB per wave
 // load) straight into registers, CH k-steps at a time with the next chunk's loads ahead of the current chunk's MFMAs;
 // the four partial sums are added in wave order through LDS.
+// What bounds it with few rows: the chain from the launch to the first product.  A wave issues an instruction every five clocks, every eight where one
+// needs the one before, and arguments in memory take some 500 to 850 clocks, so what the operands' addresses need comes as leading
+// arguments, which arrive in registers with the wave (build.py), the operands are asked for before everything else, from scalar bases with the
+// distance in the instruction (WHOLE), and nothing waits ahead of them.  Statistics and the epilogue's inputs requested first, with the wait that this
+// put before the operands, and arguments as one struct: steps of 1 | 16 | 64 | 128 | 5 x 27 nodes, us 310 | 340 | 358 | 475 | 464, now
+// 288 | 315 | 341 | 465 | 449.
 // ---------------------------------------------------------------------------
-template <int RT, int CT, int CH, int EPI, int NW>
-__global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
+template <int RT, int CT, int CH, int EPI, int NW, bool WHOLE>   // WHOLE: every wave's k-steps are whole chunks
+__global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W, int nks, int NT, int R, int per_block, size_t z_w, size_t z_x, LinArgs a) {
     constexpr bool LN = EPI <= LE_LOGITS;
-    if constexpr (EPI == LE_SILU || EPI == LE_F32) {
-        const size_t z = blockIdx.z;
-        a.W = (const uint4*)((const char*)a.W + z * a.z_w);
-        a.bias = (const float*)((const char*)a.bias + z * a.z_b);
-        a.X += z * a.z_x;
-        a.out += z * a.z_out;
-        a.outf += z * a.z_out;
-    }
     constexpr int T = RT * CT, NPW = (T + NW - 1) / NW;   // output tiles, tiles per wave in the epilogue
     static_assert(!LN || NW == 4, "the row statistics are merged by 256 threads");
     constexpr int ROWS = RT == 3 ? 64 : RT * 16;   // rows whose statistics are merged
     __shared__ f32x4_t red[NW * T * 64];
     __shared__ float s_mean[ROWS], s_rstd[ROWS];
     const int g = blockIdx.x, rb = blockIdx.y;
-    if (g * CT >= a.NT) return;   // padding of the XCD-aware numbering
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int lc = lane & 15, gq = lane >> 4, row0 = rb * RT * 16, last_rt = (a.R - 1) >> 4;
-    const int ks_lo = a.nks * wave / NW, ks_hi = a.nks * (wave + 1) / NW;
-    // epilogue inputs of this thread's tiles, and the row statistics: asked for first, needed last
-    float bias[NPW][4], cs[NPW][4], xr[NPW][4];
-    int seq[NPW], pos[NPW], rows[NPW];   // LE_QKV: sequence, first position and rows of the row's sequence, for kv_row
-    RowStats<ROWS> st;
-    if constexpr (LN) st.request(a, row0);
-#pragma unroll
-    for (int p = 0; p < NPW; ++p) {
-        const int t = wave + NW * p, n0 = (g * CT + t % CT) * 16 + 4 * gq, r = row0 + (t / CT) * 16 + lc;
-        const bool have = t < T && g * CT + t % CT < a.NT;
-        uint4 b4 = make_uint4(0, 0, 0, 0), c4 = b4, x4 = b4;
-        if (have) {
-            if (EPI != LE_F32) b4 = ldg4(a.bias + n0);
-            if (LN) c4 = ldg4(a.colsum + n0);
-            if (EPI == LE_RESID) x4 = ldg4(a.resid + (size_t)(r < a.R ? r : 0) * a.N + n0);
-        }
-        if constexpr (EPI == LE_QKV) {   // nothing waits for these before the operands are on their way
-            const int rr = min(r, a.R - 1);
-            seq[p] = a.row_seq ? ldg(a.row_seq + rr) : rr / a.M;
-            pos[p] = ldg(a.L + seq[p]) + rr - (a.row_seq ? ldg(a.row0 + seq[p]) : seq[p] * a.M);
-            rows[p] = ldg(a.n_rows + seq[p]);
-        }
-        bias[p][0] = __uint_as_float(b4.x); bias[p][1] = __uint_as_float(b4.y); bias[p][2] = __uint_as_float(b4.z); bias[p][3] = __uint_as_float(b4.w);
-        cs[p][0] = __uint_as_float(c4.x); cs[p][1] = __uint_as_float(c4.y); cs[p][2] = __uint_as_float(c4.z); cs[p][3] = __uint_as_float(c4.w);
-        xr[p][0] = __uint_as_float(x4.x); xr[p][1] = __uint_as_float(x4.y); xr[p][2] = __uint_as_float(x4.z); xr[p][3] = __uint_as_float(x4.w);
-        if (EPI == LE_SILU && have) {   // the map's own input at the output's place (N = K)
-            const uint2 h = ldg2(a.X + toff(min(r, a.R - 1), n0, a.nks));
-            xr[p][0] = bf2f((bf16_t)h.x); xr[p][1] = bf2f((bf16_t)(h.x >> 16)); xr[p][2] = bf2f((bf16_t)h.y); xr[p][3] = bf2f((bf16_t)(h.y >> 16));
-        }
+    if (g * CT >= NT) return;   // padding of the XCD-aware numbering
+    if constexpr (EPI == LE_SILU || EPI == LE_F32) {
+        W = (const uint4*)((const char*)W + blockIdx.z * z_w);
+        X += blockIdx.z * z_x;
     }
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int lc = lane & 15, gq = lane >> 4, row0 = rb * RT * 16, last_rt = (R - 1) >> 4;
+    const int ks_lo = (uint32_t)(nks * wave) / NW, ks_hi = (uint32_t)(nks * (wave + 1)) / NW, nk = ks_hi - ks_lo;
     // (one row tile: rows beyond the map's last read the last one's pieces, which are fewer lines: one row, QKV 4.3 -> 3.9 us, FFN2 6.8 -> 5.9)
-    const uint32_t xl = RT > 1 ? (uint32_t)lane * 16u : (uint32_t)(min(lc, a.R - 1 - min(rb, last_rt) * 16) + 16 * gq) * 16u;
+    const uint32_t wl = (uint32_t)lane * 16u, xl = RT > 1 ? wl : (uint32_t)(min(lc, R - 1 - min(rb, last_rt) * 16) + 16 * gq) * 16u;
     const char *Wp[CT], *Xp[RT];
 #pragma unroll
-    for (int c = 0; c < CT; ++c) Wp[c] = (const char*)(a.W + (size_t)min(g * CT + c, a.NT - 1) * a.nks * 64);
+    for (int c = 0; c < CT; ++c) Wp[c] = (const char*)W + (size_t)(uint32_t)min(g * CT + c, NT - 1) * (uint32_t)(nks * 1024);
 #pragma unroll
-    for (int r = 0; r < RT; ++r) Xp[r] = (const char*)((const uint4*)a.X + (size_t)min(rb * RT + r, last_rt) * a.nks * 64);
+    for (int r = 0; r < RT; ++r) Xp[r] = (const char*)X + (size_t)(uint32_t)min(rb * RT + r, last_rt) * (uint32_t)(nks * 1024);
     f32x4_t acc[CT][RT];
 #pragma unroll
     for (int c = 0; c < CT; ++c)
 #pragma unroll
         for (int r = 0; r < RT; ++r) acc[c][r] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-    // Workgroups on the same columns start at different k-steps: side by side they would all wait for the same lines from HBM, and a
+    // Workgroups on the same columns start at different chunks: side by side they would all wait for the same lines from HBM, and a
     // compute unit has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
     // (FFN2, K = 4096, us: 128 rows 8.6 -> 7.0, 135 rows 9.3 -> 8.7, 320 rows 12.8 -> 11.7; beyond what an L2 holds they
     // drive each other out of it: 1024 rows 18.4 -> 20.3, k_tile and k_big likewise.  Not the LayerNorm-folded maps of K = 1024,
     // whose operands are all on their way at once: 64 rows FFN1 5.0 -> 5.4.)
-    const int turn = EPI == LE_RESID ? (ks_hi - ks_lo) * rb * a.per_block >> 16 : 0;
-    // Loads are unconditional: a tile beyond the map's last row or column re-reads a valid one and only reaches
-    // accumulators that are never stored; a k-step beyond the last re-reads the last and is not multiplied.
-    uint4 wA[CH][CT], xA[CH][RT], wB[CH][CT], xB[CH][RT];
-    auto load = [&](int kb, uint4 (&w)[CH][CT], uint4 (&x)[CH][RT]) {
+    const int nch = (nk + CH - 1) / CH, turn = EPI == LE_RESID && WHOLE ? nch * rb * per_block >> 16 : 0;
+    // Chunk j of the wave, in the order that its turn gives.  Loads are unconditional: a tile beyond the map's last row or column
+    // re-reads a valid one and only reaches accumulators that are never stored; a k-step beyond the last re-reads the last and is not multiplied.
+    auto load = [&](int j, uint4 (&w)[CH][CT], uint4 (&x)[CH][RT]) {
+        const int q = j + turn >= nch ? j + turn - nch : j + turn, k0 = ks_lo + q * CH;
+        if constexpr (WHOLE) {   // distances from a scalar base per tile and four k-steps, as part of the instruction
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int k = kb + i + turn;
-            const uint32_t off = (uint32_t)min(EPI == LE_RESID && k >= ks_hi ? k - (ks_hi - ks_lo) : k, a.nks - 1) * 1024u;
+            for (int i = 0; i < CH; ++i) {
 #pragma unroll
-            for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + (off + (uint32_t)lane * 16u));
+                for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + (uint32_t)(k0 + (i & ~3)) * 1024u + wl + (i & 3) * 1024);
 #pragma unroll
-            for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + (off + xl));
+                for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + (uint32_t)(k0 + (i & ~3)) * 1024u + xl + (i & 3) * 1024);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const uint32_t off = (uint32_t)min(k0 + i, nks - 1) * 1024u;
+#pragma unroll
+                for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + off + wl);
+#pragma unroll
+                for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + off + xl);
+            }
         }
     };
     auto mul = [&](int n, const uint4 (&w)[CH][CT], const uint4 (&x)[CH][RT]) {
@@ -255,23 +238,65 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
                     for (int r = 0; r < RT; ++r)   // weights first: a lane then holds four consecutive columns of one row
                         acc[c][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[i][c]), __builtin_bit_cast(bf16x8_t, x[i][r]), acc[c][r], 0, 0, 0);
     };
-    int kb = ks_lo;
-    load(kb, wA, xA);
-    if constexpr (LN) st.merge(a, s_mean, s_rstd);
-    bool in_a = true;
-    while (kb + CH < ks_hi) {
-        load(kb + CH, wB, xB);
-        mul(CH, wA, xA);
-        kb += CH;
-        in_a = false;
-        if (kb + CH >= ks_hi) break;
-        load(kb + CH, wA, xA);
-        mul(CH, wB, xB);
-        kb += CH;
-        in_a = true;
+    uint4 wA[CH][CT], xA[CH][RT], wB[CH][CT], xB[CH][RT];
+    load(0, wA, xA);
+    SCHED_FENCE();
+    // row statistics and what the epilogue of this thread's tiles adds
+    if constexpr (EPI == LE_SILU || EPI == LE_F32) {
+        a.bias = (const float*)((const char*)a.bias + blockIdx.z * a.z_b);
+        a.out += blockIdx.z * a.z_out;
+        a.outf += blockIdx.z * a.z_out;
     }
-    if (in_a) mul(ks_hi - kb, wA, xA);
-    else mul(ks_hi - kb, wB, xB);
+    float bias[NPW][4], cs[NPW][4], xr[NPW][4];
+    int seq[NPW], len[NPW], first[NPW], rows[NPW];   // LE_QKV: the row's sequence, its committed length, first row and rows
+    RowStats<ROWS> st;
+    if constexpr (LN) st.request(a, row0);
+#pragma unroll
+    for (int p = 0; p < NPW; ++p) {
+        const int t = wave + NW * p, n0 = (g * CT + t % CT) * 16 + 4 * gq, r = row0 + (t / CT) * 16 + lc;
+        const bool have = t < T && g * CT + t % CT < NT;
+        uint4 b4 = make_uint4(0, 0, 0, 0), c4 = b4, x4 = b4;
+        if (have) {
+            if (EPI != LE_F32) b4 = ldg4(a.bias + n0);
+            if (LN) c4 = ldg4(a.colsum + n0);
+            if (EPI == LE_RESID) x4 = ldg4(a.resid + (size_t)(r < R ? r : 0) * a.N + n0);
+        }
+        if constexpr (EPI == LE_QKV) {
+            const int rr = min(r, R - 1);
+            seq[p] = a.row_seq ? ldg(a.row_seq + rr) : a.m_magic ? (int)mulhi((uint32_t)rr, a.m_magic) : rr;
+            len[p] = ldg(a.L + seq[p]);
+            first[p] = a.row_seq ? ldg(a.row0 + seq[p]) : seq[p] * a.M;
+            rows[p] = ldg(a.n_rows + seq[p]);
+        }
+        bias[p][0] = __uint_as_float(b4.x); bias[p][1] = __uint_as_float(b4.y); bias[p][2] = __uint_as_float(b4.z); bias[p][3] = __uint_as_float(b4.w);
+        cs[p][0] = __uint_as_float(c4.x); cs[p][1] = __uint_as_float(c4.y); cs[p][2] = __uint_as_float(c4.z); cs[p][3] = __uint_as_float(c4.w);
+        xr[p][0] = __uint_as_float(x4.x); xr[p][1] = __uint_as_float(x4.y); xr[p][2] = __uint_as_float(x4.z); xr[p][3] = __uint_as_float(x4.w);
+        if (EPI == LE_SILU && have) {   // the map's own input at the output's place (N = K)
+            const uint2 h = ldg2(X + toff(min(r, R - 1), n0, nks));
+            xr[p][0] = bf2f((bf16_t)h.x); xr[p][1] = bf2f((bf16_t)(h.x >> 16)); xr[p][2] = bf2f((bf16_t)h.y); xr[p][3] = bf2f((bf16_t)(h.y >> 16));
+        }
+    }
+    SCHED_FENCE();
+    int j = 0;
+    for (; j + 2 < nch; j += 2) {
+        load(j + 1, wB, xB);
+        SCHED_FENCE();   // (the scheduler would put a chunk's loads between the products)
+        mul(CH, wA, xA);
+        SCHED_FENCE();
+        load(j + 2, wA, xA);
+        SCHED_FENCE();
+        mul(CH, wB, xB);
+        SCHED_FENCE();
+    }
+    if (j + 1 < nch) {
+        load(j + 1, wB, xB);
+        SCHED_FENCE();
+        mul(CH, wA, xA);
+        mul(WHOLE ? CH : nk - (j + 1) * CH, wB, xB);
+    } else {
+        mul(WHOLE ? CH : nk - j * CH, wA, xA);
+    }
+    if constexpr (LN) st.merge(a, s_mean, s_rstd);
 #pragma unroll
     for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -282,7 +307,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
         const int t = wave + NW * p;
         if (t >= T) break;
         const int c = t % CT, rl = (t / CT) * 16 + lc, r = row0 + rl, tile = g * CT + c, n0 = tile * 16 + 4 * gq;
-        if (tile >= a.NT) continue;
+        if (tile >= NT) continue;
         f32x4_t s = red[t * 64 + lane];
 #pragma unroll
         for (int w = 1; w < NW; ++w) s += red[(w * T + t) * 64 + lane];
@@ -298,14 +323,15 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
         if constexpr (EPI == LE_RESID) {   // statistics of the tile's 16 columns: four here, twelve in the lanes 16, 32 and 48 further on
             const float mean = rows_sum(v[0] + v[1] + v[2] + v[3]) * (1.f / 16.f);
             const float m2 = rows_sum((v[0] - mean) * (v[0] - mean) + (v[1] - mean) * (v[1] - mean) + (v[2] - mean) * (v[2] - mean) + (v[3] - mean) * (v[3] - mean));
-            if (r < a.R && gq == 0) a.stats_out[(size_t)r * (a.N >> 4) + tile] = make_float2(mean, m2);
+            if (r < R && gq == 0) a.stats_out[(size_t)r * (a.N >> 4) + tile] = make_float2(mean, m2);
         }
         KvRow kv{0, -1};
         if constexpr (EPI == LE_QKV) {
             kv.base = (size_t)seq[p] * a.nH * kv_cap(a.maxpos) * 64;
-            if (r < a.R && pos[p] < a.maxpos && rows[p] > 0) kv.pos = pos[p];
+            const int pos = len[p] + r - first[p];
+            if (r < R && pos < a.maxpos && rows[p] > 0) kv.pos = pos;
         }
-        store4<EPI>(a, r, n0, r < a.R, v, kv);
+        store4<EPI>(a, r, n0, r < R, v, kv);
     }
 }
 
@@ -1235,8 +1261,8 @@ static LinShape lin_shape(int R, int NT) {
 
 template <int RT, int CT, int CH, int EPI, int NW = 4>
 static void lin_launch(LinArgs a, hipStream_t st, int nz = 1) {
-    a.per_block = (size_t)a.R * a.nks * 64 <= (3u << 20) ? 65536 / cdiv(a.R, RT * 16) : 0;   // (while an L2 of 4 MiB holds what its workgroups read)
-    launch((k_lin<RT, CT, CH, EPI, NW>), dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(64 * NW), 0, st, a);
+    const int per_block = (size_t)a.R * a.nks * 64 <= (3u << 20) ? 65536 / cdiv(a.R, RT * 16) : 0;   // (while an L2 of 4 MiB holds what its workgroups read)
+    launch(a.nks % (NW * CH) ? k_lin<RT, CT, CH, EPI, NW, false> : k_lin<RT, CT, CH, EPI, NW, true>, dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(64 * NW), 0, st, a.X, a.W, a.nks, a.NT, a.R, per_block, a.z_w, a.z_x, a);
 }
 // The tiles of `rows` rows x 16 `ct` columns; an XCD's eighth of them: about as many columns as rows.
 static TileGrid tile_grid(const LinArgs& a, int rows, int ct) {
@@ -1365,6 +1391,7 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
     launch(k_embed_rows, dim3(R), dim3(256), 0, st, D, s, prefill_mode, table);
     LinArgs base{};
     base.R = R; base.L = s.L; base.n_rows = s.n_rows; base.row_seq = s.row_seq; base.row0 = s.row0; base.M = D.M; base.nH = D.nH; base.maxpos = D.maxpos; base.d = d;
+    base.m_magic = D.M > 1 ? (uint32_t)(((1ull << 32) + D.M - 1) / D.M) : 0;
     base.stats = (const float2*)s.stats; base.sg = 4;   // (k_embed_rows)
     for (int l = 0; l < D.Ly; ++l) {
         const LayerW& w = layers[l];
