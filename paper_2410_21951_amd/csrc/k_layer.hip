@@ -34,6 +34,43 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 enum { LE_QKV = 0, LE_GELU, LE_LOGITS, LE_RESID, LE_SILU, LE_F32 };   // LE_SILU, LE_F32: first and second map of the draft heads
 
+__device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
+
+// Lines of weights that a later launch will read, brought into the L2s ahead of it by workgroups of a launch that leaves compute units idle: of each
+// group of column tiles, which workgroups of XCD (group mod 8) read, `take` pieces of 64 lines.  Lines that have only been read stay in the L2 from
+// launch to launch (32 KiB by one wave per compute unit: 1060 clocks from the own L2, 2880 from the memory-side cache or where another XCD has
+// read them, 3440 from HBM); without this the memory has nothing to do between two maps' loads: while a launch ends and the next starts (1.3 us),
+// while it finds its operands, adds and stores.  us per step, without and with it: 1 node 288 -> 265, 16 nodes 315 -> 281, 64 nodes 341 -> 327, 128 nodes
+// and 2000 keys 465 -> 443, 5 sequences of 27 nodes 449 -> 434.
+struct Touch {
+    const char* p;          // first piece of the first group
+    uint32_t stride, last;  // bytes from a group to the next; from a group's first piece to its last line
+    uint32_t take, magic;   // ceil(2^32 / take)
+    int groups;
+};
+template <int N> struct TouchList { Touch map[N]; };
+__device__ __forceinline__ int touch_pieces(const Touch& m, int xcd) { return ((m.groups - xcd + 7) >> 3) * (int)m.take; }   // of each map, for this XCD
+__device__ __forceinline__ const char* touch_line(const Touch& m, int xcd, int piece, int lane) {
+    const uint32_t g = m.take == 1 ? (uint32_t)piece : mulhi((uint32_t)piece, m.magic), part = (uint32_t)piece - g * m.take;
+    return m.p + (size_t)(g * 8 + xcd) * m.stride + min(part * 8192u + (uint32_t)lane * 128u, m.last);
+}
+// By the workgroups from column `first` on of a grid whose columns are whole groups of eight behind it, NW waves each, one lane per line.  (One load of a
+// wave on its way at a time: four are no faster.)  nz maps of each shape, z_w[i] bytes from one to the next.
+template <int NW, int N>
+__device__ __forceinline__ void touch(const TouchList<N>& t, int first, int nz, const size_t* z_w) {
+    const int xcd = blockIdx.x & 7, lane = threadIdx.x & 63, each = ((int)gridDim.x - first) >> 3, nw = each * gridDim.y * NW;
+    const int w = (int)(blockIdx.y * each + ((blockIdx.x - first) >> 3)) * NW + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+        const int n = touch_pieces(t.map[m], xcd);
+        for (int z = 0, i = w; z < nz; ++z, i -= n)
+            for (; i < n; i += nw) {
+                uint32_t v = ldg((const uint32_t*)(touch_line(t.map[m], xcd, i, lane) + (z_w ? z * z_w[m] : 0)));
+                ARRIVED(v);
+            }
+    }
+}
+
 struct LinArgs {
     const bf16_t* X;        // [R][K] operand tiles
     const uint4* W;         // [N][K] operand tiles
@@ -54,7 +91,6 @@ struct LinArgs {
 
 // Workgroup i runs on XCD i mod 8.  The first grid dimension counts column groups, padded to a multiple of 8, so that
 // the row blocks that share a weight tile share an XCD and its L2 and the tile leaves HBM once.
-__device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
 __host__ __device__ inline int pad8(int a) { return (a + 7) & ~7; }
 
 // Row statistics of the LayerNorm folded into a map, for the ROWS rows of a workgroup, in two steps: request (ahead of
@@ -171,7 +207,7 @@ __device__ __forceinline__ void store4(const LinArgs& a, int r, int n0, bool liv
 // 288 | 315 | 341 | 465 | 449.
 // ---------------------------------------------------------------------------
 template <int RT, int CT, int CH, int EPI, int NW, bool WHOLE>   // WHOLE: every wave's k-steps are whole chunks
-__global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W, int nks, int NT, int R, int per_block, size_t z_w, size_t z_x, LinArgs a) {
+__global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W, int nks, int NT, int R, int per_block, size_t z_w, size_t z_x, LinArgs a, TouchList<2> ahead) {   // ahead: for the workgroups behind the map's own
     constexpr bool LN = EPI <= LE_LOGITS;
     constexpr int T = RT * CT, NPW = (T + NW - 1) / NW;   // output tiles, tiles per wave in the epilogue
     static_assert(!LN || NW == 4, "the row statistics are merged by 256 threads");
@@ -179,7 +215,11 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W
     __shared__ f32x4_t red[NW * T * 64];
     __shared__ float s_mean[ROWS], s_rstd[ROWS];
     const int g = blockIdx.x, rb = blockIdx.y;
-    if (g * CT >= NT) return;   // padding of the XCD-aware numbering
+    if (__builtin_expect(g * CT >= NT, 0)) {   // padding of the XCD-aware numbering
+        const int first = (NT + CT * 8 - 1) / (CT * 8) * 8;
+        if (g >= first) touch<NW>(ahead, first, 1, nullptr);
+        return;
+    }
     if constexpr (EPI == LE_SILU || EPI == LE_F32) {
         W = (const uint4*)((const char*)W + blockIdx.z * z_w);
         X += blockIdx.z * z_x;
@@ -946,16 +986,20 @@ struct AttnArgs {
     const int32_t* row0;     // causal pass: each sequence's first row (its rows are n_rows many)
     const float* x;          // causal pass, where only the sequences' last rows go on: the residual stream, and
     float* x_last;           // where its last rows go, one behind the other like the attention's results (null: all rows go on)
+    int heads;               // workgroups of the first dimension from here on have nothing to attend to
+    TouchList<3> ahead;
 };
 template <bool CAUSAL, int QT, int NW, int NB>   // NB: buffers of a wave, all but one of them in flight
 __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
     constexpr int SO = 17;   // floats per row of the merge buffer: the merge reads a dimension's 16 queries' worth 64 rows apart
     __shared__ float sm_o[QT][NW * 64 * SO], sm_m[QT][NW * 16], sm_l[QT][NW * 16];
     const int bh = blockIdx.x;
+    if constexpr (QT == 1)   // (two query tiles are taken where no compute unit is idle)
+        if (bh >= a.heads) { touch<NW>(a.ahead, a.heads, 1, nullptr); return; }
     int qt0 = blockIdx.y * QT;
     if constexpr (CAUSAL) {
         // Later queries see more keys.  Workgroups i and i + 256 share a compute unit: heavy ones first, in rounds of 256 that run to and fro.
-        const int per = max(1, 256 / (int)gridDim.x), round = blockIdx.y / per, at = blockIdx.y - round * per, left = min(per, (int)gridDim.y - round * per);
+        const int per = max(1, 256 / a.heads), round = blockIdx.y / per, at = blockIdx.y - round * per, left = min(per, (int)gridDim.y - round * per);
         qt0 = ((int)gridDim.y - 1 - (round * per + (round & 1 ? left - 1 - at : at))) * QT;
     }
     if (bh >= a.B * a.nH) return;
@@ -1219,8 +1263,13 @@ __global__ __launch_bounds__(256) void k_select(Dims D, DevState s, int seq0, in
 // the start, the path stays in LDS and the residual row is requested ahead of the row of logits; the results go to the host
 // from here (us per launch, 64 nodes, 1025 logits: 11.7 -> 7.0 in a kernel trace, and no launch for the results).
 template <class T>
-__global__ __launch_bounds__(256) void k_continue(Dims D, DevState s, int seq0, int prefill_mode, int ignore_eos, int select, int32_t* host) {
+__global__ __launch_bounds__(256) void k_continue(Dims D, DevState s, int seq0, int prefill_mode, int ignore_eos, int select, int32_t* host, int nseq, TouchList<2> ahead, size_t zw1, size_t zw2) {
     __shared__ PathLds p;
+    if ((int)blockIdx.x >= nseq) {   // the draft heads' maps
+        const size_t z_w[2] = {zw1, zw2};
+        touch<4>(ahead, nseq, D.Hh, z_w);
+        return;
+    }
     const int b = seq0 + blockIdx.x;
     if (select) dev_select(D, s, b, ignore_eos, p);
     else if (!prefill_mode) dev_load_path(D, s, b, p);
@@ -1259,10 +1308,58 @@ static LinShape lin_shape(int R, int NT) {
     return best;
 }
 
+// Workgroups of further columns of a grid that idle compute units can take.
+static unsigned idle_columns(const dim3& grid) {
+    const unsigned rows = grid.y * grid.z;
+    return grid.x * rows < 256 ? (256 - grid.x * rows) / rows / 8 * 8 : 0;
+}
+// Pieces `from` .. of the groups of ct column tiles of a map, as many as `pieces` allows.
+static Touch touch_of(const void* W, int ct, int nks, int NT, int from, long pieces) {
+    const uint32_t bytes = (uint32_t)ct * nks * 1024;
+    const int groups = NT / ct, take = groups ? (int)std::min<long>(cdiv(bytes, 8192) - from, pieces / groups) : 0;
+    if (take <= 0) return Touch{};
+    return Touch{(const char*)W + (size_t)from * 8192, bytes, bytes - from * 8192 - 128, (uint32_t)take, (uint32_t)(((1ull << 32) + take - 1) / take), groups};
+}
+// The maps of a forward in the order in which they are read, and how far they have been touched.  What a launch may touch is bounded by what it can hide: it ends
+// when the last line has arrived.  Measured per idle workgroup (us per step of 1 | 64 nodes, 128 nodes and 2000 keys, 5 x 27 nodes):
+// attention 80 KiB 263 | 320 | 453 | 432, 112 KiB 263 | 324 | 450 | 445, 160 KiB 264 | 323 | 445 | 439; so by the keys it has to go through.  A map's launch
+// 32 KiB and 2 MiB in all; 6 MiB, 1 node 276; 1 MiB 265 | 327 | 454 | 438.
+struct Ahead {
+    struct Map { const void* W; int ct, nks, NT; };   // ct 0: not touched
+    std::vector<Map> maps;
+    size_t next = 0;
+    int from = 0;   // pieces of each group of map `next` that have been
+    void reading(size_t i) {
+        if (next <= i) { next = i + 1; from = 0; }
+    }
+    template <int N>
+    void take(TouchList<N>& t, int workgroups, int kib, int most_kib) {
+        long pieces = std::min((long)workgroups * kib, (long)most_kib) / 8;
+        for (int i = 0; i < N && next < maps.size();) {
+            const Map& m = maps[next];
+            if (m.ct && m.NT >= m.ct) {
+                const Touch one = touch_of(m.W, m.ct, m.nks, m.NT, from, pieces);
+                if (!one.groups) break;
+                t.map[i++] = one;
+                pieces -= (long)one.take * one.groups;
+                from += one.take;
+                if ((uint32_t)from * 8192u < one.stride) break;
+            }
+            ++next;
+            from = 0;
+        }
+    }
+};
+
 template <int RT, int CT, int CH, int EPI, int NW = 4>
-static void lin_launch(LinArgs a, hipStream_t st, int nz = 1) {
+static void lin_launch(LinArgs a, hipStream_t st, int nz = 1, Ahead* ahead = nullptr) {
     const int per_block = (size_t)a.R * a.nks * 64 <= (3u << 20) ? 65536 / cdiv(a.R, RT * 16) : 0;   // (while an L2 of 4 MiB holds what its workgroups read)
-    launch(a.nks % (NW * CH) ? k_lin<RT, CT, CH, EPI, NW, false> : k_lin<RT, CT, CH, EPI, NW, true>, dim3(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz), dim3(64 * NW), 0, st, a.X, a.W, a.nks, a.NT, a.R, per_block, a.z_w, a.z_x, a);
+    dim3 grid(pad8(cdiv(a.NT, CT)), cdiv(a.R, RT * 16), nz);
+    const unsigned idle = ahead ? idle_columns(grid) : 0;
+    TouchList<2> t{};
+    if (idle) ahead->take(t, idle * grid.y, 32, 2048);
+    if (t.map[0].groups) grid.x += idle;
+    launch(a.nks % (NW * CH) ? k_lin<RT, CT, CH, EPI, NW, false> : k_lin<RT, CT, CH, EPI, NW, true>, grid, dim3(64 * NW), 0, st, a.X, a.W, a.nks, a.NT, a.R, per_block, a.z_w, a.z_x, a, t);
 }
 // The tiles of `rows` rows x 16 `ct` columns; an XCD's eighth of them: about as many columns as rows.
 static TileGrid tile_grid(const LinArgs& a, int rows, int ct) {
@@ -1310,7 +1407,7 @@ static int map_kernel(int R, int NT, int nks, int epi) {
 }
 // big_min (tests): k_big from that many of its tiles on; -1, -2: k_tile for every map.
 template <int EPI>
-static void lin(LinArgs& a, int big_min, hipStream_t st) {
+static void lin(LinArgs& a, int big_min, Ahead* ahead, hipStream_t st) {
     a.sg_out = 4;
     const int kernel = big_min < 0 ? (big_min == -1 ? MAP_TILE_256 : MAP_TILE_128)
                        : big_min > 0 ? ((long)cdiv(a.R, 16 * BIG_RT) * cdiv(a.NT, 4 * BIG_CT) >= big_min ? MAP_BIG : MAP_LIN)
@@ -1320,29 +1417,29 @@ static void lin(LinArgs& a, int big_min, hipStream_t st) {
     if (kernel == MAP_TILE_128) { tile_launch<2, 1, EPI>(a, st); return; }
     const LinShape s = lin_shape(a.R, a.NT);
     if constexpr (EPI == LE_LOGITS) {   // (with a multiple of four column tiles 1 x 2 and 2 x 4 never take more workgroups than these)
-        if (s.rt == 2 && s.ct == 1) { lin_launch<2, 1, 8, EPI>(a, st); return; }
-        if (s.rt == 4 && s.ct == 2) { lin_launch<4, 2, 4, EPI>(a, st); return; }
+        if (s.rt == 2 && s.ct == 1) { lin_launch<2, 1, 8, EPI>(a, st, 1, ahead); return; }
+        if (s.rt == 4 && s.ct == 2) { lin_launch<4, 2, 4, EPI>(a, st, 1, ahead); return; }
     }
     if constexpr (EPI == LE_RESID) {
         // Long reductions: eight waves, so that a compute unit's 128 to 256 KB are all in flight instead of half of them (K = 4096, us:
         // 64 rows 6.7 -> 6.5, 135 rows 10.0 -> 9.3, 320 rows 13.2 -> 12.8, 512 rows 13.6 -> 13.1; sixteen spill).
         if (a.nks >= 64) {
             switch (s.rt * 8 + s.ct) {
-            case 1 * 8 + 1: lin_launch<1, 1, 8, EPI, 8>(a, st); return;
-            case 1 * 8 + 2: lin_launch<1, 2, 4, EPI, 8>(a, st); return;
-            case 2 * 8 + 2: lin_launch<2, 2, 4, EPI, 8>(a, st); return;
-            case 2 * 8 + 4: lin_launch<2, 4, 2, EPI, 8>(a, st); return;
+            case 1 * 8 + 1: lin_launch<1, 1, 8, EPI, 8>(a, st, 1, ahead); return;
+            case 1 * 8 + 2: lin_launch<1, 2, 4, EPI, 8>(a, st, 1, ahead); return;
+            case 2 * 8 + 2: lin_launch<2, 2, 4, EPI, 8>(a, st, 1, ahead); return;
+            case 2 * 8 + 4: lin_launch<2, 4, 2, EPI, 8>(a, st, 1, ahead); return;
             default: break;
             }
         }
     }
     switch (s.rt * 8 + s.ct) {
-    case 1 * 8 + 1: lin_launch<1, 1, 8, EPI>(a, st); break;
-    case 1 * 8 + 2: lin_launch<1, 2, 8, EPI>(a, st); break;
-    case 2 * 8 + 2: lin_launch<2, 2, EPI == LE_RESID ? 4 : 8, EPI>(a, st); break;
-    case 2 * 8 + 4: lin_launch<2, 4, 4, EPI>(a, st); break;
-    case 3 * 8 + 4: lin_launch<3, 4, 4, EPI>(a, st); break;
-    default: lin_launch<4, 4, 2, EPI>(a, st); break;
+    case 1 * 8 + 1: lin_launch<1, 1, 8, EPI>(a, st, 1, ahead); break;
+    case 1 * 8 + 2: lin_launch<1, 2, 8, EPI>(a, st, 1, ahead); break;
+    case 2 * 8 + 2: lin_launch<2, 2, EPI == LE_RESID ? 4 : 8, EPI>(a, st, 1, ahead); break;
+    case 2 * 8 + 4: lin_launch<2, 4, 4, EPI>(a, st, 1, ahead); break;
+    case 3 * 8 + 4: lin_launch<3, 4, 4, EPI>(a, st, 1, ahead); break;
+    default: lin_launch<4, 4, 2, EPI>(a, st, 1, ahead); break;
     }
 }
 
@@ -1357,8 +1454,12 @@ static void clock_point(const DevState& s, int ph, hipStream_t st) {
 }
 
 template <int QT, int NW, int NB>
-static void attn_launch(const AttnArgs& t, bool causal, hipStream_t st) {
-    const dim3 grid(pad8(t.B * t.nH), t.x_last ? 1 : cdiv(cdiv(t.M, 16), QT));
+static void attn_launch(AttnArgs t, bool causal, int keys, Ahead& ahead, hipStream_t st) {
+    dim3 grid(pad8(t.B * t.nH), t.x_last ? 1 : cdiv(cdiv(t.M, 16), QT));
+    t.heads = grid.x;
+    const unsigned idle = QT == 1 ? idle_columns(grid) : 0;
+    if (idle) ahead.take(t.ahead, idle * grid.y, 64 + std::min(keys / 22, 96), 24 << 10);   // (24 MiB: what the L2s hold beside everything else)
+    if (t.ahead.map[0].groups) grid.x += idle;
     if (causal) launch((k_attn<true, QT, NW, NB>), grid, dim3(64 * NW), 0, st, t);
     else launch((k_attn<false, QT, NW, NB>), grid, dim3(64 * NW), 0, st, t);
 }
@@ -1377,11 +1478,11 @@ static AttnShape attn_shape(int heads, int qt, int keys, int big_min) {
     if (qt > 1 && heads * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512)) return {2, 4};
     return {1, cdiv(keys, 32) >= 10 && heads * qt <= 512 ? 8 : 4};
 }
-static void attn(const AttnArgs& t, bool causal, int keys, int big_min, hipStream_t st) {
+static void attn(const AttnArgs& t, bool causal, int keys, int big_min, Ahead& ahead, hipStream_t st) {
     const AttnShape s = attn_shape(t.B * t.nH, t.x_last ? 1 : cdiv(t.M, 16), keys, big_min);
-    if (s.tiles == 2) attn_launch<2, 4, 3>(t, causal, st);
-    else if (s.waves == 8) attn_launch<1, 8, 2>(t, causal, st);
-    else attn_launch<1, 4, 3>(t, causal, st);
+    if (s.tiles == 2) attn_launch<2, 4, 3>(t, causal, keys, ahead, st);
+    else if (s.waves == 8) attn_launch<1, 8, 2>(t, causal, keys, ahead, st);
+    else attn_launch<1, 4, 3>(t, causal, keys, ahead, st);
 }
 
 void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& layers, int table, int prefill_mode, bool head, int big_min, hipStream_t st) {
@@ -1393,6 +1494,20 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
     base.R = R; base.L = s.L; base.n_rows = s.n_rows; base.row_seq = s.row_seq; base.row0 = s.row0; base.M = D.M; base.nH = D.nH; base.maxpos = D.maxpos; base.d = d;
     base.m_magic = D.M > 1 ? (uint32_t)(((1ull << 32) + D.M - 1) / D.M) : 0;
     base.stats = (const float2*)s.stats; base.sg = 4;   // (k_embed_rows)
+    Ahead ahead;
+    {
+        auto map = [&](const void* W, int r, int N, int K, int epi) {
+            const int NT = cdiv(N, 16);
+            ahead.maps.push_back({W, big_min || map_kernel(r, NT, K >> 5, epi) != MAP_LIN ? 0 : lin_shape(r, NT).ct, K >> 5, NT});
+        };
+        const int rows = D.last_only ? D.B : R;   // behind the last layer's attention
+        ahead.maps.reserve(4 * D.Ly + 1);
+        for (const LayerW& w : layers) {
+            const int r = &w == &layers.back() ? rows : R;
+            map(w.Wqkv, R, 3 * d, d, LE_QKV); map(w.Wo, r, d, d, LE_RESID); map(w.W1, r, D.F, d, LE_GELU); map(w.W2, r, d, D.F, LE_RESID);
+        }
+        if (head) map(s.W_out, rows, D.V1, d, LE_LOGITS);
+    }
     for (int l = 0; l < D.Ly; ++l) {
         const LayerW& w = layers[l];
         bf16_t *Kc = (bf16_t*)s.Kc + l * kv_layer, *Vc = (bf16_t*)s.Vc + l * kv_layer;
@@ -1400,32 +1515,36 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         a.X = s.xb; a.W = (const uint4*)w.Wqkv; a.bias = w.t_qkv; a.colsum = w.cs_qkv; a.nks = d >> 5; a.N = 3 * d; a.NT = a.N >> 4;
         a.out = (bf16_t*)s.q; a.Kc = Kc; a.Vc = Vc;
         clock_point(s, 1 + 5 * l, st);
-        lin<LE_QKV>(a, big_min, st);
+        ahead.reading(4 * l);
+        lin<LE_QKV>(a, big_min, &ahead, st);
         const bool end = l + 1 == D.Ly;
         if (end && prefill_mode && !head) break;   // what follows the last layer's keys and values is for the vocabulary map
-        AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos, s.row0, s.x, nullptr};
+        AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos, s.row0, s.x, nullptr, 0, {}};
         float* x = s.x;
         if (end && D.last_only) x = t.x_last = (float*)s.hid;   // (free until FFN1)
         clock_point(s, 2 + 5 * l, st);
-        attn(t, table == 1, D.keys, big_min, st);
+        attn(t, table == 1, D.keys, big_min, ahead, st);
         LinArgs o = base;
         o.X = (const bf16_t*)s.att; o.W = (const uint4*)w.Wo; o.bias = w.bo; o.nks = d >> 5; o.N = d; o.NT = d >> 4;
         o.out = s.xb; o.outf = s.x; o.stats_out = (float2*)s.stats;
         if (end && D.last_only) base.R = o.R = D.B;
         o.resid = x;
         clock_point(s, 3 + 5 * l, st);
-        lin<LE_RESID>(o, big_min, st);
+        ahead.reading(4 * l + 1);
+        lin<LE_RESID>(o, big_min, &ahead, st);
         base.sg = o.sg_out;
         LinArgs f = base;
         f.X = s.xb; f.W = (const uint4*)w.W1; f.bias = w.t_w1; f.colsum = w.cs_w1; f.nks = d >> 5; f.N = D.F; f.NT = D.F >> 4;
         f.out = (bf16_t*)s.hid;
         clock_point(s, 4 + 5 * l, st);
-        lin<LE_GELU>(f, big_min, st);
+        ahead.reading(4 * l + 2);
+        lin<LE_GELU>(f, big_min, &ahead, st);
         LinArgs g = base;
         g.X = (const bf16_t*)s.hid; g.W = (const uint4*)w.W2; g.bias = w.b2; g.nks = D.F >> 5; g.N = d; g.NT = d >> 4;
         g.out = s.xb; g.outf = s.x; g.resid = s.x; g.stats_out = (float2*)s.stats;
         clock_point(s, 5 + 5 * l, st);
-        lin<LE_RESID>(g, big_min, st);
+        ahead.reading(4 * l + 3);
+        lin<LE_RESID>(g, big_min, &ahead, st);
         base.sg = g.sg_out;
     }
     if (head) {
@@ -1433,7 +1552,8 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         a.X = s.xb; a.W = (const uint4*)s.W_out; a.bias = s.t_out; a.colsum = s.cs_out; a.nks = d >> 5; a.N = D.V1; a.NT = cdiv(D.V1, 16);
         a.outf = s.logits;
         clock_point(s, 1 + 5 * D.Ly + TP_HEAD, st);
-        lin<LE_LOGITS>(a, big_min, st);
+        ahead.reading(4 * D.Ly);
+        lin<LE_LOGITS>(a, big_min, &ahead, st);
     }
 }
 
@@ -1451,19 +1571,26 @@ void launch_verify_tail(const Dims& D, const DevState& s, int tau, int ignore_eo
 void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>& draft, int seq0, int nseq, int prefill_mode, int ignore_eos, bool select, int32_t* host, int dtype, hipStream_t st) {
     const int H = 1 + 5 * D.Ly;
     clock_point(s, H + TP_FINAL, st);
-    launch(dtype ? k_continue<bf16_t> : k_continue<float>, dim3(nseq), dim3(256), 0, st, D, s, seq0, prefill_mode, ignore_eos, select ? 1 : 0, host);
+    auto ahead = [&](const void* a, const void* b) { return D.Hh > 1 ? (size_t)((const char*)b - (const char*)a) : 0; };
+    const DraftW &d0 = draft[0], &d1 = draft[D.Hh > 1 ? 1 : 0];
+    const size_t zw1 = ahead(d0.W1, d1.W1), zw2 = ahead(d0.W2, d1.W2);
+    TouchList<2> t{};   // the draft heads' maps (us per step: 1 node 267.2 -> 265.0, 64 nodes 325.4 -> 324.0)
+    unsigned idle = dtype ? idle_columns(dim3(nseq)) : 0;
+    const long pieces = (long)idle * 10 / D.Hh;
+    t.map[0] = touch_of(d0.W1, 1, D.d >> 5, D.d >> 4, 0, pieces);
+    t.map[1] = touch_of(d0.W2, 1, D.d >> 5, cdiv(D.V1, 16), 0, pieces - (long)t.map[0].take * t.map[0].groups);
+    if (!t.map[0].groups) idle = 0;
+    launch(dtype ? k_continue<bf16_t> : k_continue<float>, dim3(nseq + idle), dim3(256), 0, st, D, s, seq0, prefill_mode, ignore_eos, select ? 1 : 0, host, nseq, t, zw1, zw2);
     if (dtype) {
-        auto ahead = [&](const void* a, const void* b) { return D.Hh > 1 ? (size_t)((const char*)b - (const char*)a) : 0; };
-        const DraftW &d0 = draft[0], &d1 = draft[D.Hh > 1 ? 1 : 0];
         LinArgs a{};
         a.X = (const bf16_t*)s.hbest; a.W = (const uint4*)d0.W1; a.bias = d0.b1; a.nks = D.d >> 5; a.N = D.d; a.NT = D.d >> 4; a.R = D.B;
-        a.out = (bf16_t*)s.rdraft; a.z_w = ahead(d0.W1, d1.W1); a.z_b = ahead(d0.b1, d1.b1); a.z_out = s.draft_stride;
+        a.out = (bf16_t*)s.rdraft; a.z_w = zw1; a.z_b = ahead(d0.b1, d1.b1); a.z_out = s.draft_stride;
         clock_point(s, H + TP_COMMIT, st);
         if (D.B <= 16) lin_launch<1, 1, 8, LE_SILU>(a, st, D.Hh);
         else lin_launch<4, 1, 4, LE_SILU>(a, st, D.Hh);
         LinArgs z{};
         z.X = (const bf16_t*)s.rdraft; z.W = (const uint4*)d0.W2; z.nks = D.d >> 5; z.N = D.V1; z.NT = cdiv(D.V1, 16); z.R = D.B;
-        z.outf = s.zdraft; z.z_w = ahead(d0.W2, d1.W2); z.z_x = s.draft_stride; z.z_out = (size_t)D.Bmax * D.V1;
+        z.outf = s.zdraft; z.z_w = zw2; z.z_x = s.draft_stride; z.z_out = (size_t)D.Bmax * D.V1;
         clock_point(s, H + TP_DRAFT2, st);
         if (D.B <= 16) lin_launch<1, 1, 8, LE_F32>(z, st, D.Hh);
         else lin_launch<4, 1, 4, LE_F32>(z, st, D.Hh);

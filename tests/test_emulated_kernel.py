@@ -6,11 +6,13 @@ waves have no k-steps of a linear map at all; 40, 72 and 256 rows (ragged tiles,
 kernels); both shapes of k_tile; eight waves on a reduction of 2048 and on more than 288 keys; lists, edges and scores of rows of more than 4096 logits; the error word raised from the host; models whose logits are all NaN (no arg-max, no draft lists: the
 step must stay inside its buffers); an arena that arrives full of NaN bits; one linear map of more than 4 GiB; compaction of one
 sequence beside a pending one; left-over errors of other HIP calls and refused launches; the pinned result blocks."""
+import ctypes as C
 import os
 import shutil
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -117,3 +119,24 @@ def test_attention_shapes(emu_lib):
             for heads, beside in ((512 // (qt // 2), 528 // (qt // 2)), (256 // qt, 240 // qt), (512 // qt, 496 // qt)):
                 if heads and beside:
                     assert pick(heads, qt, keys, 0) == pick(beside, qt, keys, 0), (heads, qt, keys)
+
+
+@pytest.mark.parametrize("ct,nks,NT,start,pieces", [(1, 32, 64, 0, 10000), (2, 32, 192, 0, 10000), (4, 32, 65, 0, 10000), (1, 128, 64, 0, 400), (1, 128, 64, 6, 10000),
+                                                    (1, 2, 3, 0, 10000), (2, 18, 7, 0, 10000), (3, 6, 40, 1, 30), (1, 32, 64, 0, 63), (4, 2, 3, 0, 10000)])
+def test_touched_lines(emu_lib, ct, nks, NT, start, pieces):
+    """Weights touched ahead: from piece `start` of 64 lines of each group of column tiles on, as many as `pieces` allows, every line in its group, by
+    the XCD whose workgroups read the group, and none outside the map."""
+    f = C.CDLL(emu_lib).emu_touch_lines
+    group, groups = ct * nks * 1024, NT // ct
+    lines, xcds = np.zeros((20000, 64), np.int64), np.zeros(20000, np.int32)
+    n = f(ct, nks, NT, start, pieces, lines.ctypes.data_as(C.c_void_p), xcds.ctypes.data_as(C.c_void_p))
+    take = min(-(-group // 8192) - start, pieces // groups) if groups else 0
+    want = {(g, line) for g in range(groups) for line in range(start * 64, min((start + take) * 64, group // 128))}
+    got = set()
+    for row, x in zip(lines[:n], xcds[:n]):
+        for at in row:
+            g, off = divmod(int(at), group)
+            assert g % 8 == x and off % 128 == 0 and 0 <= g < groups
+            got.add((g, off // 128))
+    assert got == want
+    assert n == take * groups
