@@ -14,7 +14,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # default goal (registers for occupancy) buys nothing there
 # -amdgpu-kernarg-preload-count: a kernel's leading scalar arguments arrive in registers with the wave
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
-         "-mllvm", "-amdgpu-sched-strategy=max-ilp", "-mllvm", "-amdgpu-kernarg-preload-count=8",
+         "-mllvm", "-amdgpu-sched-strategy=max-ilp", "-mllvm", "-amdgpu-kernarg-preload-count=10",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-result", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 

@@ -976,13 +976,11 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 // to arrive merging (2000 keys, 64 queries: 8.6 instead of 9.7, 1000 keys: 8.2 instead of 6.9); two blocks per step
 // (2000 keys: 9.3, 320 keys: 5.2 instead of 4.5).
 // ---------------------------------------------------------------------------
-struct AttnArgs {
-    const bf16_t* q;
+struct AttnArgs {   // what the first loads need is in k_attn's leading arguments
     bf16_t* att;
-    const bf16_t *Kc, *Vc;   // this layer's cache
-    const int32_t *L, *n_rows;
+    const int32_t* n_rows;
     const uint32_t* mask;
-    int B, M, nH, d, maxpos;
+    int M;
     const int32_t* row0;     // causal pass: each sequence's first row (its rows are n_rows many)
     const float* x;          // causal pass, where only the sequences' last rows go on: the residual stream, and
     float* x_last;           // where its last rows go, one behind the other like the attention's results (null: all rows go on)
@@ -990,28 +988,51 @@ struct AttnArgs {
     TouchList<3> ahead;
 };
 template <bool CAUSAL, int QT, int NW, int NB>   // NB: buffers of a wave, all but one of them in flight
-__global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
+__global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(const bf16_t* q, const bf16_t* Kc, const bf16_t* Vc, const int32_t* L_of, int n_heads, int nH, uint32_t nH_magic, int maxpos, int blocks, uint32_t y_share, AttnArgs a) {
     constexpr int SO = 17;   // floats per row of the merge buffer: the merge reads a dimension's 16 queries' worth 64 rows apart
     __shared__ float sm_o[QT][NW * 64 * SO], sm_m[QT][NW * 16], sm_l[QT][NW * 16];
     const int bh = blockIdx.x;
-    if constexpr (QT == 1)   // (two query tiles are taken where no compute unit is idle)
-        if (bh >= a.heads) { touch<NW>(a.ahead, a.heads, 1, nullptr); return; }
+    if (__builtin_expect(bh >= n_heads, 0)) {
+        if constexpr (QT == 1)   // (two query tiles are taken where no compute unit is idle)
+            if (bh >= a.heads) touch<NW>(a.ahead, a.heads, 1, nullptr);
+        return;
+    }
+    const int b = nH_magic ? (int)mulhi((uint32_t)bh, nH_magic) : bh, h = bh - b * nH, L = ldg(L_of + b);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, gq = lane >> 4, c = lane & 15;
+    const size_t hb = (size_t)bh * kv_cap(maxpos) * 64;
+    const bf16_t *Kh = Kc + hb, *Vh = Vc + hb;
+    uint4 buf[NB][8];
+    auto load_at = [&](int at, uint4 (&kvb)[8]) {
+        const uint32_t off = (uint32_t)at * 2048u + lane * 8u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { kvb[i] = ldg4(Kh + (off + i * 512)); kvb[4 + i] = ldg4(Vh + (off + i * 512)); }
+    };
+    // The workgroups of a head start at different blocks: side by side they would all wait for the same lines from HBM, and a compute unit
+    // has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
+    int turn = (int)mulhi((uint32_t)(blocks * (int)blockIdx.y), y_share);
+    // A wave's first block is asked for before anything has been read from memory, from where it lies if the sequence has `blocks` blocks: the host's upper bound,
+    // which is exact where every step's tokens are fetched.  Otherwise the chain of loads is arguments, length, keys, 2900 clocks until the
+    // first keys are on their way, behind everything that the idle workgroups touch (with this and masks without branches, us per step: 64 nodes
+    // 328 -> 325, 128 nodes and 2000 keys 443 -> 434, 16 x 64 nodes 930 -> 925, 64 x 32 nodes 1501 -> 1489).  Measured and not kept: 16 waves for up to 16
+    // blocks (64 nodes 329), keys and values touched by the launch before (no change).
+    const int asked = CAUSAL ? -1 : wave + turn < blocks ? wave + turn : max(wave + turn - blocks, 0);
+    if constexpr (!CAUSAL) {
+        load_at(min(asked, (kv_cap(maxpos) >> 5) - 1), buf[0]);
+        SCHED_FENCE();
+    }
     int qt0 = blockIdx.y * QT;
     if constexpr (CAUSAL) {
         // Later queries see more keys.  Workgroups i and i + 256 share a compute unit: heavy ones first, in rounds of 256 that run to and fro.
         const int per = max(1, 256 / a.heads), round = blockIdx.y / per, at = blockIdx.y - round * per, left = min(per, (int)gridDim.y - round * per);
         qt0 = ((int)gridDim.y - 1 - (round * per + (round & 1 ? left - 1 - at : at))) * QT;
     }
-    if (bh >= a.B * a.nH) return;
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, gq = lane >> 4, c = lane & 15;
-    const int b = bh / a.nH, h = bh - b * a.nH;
-    const int n_rows = ldg(a.n_rows + b), L = ldg(a.L + b);
+    const int n_rows = ldg(a.n_rows + b);
     const int M = CAUSAL ? n_rows : a.M, row0 = CAUSAL ? ldg(a.row0 + b) : b * a.M;   // the sequence's rows
     const bool last_only = CAUSAL && a.x_last;
     if constexpr (CAUSAL) {
         if (last_only) {
             qt0 = (M - 1) >> 4;
-            if (tid < 16) *(float4*)(a.x_last + (size_t)b * a.d + h * 64 + 4 * tid) = *(const float4*)(a.x + (size_t)(row0 + M - 1) * a.d + h * 64 + 4 * tid);
+            if (tid < 16) *(float4*)(a.x_last + (size_t)b * nH * 64 + h * 64 + 4 * tid) = *(const float4*)(a.x + (size_t)(row0 + M - 1) * nH * 64 + h * 64 + 4 * tid);
         }
         if (qt0 * 16 >= M) return;
     }
@@ -1021,8 +1042,8 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
         node[t] = min((qt0 + t) * 16 + c, M - 1);
-        Q0[t] = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(row0 + node[t], h * 64 + 8 * gq, a.d >> 5)));
-        Q1[t] = __builtin_bit_cast(bf16x8_t, ldg4(a.q + toff(row0 + node[t], h * 64 + 32 + 8 * gq, a.d >> 5)));
+        Q0[t] = __builtin_bit_cast(bf16x8_t, ldg4(q + toff(row0 + node[t], h * 64 + 8 * gq, nH * 2)));
+        Q1[t] = __builtin_bit_cast(bf16x8_t, ldg4(q + toff(row0 + node[t], h * 64 + 32 + 8 * gq, nH * 2)));
         mw[t] = make_uint4(0, 0, 0, 0);
         if constexpr (!CAUSAL) mw[t] = ldg4(a.mask + (size_t)node[t] * MASK_WORDS);
     }
@@ -1030,7 +1051,7 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
     const int q_out = tid / (64 / DT), d_out = tid % (64 / DT) * DT;
     auto put = [&](int nd, const float (&o)[DT]) {
         if (nd >= M || (last_only && nd != M - 1)) return;
-        bf16_t* to = a.att + toff(last_only ? b : row0 + nd, h * 64 + d_out, a.d >> 5);
+        bf16_t* to = a.att + toff(last_only ? b : row0 + nd, h * 64 + d_out, nH * 2);
         if constexpr (DT == 4) *(uint2*)to = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
         else *(uint32_t*)to = pack_bf16(o[0], o[1]);
     };
@@ -1043,13 +1064,10 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
         return;
     }
     // (a causal pass: no query of the workgroup sees keys behind its last row)
-    const int T = min(CAUSAL ? L + min((qt0 + QT) * 16, M) : L + M, a.maxpos);
-    const size_t hb = ((size_t)b * a.nH + h) * kv_cap(a.maxpos) * 64;
-    const bf16_t *Kh = a.Kc + hb, *Vh = a.Vc + hb;
+    const int T = min(CAUSAL ? L + min((qt0 + QT) * 16, M) : L + M, maxpos);
     const int nblk = (T + 31) >> 5;
-    // The workgroups of a head start at different blocks: side by side they would all wait for the same lines from HBM, and a compute unit
-    // has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
-    const int turn = nblk * (int)blockIdx.y / (int)gridDim.y;
+    if constexpr (CAUSAL) turn = (int)mulhi((uint32_t)(nblk * (int)blockIdx.y), y_share);
+    else if (turn >= nblk) turn = 0;
     auto at_turn = [&](int i) { return i + turn < nblk ? i + turn : i + turn - nblk; };
     // Loads are unconditional, so that the waits count exactly the loads behind: past the last block every lane reads the same
     // 16 bytes, which is one line.
@@ -1068,19 +1086,20 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) O[t][i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     }
-    uint4 buf[NB][8];
     if (wave < nblk) {
+        if (asked != at_turn(wave)) load_block(wave, buf[0]);
 #pragma unroll
-        for (int j = 0; j < NB - 1; ++j) load_block(wave + NW * j, buf[j]);
+        for (int j = 1; j < NB - 1; ++j) load_block(wave + NW * j, buf[j]);
     }
     // Which of the eight keys m .. m + 7 of this forward (negative: committed ones) the lane's query sees, without a branch: bits of its
     // mask row, or in a causal pass keys up to its own.
     auto visible = [&](int t, int m) -> unsigned {
         if constexpr (CAUSAL) return (1u << max(0, min(8, node[t] + 1 - m))) - 1u;
-        const int at = max(m, 0), w = at >> 5, sh = at & 31, before = min(8, at - m);
-        const uint32_t lo = w == 0 ? mw[t].x : w == 1 ? mw[t].y : w == 2 ? mw[t].z : w == 3 ? mw[t].w : 0u;
-        const uint32_t hi = w == 0 ? mw[t].y : w == 1 ? mw[t].z : w == 2 ? mw[t].w : 0u;
-        const uint32_t bits = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 0xffu;
+        const int at = max(m, 0), before = min(8, at - m);
+        const bool odd = at & 32, upper = at & 64;   // (selected in pairs: a chain of four cases becomes branches)
+        const uint32_t l0 = odd ? mw[t].y : mw[t].x, l1 = odd ? mw[t].w : mw[t].z, h0 = odd ? mw[t].z : mw[t].y, h1 = odd ? 0u : mw[t].w;
+        const uint32_t lo = upper ? l1 : l0, hi = upper ? h1 : h0;
+        const uint32_t bits = at < 128 ? (uint32_t)((((uint64_t)hi << 32) | lo) >> (at & 31)) & 0xffu : 0u;
         return ((bits << before) | ((1u << before) - 1u)) & 0xffu;
     };
     auto process = [&](const int blk, const uint4 (&cur)[8]) {
@@ -1097,16 +1116,19 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(AttnArgs a) {
             // this lane: query c, keys v0 + 0..3 (sa) and v0 + 4..7 (sb).  Instantiated twice: blocks inside the committed
             // cache need no mask tests.  The running maximum is of the unscaled scores; exp((s - m) / 8) = 2^(s c - m c).
             auto softmax_block = [&](const unsigned okm) {
-                float mx = -1e30f;
+                float mx = -1e30f, sc[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) mx = fmaxf(mx, (okm >> j) & 1u ? (j < 4 ? sa[j] : sb[j - 4]) : -1e30f);
+                for (int j = 0; j < 8; ++j) {
+                    sc[j] = (okm >> j) & 1u ? (j < 4 ? sa[j] : sb[j - 4]) : -INFINITY;   // (2^-inf is 0)
+                    mx = fmaxf(mx, sc[j]);
+                }
                 m_new[t] = fmaxf(m_run[t], rows_max(mx));
                 const float mc = m_new[t] * SCALE;
                 psum[t] = 0.f;
 #pragma unroll
                 for (int j = 0; j < 8; j += 2) {
-                    const float p0f = (okm >> j) & 1u ? __builtin_amdgcn_exp2f(__builtin_fmaf(j < 4 ? sa[j] : sb[j - 4], SCALE, -mc)) : 0.f;
-                    const float p1f = (okm >> (j + 1)) & 1u ? __builtin_amdgcn_exp2f(__builtin_fmaf(j < 4 ? sa[j + 1] : sb[j - 3], SCALE, -mc)) : 0.f;
+                    const float p0f = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[j], SCALE, -mc));
+                    const float p1f = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[j + 1], SCALE, -mc));
                     psum[t] += p0f + p1f;
                     pk[t][j >> 1] = pack_bf16(p0f, p1f);
                 }
@@ -1313,10 +1335,9 @@ static unsigned idle_columns(const dim3& grid) {
     const unsigned rows = grid.y * grid.z;
     return grid.x * rows < 256 ? (256 - grid.x * rows) / rows / 8 * 8 : 0;
 }
-// Pieces `from` .. of the groups of ct column tiles of a map, as many as `pieces` allows.
-static Touch touch_of(const void* W, int ct, int nks, int NT, int from, long pieces) {
-    const uint32_t bytes = (uint32_t)ct * nks * 1024;
-    const int groups = NT / ct, take = groups ? (int)std::min<long>(cdiv(bytes, 8192) - from, pieces / groups) : 0;
+// Pieces `from` .. of groups of so many bytes, as many as `pieces` allows.
+static Touch touch_of(const void* W, uint32_t bytes, int groups, int from, long pieces) {
+    const int take = groups > 0 ? (int)std::min<long>(cdiv(bytes, 8192) - from, pieces / groups) : 0;
     if (take <= 0) return Touch{};
     return Touch{(const char*)W + (size_t)from * 8192, bytes, bytes - from * 8192 - 128, (uint32_t)take, (uint32_t)(((1ull << 32) + take - 1) / take), groups};
 }
@@ -1325,7 +1346,7 @@ static Touch touch_of(const void* W, int ct, int nks, int NT, int from, long pie
 // attention 80 KiB 263 | 320 | 453 | 432, 112 KiB 263 | 324 | 450 | 445, 160 KiB 264 | 323 | 445 | 439; so by the keys it has to go through.  A map's launch
 // 32 KiB and 2 MiB in all; 6 MiB, 1 node 276; 1 MiB 265 | 327 | 454 | 438.
 struct Ahead {
-    struct Map { const void* W; int ct, nks, NT; };   // ct 0: not touched
+    struct Map { const void* W; uint32_t bytes; int groups; };   // bytes of a group; groups 0: not touched
     std::vector<Map> maps;
     size_t next = 0;
     int from = 0;   // pieces of each group of map `next` that have been
@@ -1337,13 +1358,13 @@ struct Ahead {
         long pieces = std::min((long)workgroups * kib, (long)most_kib) / 8;
         for (int i = 0; i < N && next < maps.size();) {
             const Map& m = maps[next];
-            if (m.ct && m.NT >= m.ct) {
-                const Touch one = touch_of(m.W, m.ct, m.nks, m.NT, from, pieces);
+            if (m.groups > 0) {
+                const Touch one = touch_of(m.W, m.bytes, m.groups, from, pieces);
                 if (!one.groups) break;
                 t.map[i++] = one;
                 pieces -= (long)one.take * one.groups;
                 from += one.take;
-                if ((uint32_t)from * 8192u < one.stride) break;
+                if ((uint32_t)from * 8192u < m.bytes) break;
             }
             ++next;
             from = 0;
@@ -1453,15 +1474,17 @@ static void clock_point(const DevState& s, int ph, hipStream_t st) {
 #endif
 }
 
+struct AttnCall { const bf16_t *q, *Kc, *Vc; const int32_t* L; int B, M, nH, maxpos; AttnArgs a; };
 template <int QT, int NW, int NB>
-static void attn_launch(AttnArgs t, bool causal, int keys, Ahead& ahead, hipStream_t st) {
-    dim3 grid(pad8(t.B * t.nH), t.x_last ? 1 : cdiv(cdiv(t.M, 16), QT));
-    t.heads = grid.x;
+static void attn_launch(const AttnCall& t, bool causal, int keys, Ahead& ahead, hipStream_t st) {
+    AttnArgs a = t.a;
+    dim3 grid(pad8(t.B * t.nH), a.x_last ? 1 : cdiv(cdiv(t.M, 16), QT));
+    a.heads = grid.x;
     const unsigned idle = QT == 1 ? idle_columns(grid) : 0;
-    if (idle) ahead.take(t.ahead, idle * grid.y, 64 + std::min(keys / 22, 96), 24 << 10);   // (24 MiB: what the L2s hold beside everything else)
-    if (t.ahead.map[0].groups) grid.x += idle;
-    if (causal) launch((k_attn<true, QT, NW, NB>), grid, dim3(64 * NW), 0, st, t);
-    else launch((k_attn<false, QT, NW, NB>), grid, dim3(64 * NW), 0, st, t);
+    if (idle) ahead.take(a.ahead, idle * grid.y, 64 + std::min(keys / 22, 96), 24 << 10);   // (24 MiB: what the L2s hold beside everything else)
+    if (a.ahead.map[0].groups) grid.x += idle;
+    launch(causal ? k_attn<true, QT, NW, NB> : k_attn<false, QT, NW, NB>, grid, dim3(64 * NW), 0, st, t.q, t.Kc, t.Vc, t.L, t.B * t.nH, t.nH, (uint32_t)(t.nH > 1 ? ((1ull << 32) + t.nH - 1) / t.nH : 0),
+           t.maxpos, cdiv(std::min(keys, t.maxpos), 32), (uint32_t)(grid.y > 1 ? (1ull << 32) / grid.y : 0), a);
 }
 // Query tiles and waves of a workgroup for `heads` heads (of all sequences) of qt query tiles and up to `keys` keys (an upper bound of the longest
 // sequence's): two query tiles from two workgroups per compute unit on, else eight waves while every one has a key block to take and
@@ -1478,8 +1501,8 @@ static AttnShape attn_shape(int heads, int qt, int keys, int big_min) {
     if (qt > 1 && heads * cdiv(qt, 2) >= (big_min > 0 ? big_min : 512)) return {2, 4};
     return {1, cdiv(keys, 32) >= 10 && heads * qt <= 512 ? 8 : 4};
 }
-static void attn(const AttnArgs& t, bool causal, int keys, int big_min, Ahead& ahead, hipStream_t st) {
-    const AttnShape s = attn_shape(t.B * t.nH, t.x_last ? 1 : cdiv(t.M, 16), keys, big_min);
+static void attn(const AttnCall& t, bool causal, int keys, int big_min, Ahead& ahead, hipStream_t st) {
+    const AttnShape s = attn_shape(t.B * t.nH, t.a.x_last ? 1 : cdiv(t.M, 16), keys, big_min);
     if (s.tiles == 2) attn_launch<2, 4, 3>(t, causal, keys, ahead, st);
     else if (s.waves == 8) attn_launch<1, 8, 2>(t, causal, keys, ahead, st);
     else attn_launch<1, 4, 3>(t, causal, keys, ahead, st);
@@ -1497,8 +1520,9 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
     Ahead ahead;
     {
         auto map = [&](const void* W, int r, int N, int K, int epi) {
-            const int NT = cdiv(N, 16);
-            ahead.maps.push_back({W, big_min || map_kernel(r, NT, K >> 5, epi) != MAP_LIN ? 0 : lin_shape(r, NT).ct, K >> 5, NT});
+            const int NT = cdiv(N, 16), ct = lin_shape(r, NT).ct;
+            const uint32_t bytes = (uint32_t)ct * (K >> 5) * 1024;
+            ahead.maps.push_back({W, bytes, big_min || map_kernel(r, NT, K >> 5, epi) != MAP_LIN ? 0 : NT / ct});
         };
         const int rows = D.last_only ? D.B : R;   // behind the last layer's attention
         ahead.maps.reserve(4 * D.Ly + 1);
@@ -1519,9 +1543,9 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         lin<LE_QKV>(a, big_min, &ahead, st);
         const bool end = l + 1 == D.Ly;
         if (end && prefill_mode && !head) break;   // what follows the last layer's keys and values is for the vocabulary map
-        AttnArgs t{(const bf16_t*)s.q, (bf16_t*)s.att, Kc, Vc, s.L, s.n_rows, s.t_mask[table], D.B, D.M, D.nH, d, D.maxpos, s.row0, s.x, nullptr, 0, {}};
+        AttnCall t{(const bf16_t*)s.q, Kc, Vc, s.L, D.B, D.M, D.nH, D.maxpos, {(bf16_t*)s.att, s.n_rows, s.t_mask[table], D.M, s.row0, s.x, nullptr, 0, {}}};
         float* x = s.x;
-        if (end && D.last_only) x = t.x_last = (float*)s.hid;   // (free until FFN1)
+        if (end && D.last_only) x = t.a.x_last = (float*)s.hid;   // (free until FFN1)
         clock_point(s, 2 + 5 * l, st);
         attn(t, table == 1, D.keys, big_min, ahead, st);
         LinArgs o = base;
@@ -1577,8 +1601,8 @@ void launch_continue(const Dims& D, const DevState& s, const std::vector<DraftW>
     TouchList<2> t{};   // the draft heads' maps (us per step: 1 node 267.2 -> 265.0, 64 nodes 325.4 -> 324.0)
     unsigned idle = dtype ? idle_columns(dim3(nseq)) : 0;
     const long pieces = (long)idle * 10 / D.Hh;
-    t.map[0] = touch_of(d0.W1, 1, D.d >> 5, D.d >> 4, 0, pieces);
-    t.map[1] = touch_of(d0.W2, 1, D.d >> 5, cdiv(D.V1, 16), 0, pieces - (long)t.map[0].take * t.map[0].groups);
+    t.map[0] = touch_of(d0.W1, (D.d >> 5) * 1024, D.d >> 4, 0, pieces);
+    t.map[1] = touch_of(d0.W2, (D.d >> 5) * 1024, cdiv(D.V1, 16), 0, pieces - (long)t.map[0].take * t.map[0].groups);
     if (!t.map[0].groups) idle = 0;
     launch(dtype ? k_continue<bf16_t> : k_continue<float>, dim3(nseq + idle), dim3(256), 0, st, D, s, seq0, prefill_mode, ignore_eos, select ? 1 : 0, host, nseq, t, zw1, zw2);
     if (dtype) {
