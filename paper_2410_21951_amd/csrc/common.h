@@ -294,6 +294,7 @@ struct GemmArgs {
     void *Kc, *Vc;      // layer base of the cache
     const int32_t* L;
     int M, nH, maxpos, d;
+    uint32_t m_magic;   // ceil(2^32 / M) (0: M = 1)
     const float *ln_g, *ln_b;      // X = LayerNorm of these rows with this scale and shift (null: the rows as they are)
     size_t z_w, z_b, z_x, z_out;   // several draft heads in one launch: how far a head's weights, bias (bytes), X and result (elements) are ahead of the previous head's
 };

@@ -30,62 +30,89 @@ __device__ __forceinline__ float gelu_f(float v) { return 0.5f * v * (1.f + erff
 __device__ __forceinline__ float silu_f(float v) { return v / (1.f + __expf(-v)); }
 
 // ---------------------------------------------------------------------------
-// Y = X W^T (+ bias) with the epilogues of common.h, X = LayerNorm(x) where GemmArgs::ln_g is given.  One workgroup per
+// Y = X W^T (+ bias) with the epilogues of common.h, X = LayerNorm(x) where LN.  One workgroup per
 // 16 rows x 16 columns, the four waves split the reduction in steps of 16 (a lane's four consecutive values of a row are
 // four matrix instructions' operands; both operands take the same order, so no value moves between lanes), eight steps
 // requested at a time.  A wave keeps 16 accumulators, which makes 64 partial sums of K / 64 products, added pairwise, in the
 // wave and then through LDS: with one chain of K / 4 per wave a model's logits were twice as far from 64-bit arithmetic (two
 // and three layers: 4.4e-7 and 5.2e-7 against 2.4e-7 and 2.5e-7) and a step took 1 to 3 % less (two layers, d = 256, 16 rows:
 // 94 us against 96).  Launch bounds of two: the accumulators stay where additions can read them (2.5 % of a step).
+// What bounds it is the chain of waits from the launch to the store, so what the first loads' addresses need arrives in registers with the wave (the
+// leading arguments), the epilogue's inputs are asked for before the products, and every thread finishes one output.  (One wave finishing all,
+// with bias, residual value and length read at the end and the kind of map found at run time: a step of two layers, d = 256, 16 rows, 94.6 us; now 72.7.)
+// u0, u1: LN: scale and shift; else what a draft head's weights (bytes) and X (elements) are ahead of the previous head's.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 2) void k_lin32(GemmArgs a) {
+template <int EPI, bool LN>
+__global__ __launch_bounds__(256, 2) void k_lin32(const float* X, const float* W, int R, int K, int N, size_t u0, size_t u1, GemmArgs a) {
     constexpr int CH = 8;
     __shared__ f32x4_t red[4 * 64];
     __shared__ float s_mean[16], s_rstd[16];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lc = lane & 15, gq = lane >> 4;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lc = lane & 15, gq = lane >> 4;
     const int n0 = blockIdx.x * 16, r0 = blockIdx.y * 16, z = blockIdx.z;
-    const float* X = (const float*)a.X + z * a.z_x;
-    const float* W = (const float*)((const char*)a.W + z * a.z_w) + (size_t)min(n0 + lc, a.N - 1) * a.K + 4 * gq;
-    const float* xrow = X + (size_t)min(r0 + lc, a.R - 1) * a.K + 4 * gq;
-    const int steps = a.K >> 4, lo = (steps * wave) >> 2, hi = (steps * (wave + 1)) >> 2;
+    const float *ln_g = nullptr, *ln_b = nullptr;
+    if constexpr (LN) {
+        ln_g = (const float*)u0;
+        ln_b = (const float*)u1;
+    } else {
+        W = (const float*)((const char*)W + z * u0);
+        X += z * u1;
+    }
+    const float* Wt = W + (size_t)n0 * K;   // the workgroup's columns and rows
+    const float* Xt = X + (size_t)r0 * K;
+    const uint32_t wrow = (uint32_t)min(lc, N - 1 - n0) * (uint32_t)K + 4u * gq, xrow = (uint32_t)min(lc, R - 1 - r0) * (uint32_t)K + 4u * gq;
+    const int steps = K >> 4, lo = (steps * wave) >> 2, hi = (steps * (wave + 1)) >> 2;
     float4 w[CH], x[CH], lg[CH], lb[CH];
-    auto load = [&](int s) {
+    auto load4 = [&](int s, int i0) {   // steps s + i0 .. s + i0 + 3; one beyond the last re-reads it and is not multiplied
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
+        for (int i = i0; i < i0 + 4; ++i) {
             const int k = 16 * min(s + i, steps - 1);
-            w[i] = ldgf4(W + k);
-            x[i] = ldgf4(xrow + k);
-            if (a.ln_g) { lg[i] = ldgf4(a.ln_g + k + 4 * gq); lb[i] = ldgf4(a.ln_b + k + 4 * gq); }
+            w[i] = ldgf4(Wt + k + wrow);
+            x[i] = ldgf4(Xt + k + xrow);
+            if constexpr (LN) { lg[i] = ldgf4(ln_g + k + 4 * gq); lb[i] = ldgf4(ln_b + k + 4 * gq); }
         }
     };
-    if (a.ln_g) {   // mean and variance of the 16 rows: 16 threads each (biased variance, eps 1e-5)
-        constexpr int NV = 6;   // values up to K = 384 stay in registers and are requested at once
-        const int row = tid >> 4, part = tid & 15;
-        const float* p = X + (size_t)min(r0 + row, a.R - 1) * a.K + 4 * part;
-        float4 v[NV];
+    auto load = [&](int s) {
+        load4(s, 0);
+        if (s + 4 < hi) load4(s, 4);
+    };
+    constexpr int NV = 6;   // values up to K = 384 stay in registers and are requested at once
+    const int row = tid >> 4, part = tid & 15;
+    const float* p = Xt + (uint32_t)min(row, R - 1 - r0) * (uint32_t)K + 4 * part;
+    float4 v[NV];
+    if constexpr (LN)
 #pragma unroll
-        for (int j = 0; j < NV; ++j) v[j] = 64 * j + 4 * part < a.K ? ldgf4(p + 64 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
-        load(lo);
+        for (int j = 0; j < NV; ++j) v[j] = 64 * j + 4 * part < K ? ldgf4(p + 64 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    load(lo);
+    // this thread's output, and what it needs beside the sum
+    const int r = r0 + lc, n = n0 + 4 * gq + wave, rr = min(r, R - 1), nn = min(n, N - 1);
+    float bias = 0.f, old = 0.f;
+    int pos = 0, seq = 0;
+    if (EPI != EPI_F32) bias = ldg((const float*)((const char*)a.bias + z * a.z_b) + nn);
+    if (EPI == EPI_RESID) old = ldg(a.outf + (size_t)rr * N + nn);
+    if (EPI == EPI_SILU_RESID) old = ldg(X + (size_t)rr * K + nn);
+    if (EPI == EPI_QKV) {
+        seq = a.m_magic ? (int)(((uint64_t)(uint32_t)rr * a.m_magic) >> 32) : rr;
+        pos = ldg(a.L + seq);
+    }
+    if constexpr (LN) {   // mean and variance of the 16 rows: 16 threads each (biased variance, eps 1e-5)
         float sum = 0.f;
 #pragma unroll
         for (int j = 0; j < NV; ++j) sum += (v[j].x + v[j].y) + (v[j].z + v[j].w);
-        for (int k = 64 * NV; k + 4 * part < a.K; k += 64) { const float4 u = ldgf4(p + k); sum += (u.x + u.y) + (u.z + u.w); }
-        const float mu = row16_sum(sum) / a.K;
+        for (int k = 64 * NV; k + 4 * part < K; k += 64) { const float4 u = ldgf4(p + k); sum += (u.x + u.y) + (u.z + u.w); }
+        const float mu = row16_sum(sum) / K;
         float sq = 0.f;
         auto add = [&](const float4& u) {
             sq += ((u.x - mu) * (u.x - mu) + (u.y - mu) * (u.y - mu)) + ((u.z - mu) * (u.z - mu) + (u.w - mu) * (u.w - mu));
         };
 #pragma unroll
         for (int j = 0; j < NV; ++j)
-            if (64 * j + 4 * part < a.K) add(v[j]);
-        for (int k = 64 * NV; k + 4 * part < a.K; k += 64) add(ldgf4(p + k));
+            if (64 * j + 4 * part < K) add(v[j]);
+        for (int k = 64 * NV; k + 4 * part < K; k += 64) add(ldgf4(p + k));
         sq = row16_sum(sq);
-        if (part == 0) { s_mean[row] = mu; s_rstd[row] = rsqrtf(sq / a.K + LN_EPS); }
+        if (part == 0) { s_mean[row] = mu; s_rstd[row] = rsqrtf(sq / K + LN_EPS); }
         __syncthreads();
-    } else {
-        load(lo);
     }
-    const float mu = a.ln_g ? s_mean[lc] : 0.f, rstd = a.ln_g ? s_rstd[lc] : 1.f;
+    const float mu = LN ? s_mean[lc] : 0.f, rstd = LN ? s_rstd[lc] : 1.f;
     f32x4_t acc[4][4];   // [step mod 4][which of a lane's four values]
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i >> 2][i & 3] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
@@ -94,54 +121,56 @@ __global__ __launch_bounds__(256, 2) void k_lin32(GemmArgs a) {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             if (s + i >= hi) break;
-            float4 v = x[i];
-            if (a.ln_g) {
+            float4 u = x[i];
+            if constexpr (LN) {
                 const float4 g = lg[i], b = lb[i];
-                v = make_float4((v.x - mu) * rstd * g.x + b.x, (v.y - mu) * rstd * g.y + b.y, (v.z - mu) * rstd * g.z + b.z, (v.w - mu) * rstd * g.w + b.w);
+                u = make_float4((u.x - mu) * rstd * g.x + b.x, (u.y - mu) * rstd * g.y + b.y, (u.z - mu) * rstd * g.z + b.z, (u.w - mu) * rstd * g.w + b.w);
             }
             f32x4_t(&a4)[4] = acc[i & 3];
-            a4[0] = mfma_16x16x4(w[i].x, v.x, a4[0]);   // weights first: a lane then holds four consecutive columns of one row
-            a4[1] = mfma_16x16x4(w[i].y, v.y, a4[1]);
-            a4[2] = mfma_16x16x4(w[i].z, v.z, a4[2]);
-            a4[3] = mfma_16x16x4(w[i].w, v.w, a4[3]);
+            a4[0] = mfma_16x16x4(w[i].x, u.x, a4[0]);   // weights first: a lane then holds four consecutive columns of one row
+            a4[1] = mfma_16x16x4(w[i].y, u.y, a4[1]);
+            a4[2] = mfma_16x16x4(w[i].z, u.z, a4[2]);
+            a4[3] = mfma_16x16x4(w[i].w, u.w, a4[3]);
         }
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i][0] = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
     red[tid] = (acc[0][0] + acc[1][0]) + (acc[2][0] + acc[3][0]);
     __syncthreads();
-    if (wave) return;
-    const f32x4_t s = (red[lane] + red[64 + lane]) + (red[128 + lane] + red[192 + lane]);
-    const int r = r0 + lc;
-    if (r >= a.R) return;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int n = n0 + 4 * gq + j;
-        if (n >= a.N) break;
-        float v = s[j];
-        if (a.bias) v += ((const float*)((const char*)a.bias + z * a.z_b))[n];
-        switch (a.epi) {
-        case EPI_GELU: ((float*)a.out)[(size_t)r * a.N + n] = gelu_f(v); break;
-        case EPI_RESID: a.outf[(size_t)r * a.N + n] += v; break;
-        case EPI_F32: a.outf[z * a.z_out + (size_t)r * a.N + n] = v; break;
-        case EPI_SILU_RESID: ((float*)a.out)[z * a.z_out + (size_t)r * a.N + n] = X[(size_t)r * a.K + n] + silu_f(v); break;
-        case EPI_QKV: {
-            if (n < a.d) { ((float*)a.out)[(size_t)r * a.d + n] = v; break; }
-            const int which = n / a.d - 1, c = n % a.d, head = c >> 6, dim = c & 63;
-            const int b = r / a.M, pos = a.L[b] + r % a.M;
-            if (pos < a.maxpos) {
-                const size_t hb = ((size_t)b * a.nH + head) * kv_cap(a.maxpos) * 64;
-                if (which) ((float*)a.Vc)[hb + vc_off(pos, dim)] = v;
-                else ((float*)a.Kc)[hb + kc_off(pos, dim)] = v;
-            }
-            break;
-        }
+    auto sum_of = [&](int w) { return ((const float*)&red[w * 64 + lane])[wave]; };
+    const float y = ((sum_of(0) + sum_of(1)) + (sum_of(2) + sum_of(3))) + bias;
+    if (r >= R || n >= N) return;
+    if constexpr (EPI == EPI_GELU) ((float*)a.out)[(size_t)r * N + n] = gelu_f(y);
+    if constexpr (EPI == EPI_RESID) a.outf[(size_t)r * N + n] = old + y;
+    if constexpr (EPI == EPI_F32) a.outf[z * a.z_out + (size_t)r * N + n] = y;
+    if constexpr (EPI == EPI_SILU_RESID) ((float*)a.out)[z * a.z_out + (size_t)r * N + n] = old + silu_f(y);
+    if constexpr (EPI == EPI_QKV) {   // (a workgroup's columns are all queries, all keys or all values: d is a multiple of 64)
+        if (n0 < a.d) { ((float*)a.out)[(size_t)r * a.d + n] = y; return; }
+        const int which = n0 >= 2 * a.d, c = n - (which + 1) * a.d, head = c >> 6, dim = c & 63;
+        pos += r - seq * a.M;
+        if (pos < a.maxpos) {
+            const size_t hb = ((size_t)seq * a.nH + head) * kv_cap(a.maxpos) * 64;
+            if (which) ((float*)a.Vc)[hb + vc_off(pos, dim)] = y;
+            else ((float*)a.Kc)[hb + kc_off(pos, dim)] = y;
         }
     }
 }
 
+template <int EPI, bool LN>
+static void lin32_launch(const GemmArgs& a, hipStream_t st, int nz) {
+    launch(k_lin32<EPI, LN>, dim3(cdiv(a.N, 16), cdiv(a.R, 16), nz), dim3(256), 0, st, (const float*)a.X, (const float*)a.W, a.R, a.K, a.N,
+           LN ? (size_t)(uintptr_t)a.ln_g : a.z_w, LN ? (size_t)(uintptr_t)a.ln_b : a.z_x, a);
+}
 static void lin32(const GemmArgs& a, hipStream_t st, int nz = 1) {
-    launch(k_lin32, dim3(cdiv(a.N, 16), cdiv(a.R, 16), nz), dim3(256), 0, st, a);
+    switch (a.epi) {
+    case EPI_QKV: lin32_launch<EPI_QKV, true>(a, st, nz); break;
+    case EPI_GELU: lin32_launch<EPI_GELU, true>(a, st, nz); break;
+    case EPI_RESID: lin32_launch<EPI_RESID, false>(a, st, nz); break;
+    case EPI_SILU_RESID: lin32_launch<EPI_SILU_RESID, false>(a, st, nz); break;
+    default:
+        if (a.ln_g) lin32_launch<EPI_F32, true>(a, st, nz);
+        else lin32_launch<EPI_F32, false>(a, st, nz);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -230,6 +259,7 @@ void launch_layers32(const Dims& D, const DevState& s, const std::vector<LayerW>
     launch_embed32(D, s, prefill_mode, table, st);
     GemmArgs base{};
     base.R = R; base.L = s.L; base.M = D.M; base.nH = D.nH; base.maxpos = D.maxpos; base.d = D.d;
+    base.m_magic = D.M > 1 ? (uint32_t)(((1ull << 32) + D.M - 1) / D.M) : 0;
     for (int l = 0; l < D.Ly; ++l) {
         const LayerW& w = layers[l];
         GemmArgs a = base;
