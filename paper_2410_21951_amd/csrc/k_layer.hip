@@ -102,11 +102,11 @@ struct RowStats {
     const float2* sp[PASS];
     float c0[PASS];
     uint4 v[PASS][NV];
-    __device__ __forceinline__ void request(const LinArgs& a, int row0) {
-        const int tiles = a.nks * 32 >> a.sg, part = threadIdx.x % TPR;
+    __device__ __forceinline__ void request(const LinArgs& a, const float2* stats, int nks, int R, int row0) {
+        const int tiles = nks * 32 >> a.sg, part = threadIdx.x % TPR;
 #pragma unroll
         for (int p = 0; p < PASS; ++p) {
-            sp[p] = a.stats + (size_t)min(row0 + p * (256 / TPR) + (int)threadIdx.x / TPR, a.R - 1) * tiles;
+            sp[p] = stats + (size_t)min(row0 + p * (256 / TPR) + (int)threadIdx.x / TPR, R - 1) * tiles;
             c0[p] = ldg(&sp[p]->x);
 #pragma unroll
             for (int j = 0; j < NV; ++j)
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W
     float bias[NPW][4], cs[NPW][4], xr[NPW][4];
     int seq[NPW], len[NPW], first[NPW], rows[NPW];   // LE_QKV: the row's sequence, its committed length, first row and rows
     RowStats<ROWS> st;
-    if constexpr (LN) st.request(a, row0);
+    if constexpr (LN) st.request(a, a.stats, nks, R, row0);
 #pragma unroll
     for (int p = 0; p < NPW; ++p) {
         const int t = wave + NW * p, n0 = (g * CT + t % CT) * 16 + 4 * gq, r = row0 + (t / CT) * 16 + lc;
@@ -457,11 +457,30 @@ __device__ __forceinline__ void store16(const LinArgs& a, int r, int n0, int hi,
 
 // Which tile a workgroup takes.  Workgroup i runs on XCD i mod 8: every XCD gets an eighth of the tiles, consecutive in
 // strips of `strip` column tiles, so that the rows and columns which its L2 fetches are about the same number.
-struct TileGrid { int gr, gc, strip; };
+// (n: tiles; gs: those of a strip; magics: ceil(2^32 / gs), ceil(2^32 / strip), or 0 where a quotient by them is not exact for every tile.)
+struct TileGrid { int gr, gc, strip, n, gs; uint32_t gs_magic, strip_magic; };
+__device__ __forceinline__ uint32_t div_magic(uint32_t a, uint32_t by, uint32_t magic) { return magic ? mulhi(a, magic) : a / by; }
+// Row and column tile of this workgroup, or false.  What every workgroup needs comes first, as arguments that arrive with the wave, and is found without a
+// division (64 x 32 nodes 1499 -> 1487 us per step, its prompts 12 350 -> 12 180, 5 x 27 nodes 439 -> 433); a last strip that is narrower than the
+// others is found from the rest.
+__device__ __forceinline__ bool tile_of(int n, int gs, uint32_t gs_magic, int strip, uint32_t strip_magic, const TileGrid& g, int* row, int* col) {
+    const int xcd = blockIdx.x & 7, lo = (n * xcd) >> 3, i = lo + (int)(blockIdx.x >> 3);
+    if (i >= (n * (xcd + 1)) >> 3) return false;
+    const int s = (int)div_magic((uint32_t)i, (uint32_t)gs, gs_magic), in = i - s * gs;
+    int w = strip;
+    if (n - s * gs >= gs) {
+        *row = (int)div_magic((uint32_t)in, (uint32_t)strip, strip_magic);
+    } else {
+        w = g.gc - s * strip;
+        *row = in / w;
+    }
+    *col = s * strip + in - *row * w;
+    return true;
+}
 
 constexpr int BIG_RT = 4, BIG_CT = 2;   // row tiles of a workgroup, column tiles of a wave
 template <int EPI>
-__global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
+__global__ __launch_bounds__(256, 3) void k_big(const bf16_t* X, const uint4* Wt, const float2* stats, int nks, int NT, int R, int n, int gs, uint32_t gs_magic, int strip, LinArgs a, TileGrid g) {
     constexpr bool LN = EPI <= LE_LOGITS;
     constexpr int NRT = BIG_RT, NCT = BIG_CT, DEPTH = 2;   // DEPTH: stages in registers
     static_assert(4 % DEPTH == 0, "stage c uses register set c mod DEPTH by c mod 4");
@@ -473,34 +492,31 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
         // Workgroup i runs on XCD i mod 8: the XCD has an eighth of the columns, whose weights leave HBM once.
         rb = blockIdx.y;
         ct0 = blockIdx.x * 4 * NCT;
-        if (ct0 >= a.NT) return;   // padding of that numbering
+        if (ct0 >= NT) return;   // padding of that numbering
     } else {
-        const int n = g.gr * g.gc, xcd = blockIdx.x & 7, lo = (n * xcd) >> 3, i = lo + (int)(blockIdx.x >> 3);
-        if (i >= (n * (xcd + 1)) >> 3) return;
-        const int s = i / (g.gr * g.strip), in = i - s * g.gr * g.strip, w = min(g.strip, g.gc - s * g.strip);
-        rb = in / w;
-        ct0 = (s * g.strip + in % w) * 4 * NCT;
+        if (!tile_of(n, gs, gs_magic, strip, g.strip_magic, g, &rb, &ct0)) return;
+        ct0 *= 4 * NCT;
     }
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int row0 = rb * ROWS, last_rt = (a.R - 1) >> 4;
+    const int row0 = rb * ROWS, last_rt = (R - 1) >> 4;
     const int wt0 = ct0 + wave * NCT;      // this wave's first column tile
-    const int nst = a.nks >> 1;            // stages (K is a multiple of 64)
+    const int nst = nks >> 1;            // stages (K is a multiple of 64)
     RowStats<ROWS> st;
-    if constexpr (LN) st.request(a, row0);
+    if constexpr (LN) st.request(a, stats, nks, R, row0);
     // Tiles beyond the map's last row or column re-read a valid one and only reach accumulators that are never stored.
     const char* Xp[NA];
 #pragma unroll
     for (int j = 0; j < NA; ++j) {         // the wave's tiles of a stage: T = wave + 4 j is row tile T >> 1, k-step T & 1
         const int T = wave + 4 * j;
-        Xp[j] = (const char*)((const uint4*)a.X + ((size_t)min(rb * NRT + (T >> 1), last_rt) * a.nks + (T & 1)) * 64);
+        Xp[j] = (const char*)((const uint4*)X + ((size_t)min(rb * NRT + (T >> 1), last_rt) * nks + (T & 1)) * 64);
     }
     const int second = (lane >> 4) & 1, piece = (lane & 15) + 16 * (lane >> 5);   // operand lane -> tile of the pair, piece of the tile's first half
     // Tiles by a 64-bit base of the wave and a 32-bit distance from it: a map may hold more than 4 GiB.
-    const int wt_first = min(wt0, a.NT - 1);
-    const char* Wp = (const char*)a.W + (size_t)wt_first * a.nks * 1024;
+    const int wt_first = min(wt0, NT - 1);
+    const char* Wp = (const char*)Wt + (size_t)wt_first * nks * 1024;
     uint32_t woff[NC2];
 #pragma unroll
-    for (int c = 0; c < NC2; ++c) woff[c] = (uint32_t)(min(wt0 + 2 * c + second, a.NT - 1) - wt_first) * (uint32_t)a.nks * 1024u + (uint32_t)piece * 16u;
+    for (int c = 0; c < NC2; ++c) woff[c] = (uint32_t)(min(wt0 + 2 * c + second, NT - 1) - wt_first) * (uint32_t)nks * 1024u + (uint32_t)piece * 16u;
     auto loadA = [&](int c, uint4 (&x)[NA]) {
         const uint32_t off = (uint32_t)min(c, nst - 1) * 2048u + (uint32_t)lane * 16u;
 #pragma unroll
@@ -609,14 +625,14 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
         float bias[4][4], cs[4][4], xr[NR2][4][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int tile = min(wt0 + 2 * ci + (q >> 1), a.NT - 1), n0 = tile * 16 + 8 * (q & 1) + 4 * hi;
+            const int tile = min(wt0 + 2 * ci + (q >> 1), NT - 1), n0 = tile * 16 + 8 * (q & 1) + 4 * hi;
             const uint4 b4 = ldg4(a.bias + n0), c4 = LN ? ldg4(a.colsum + n0) : make_uint4(0, 0, 0, 0);
             bias[q][0] = __uint_as_float(b4.x); bias[q][1] = __uint_as_float(b4.y); bias[q][2] = __uint_as_float(b4.z); bias[q][3] = __uint_as_float(b4.w);
             cs[q][0] = __uint_as_float(c4.x); cs[q][1] = __uint_as_float(c4.y); cs[q][2] = __uint_as_float(c4.z); cs[q][3] = __uint_as_float(c4.w);
             if constexpr (EPI == LE_RESID)
 #pragma unroll
                 for (int ri = 0; ri < NR2; ++ri) {
-                    const uint4 x4 = ldg4(a.resid + (size_t)min(row0 + ri * 32 + lr, a.R - 1) * a.N + n0);
+                    const uint4 x4 = ldg4(a.resid + (size_t)min(row0 + ri * 32 + lr, R - 1) * a.N + n0);
                     xr[ri][q][0] = __uint_as_float(x4.x); xr[ri][q][1] = __uint_as_float(x4.y); xr[ri][q][2] = __uint_as_float(x4.z); xr[ri][q][3] = __uint_as_float(x4.w);
                 }
         }
@@ -655,11 +671,11 @@ __global__ __launch_bounds__(256, 3) void k_big(LinArgs a, TileGrid g) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) sq += (v[t][e] - mu) * (v[t][e] - mu);
                 sq = half_sum(sq);
-                if (r < a.R && hi == 0 && wt0 + 2 * ci < a.NT) a.stats_out[(size_t)r * (a.N >> 5) + ((wt0 + 2 * ci) >> 1)] = make_float2(mu, sq);
+                if (r < R && hi == 0 && wt0 + 2 * ci < NT) a.stats_out[(size_t)r * (a.N >> 5) + ((wt0 + 2 * ci) >> 1)] = make_float2(mu, sq);
             }
 #pragma unroll
             for (int t = 0; t < 2; ++t)
-                if (wt0 + 2 * ci + t < a.NT) store16<EPI>(a, r, (wt0 + 2 * ci + t) * 16, hi, v[t], kv[ri]);
+                if (wt0 + 2 * ci + t < NT) store16<EPI>(a, r, (wt0 + 2 * ci + t) * 16, hi, v[t], kv[ri]);
         }
     }
 }
@@ -706,7 +722,7 @@ template <int RG, int CG> struct TileShape {
 };
 
 template <int RG, int CG, int EPI>
-__global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
+__global__ __launch_bounds__(512) void k_tile(const bf16_t* X, const uint4* W, const float2* stats, int nks, int NT, int R, int n, int gs, uint32_t gs_magic, int strip, LinArgs a, TileGrid t) {
     using S = TileShape<RG, CG>;
     constexpr bool LN = EPI <= LE_LOGITS;
     constexpr int NB = S::NB, KSP = S::KSP, KB = S::KB, NS = S::NS, LPW = S::LPW, SPW = S::SPW, ROWS = 64 * RG;
@@ -716,30 +732,28 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
     __shared__ float4 s_bias[16 * CG], s_cs[16 * CG];
     int row0, ct0;   // first row and column tile
     {
-        const int n = t.gr * t.gc, xcd = blockIdx.x & 7, lo = (n * xcd) >> 3, i = lo + (int)(blockIdx.x >> 3);
-        if (i >= (n * (xcd + 1)) >> 3) return;
-        const int s = i / (t.gr * t.strip), in = i - s * t.gr * t.strip, w = min(t.strip, t.gc - s * t.strip);
-        row0 = in / w * ROWS;
-        ct0 = (s * t.strip + in % w) * 4 * CG;
+        if (!tile_of(n, gs, gs_magic, strip, t.strip_magic, t, &row0, &ct0)) return;
+        row0 *= ROWS;
+        ct0 *= 4 * CG;
     }
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int rg = wave / CG % RG, cg = wave % CG, kq = wave / NB;   // the wave's block and its share of the reduction
-    const int nst = (a.nks + KB - 1) / KB;
+    const int nst = (nks + KB - 1) / KB;
     // row statistics: TPR threads of a row read two groups at a time, NV such pieces asked for here
     constexpr int TPR = 512 / ROWS, NV = TPR < 8 ? 8 : 4;
-    const int groups = (a.nks * 32) >> a.sg;
+    const int groups = (nks * 32) >> a.sg;
     const float2* sp = nullptr;
     float c0 = 0.f;
     uint4 sv[NV];
     if constexpr (LN) {
-        sp = a.stats + (size_t)min(row0 + tid / TPR, a.R - 1) * groups;
+        sp = stats + (size_t)min(row0 + tid / TPR, R - 1) * groups;
         c0 = ldg(&sp->x);
 #pragma unroll
         for (int j = 0; j < NV; ++j) sv[j] = ldg4(sp + (2 * (tid % TPR + j * TPR) < groups ? 2 * (tid % TPR + j * TPR) : 0));
     }
     float bias_in = 0.f, cs_in = 0.f;   // one column's per thread of the first waves
     if (tid < 64 * CG) {
-        const int n = min(ct0 * 16 + tid, a.NT * 16 - 1);
+        const int n = min(ct0 * 16 + tid, NT * 16 - 1);
         bias_in = ldg(a.bias + n);
         if constexpr (LN) cs_in = ldg(a.colsum + n);
     }
@@ -750,15 +764,15 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
         const int T = (wave + 8 * i) / KB;
-        base[i] = T < 4 * RG ? (const char*)a.X + (size_t)min((row0 >> 4) + T, (a.R - 1) >> 4) * a.nks * 1024
-                             : (const char*)a.W + (size_t)min(ct0 + T - 4 * RG, a.NT - 1) * a.nks * 1024;
+        base[i] = T < 4 * RG ? (const char*)X + (size_t)min((row0 >> 4) + T, (R - 1) >> 4) * nks * 1024
+                             : (const char*)W + (size_t)min(ct0 + T - 4 * RG, NT - 1) * nks * 1024;
     }
     auto fetch = [&](int s, int buf, int i0, int i1) {   // loads i0 .. i1 - 1 of stage s
 #pragma unroll
         for (int i = 0; i < LPW; ++i)
             if (i >= i0 && i < i1) {
                 const int j = wave + 8 * i;
-                fill_lds(ring + (buf * S::KIB + j) * 64, base[i] + (uint32_t)min(s * KB + j % KB, a.nks - 1) * 1024u, lane);
+                fill_lds(ring + (buf * S::KIB + j) * 64, base[i] + (uint32_t)min(s * KB + j % KB, nks - 1) * 1024u, lane);
             }
     };
 #pragma unroll
@@ -804,7 +818,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
                 }
             }
             SCHED_FENCE();
-            if (KB == 2 || s * KB + (kq * SPW + sl) / 2 < a.nks) mul(x[sl & 1], w[sl & 1]);
+            if (KB == 2 || s * KB + (kq * SPW + sl) / 2 < nks) mul(x[sl & 1], w[sl & 1]);
             SCHED_FENCE();
         }
         buf = next;
@@ -823,7 +837,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 #pragma unroll
             for (int tt = 0; tt < TB; ++tt)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) xr[i][tt][h] = ldg4(a.resid + (size_t)min(r[i], a.R - 1) * a.N + min(tile0 + tt, a.NT - 1) * 16 + 8 * h + 4 * hi);
+                for (int h = 0; h < 2; ++h) xr[i][tt][h] = ldg4(a.resid + (size_t)min(r[i], R - 1) * a.N + min(tile0 + tt, NT - 1) * 16 + 8 * h + 4 * hi);
     KvRow kv[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
@@ -858,7 +872,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
         if (tid % TPR == 0) {
             const float m2 = s2 + (float)(1 << a.sg) * fmaxf(s3 - s1 * s1 / groups, 0.f);
             s_mean[tid / TPR] = c0 + s1 / groups;
-            s_rstd[tid / TPR] = rsqrtf(m2 / (a.nks * 32) + LN_EPS);
+            s_rstd[tid / TPR] = rsqrtf(m2 / (nks * 32) + LN_EPS);
         }
     }
     // The block's outputs: piece u of 32 rows x 16 columns, u = 4 (row block) + column tile; a lane holds eight values of one
@@ -900,7 +914,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
     }
     // Everything the epilogue reads has arrived before its first store: a wait between the stores would wait for them too
     // (loads and stores share one counter).
-    if (tile0 >= a.NT) return;
+    if (tile0 >= NT) return;
     if constexpr (EPI == LE_RESID)
 #pragma unroll
         for (int i = 0; i < RB; ++i)
@@ -946,7 +960,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
 #pragma unroll
                         for (int e = 0; e < 8; ++e) sq += (y[i][tt][e] - mu) * (y[i][tt][e] - mu);
                 sq = half_sum(sq);
-                if (r[i] < a.R && hi == 0) a.stats_out[(size_t)r[i] * (a.N >> a.sg_out) + at] = make_float2(mu, sq);
+                if (r[i] < R && hi == 0) a.stats_out[(size_t)r[i] * (a.N >> a.sg_out) + at] = make_float2(mu, sq);
             };
             if (a.sg_out > 4) stats(0, TB, (tile0 * 16) >> a.sg_out);
             else
@@ -955,7 +969,7 @@ __global__ __launch_bounds__(512) void k_tile(LinArgs a, TileGrid t) {
         }
 #pragma unroll
         for (int tt = 0; tt < TB; ++tt)
-            if (tile0 + tt < a.NT) store16<EPI>(a, r[i], (tile0 + tt) * 16, hi, y[i][tt], kv[i]);
+            if (tile0 + tt < NT) store16<EPI>(a, r[i], (tile0 + tt) * 16, hi, y[i][tt], kv[i]);
     }
 }
 
@@ -1386,19 +1400,24 @@ static void lin_launch(LinArgs a, hipStream_t st, int nz = 1, Ahead* ahead = nul
 static TileGrid tile_grid(const LinArgs& a, int rows, int ct) {
     TileGrid g{cdiv(a.R, rows), cdiv(a.NT, ct), 1};
     while (g.strip < g.gc && (long)g.strip * g.strip * ct * 16 * 8 < (long)g.gr * g.gc * rows) ++g.strip;
+    g.n = g.gr * g.gc;
+    g.gs = g.gr * g.strip;
+    const bool exact = (long)g.n * g.gs < 1l << 32;   // (n >= gs > strip: a quotient's error stays below one part of the divisor)
+    g.gs_magic = exact ? (uint32_t)(((1ull << 32) + g.gs - 1) / g.gs) : 0;
+    g.strip_magic = exact ? (uint32_t)(((1ull << 32) + g.strip - 1) / g.strip) : 0;
     return g;
 }
 template <int EPI>
 static void big_launch(LinArgs& a, hipStream_t st) {
     const TileGrid g = tile_grid(a, BIG_RT * 16, 4 * BIG_CT);
     a.sg_out = 5;
-    launch(k_big<EPI>, EPI == LE_RESID ? dim3(8 * cdiv(g.gr * g.gc, 8)) : dim3(pad8(g.gc), g.gr), dim3(256), 0, st, a, g);
+    launch(k_big<EPI>, EPI == LE_RESID ? dim3(8 * cdiv(g.gr * g.gc, 8)) : dim3(pad8(g.gc), g.gr), dim3(256), 0, st, a.X, a.W, a.stats, a.nks, a.NT, a.R, g.n, g.gs, g.gs_magic, g.strip, a, g);
 }
 template <int RG, int CG, int EPI>
 static void tile_launch(LinArgs& a, hipStream_t st) {
     const TileGrid g = tile_grid(a, 64 * RG, 4 * CG);
     a.sg_out = TileShape<RG, CG>::KSP > 1 ? 5 : a.N % 128 ? 4 : 6;   // (a wave's columns as one entry where that leaves a row an even number)
-    launch((k_tile<RG, CG, EPI>), dim3(8 * cdiv(g.gr * g.gc, 8)), dim3(512), 0, st, a, g);
+    launch((k_tile<RG, CG, EPI>), dim3(8 * cdiv(g.n, 8)), dim3(512), 0, st, a.X, a.W, a.stats, a.nks, a.NT, a.R, g.n, g.gs, g.gs_magic, g.strip, a, g);
 }
 // Which kernel: the one that is estimated to take least.  us per launch, fitted to 1445 maps of whole steps, each run with all four kernels (widths
 // of 64 to 1024 with hidden layers of two and four times that, 64 to 16 384 rows, vocabulary maps of 1025 and 16 001 columns): the choice takes

@@ -140,3 +140,13 @@ def test_touched_lines(emu_lib, ct, nks, NT, start, pieces):
             got.add((g, off // 128))
     assert got == want
     assert n == take * groups
+
+
+@pytest.mark.parametrize("R,NT,rows,ct", [(2048, 256, 256, 8), (1024, 64, 64, 8), (3200, 64, 128, 4), (300, 65, 64, 8), (65, 1, 64, 8), (64, 1001, 64, 8), (577, 36, 128, 4), (2000, 24, 256, 8)])
+@pytest.mark.parametrize("exact", [1, 0])
+def test_every_tile_is_taken_once(emu_lib, R, NT, rows, ct, exact):
+    """The tiles of the many-row maps in blocks per XCD, by multiplications and by the divisions that stand in for them in very large grids."""
+    out = np.full((20000, 2), -1, np.int32)
+    n = C.CDLL(emu_lib).emu_tiles(R, NT, rows, ct, exact, out.ctypes.data_as(C.c_void_p))
+    got = [tuple(t) for t in out[:n] if t[0] >= 0]
+    assert sorted(got) == [(r, c) for r in range(-(-R // rows)) for c in range(-(-NT // ct))]
