@@ -1023,14 +1023,17 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(const bf16_t* 
     };
     // The workgroups of a head start at different blocks: side by side they would all wait for the same lines from HBM, and a compute unit
     // has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
-    int turn = (int)mulhi((uint32_t)(blocks * (int)blockIdx.y), y_share);
+    auto turn_of = [&](int n) { return (int)mulhi((uint32_t)(n * (int)blockIdx.y), y_share); };
     // A wave's first block is asked for before anything has been read from memory, from where it lies if the sequence has `blocks` blocks: the host's upper bound,
-    // which is exact where every step's tokens are fetched.  Otherwise the chain of loads is arguments, length, keys, 2900 clocks until the
-    // first keys are on their way, behind everything that the idle workgroups touch (with this and masks without branches, us per step: 64 nodes
+    // which is exact where every step's tokens are fetched.  It is no more than a guess where to read: which wave takes which block follows from the sequence's own
+    // length, so the order of a result's sums depends neither on whether tokens were fetched nor on the other sequences (as long as attn_shape takes the same waves).  Without it the chain of loads is arguments, length, keys, 2900
+    // clocks until the first keys are on their way, behind everything that the idle workgroups touch (with this and masks without branches, us per step: 64 nodes
     // 328 -> 325, 128 nodes and 2000 keys 443 -> 434, 16 x 64 nodes 930 -> 925, 64 x 32 nodes 1501 -> 1489).  Measured and not kept: 16 waves for up to 16
     // blocks (64 nodes 329), keys and values touched by the launch before (no change).
-    const int asked = CAUSAL ? -1 : wave + turn < blocks ? wave + turn : max(wave + turn - blocks, 0);
+    int asked = -1;
     if constexpr (!CAUSAL) {
+        asked = wave + turn_of(blocks);
+        if (asked >= blocks) asked = max(asked - blocks, 0);
         load_at(min(asked, (kv_cap(maxpos) >> 5) - 1), buf[0]);
         SCHED_FENCE();
     }
@@ -1080,8 +1083,7 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(const bf16_t* 
     // (a causal pass: no query of the workgroup sees keys behind its last row)
     const int T = min(CAUSAL ? L + min((qt0 + QT) * 16, M) : L + M, maxpos);
     const int nblk = (T + 31) >> 5;
-    if constexpr (CAUSAL) turn = (int)mulhi((uint32_t)(nblk * (int)blockIdx.y), y_share);
-    else if (turn >= nblk) turn = 0;
+    const int turn = turn_of(nblk);
     auto at_turn = [&](int i) { return i + turn < nblk ? i + turn : i + turn - nblk; };
     // Loads are unconditional, so that the waits count exactly the loads behind: past the last block every lane reads the same
     // 16 bytes, which is one line.

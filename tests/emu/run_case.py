@@ -159,6 +159,80 @@ if dtype == "long-rows":
     print("emulated long rows: compared", flush=True)
     sys.stdout.flush()
     os._exit(0)
+if dtype == "bf16-attn-bound":
+    # The tree attention with several query tiles: results are right and the same bits whatever upper bound of the keys the host has (exact, a block
+    # too long, the whole cache) and whichever sequences lie beside a sequence; four and eight waves, one and two query tiles per workgroup.
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    lib, f32 = V._lib, np.float32
+    p = lambda a: a.ctypes.data_as(C.c_void_p)
+
+    def bf16(a):
+        u = a.astype(f32).view(np.uint32)
+        return ((u + 0x7fff + ((u >> 16) & 1)) & 0xffff0000).astype(np.uint32).view(f32)
+    rng = np.random.default_rng(98)
+    for M, lengths, maxpos, big_min in ((33, (61, 159), 256, 0), (49, (78, 130), 256, 0), (96, (31, 100), 264, 1), (40, (350, 470), 560, 0)):
+        B, nH, cap = 2, 1, (maxpos + 31) // 32 * 32
+        q, K, Vv = bf16(3 * rng.standard_normal((B * M, nH * 64))), bf16(rng.standard_normal((B, nH, cap, 64))), bf16(rng.standard_normal((B, nH, cap, 64)))
+        tree = make_tree(M, (10, 10, 10))
+        see = np.zeros((M, 128), bool)
+        for n in range(M):
+            m = n
+            while m >= 0:
+                see[n, m] = True
+                m = tree.parent[m]
+        mask = np.packbits(see, axis=1, bitorder="little").view(np.uint32).copy()
+        L = np.array(lengths, np.int32)
+
+        def run(sel, keys):
+            out = np.zeros((len(sel) * M, nH * 64), f32)
+            rows = np.concatenate([q[b * M:(b + 1) * M] for b in sel])
+            lib.emu_attn(p(rows), p(np.ascontiguousarray(K[sel])), p(np.ascontiguousarray(Vv[sel])), p(L[sel].copy()), len(sel), M, nH, maxpos, p(mask), keys, big_min, p(out))
+            return out
+        own = np.concatenate([run([b], int(L[b]) + M) for b in range(B)])
+        for b in range(B):
+            T = L[b] + M
+            sc = q[b * M:(b + 1) * M].astype(np.float64) @ K[b, 0, :T].astype(np.float64).T / 8
+            sc[:, L[b]:][~see[:, :M]] = -np.inf
+            w = np.exp(sc - sc.max(1, keepdims=True))
+            want = w @ Vv[b, 0, :T].astype(np.float64) / w.sum(1, keepdims=True)
+            err = np.abs(own[b * M:(b + 1) * M] - want).max()
+            # weights and result each rounded to bf16: 2^-9 of the largest value each, and a tenth for the fp32 sums
+            assert err < 1.1 * 2.0 ** -8 * np.abs(Vv[b]).max(), (M, b, err)
+        for keys in (int(L.max()) + M, int(L.max()) + M + 32, maxpos):
+            assert np.array_equal(run([0, 1], keys), own), (M, lengths, keys)
+        print(f"attention of {M} nodes: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
+if dtype == "bf16-unfetched":
+    # Steps whose tokens are fetched and steps whose tokens are not (the host's bound of the length grows by the longest path) leave the same bits: three
+    # query tiles, lengths at which the bound is a block longer than the sequence.
+    from paper_2410_21951_amd import Vadusa, TreeArrays, DBG
+    cfg = ModelConfig(n_layers=1, d_model=64, n_heads=1, head_dim=64, d_ffn=64, speech_vocab=71, text_vocab=20,
+                      n_draft_heads=4, max_positions=256, dtype="bf16")
+    W = make_weights(cfg, 85, std=0.08)
+    rng = np.random.default_rng(86)
+    text, prompt = [rng.integers(0, cfg.text_vocab, 2).astype(np.int32)], [rng.integers(0, cfg.speech_vocab, 134).astype(np.int32)]
+    t = make_tree(48, (10, 10, 10, 10))
+    tree = TreeArrays(t.parent, t.rank)
+    got = []
+    for mode in ("fetched", "unfetched"):
+        dev = Vadusa(cfg, max_batch=1, max_tree_nodes=48, ignore_eos=True, prefill_chunk=144)
+        dev.load_weights(W)
+        dev.prefill(text, prompt)
+        lengths = []
+        for i in range(3):
+            dev.step(tree, 1, sync=mode == "fetched")
+            if mode == "fetched":
+                lengths.append(136 + len(dev.read_output(0)))
+        got.append((dev.read_output(0).tolist(), dev.debug(DBG.LOGITS).copy()))
+        if mode == "fetched":
+            # the third step's bound without fetching: five rows more per step
+            assert -(-(136 + 2 * 5 + 48) // 32) > -(-(lengths[1] + 48) // 32), lengths
+    assert got[1][0] == got[0][0] and np.array_equal(got[1][1], got[0][1])
+    print("emulated unfetched steps: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype == "bf16-giveup":
     # the error word, raised from the host: the next synchronising call reports it, later calls refuse, a prefill
     # recovers and decodes the same tokens

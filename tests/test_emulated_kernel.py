@@ -38,6 +38,15 @@ def test_emulated_step_matches_oracle(emu_lib, dtype):
     assert ("recovered" if dtype == "bf16-giveup" else "stayed in bounds" if dtype.endswith("-nan") else "compared") in r.stdout
 
 
+@pytest.mark.parametrize("case", ["bf16-attn-bound", "bf16-unfetched"])
+def test_results_do_not_depend_on_the_hosts_bound(emu_lib, case):
+    """The attention's sums follow from a sequence's own length, not from the upper bound that the host has of the longest one."""
+    r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "run_case.py"), emu_lib, case],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=600, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+    assert "compared" in r.stdout
+
+
 def test_tile_shapes_of_the_gpu_tests(emu_lib):
     """The shapes that the GPU tests of k_lin name are those that the library picks, and each shape is among them."""
     import ctypes as C

@@ -125,6 +125,42 @@ def test_step_equals_verify_plus_compact_and_async_and_reproducible():
     assert all(len(o) >= 12 for o in outs[0])
 
 
+@pytest.mark.parametrize("nodes,prompts", [(33, (150, 60)), (72, (135, 129)), (48, (330, 345))])
+def test_steps_with_several_query_tiles_are_reproducible(nodes, prompts):
+    """Fetched and unfetched steps, and separate verification and compaction, leave the same bits with several query tiles of the attention, where
+    the host's upper bound of the length reaches a block of keys more than the sequence has (four waves below 288 keys, eight above 289)."""
+    from paper_2410_21951_amd import DBG
+    print("query tiles", nodes, prompts, flush=True)
+    cfg = ModelConfig(**dict(CFG.__dict__, max_positions=512))
+    W = make_weights(cfg, 4, std=0.08)
+    rng = np.random.default_rng(7)
+    text = [rng.integers(0, cfg.text_vocab, 2).astype(np.int32) for _ in prompts]
+    prompt = [rng.integers(0, cfg.speech_vocab, n).astype(np.int32) for n in prompts]
+    tree = _tree(make_tree(nodes, (10, 10, 10)))
+    got, crossed = [], False
+    for mode in ("sync", "split", "async"):
+        dev = _dev(cfg, max_batch=2, max_tree_nodes=nodes, ignore_eos=True, prefill_chunk=512)
+        dev.load_weights(W)
+        dev.prefill(text, prompt)
+        for i in range(8):
+            if mode == "sync":
+                dev.step(tree, 1)
+                have = max(2 + n + len(dev.read_output(b)) for b, n in enumerate(prompts))
+                crossed |= (have + nodes + 31) // 32 < (max(prompts) + 2 + 4 * (i + 1) + nodes + 31) // 32 and i < 7
+            elif mode == "async":
+                dev.step(tree, 1, sync=False)
+            else:
+                dev.verify(tree, 1)
+                dev.kv_compact(-1)
+        got.append(([dev.read_output(b).tolist() for b in range(2)], dev.debug(DBG.LOGITS).copy(),
+                    [dev.read_kv(cfg.n_layers - 1, b, which, 0, 2 + prompts[b] + 8) for b in range(2) for which in range(2)]))
+        dev.close()
+    assert crossed
+    for other in got[1:]:
+        assert other[0] == got[0][0] and np.array_equal(other[1], got[0][1])
+        assert all(np.array_equal(a, b) for a, b in zip(other[2], got[0][2]))
+
+
 def test_a_kernel_that_gave_up_is_reported_and_prefill_recovers():
     """The error word, raised from the host (no kernel raises it today).  The next synchronising call reports
     VADUSA_EHIP, every later call (the debug readers included) refuses with VADUSA_ESTATE, vadusa_prefill resets the
