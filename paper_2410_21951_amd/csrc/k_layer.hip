@@ -990,6 +990,10 @@ __global__ __launch_bounds__(512) void k_tile(const bf16_t* X, const uint4* W, c
 // to arrive merging (2000 keys, 64 queries: 8.6 instead of 9.7, 1000 keys: 8.2 instead of 6.9); two blocks per step
 // (2000 keys: 9.3, 320 keys: 5.2 instead of 4.5).
 // ---------------------------------------------------------------------------
+// The block at which workgroup y of a head's `tiles` starts: floor(blocks y / tiles), exact while blocks tiles^2 < 2^32 (at most 64 tiles: 2^20 blocks of 32 keys; beyond, at
+// most one more, which is still a block of the sequence).
+__host__ __device__ inline uint32_t turn_magic(uint32_t tiles) { return tiles > 1 ? (uint32_t)(((1ull << 32) + tiles - 1) / tiles) : 0; }
+__device__ __forceinline__ int turn_of(int blocks, uint32_t y, uint32_t magic) { return (int)mulhi((uint32_t)blocks * y, magic); }
 struct AttnArgs {   // what the first loads need is in k_attn's leading arguments
     bf16_t* att;
     const int32_t* n_rows;
@@ -1002,7 +1006,7 @@ struct AttnArgs {   // what the first loads need is in k_attn's leading argument
     TouchList<3> ahead;
 };
 template <bool CAUSAL, int QT, int NW, int NB>   // NB: buffers of a wave, all but one of them in flight
-__global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(const bf16_t* q, const bf16_t* Kc, const bf16_t* Vc, const int32_t* L_of, int n_heads, int nH, uint32_t nH_magic, int maxpos, int blocks, uint32_t y_share, AttnArgs a) {
+__global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(const bf16_t* q, const bf16_t* Kc, const bf16_t* Vc, const int32_t* L_of, int n_heads, int nH, uint32_t nH_magic, int maxpos, int blocks, uint32_t y_magic, AttnArgs a) {
     constexpr int SO = 17;   // floats per row of the merge buffer: the merge reads a dimension's 16 queries' worth 64 rows apart
     __shared__ float sm_o[QT][NW * 64 * SO], sm_m[QT][NW * 16], sm_l[QT][NW * 16];
     const int bh = blockIdx.x;
@@ -1023,7 +1027,6 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(const bf16_t* 
     };
     // The workgroups of a head start at different blocks: side by side they would all wait for the same lines from HBM, and a compute unit
     // has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
-    auto turn_of = [&](int n) { return (int)mulhi((uint32_t)(n * (int)blockIdx.y), y_share); };
     // A wave's first block is asked for before anything has been read from memory, from where it lies if the sequence has `blocks` blocks: the host's upper bound,
     // which is exact where every step's tokens are fetched.  It is no more than a guess where to read: which wave takes which block follows from the sequence's own
     // length, so the order of a result's sums depends neither on whether tokens were fetched nor on the other sequences (as long as attn_shape takes the same waves).  Without it the chain of loads is arguments, length, keys, 2900
@@ -1032,7 +1035,7 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(const bf16_t* 
     // blocks (64 nodes 329), keys and values touched by the launch before (no change).
     int asked = -1;
     if constexpr (!CAUSAL) {
-        asked = wave + turn_of(blocks);
+        asked = wave + turn_of(blocks, blockIdx.y, y_magic);
         if (asked >= blocks) asked = max(asked - blocks, 0);
         load_at(min(asked, (kv_cap(maxpos) >> 5) - 1), buf[0]);
         SCHED_FENCE();
@@ -1083,7 +1086,7 @@ __global__ __launch_bounds__(64 * NW, NB > 2 ? 1 : 4) void k_attn(const bf16_t* 
     // (a causal pass: no query of the workgroup sees keys behind its last row)
     const int T = min(CAUSAL ? L + min((qt0 + QT) * 16, M) : L + M, maxpos);
     const int nblk = (T + 31) >> 5;
-    const int turn = turn_of(nblk);
+    const int turn = turn_of(nblk, blockIdx.y, y_magic);
     auto at_turn = [&](int i) { return i + turn < nblk ? i + turn : i + turn - nblk; };
     // Loads are unconditional, so that the waits count exactly the loads behind: past the last block every lane reads the same
     // 16 bytes, which is one line.
@@ -1505,7 +1508,7 @@ static void attn_launch(const AttnCall& t, bool causal, int keys, Ahead& ahead, 
     if (idle) ahead.take(a.ahead, idle * grid.y, 64 + std::min(keys / 22, 96), 24 << 10);   // (24 MiB: what the L2s hold beside everything else)
     if (a.ahead.map[0].groups) grid.x += idle;
     launch(causal ? k_attn<true, QT, NW, NB> : k_attn<false, QT, NW, NB>, grid, dim3(64 * NW), 0, st, t.q, t.Kc, t.Vc, t.L, t.B * t.nH, t.nH, (uint32_t)(t.nH > 1 ? ((1ull << 32) + t.nH - 1) / t.nH : 0),
-           t.maxpos, cdiv(std::min(keys, t.maxpos), 32), (uint32_t)(grid.y > 1 ? (1ull << 32) / grid.y : 0), a);
+           t.maxpos, cdiv(std::min(keys, t.maxpos), 32), turn_magic(grid.y), a);
 }
 // Query tiles and waves of a workgroup for `heads` heads (of all sequences) of qt query tiles and up to `keys` keys (an upper bound of the longest
 // sequence's): two query tiles from two workgroups per compute unit on, else eight waves while every one has a key block to take and

@@ -47,6 +47,16 @@ def test_results_do_not_depend_on_the_hosts_bound(emu_lib, case):
     assert "compared" in r.stdout
 
 
+def test_workgroups_of_a_head_start_apart(emu_lib):
+    """The key block at which each query tile's workgroup starts is blocks * y / tiles, rounded down, without a division."""
+    f = C.CDLL(emu_lib).emu_turns
+    out = np.zeros(64, np.int32)
+    for tiles in range(1, 65):
+        for blocks in [*range(1, 140), 1000, 3328, 16384, (1 << 20) - 1]:
+            f(blocks, tiles, out.ctypes.data_as(C.c_void_p))
+            assert np.array_equal(out[:tiles], blocks * np.arange(tiles) // tiles), (blocks, tiles)
+
+
 def test_tile_shapes_of_the_gpu_tests(emu_lib):
     """The shapes that the GPU tests of k_lin name are those that the library picks, and each shape is among them."""
     import ctypes as C
