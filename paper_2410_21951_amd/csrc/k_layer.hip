@@ -239,32 +239,33 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W
     for (int c = 0; c < CT; ++c)
 #pragma unroll
         for (int r = 0; r < RT; ++r) acc[c][r] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-    // Workgroups on the same columns start at different chunks: side by side they would all wait for the same lines from HBM, and a
+    // Workgroups on the same columns start at different k-steps: side by side they would all wait for the same lines from HBM, and a
     // compute unit has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
     // (FFN2, K = 4096, us: 128 rows 8.6 -> 7.0, 135 rows 9.3 -> 8.7, 320 rows 12.8 -> 11.7; beyond what an L2 holds they
     // drive each other out of it: 1024 rows 18.4 -> 20.3, k_tile and k_big likewise.  Not the LayerNorm-folded maps of K = 1024,
     // whose operands are all on their way at once: 64 rows FFN1 5.0 -> 5.4.)
-    const int nch = (nk + CH - 1) / CH, turn = EPI == LE_RESID && WHOLE ? nch * rb * per_block >> 16 : 0;
-    // Chunk j of the wave, in the order that its turn gives.  Loads are unconditional: a tile beyond the map's last row or column
-    // re-reads a valid one and only reaches accumulators that are never stored; a k-step beyond the last re-reads the last and is not multiplied.
+    const int nch = (nk + CH - 1) / CH, turn = EPI == LE_RESID ? nk * rb * per_block >> 16 : 0;
+    // Chunk j of the wave.  Loads are unconditional: a tile beyond the map's last row or column re-reads a valid one and only reaches
+    // accumulators that are never stored; a k-step beyond the last re-reads a valid one and is not multiplied.
     auto load = [&](int j, uint4 (&w)[CH][CT], uint4 (&x)[CH][RT]) {
-        const int q = j + turn >= nch ? j + turn - nch : j + turn, k0 = ks_lo + q * CH;
-        if constexpr (WHOLE) {   // distances from a scalar base per tile and four k-steps, as part of the instruction
+        if constexpr (WHOLE && EPI != LE_RESID) {   // distances from a scalar base per tile and four k-steps, as part of the instruction
 #pragma unroll
             for (int i = 0; i < CH; ++i) {
+                const uint32_t off = (uint32_t)(ks_lo + j * CH + (i & ~3)) * 1024u;
 #pragma unroll
-                for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + (uint32_t)(k0 + (i & ~3)) * 1024u + wl + (i & 3) * 1024);
+                for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + off + wl + (i & 3) * 1024);
 #pragma unroll
-                for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + (uint32_t)(k0 + (i & ~3)) * 1024u + xl + (i & 3) * 1024);
+                for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + off + xl + (i & 3) * 1024);
             }
         } else {
 #pragma unroll
             for (int i = 0; i < CH; ++i) {
-                const uint32_t off = (uint32_t)min(k0 + i, nks - 1) * 1024u;
+                const int q = j * CH + i + turn, k = ks_lo + (EPI == LE_RESID && q >= nk ? q - nk : q);
+                const uint32_t off = (uint32_t)(WHOLE ? k : min(k, nks - 1)) * 1024u;
 #pragma unroll
-                for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + off + wl);
+                for (int c = 0; c < CT; ++c) w[i][c] = ldg4(Wp[c] + (off + wl));
 #pragma unroll
-                for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + off + xl);
+                for (int r = 0; r < RT; ++r) x[i][r] = ldg4(Xp[r] + (off + xl));
             }
         }
     };

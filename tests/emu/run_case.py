@@ -233,6 +233,47 @@ if dtype == "bf16-unfetched":
     print("emulated unfetched steps: compared", flush=True)
     sys.stdout.flush()
     os._exit(0)
+if dtype == "bf16-lin-turns":
+    # Maps behind which the residual stream is written: a row block's workgroups go through a wave's k-steps from rb / row blocks of them on, also where the
+    # k-steps are no whole number of chunks.  So a row block gives the bits that it gives as the first one (which starts at the first
+    # k-step) on operands whose k-steps are moved around by that much.
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    lib, f32 = V._lib, np.float32
+    p = lambda a: C.c_void_p(a.ctypes.data)
+
+    def bf16(a):
+        return (a.astype(f32).view(np.uint32) & 0xffff0000).view(f32)
+
+    def run(X, W):
+        out = np.zeros((len(X), len(W)), f32)
+        return out, lib.emu_lin_resid(p(X), p(W), len(X), len(W), X.shape[1], p(out))
+    rng = np.random.default_rng(99)
+    # one chunk and less per wave, several and a rest, whole ones; four and eight waves; one and two row tiles, a ragged last block
+    for R, N, K in ((64, 16, 192), (40, 16, 768), (64, 32, 1024), (64, 16, 2048), (48, 32, 2240), (130, 1024, 384)):
+        X, W = bf16(rng.standard_normal((R, K))), bf16(rng.standard_normal((N, K)))
+        out, shape = run(X, W)
+        rows, nks = shape // 16 * 16, K // 32
+        want = X.astype(np.float64) @ W.astype(np.float64).T
+        assert np.abs(out - want).max() < 1e-4 * np.sqrt(K), (R, N, K)
+        nw, blocks = 8 if nks >= 64 else 4, -(-R // rows)
+        moved = 0
+        for rb in range(1, blocks) if N < 1024 else (blocks - 1,):
+            order = []
+            for w in range(nw):
+                lo, hi = nks * w // nw, nks * (w + 1) // nw
+                turn = (hi - lo) * rb * (65536 // blocks) >> 16
+                moved += turn > 0
+                order += [lo + (i + turn) % (hi - lo) for i in range(hi - lo)]
+            at = (np.array(order)[:, None] * 32 + np.arange(32)).ravel()
+            mine = X[rb * rows:(rb + 1) * rows]
+            first = np.concatenate([mine, X])[:R]
+            got, _ = run(np.ascontiguousarray(first[:, at]), np.ascontiguousarray(W[:, at]))
+            assert np.array_equal(got[:len(mine)], out[rb * rows:rb * rows + len(mine)]), (R, N, K, rb)
+        assert moved
+        print(f"turns of {R} x {N} x {K}: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype == "bf16-giveup":
     # the error word, raised from the host: the next synchronising call reports it, later calls refuse, a prefill
     # recovers and decodes the same tokens

@@ -47,6 +47,13 @@ def test_results_do_not_depend_on_the_hosts_bound(emu_lib, case):
     assert "compared" in r.stdout
 
 
+def test_row_blocks_start_at_different_k_steps(emu_lib):
+    r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "run_case.py"), emu_lib, "bf16-lin-turns"],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=600, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+    assert "compared" in r.stdout
+
+
 def test_workgroups_of_a_head_start_apart(emu_lib):
     """The key block at which each query tile's workgroup starts is blocks * y / tiles, rounded down, without a division."""
     f = C.CDLL(emu_lib).emu_turns
