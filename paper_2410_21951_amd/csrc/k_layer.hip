@@ -96,7 +96,7 @@ __host__ __device__ inline int pad8(int a) { return (a + 7) & ~7; }
 // Row statistics of the LayerNorm folded into a map, for the ROWS rows of a workgroup, in two steps: request (ahead of
 // the operands, so that they return first) and merge (while the operands are on their way).  Eight (sixteen)
 // neighbouring lanes share a row and read its tile statistics two at a time, 128 (256) contiguous bytes per load.
-template <int ROWS>
+template <int ROWS, int OTHER>
 struct RowStats {
     static constexpr int TPR = ROWS >= 32 ? 8 : 16, PASS = ROWS * TPR / 256, NV = 32 / TPR;   // NV loads: the 64 tiles of K = 1024
     const float2* sp[PASS];
@@ -118,15 +118,17 @@ struct RowStats {
 #pragma unroll
         for (int p = 0; p < PASS; ++p) {
             float s1 = 0.f, s2 = 0.f, s3 = 0.f;   // sums of the tile means' distances from c0, of the tiles' squared deviations, of the squared distances
-            auto add = [&](const uint4& w) {
+            // Which of two squares enters their sum without having been rounded is said here.  Left to the compiler it changes with the code around it, and
+            // with it the last bit of a row's variance (OTHER: the pieces of the first of two passes in which it has always been the second one).
+            auto add = [&](const uint4& w, bool second = false) {
                 const float d0 = __uint_as_float(w.x) - c0[p], d1 = __uint_as_float(w.z) - c0[p];
                 s1 += d0 + d1;
                 s2 += __uint_as_float(w.y) + __uint_as_float(w.w);
-                s3 += d0 * d0 + d1 * d1;
+                s3 += second ? __builtin_fmaf(d1, d1, d0 * d0) : __builtin_fmaf(d0, d0, d1 * d1);
             };
 #pragma unroll
             for (int j = 0; j < NV; ++j)
-                if (2 * (part + j * TPR) < tiles) add(v[p][j]);
+                if (2 * (part + j * TPR) < tiles) add(v[p][j], PASS == 2 && p == 0 && j > 0 && j <= OTHER);
             for (int t = 2 * (part + NV * TPR); t < tiles; t += 2 * TPR) add(ldg4(sp[p] + t));
             auto sum = [](float x) {
                 x = quad_sum(x);
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W
     }
     float bias[NPW][4], cs[NPW][4], xr[NPW][4];
     int seq[NPW], len[NPW], first[NPW], rows[NPW];   // LE_QKV: the row's sequence, its committed length, first row and rows
-    RowStats<ROWS> st;
+    RowStats<ROWS, EPI == LE_QKV ? 1 : 2> st;
     if constexpr (LN) st.request(a, a.stats, nks, R, row0);
 #pragma unroll
     for (int p = 0; p < NPW; ++p) {
@@ -502,7 +504,7 @@ __global__ __launch_bounds__(256, 3) void k_big(const bf16_t* X, const uint4* Wt
     const int row0 = rb * ROWS, last_rt = (R - 1) >> 4;
     const int wt0 = ct0 + wave * NCT;      // this wave's first column tile
     const int nst = nks >> 1;            // stages (K is a multiple of 64)
-    RowStats<ROWS> st;
+    RowStats<ROWS, 1> st;
     if constexpr (LN) st.request(a, stats, nks, R, row0);
     // Tiles beyond the map's last row or column re-read a valid one and only reach accumulators that are never stored.
     const char* Xp[NA];
