@@ -1554,8 +1554,11 @@ void launch_layers(const Dims& D, const DevState& s, const std::vector<LayerW>& 
         const int rows = D.last_only ? D.B : R;   // behind the last layer's attention
         ahead.maps.reserve(4 * D.Ly + 1);
         for (const LayerW& w : layers) {
-            const int r = &w == &layers.back() ? rows : R;
-            map(w.Wqkv, R, 3 * d, d, LE_QKV); map(w.Wo, r, d, d, LE_RESID); map(w.W1, r, D.F, d, LE_GELU); map(w.W2, r, d, D.F, LE_RESID);
+            const bool end = &w == &layers.back();
+            const int r = end ? rows : R;
+            map(w.Wqkv, R, 3 * d, d, LE_QKV);
+            if (end && prefill_mode && !head) break;   // (as below)
+            map(w.Wo, r, d, d, LE_RESID); map(w.W1, r, D.F, d, LE_GELU); map(w.W2, r, d, D.F, LE_RESID);
         }
         if (head) map(s.W_out, rows, D.V1, d, LE_LOGITS);
     }

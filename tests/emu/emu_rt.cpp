@@ -138,6 +138,31 @@ void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t
     b_done.wait("done");
 }
 
+// ---- what is touched ahead ----
+extern "C" { int emu_logging = 0; }
+struct Event { uint64_t launch, what, address, x, y; };   // what: 0 a touched line by workgroup x, 1 a linear map (x: bytes to the next of y maps)
+static std::mutex& g_events_lock = *new std::mutex;
+static std::vector<Event>& g_events = *new std::vector<Event>;
+static uint64_t g_launch = 0;
+void emu_log_launch() { ++g_launch; }
+void emu_log_map(const void* weights, size_t stride, unsigned maps) { g_events.push_back({g_launch, 1, (uint64_t)weights, stride, maps}); }
+uint32_t emu_touch_load(const uint32_t* p) {
+    const uint32_t v = *(const volatile uint32_t*)p;
+    if (emu_logging) {
+        std::lock_guard<std::mutex> lk(g_events_lock);
+        g_events.push_back({g_launch, 0, (uint64_t)p, blockIdx.x, blockIdx.y});
+    }
+    return v;
+}
+// Takes the events since the last call, oldest first, five words each; returns how many there are.
+extern "C" size_t emu_take_events(uint64_t* out, size_t room) {
+    const size_t n = g_events.size();
+    if (!out) return n;
+    memcpy(out, g_events.data(), std::min(n, room) * sizeof(Event));
+    g_events.clear();
+    return n;
+}
+
 void emu_syncthreads() { b_sync.wait("__syncthreads"); }
 void emu_yield() { sched_yield(); }
 long long emu_clock() { return ++g_clock; }

@@ -274,6 +274,66 @@ if dtype == "bf16-lin-turns":
         print(f"turns of {R} x {N} x {K}: compared", flush=True)
     sys.stdout.flush()
     os._exit(0)
+def taken_events():
+    """(launch, what, address, x, y) of everything since the last call (see tests/emu/emu_rt.cpp)."""
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    f = V._lib.emu_take_events
+    f.restype, f.argtypes = C.c_size_t, [C.c_void_p, C.c_size_t]
+    a = np.zeros((f(None, 0), 5), np.uint64)
+    f(a.ctypes.data_as(C.c_void_p), len(a))
+    return a.astype(np.int64)
+
+
+if dtype == "bf16-touched":
+    # What idle workgroups touch over a prompt of three passes and a step: lines of the weights of a map that a later launch of the same pass reads, each
+    # once a pass.  Two layers of several column groups each, more pieces than one launch may touch.
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    from paper_2410_21951_amd import Vadusa, TreeArrays
+    cfg = ModelConfig(n_layers=2, d_model=192, n_heads=3, head_dim=64, d_ffn=384, speech_vocab=71, text_vocab=20,
+                      n_draft_heads=3, max_positions=96, dtype="bf16")
+    d, F = cfg.d_model, cfg.d_ffn
+    W = make_weights(cfg, 71, std=0.05)
+    rng = np.random.default_rng(87)
+    t = make_tree(8, (3, 2))
+    dev = Vadusa(cfg, max_batch=1, max_tree_nodes=8, ignore_eos=True, prefill_chunk=16)
+    dev.load_weights(W)
+    C.c_int.in_dll(V._lib, "emu_logging").value = 1
+    dev.prefill([rng.integers(0, cfg.text_vocab, 3).astype(np.int32)], [rng.integers(0, cfg.speech_vocab, 37).astype(np.int32)])
+    dev.step(TreeArrays(t.parent, t.rank), 1)
+    ev = taken_events()
+    maps, lines = ev[ev[:, 1] == 1], ev[ev[:, 1] == 0]
+    # the step's maps in the order of their launches: all that there are
+    layer = [3 * d * d, d * d, F * d, d * F]
+    size = [2 * n for n in layer * 2 + [80 * d, d * d, 80 * d]]
+    step = maps[-len(size):]
+    start = list(step[:, 2])
+    assert len(set(start)) == len(size) and list(step[:, 4]) == [1] * 9 + [3, 3]
+    passes = np.flatnonzero(maps[:, 2] == start[0])              # the first map of each pass
+    assert [len(p) for p in np.split(maps, passes[1:])] == [5, 5, 11, 11]   # earlier prompt passes end behind the last layer's QKV
+    bounds = [(a + z * int(m[3]), a + z * int(m[3]) + n, i) for i, (a, n, m) in enumerate(zip(start, size, step)) for z in range(int(m[4]))]
+    touched = set()
+    seen = {}
+    for launch, _, at, x, y in lines:
+        inside = [i for lo, hi, i in bounds if lo <= at and at + 4 <= hi]
+        assert len(inside) == 1, f"line {at:x} touched by launch {launch} is not of one map"
+        i = inside[0]
+        after = maps[maps[:, 0] > launch]
+        read = after[after[:, 2] == start[i]]
+        assert len(read), f"map {i} touched by launch {launch} is not read any more"
+        again = after[after[:, 2] == start[0]]                   # the next pass
+        assert i == 0 or not len(again) or read[0, 0] < again[0, 0], f"map {i} touched by launch {launch} is not read in its pass"
+        assert (at - start[i] if i < 9 else at - min(lo for lo, hi, k in bounds if k == i and lo <= at < hi)) % 128 == 0
+        n_pass = int((maps[passes, 0] <= launch).sum())
+        key = (n_pass, int(at))
+        assert seen.setdefault(key, (launch, x, y)) == (launch, x, y), f"line {at:x} touched again by launch {launch}"
+        touched.add(i)
+    print(f"touched {len(seen)} lines of maps {sorted(touched)}", flush=True)
+    assert touched == set(range(1, 11))                          # (nothing is idle ahead of a pass's first map)
+    print("emulated touched weights: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype == "bf16-giveup":
     # the error word, raised from the host: the next synchronising call reports it, later calls refuse, a prefill
     # recovers and decodes the same tokens

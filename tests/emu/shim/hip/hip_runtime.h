@@ -9,6 +9,7 @@
 #include <cstring>
 #include <functional>
 #include <tuple>
+#include <type_traits>
 #include <utility>
 
 #define __global__
@@ -71,10 +72,27 @@ static inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = (
 
 // ---- launch ----
 void emu_launch(const std::function<void()>& body, dim3 grid, dim3 block, size_t shmem);
+// While emu_logging is set: which linear map a launch computes (kernels whose first arguments are activations and weights; stride: of the maps of a
+// grid's third dimension, in bytes), and every weight line that idle workgroups touch.
+extern "C" int emu_logging;
+uint32_t emu_touch_load(const uint32_t* p);
+void emu_log_launch();
+void emu_log_map(const void* weights, size_t stride, unsigned maps);
+template <class Args> void emu_note_launch(const Args& args, dim3 grid) {
+    emu_log_launch();
+    if constexpr (std::tuple_size_v<Args> > 6) {
+        if constexpr (std::is_same_v<std::tuple_element_t<0, Args>, const uint16_t*> && std::is_same_v<std::tuple_element_t<1, Args>, const uint4*>) {
+            size_t stride = 0;
+            if constexpr (std::is_same_v<std::tuple_element_t<6, Args>, size_t>) stride = std::get<6>(args);
+            emu_log_map(std::get<1>(args), stride, grid.z);
+        }
+    }
+}
 template <class... KA, class... A>
 hipError_t hipLaunchKernelGGL(void (*k)(KA...), dim3 grid, dim3 block, size_t shmem, hipStream_t, A&&... a) {
     if (emu_fail_launch > 0 && --emu_fail_launch == 0) return hipErrorUnknown;
     std::tuple<KA...> args(std::forward<A>(a)...);
+    if (emu_logging) emu_note_launch(args, grid);
     emu_launch([=]() { std::apply(k, args); }, grid, block, shmem);
     return hipSuccess;
 }
