@@ -3,12 +3,14 @@
 #include <hip/hip_runtime.h>
 
 #include <chrono>
-#include <condition_variable>
+#include <climits>
 #include <execinfo.h>
+#include <linux/futex.h>
 #include <mutex>
 #include <sched.h>
 #include <signal.h>
 #include <sys/mman.h>
+#include <sys/syscall.h>
 #include <thread>
 #include <unistd.h>
 #include <vector>
@@ -39,36 +41,50 @@ static void note() {
     if (t_id >= 0) { g_where[t_id] = emu_where; g_wline[t_id] = emu_line; }
 }
 
+// Arrivals and members in one word, so that a thread that leaves and one that arrives cannot both miss that everyone is there; waiters sleep on the
+// generation (a condition variable would have every woken thread queue for its mutex: four times the time of a launch).
 struct Barrier {
-    std::mutex m;
-    std::condition_variable cv;
-    int count = 0, n = 0;
-    uint64_t gen = 0;
-    void init(int n_) { n = n_; count = 0; }
-    void grow(int n_) { std::unique_lock<std::mutex> lk(m); n = n_; }   // while the launching thread is not waiting: nobody is released
+    std::atomic<uint64_t> state{0};   // members << 32 | arrived
+    std::atomic<uint32_t> gen{0};
+    void init(int n) { state = (uint64_t)n << 32; }
+    void grow(int n) {   // while the launching thread is not waiting: nobody is released
+        uint64_t s = state;
+        while (!state.compare_exchange_weak(s, (uint64_t)n << 32 | (uint32_t)s)) {}
+    }
+    void release() {
+        ++gen;
+        syscall(SYS_futex, &gen, FUTEX_WAKE_PRIVATE, INT_MAX, nullptr, nullptr, 0);
+    }
     void wait(const char* what) {
         note();
-        std::unique_lock<std::mutex> lk(m);
-        const uint64_t g = gen;
-        if (++count >= n) { count = 0; ++gen; cv.notify_all(); return; }
-        if (what[0] == 's' && what[1] == 't') { cv.wait(lk, [&] { return gen != g; }); return; }   // idle pool
-        // the launching thread waits for the whole launch: long for a large case, and a hang inside
-        // it is reported by the workers' own waits
-        if (what[0] == 'd' && what[1] == 'o') { cv.wait(lk, [&] { return gen != g; }); return; }
-        // a wait that outlasts the limit is taken for a deadlock; the end-of-launch wait of a large
-        // case legitimately takes long (EMU_WAIT_SECONDS raises the limit)
+        const uint32_t g = gen;
+        uint64_t s = state, next;
+        do next = (uint32_t)s + 1 >= s >> 32 ? s >> 32 << 32 : s + 1;
+        while (!state.compare_exchange_weak(s, next));
+        if (!(uint32_t)next) { release(); return; }
+        // the idle pool waits for ever, and the launching thread for the whole launch: long for a large case, and a hang inside it is reported by the
+        // workers' own waits.  Any other wait that outlasts the limit is taken for a deadlock (EMU_WAIT_SECONDS raises it).
+        const bool for_ever = (what[0] == 's' && what[1] == 't') || (what[0] == 'd' && what[1] == 'o');
         static const int limit = getenv("EMU_WAIT_SECONDS") ? atoi(getenv("EMU_WAIT_SECONDS")) : 60;
-        if (!cv.wait_for(lk, std::chrono::seconds(limit), [&] { return gen != g; })) {
-            fprintf(stderr, "[emu] barrier '%s' timed out: %d of %d arrived (thread %d)\n", what, count, n, t_id);
-            dump_all("deadlock");
-            abort();
+        const auto until = std::chrono::steady_clock::now() + std::chrono::seconds(limit);
+        while (gen == g) {
+            const timespec second{1, 0};
+            syscall(SYS_futex, &gen, FUTEX_WAIT_PRIVATE, g, for_ever ? nullptr : &second, nullptr, 0);
+            if (!for_ever && gen == g && std::chrono::steady_clock::now() > until) {
+                fprintf(stderr, "[emu] barrier '%s' timed out: %d of %d arrived (thread %d)\n", what, (int)(uint32_t)state, (int)(state >> 32), t_id);
+                dump_all("deadlock");
+                abort();
+            }
         }
     }
     // a thread that leaves the kernel no longer takes part in __syncthreads
     void leave() {
-        std::unique_lock<std::mutex> lk(m);
-        --n;
-        if (n > 0 && count >= n) { count = 0; ++gen; cv.notify_all(); }
+        uint64_t s = state, next;
+        do {
+            next = s - (1ull << 32);
+            if (next >> 32 && (uint32_t)next >= next >> 32) next = next >> 32 << 32;
+        } while (!state.compare_exchange_weak(s, next));
+        if ((uint32_t)s && !(uint32_t)next) release();
     }
 };
 
