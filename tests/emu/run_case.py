@@ -334,6 +334,36 @@ if dtype == "bf16-touched":
     print("emulated touched weights: compared", flush=True)
     sys.stdout.flush()
     os._exit(0)
+if dtype == "bf16-touch-grid":
+    # The pieces that idle workgroups share out: every line of a piece by exactly one lane, on the XCD whose workgroups read its group, from buffers that end at
+    # a guard page.  Four and eight waves, several rows of the grid, a first column that is no multiple of eight, several maps of one
+    # shape, fewer workgroups than pieces and more.
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    lib = V._lib
+    C.c_int.in_dll(lib, "emu_logging").value = 1
+    for waves, first, columns, rows, nz, maps in (
+            (4, 16, 8, 1, 1, [(1, 6, 12, 0, 1000)]), (8, 8, 16, 3, 1, [(2, 6, 40, 0, 1000), (1, 20, 9, 1, 1000)]), (4, 1, 24, 1, 3, [(1, 6, 12, 0, 1000), (1, 6, 5, 0, 1000)]),
+            (4, 5, 8, 1, 4, [(1, 10, 17, 0, 34), (1, 10, 3, 0, 3)]), (8, 24, 8, 2, 2, [(4, 6, 32, 2, 7), (1, 2, 1, 0, 9)]), (4, 64, 192, 1, 1, [(1, 4, 3, 0, 100)])):
+        n = len(maps)
+        one = [NT * nks * 1024 for _, nks, NT, _, _ in maps]
+        base = [lib.emu_alloc(nz * b, 0) for b in one]           # (sizes are multiples of 256: the last map ends at the guard page)
+        ints = lambda k: (C.c_int * n)(*(m[k] for m in maps))
+        lib.emu_touch_grid(waves, first, columns, rows, nz, n, (C.c_void_p * n)(*base), ints(0), ints(1), ints(2), ints(3), ints(4), (C.c_size_t * n)(*one))
+        ev = taken_events()
+        got = sorted((int(at), int(x) % 8) for _, _, at, x, y in ev)
+        assert all(first <= x < first + columns and y < rows for _, _, _, x, y in ev)
+        want = []
+        for (ct, nks, NT, start, pieces), b, bytes_ in zip(maps, base, one):
+            group, groups = ct * nks * 1024, NT // ct
+            take = max(min(-(-group // 8192) - start, pieces // groups), 0)
+            want += [(b + z * bytes_ + g * group + min((start + i) * 8192 + lane * 128, group - 128), g % 8)
+                     for z in range(nz) for g in range(groups) for i in range(take) for lane in range(64)]
+        assert got == sorted(want), (waves, first, columns, rows, nz, maps)
+        assert want
+        print(f"{len(want)} lines by {columns} x {rows} workgroups of {waves} waves: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype == "bf16-giveup":
     # the error word, raised from the host: the next synchronising call reports it, later calls refuse, a prefill
     # recovers and decodes the same tokens

@@ -47,6 +47,60 @@ def test_results_do_not_depend_on_the_hosts_bound(emu_lib, case):
     assert "compared" in r.stdout
 
 
+@pytest.mark.parametrize("case", ["bf16-touched", "bf16-touch-grid"])
+def test_weights_touched_ahead(emu_lib, case):
+    r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "run_case.py"), emu_lib, case],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=600, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+    assert "compared" in r.stdout
+
+
+def test_what_is_touched_is_what_is_read_next(emu_lib):
+    """A launch touches, from where the last one stopped, the maps behind the one that is being read, in their order, up to three of them and within what it
+    may; a map is left behind once it is read, and one that k_lin does not take is passed over."""
+    f = C.CDLL(emu_lib).emu_ahead
+    rng = np.random.default_rng(11)
+    ints = lambda a: (C.c_int * len(a))(*map(int, a))
+    stopped = finished = 0
+    for _ in range(300):
+        n = int(rng.integers(1, 14))
+        groups = np.where(rng.random(n) < 0.2, 0, rng.integers(1, 200, n))
+        size = 1024 * rng.integers(1, 129, n)
+        reading, workgroups = [], []
+        for m in range(n):                                       # launches without a map of their own between the maps'
+            if rng.random() < 0.5:
+                reading.append(-1)
+                workgroups.append(0 if rng.random() < 0.4 else 8 * int(rng.integers(1, 31)))
+            reading.append(m)
+            workgroups.append(0 if rng.random() < 0.4 else 8 * int(rng.integers(1, 31)))
+        kib, most = rng.integers(8, 161, len(reading)), rng.integers(100, 25000, len(reading))
+        out = np.zeros((len(reading), 3, 4), np.int32)
+        f(n, ints(groups), ints(size), len(reading), ints(reading), ints(workgroups), ints(kib), ints(most), out.ctypes.data_as(C.c_void_p))
+        at = [0] * n                                             # pieces of each group that have been touched
+        now = -1
+        for k, mine in enumerate(out):
+            now = max(now, reading[k])
+            took = [tuple(t) for t in mine if t[0] >= 0]
+            budget = min(workgroups[k] * int(kib[k]), int(most[k])) // 8 if workgroups[k] else 0
+            nxt = [m for m in range(now + 1, n) if groups[m] and at[m] * 8192 < size[m]]
+            want = []
+            while budget and nxt and len(want) < 3:
+                m = nxt.pop(0)
+                take = min(-(-int(size[m]) // 8192) - at[m], budget // int(groups[m]))
+                if not take:
+                    stopped += 1
+                    break
+                want.append((m, at[m], take, int(groups[m])))
+                budget -= take * int(groups[m])
+                at[m] += take
+                if at[m] * 8192 < size[m]:
+                    stopped += 1
+                    break
+                finished += 1
+            assert took == want, (k, took, want)
+    assert stopped > 100 and finished > 100
+
+
 def test_row_blocks_start_at_different_k_steps(emu_lib):
     r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "run_case.py"), emu_lib, "bf16-lin-turns"],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=600, text=True)
