@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <string>
 #include <tuple>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -285,7 +286,7 @@ enum {
 struct GemmArgs {
     const void* X;      // [R][K]
     const void* W;      // [N][K]
-    const float* bias;  // [N] or null
+    const float* bias;  // [N] (not read for EPI_F32)
     int R, K, N;
     int epi;
     void* out;          // [R][N]

@@ -40,10 +40,11 @@ __device__ __forceinline__ float silu_f(float v) { return v / (1.f + __expf(-v))
 // What bounds it is the chain of waits from the launch to the store, so what the first loads' addresses need arrives in registers with the wave (the
 // leading arguments), the epilogue's inputs are asked for before the products, and every thread finishes one output.  (One wave finishing all,
 // with bias, residual value and length read at the end and the kind of map found at run time: a step of two layers, d = 256, 16 rows, 94.6 us; now 72.7.)
-// u0, u1: LN: scale and shift; else what a draft head's weights (bytes) and X (elements) are ahead of the previous head's.
+// u0, u1: LayerNorm's scale and shift (U: a pointer, LN), or what a draft head's weights (bytes) and X (elements) are ahead of the previous head's (U: a number).
 // ---------------------------------------------------------------------------
-template <int EPI, bool LN>
-__global__ __launch_bounds__(256, 2) void k_lin32(const float* X, const float* W, int R, int K, int N, size_t u0, size_t u1, GemmArgs a) {
+template <int EPI, class U>
+__global__ __launch_bounds__(256, 2) void k_lin32(const float* X, const float* W, int R, int K, int N, U u0, U u1, GemmArgs a) {
+    constexpr bool LN = std::is_same<U, const float*>::value;
     constexpr int CH = 8;
     __shared__ f32x4_t red[4 * 64];
     __shared__ float s_mean[16], s_rstd[16];
@@ -51,8 +52,8 @@ __global__ __launch_bounds__(256, 2) void k_lin32(const float* X, const float* W
     const int n0 = blockIdx.x * 16, r0 = blockIdx.y * 16, z = blockIdx.z;
     const float *ln_g = nullptr, *ln_b = nullptr;
     if constexpr (LN) {
-        ln_g = (const float*)u0;
-        ln_b = (const float*)u1;
+        ln_g = u0;
+        ln_b = u1;
     } else {
         W = (const float*)((const char*)W + z * u0);
         X += z * u1;
@@ -156,20 +157,19 @@ __global__ __launch_bounds__(256, 2) void k_lin32(const float* X, const float* W
     }
 }
 
-template <int EPI, bool LN>
-static void lin32_launch(const GemmArgs& a, hipStream_t st, int nz) {
-    launch(k_lin32<EPI, LN>, dim3(cdiv(a.N, 16), cdiv(a.R, 16), nz), dim3(256), 0, st, (const float*)a.X, (const float*)a.W, a.R, a.K, a.N,
-           LN ? (size_t)(uintptr_t)a.ln_g : a.z_w, LN ? (size_t)(uintptr_t)a.ln_b : a.z_x, a);
+template <int EPI, class U>
+static void lin32_launch(const GemmArgs& a, U u0, U u1, hipStream_t st, int nz) {
+    launch(k_lin32<EPI, U>, dim3(cdiv(a.N, 16), cdiv(a.R, 16), nz), dim3(256), 0, st, (const float*)a.X, (const float*)a.W, a.R, a.K, a.N, u0, u1, a);
 }
 static void lin32(const GemmArgs& a, hipStream_t st, int nz = 1) {
     switch (a.epi) {
-    case EPI_QKV: lin32_launch<EPI_QKV, true>(a, st, nz); break;
-    case EPI_GELU: lin32_launch<EPI_GELU, true>(a, st, nz); break;
-    case EPI_RESID: lin32_launch<EPI_RESID, false>(a, st, nz); break;
-    case EPI_SILU_RESID: lin32_launch<EPI_SILU_RESID, false>(a, st, nz); break;
+    case EPI_QKV: lin32_launch<EPI_QKV>(a, a.ln_g, a.ln_b, st, nz); break;
+    case EPI_GELU: lin32_launch<EPI_GELU>(a, a.ln_g, a.ln_b, st, nz); break;
+    case EPI_RESID: lin32_launch<EPI_RESID>(a, a.z_w, a.z_x, st, nz); break;
+    case EPI_SILU_RESID: lin32_launch<EPI_SILU_RESID>(a, a.z_w, a.z_x, st, nz); break;
     default:
-        if (a.ln_g) lin32_launch<EPI_F32, true>(a, st, nz);
-        else lin32_launch<EPI_F32, false>(a, st, nz);
+        if (a.ln_g) lin32_launch<EPI_F32>(a, a.ln_g, a.ln_b, st, nz);
+        else lin32_launch<EPI_F32>(a, a.z_w, a.z_x, st, nz);
     }
 }
 

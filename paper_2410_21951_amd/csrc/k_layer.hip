@@ -93,8 +93,8 @@ struct LinArgs {
 // the row blocks that share a weight tile share an XCD and its L2 and the tile leaves HBM once.
 __host__ __device__ inline int pad8(int a) { return (a + 7) & ~7; }
 
-// Row statistics of the LayerNorm folded into a map, for the ROWS rows of a workgroup, in two steps: request (ahead of
-// the operands, so that they return first) and merge (while the operands are on their way).  Eight (sixteen)
+// Row statistics of the LayerNorm folded into a map, for the ROWS rows of a workgroup, in two steps: request (k_lin: behind its first
+// operands, k_big: ahead of them) and merge (k_lin: behind the products, k_big: while the operands are on their way).  Eight (sixteen)
 // neighbouring lanes share a row and read its tile statistics two at a time, 128 (256) contiguous bytes per load.
 template <int ROWS, int OTHER>
 struct RowStats {
