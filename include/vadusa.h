@@ -33,6 +33,9 @@
  *    block to the next vadusa_create() of the process, which frees those it does
  *    not use.  Where there is none to be had, results take an ordinary copy.
  *  - All kernels are enqueued on the HIP stream given to vadusa_create().
+ *    Launches that leave compute units idle have them read weights of the launches
+ *    behind them, up to 24 MiB each: other work on the same GPU shares its memory
+ *    with these loads.
  *  - Speech token ids are 0..V-1, the end-of-sequence id is V (= speech_vocab);
  *    logits have V+1 entries.
  */

@@ -40,8 +40,9 @@ __device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return (uint
 // group of column tiles, which workgroups of XCD (group mod 8) read, `take` pieces of 64 lines.  Lines that have only been read stay in the L2 from
 // launch to launch (32 KiB by one wave per compute unit: 1060 clocks from the own L2, 2880 from the memory-side cache or where another XCD has
 // read them, 3440 from HBM); without this the memory has nothing to do between two maps' loads: while a launch ends and the next starts (1.3 us),
-// while it finds its operands, adds and stores.  us per step, without and with it: 1 node 288 -> 265, 16 nodes 315 -> 281, 64 nodes 341 -> 327, 128 nodes
-// and 2000 keys 465 -> 443, 5 sequences of 27 nodes 449 -> 434.
+// while it finds its operands, adds and stores.  us per step, without and with it: 1 node 279 -> 261, 16 nodes 306 -> 274, 64 nodes 331 -> 319, 128 nodes
+// and 2000 keys 449 -> 429, 5 sequences of 27 nodes 437 -> 424, 8 of 64 674 -> 676 (d = 1024); d = 768: 226 -> 224, 244 -> 238, 278 -> 275, 389 -> 375, 333 -> 327; d = 640,
+// 512 and 256: within 1.5 % either way.  Idle is a compute unit that this launch leaves so: work of other streams and contexts on the GPU shares the memory with these loads.
 struct Touch {
     const char* p;          // first piece of the first group
     uint32_t stride, last;  // bytes from a group to the next; from a group's first piece to its last line
@@ -205,10 +206,10 @@ __device__ __forceinline__ void store4(const LinArgs& a, int r, int n0, bool liv
 // needs the one before, and arguments in memory take some 500 to 850 clocks, so what the operands' addresses need comes as leading
 // arguments, which arrive in registers with the wave (build.py), the operands are asked for before everything else, from scalar bases with the
 // distance in the instruction (WHOLE), and nothing waits ahead of them.  Statistics and the epilogue's inputs requested first, with the wait that this
-// put before the operands, and arguments as one struct: steps of 1 | 16 | 64 | 128 | 5 x 27 nodes, us 310 | 340 | 358 | 475 | 464, now
-// 288 | 315 | 341 | 465 | 449.
+// put before the operands, and arguments as one struct: steps of 1 | 16 | 64 | 128 | 5 x 27 nodes, us 310 | 340 | 358 | 475 | 464, with this change alone
+// 288 | 315 | 341 | 465 | 449.  At d = 256 to 768, together with the attention's early keys and the touched weights, 64 nodes: 232 -> 221 (256), 254 -> 247, 258 -> 250, 293 -> 275 (768).
 // ---------------------------------------------------------------------------
-template <int RT, int CT, int CH, int EPI, int NW, bool WHOLE>   // WHOLE: every wave's k-steps are whole chunks
+template <int RT, int CT, int CH, int EPI, int NW, bool WHOLE>   // WHOLE: every wave's k-steps are whole chunks (no load is clamped)
 __global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W, int nks, int NT, int R, int per_block, size_t z_w, size_t z_x, LinArgs a, TouchList<2> ahead) {   // ahead: for the workgroups behind the map's own
     constexpr bool LN = EPI <= LE_LOGITS;
     constexpr int T = RT * CT, NPW = (T + NW - 1) / NW;   // output tiles, tiles per wave in the epilogue
@@ -245,7 +246,8 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const bf16_t* X, const uint4* W
     // compute unit has no more than some 64 KB of misses on their way; so each brings in a part that the others find in the L2.
     // (FFN2, K = 4096, us: 128 rows 8.6 -> 7.0, 135 rows 9.3 -> 8.7, 320 rows 12.8 -> 11.7; beyond what an L2 holds they
     // drive each other out of it: 1024 rows 18.4 -> 20.3, k_tile and k_big likewise.  Not the LayerNorm-folded maps of K = 1024,
-    // whose operands are all on their way at once: 64 rows FFN1 5.0 -> 5.4.)
+    // whose operands are all on their way at once: 64 rows FFN1 5.0 -> 5.4.  Steps with and without it, us: d = 512, 128 nodes 265 | 271, d = 640 279 | 284, d = 768,
+    // 64 nodes 275 | 282; d = 512, 64 nodes, where a wave's k-steps are one chunk, 247 | 242.)
     const int nch = (nk + CH - 1) / CH, turn = EPI == LE_RESID ? nk * rb * per_block >> 16 : 0;
     // Chunk j of the wave.  Loads are unconditional: a tile beyond the map's last row or column re-reads a valid one and only reaches
     // accumulators that are never stored; a k-step beyond the last re-reads a valid one and is not multiplied.
@@ -1366,7 +1368,7 @@ static Touch touch_of(const void* W, uint32_t bytes, int groups, int from, long 
 // The maps of a forward in the order in which they are read, and how far they have been touched.  What a launch may touch is bounded by what it can hide: it ends
 // when the last line has arrived.  Measured per idle workgroup (us per step of 1 | 64 nodes, 128 nodes and 2000 keys, 5 x 27 nodes):
 // attention 80 KiB 263 | 320 | 453 | 432, 112 KiB 263 | 324 | 450 | 445, 160 KiB 264 | 323 | 445 | 439; so by the keys it has to go through.  A map's launch
-// 32 KiB and 2 MiB in all; 6 MiB, 1 node 276; 1 MiB 265 | 327 | 454 | 438.
+// 32 KiB and 2 MiB in all; 6 MiB, 1 node 276; 1 MiB 265 | 327 | 454 | 438.  (All at d = 1024; what these bounds give at other widths stands at Touch.)
 struct Ahead {
     struct Map { const void* W; uint32_t bytes; int groups; };   // bytes of a group; groups 0: not touched
     std::vector<Map> maps;
@@ -1410,7 +1412,7 @@ static TileGrid tile_grid(const LinArgs& a, int rows, int ct) {
     while (g.strip < g.gc && (long)g.strip * g.strip * ct * 16 * 8 < (long)g.gr * g.gc * rows) ++g.strip;
     g.n = g.gr * g.gc;
     g.gs = g.gr * g.strip;
-    const bool exact = (long)g.n * g.gs < 1l << 32;   // (n >= gs > strip: a quotient's error stays below one part of the divisor)
+    const bool exact = (long)g.n * g.gs < 1l << 32;   // (both divisors are at most gs and both dividends below n: dividend x error < 2^32)
     g.gs_magic = exact ? (uint32_t)(((1ull << 32) + g.gs - 1) / g.gs) : 0;
     g.strip_magic = exact ? (uint32_t)(((1ull << 32) + g.strip - 1) / g.strip) : 0;
     return g;
@@ -1508,7 +1510,7 @@ static void attn_launch(const AttnCall& t, bool causal, int keys, Ahead& ahead, 
     dim3 grid(pad8(t.B * t.nH), a.x_last ? 1 : cdiv(cdiv(t.M, 16), QT));
     a.heads = grid.x;
     const unsigned idle = QT == 1 ? idle_columns(grid) : 0;
-    if (idle) ahead.take(a.ahead, idle * grid.y, 64 + std::min(keys / 22, 96), 24 << 10);   // (24 MiB: what the L2s hold beside everything else)
+    if (idle) ahead.take(a.ahead, idle * grid.y, 64 + std::min(keys / 22, 96), 24 << 10);   // (24 MiB: three of the 4 MiB of each of the eight L2s)
     if (a.ahead.map[0].groups) grid.x += idle;
     launch(causal ? k_attn<true, QT, NW, NB> : k_attn<false, QT, NW, NB>, grid, dim3(64 * NW), 0, st, t.q, t.Kc, t.Vc, t.L, t.B * t.nH, t.nH, (uint32_t)(t.nH > 1 ? ((1ull << 32) + t.nH - 1) / t.nH : 0),
            t.maxpos, cdiv(std::min(keys, t.maxpos), 32), turn_magic(grid.y), a);
