@@ -49,7 +49,8 @@ MFMA_PEAK_TFLOPS = 2500.0   # dense bf16
 def measured_traffic(workload):
     """HBM bytes per step from the rocprofv3 --pmc runs (FETCH_SIZE + WRITE_SIZE, scaled by a
     copy kernel of known size); the summary under profiles/ carries the figure on a `traffic_bytes_per_launch:`
-    line.  None when no such measurement exists for the workload."""
+    line.  None when no such measurement exists for the workload, or where it bounds the traffic without giving it
+    (launches of a counted run stand apart, so lines touched ahead of their launch are fetched twice)."""
     path = os.path.join(ROOT, "profiles", f"step_{workload}_pmc.md")
     try:
         for line in open(path):
