@@ -364,6 +364,53 @@ if dtype == "bf16-touch-grid":
         print(f"{len(want)} lines by {columns} x {rows} workgroups of {waves} waves: compared", flush=True)
     sys.stdout.flush()
     os._exit(0)
+if dtype == "bf16-row-stats":
+    # The row statistics that a map with a folded LayerNorm merges: the same bits as in this order, lane by lane, with one of a pair's squares
+    # unrounded where the other is added to it.  The map is of zeros with column sums of -1, so an output is the row's 1 / standard deviation times its mean.
+    import ctypes as C
+    import paper_2410_21951_amd.vadusa as V
+    lib, f32 = V._lib, np.float32
+    p = lambda a: C.c_void_p(a.ctypes.data)
+    rng = np.random.default_rng(101)
+    for rt, big, nks in ((1, False, 32), (2, False, 32), (4, False, 32), (4, True, 32), (2, False, 6), (4, False, 20), (4, True, 40)):
+        R, tiles = 16 * rt, 2 * nks
+        N = 128 if big else R
+        X, W = np.zeros(R * nks * 32, np.uint16), np.zeros(N * nks * 32, np.uint16)
+        bias, cs, out = np.zeros(N, f32), np.full(N, -1, f32), np.zeros((R, N), f32)
+        st = np.stack([rng.standard_normal((R, tiles)) + 3, rng.random((R, tiles)) * 16], axis=2).astype(f32)
+        if big:
+            lib.emu_big_logits(p(X), p(W), p(bias), p(cs), p(st), p(out), nks, N // 16, R, C.c_uint(0))
+        else:
+            lib.emu_lin_logits(p(X), p(W), p(bias), p(cs), p(st), p(out), nks, R, rt)
+        lanes = 8 if rt > 1 else 16                              # neighbouring lanes of a row, 32 / lanes pairs each, the rest behind them
+        first = 32 // lanes
+        want = np.zeros(R, f32)
+        for r in range(R):
+            c0 = st[r, 0, 0]
+            s = np.zeros((lanes, 3), f32)
+            for part in range(lanes):
+                for j in range(-(-tiles // (2 * lanes))):
+                    t = 2 * (part + j * lanes)
+                    if t >= tiles:
+                        continue
+                    d0, d1 = st[r, t, 0] - c0, st[r, t + 1, 0] - c0
+                    # workgroups of 64 rows, the first half of them: the second square stays unrounded in piece 1 (k_lin's vocabulary map: 1 and 2)
+                    if rt == 4 and r < 32 and j < first and 0 < j <= (1 if big else 2):
+                        d0, d1 = d1, d0
+                    pair = f32(np.float64(d0) * np.float64(d0) + np.float64(d1 * d1))     # (53 bits hold both: rounded once, but for ties)
+                    s[part] += np.array([d0 + d1, st[r, t, 1] + st[r, t + 1, 1], pair], f32)
+            for mask in (1, 2, 7, 15)[:3 if lanes == 8 else 4]:
+                s = s + s[np.arange(lanes) ^ mask]
+            s1, s2, s3 = s[0]
+            m2 = s2 + f32(16) * max(s3 - s1 * s1 / f32(tiles), f32(0))
+            want[r] = (c0 + s1 / f32(tiles)) * (f32(1) / np.sqrt(m2 / f32(nks * 32) + f32(1e-5)))
+        assert (out == out[:, :1]).all()
+        same = out[:, 0] == want
+        print(f"statistics of {R} rows of {tiles} tiles, {'k_big' if big else 'k_lin'}: {int(same.sum())} of {R} the same bits", flush=True)
+        assert same.all(), np.flatnonzero(~same)
+    print("emulated row statistics: compared", flush=True)
+    sys.stdout.flush()
+    os._exit(0)
 if dtype == "bf16-giveup":
     # the error word, raised from the host: the next synchronising call reports it, later calls refuse, a prefill
     # recovers and decodes the same tokens

@@ -5,7 +5,8 @@ without a GPU.  The smallest legal model (d = 64, one head), where two of a work
 waves have no k-steps of a linear map at all; 40, 72 and 256 rows (ragged tiles, masks of several words, the many-row
 kernels); both shapes of k_tile; eight waves on a reduction of 2048 and on more than 288 keys; lists, edges and scores of rows of more than 4096 logits; the error word raised from the host; models whose logits are all NaN (no arg-max, no draft lists: the
 step must stay inside its buffers); an arena that arrives full of NaN bits; one linear map of more than 4 GiB; compaction of one
-sequence beside a pending one; left-over errors of other HIP calls and refused launches; the pinned result blocks."""
+sequence beside a pending one; left-over errors of other HIP calls and refused launches; the pinned result blocks; the order of sums: row
+statistics, the k-steps of row blocks, the attention under other bounds of its keys; what idle workgroups touch."""
 import ctypes as C
 import os
 import shutil
@@ -36,6 +37,13 @@ def test_emulated_step_matches_oracle(emu_lib, dtype):
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=600, text=True)
     assert r.returncode == 0, r.stdout[-3000:]
     assert ("recovered" if dtype == "bf16-giveup" else "stayed in bounds" if dtype.endswith("-nan") else "compared") in r.stdout
+
+
+def test_row_statistics_are_added_in_one_order(emu_lib):
+    r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "run_case.py"), emu_lib, "bf16-row-stats"],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, timeout=600, text=True)
+    assert r.returncode == 0, r.stdout[-3000:]
+    assert "compared" in r.stdout
 
 
 @pytest.mark.parametrize("case", ["bf16-attn-bound", "bf16-unfetched"])
